@@ -28,6 +28,9 @@ def hipcc() -> str:
 def flags():
     return ["-O3", f"--offload-arch={ARCH}", "-fPIC", "-std=c++17", "-ffp-contract=off",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+            # three-address FP64 FMA only: the two-address form needs a copy of
+            # every polynomial coefficient it accumulates into
+            "-Xclang", "-target-feature", "-Xclang", "-fmacf64-inst",
             "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 

@@ -97,7 +97,6 @@ static void derive(const sdpd_params *P, const int nc[3], DevParams &d)
     d.ncell = 1;
     for (int k = 0; k < 3; ++k) {
         d.box[k] = P->box[k];
-        d.half_box[k] = 0.5 * P->box[k];
         d.nc[k] = nc[k];
         d.inv_cell[k] = (double)nc[k] / P->box[k];
         d.ncell *= nc[k];
@@ -130,8 +129,10 @@ static void derive(const sdpd_params *P, const int nc[3], DevParams &d)
     d.eps_exp = P->A * P->kB / P->Cv;
     d.kpar_c = (10.0 / 3.0 * P->eta + 4.0 * P->zeta) * P->m * P->m;
     d.kperp_c = (5.0 / 3.0 * P->eta - P->zeta) * P->m * P->m;
-    d.two_over_Cv = 2.0 / P->Cv;
-    d.b2_c = 4.0 * P->kB / P->m;
+    d.d_c = P->kB * (2.0 / P->Cv);
+    d.b2_red = 4.0 * P->kB / P->m / P->Cv;
+    d.kpar_over_kperp = d.kpar_c / d.kperp_c;
+    for (int k = 0; k < 3; ++k) d.inv_box[k] = 1.0 / P->box[k];
     d.ent_c = P->Cv / P->kB - 1.0;
     d.m_over_8 = P->m / 8.0;
     d.m_over_2 = P->m / 2.0;
@@ -145,9 +146,9 @@ static void derive(const sdpd_params *P, const int nc[3], DevParams &d)
     d.cW_f = (float)d.cW;
     d.cF_f = (float)d.cF;
     d.inv_Cv_f = (float)d.inv_Cv;
-    d.d_c_f = (float)(d.kB * d.two_over_Cv);
+    d.d_c_f = (float)d.d_c;
     d.inv_m_f = (float)d.inv_m;
-    d.b2_c_f = (float)d.b2_c;
+    d.b2_c_f = (float)(4.0 * P->kB / P->m);
     d.kperp_c_f = (float)d.kperp_c;
     d.div_per = make_fastdiv((uint32_t)std::max<int64_t>(d.ncell / 8, 1));
     d.div_hx = make_fastdiv((uint32_t)std::max(nc[0] / 2, 1));
@@ -168,7 +169,7 @@ static void free_ctx(sdpd_ctx *c)
                     c->perm, c->cell_sorted, c->tq, c->tp, c->teps, c->trho, c->tf, c->tid,
                     c->masks, c->counters, c->err, c->obs_partial, c->obs_out,
                     c->dparams, c->task_count, c->task_np, c->pair_off, c->part_off,
-                    c->part_list, c->pairs, c->draws, c->q4f, c->dstep, c->q4,
+                    c->part_list, c->pairs, c->rec_buf, c->lvl_end, c->flow_rec, c->q4f, c->dstep, c->q4,
                     c->sweep, c->epoch, c->sweep_order};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
@@ -224,6 +225,11 @@ static void record_to_stats(const double *rec, sdpd_stats *st)
 // per-step observable records kept on the device by sdpd_step (allocated
 // once, at context creation)
 static const int64_t STEP_RECORDS = 64;
+
+// Boxes of at most this many particles sweep on their own by one launch per
+// group (see fd_prepare_sweep) after one launch that forms the records of the
+// whole sweep; larger ones form them in the sweep's launches.
+static const int64_t kWholeRecordsMaxParticles = (int64_t)1 << 14;
 
 static int alloc_records(sdpd_ctx *c)
 {
@@ -283,13 +289,11 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
             hipSuccess || lds <= 0)
             lds = 65536;
         c->max_lds = lds;
-        // the LDS share of one sweep workgroup when the CU holds two waves
-        // per SIMD (eight waves per CU); the default capacities stay within it
         int per_cu = 0;
         if (hipDeviceGetAttribute(&per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
                                   c->device) != hipSuccess || per_cu <= 0)
             per_cu = 65536;
-        c->lds_share = std::max(per_cu / 8 * FD_WAVES, 4096);
+        c->lds_cu = per_cu;
     }
     fd_default_tuning(c);
     // schedule capacity: 64 pairs per particle (a jittered lattice has ~39),
@@ -324,10 +328,15 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     rc = rc ? rc : dalloc(&c->pair_off, (size_t)NMASK * nce + 1);
     rc = rc ? rc : dalloc(&c->part_off, (size_t)NMASK * nce + 1);
     rc = rc ? rc : dalloc(&c->pairs, (size_t)c->pair_cap);
-    rc = rc ? rc : dalloc(&c->draws, (size_t)4 * c->pair_cap);
     rc = rc ? rc : dalloc(&c->epoch, (size_t)c->ncell + 1);
     rc = rc ? rc : dalloc(&c->dstep, 1);
     rc = rc ? rc : dalloc(&c->part_list, (size_t)c->part_cap);
+    // pair records: of one group of the sweep (it touches every cell once: at
+    // most 32 pairs per particle), for small boxes of a whole sweep
+    const bool whole = c->n <= kWholeRecordsMaxParticles;
+    c->rec_bytes = sizeof(double) * (whole ? 8 : 4) * (size_t)c->pair_cap;
+    rc = rc ? rc : dalloc(&c->rec_buf, c->rec_bytes / sizeof(double));
+    if (whole) rc = rc ? rc : dalloc(&c->lvl_end, (size_t)NMASK * nce * 64);
     if (!rc)
         rc = check_hip(hipMemcpyAsync(c->dparams, &c->dp, sizeof c->dp, hipMemcpyHostToDevice,
                                       c->stream));

@@ -14,21 +14,29 @@
 // order between pairs sharing a particle gives the same result.
 //
 // GPU schedule.  The scheduling pass (schedule.hip) has stored, for every
-// task, its active pairs with their conflict level.  A workgroup (FD_WAVES
-// waves) takes a range of consecutive tasks of one phase, stages in LDS the
-// momenta and energies of the particles that take part in a pair, sorts the
-// range's pairs by level and applies the pairs of one level (which share no
-// particle) as parallel steps over its lanes.  The number of level steps of
-// a batch is set by its deepest task (the longest chain of pairs that share
-// a particle, in round order), not by its size.  Positions, densities and ids do
-// not change during the sweep: positions and densities are packed once per
-// sweep into one (x, y, z, rho) record per particle and read from global
-// memory two level steps ahead of their use, which keeps the LDS footprint
-// at 36 B per particle and leaves room for more resident waves.  The random
-// draws of a pair depend only on (step, ids): after the level sort they are
-// computed for all of the batch's pairs at full lane occupancy (which also
-// orients every pair, i = smaller id) and stored in sorted order in a global
-// buffer, from which the level steps prefetch them with the positions.
+// task, its active pairs with their conflict level.  A workgroup (one wave)
+// takes a range of consecutive tasks of one phase, sorts the range's pairs by
+// level, forms a record of each pair (unit vector, friction exponent, random
+// draws: everything that does not change during the sweep) at full lane
+// occupancy in that order, stages in LDS the momenta and energies of the
+// particles that take part, and applies the pairs of one level (which share no
+// particle) 64 at a time, the records of the next step in flight meanwhile.
+// The number of level steps of a batch is set by its deepest task (the longest
+// chain of pairs that share a particle, in round order), not by its size, so a
+// step holds 28 pairs on average: what can be worked out beforehand leaves the
+// steps.
+//
+// What bounds it (2^20 particles, 38 million pairs, MI355X): VALU issue.  A
+// step at three waves per SIMD takes as much longer as there are waves (3,100
+// against 4,500 cycles at two), so only fewer instructions help: the records
+// with the pair update in scalars of the pair (fd_pair) took the step from
+// ~560 to ~320 VALU instructions and the sweep from 2.285 to 1.96 ms, constants
+// kept out of the way of the steps (fd_math.hpp, `reread`) and FP64 FMAs
+// without coefficient copies to 1.90 ms, three waves per SIMD in 168 registers
+// to 1.81 ms.  Forming the records in a launch of its own, for all ranges
+// before the sweep, was slower for large boxes (1.07 + 1.46 ms: 2.4 GB of
+// records go through HBM instead of the workgroups' slices in the last-level
+// cache), faster only for small ones (see fd_levels).
 //
 // Phases that touch disjoint cells commute.  Phase 1 + 8 o + pi touches the
 // cells of parity pi (as A) and pi ^ b_o (as B = A + delta_o, b_o the parity
@@ -69,42 +77,59 @@ struct FdLaunch {
     int64_t wg_end[FD_MAXPH];        // cumulative workgroup counts
 };
 
-// dynamic LDS layout: p[3][cap_p], eps[cap_p] (doubles), then gidx[cap_p],
-// sorted[cap_e] and the small tables (32-bit)
+// dynamic LDS layout: gidx[cap_p] and the level tables (32-bit), then one area
+// that holds first the sorted pair list [cap_e] (32-bit) and, once the pairs'
+// records are formed, the state (p_x, p_y, p_z, eps)[cap_p] (doubles)
+constexpr int FD_TABLE_WORDS = 2 * (FD_NLVL + 2);
+__host__ __device__ inline int fd_lds_area(int cap_p)   // byte offset of the shared area
+{
+    return (4 * (cap_p + FD_TABLE_WORDS) + 15) & ~15;
+}
 __host__ __device__ inline size_t fd_lds_bytes(int cap_p, int cap_e)
 {
-    return (size_t)36 * cap_p + (size_t)4 * cap_e + 4 * (3 * (FD_NLVL + 2) + 2 * (FD_MAXTASKS + 1) + 2);
+    const size_t st = (size_t)32 * cap_p, so = (size_t)4 * cap_e;
+    return (size_t)fd_lds_area(cap_p) + (st > so ? st : so);
 }
+// what a tuning is checked against (sdpd_tune): the list beside the state
+inline size_t fd_lds_checked_bytes(int cap_p, int cap_e)
+{
+    return (size_t)36 * cap_p + (size_t)4 * cap_e + 1320;
+}
+
+struct FdLds {
+    uint32_t *gidx, *hist, *cur;
+    uint32_t *sorted;   // A-side | B-side << 16
+    double2 *st;        // (p_x, p_y), (p_z, eps) per particle; the same memory
+    __device__ __forceinline__ FdLds(unsigned char *lds, int cap_p)
+    {
+        gidx = (uint32_t *)lds;
+        hist = gidx + cap_p;
+        cur = hist + (FD_NLVL + 2);
+        sorted = (uint32_t *)(lds + fd_lds_area(cap_p));
+        st = (double2 *)sorted;
+    }
+};
 
 constexpr uint64_t POS_MASK = (1ull << 25) - 1ull;   // list position field of a pair entry
 
-// read-only data of the (oriented) pair at sorted position e: batch particle
-// indices from the LDS list, then the (x, y, z, rho) records of both
-// particles and the stored draws; loads are issued, not waited for
-__device__ __forceinline__ void fd_gather(const uint32_t *s_sorted, const uint32_t *s_gidx,
-                                          const double4 *__restrict__ qrho,
-                                          const double *__restrict__ draws, int e,
-                                          int &li, int &lj, PairGeo &g)
-{
-    const uint32_t pr = s_sorted[e];
-    li = (int)(pr & 0xFFFFu);
-    lj = (int)(pr >> 16);
-    const double4 a = qrho[s_gidx[li]], b = qrho[s_gidx[lj]];
-    g.xi = a.x;
-    g.yi = a.y;
-    g.zi = a.z;
-    g.rho_i = a.w;
-    g.xj = b.x;
-    g.yj = b.y;
-    g.zj = b.z;
-    g.rho_j = b.w;
-    const double2 *d = reinterpret_cast<const double2 *>(draws) + 2 * (int64_t)e;
-    const double2 d01 = d[0], d23 = d[1];
-    g.G0 = d01.x;
-    g.G1 = d01.y;
-    g.G2 = d23.x;
-    g.U = d23.y;
-}
+// The records of one batch (PairRec): four planes of n entries of 16 bytes
+struct RecPlanes {
+    double2 *p;
+    int64_t n;
+    __device__ __forceinline__ void store(int e, const PairRec &r) const
+    {
+        p[e] = make_double2(r.ex, r.ey);
+        p[n + e] = make_double2(r.ez, r.y);
+        p[2 * n + e] = make_double2(r.G0, r.G1);
+        p[3 * n + e] = make_double2(r.G2, __hiloint2double((int)r.ij, (int)r.u));
+    }
+    __device__ __forceinline__ PairRec load(int e) const
+    {
+        const double2 a = p[e], b = p[n + e], c = p[2 * n + e], d = p[3 * n + e];
+        return PairRec{a.x, a.y, b.x, b.y, c.x, c.y, d.x, (uint32_t)__double2loint(d.y),
+                       (uint32_t)__double2hiint(d.y)};
+    }
+};
 
 // Momenta and energies are the state that workgroups hand on to each other.
 // COHERENT (the one-launch sweep): another workgroup of the same kernel, on
@@ -134,375 +159,449 @@ struct FdArgs {
     const uint32_t *part_list;
     uint32_t pair_cap, part_cap;
     const uint64_t *dstep;
-    double dt;
-    double *draws;
+    double dt, y_c;         // time step of the sweep; prefactor of a pair's exponent
+    double2 *rec;           // pair records, batch by batch
+    int64_t rec_stride;     // one-launch sweep: 16-byte units of a workgroup's slice
+    uint16_t *lvl;          // records formed by k_fd_records: per batch (at its first task): end of each level, FD_NLVL entries
     uint32_t *err;
 };
 
-// One task range: workgroup-range index b of the launch L (a range of
-// consecutive tasks of one of its phases), staged, sorted, drawn and applied
-// level by level.  K: 0 = general, 1 = the common case (EMS, Lucy kernel,
-// zeta = 0) fixed at compile time, 2 = that case with the FP32 proposal of
-// mixed precision.
-// wait() is called once, before the first access to momenta and energies:
-// everything before it (entries, lists, ids, positions, the draws) is fixed
-// during the sweep, so the level sort and the draws of a range overlap the
-// wait for its predecessors.
-template <int K, bool COHERENT, bool VREG, int SPL, class Wait>
-__device__ __forceinline__ void fd_range(const DevParams &P, const FdLaunch &L, int64_t b,
-                                         unsigned char *lds, const FdArgs &A, FdCount &cnt,
-                                         bool &negeps, Wait &wait)
+// x (kernel arguments or parameters in memory, unchanged during the launch)
+// read anew from here on: scalar loads that cannot move above this point, so
+// that what one part of a range needs is not held in registers (and spilled)
+// through the others
+template <class T>
+__device__ __forceinline__ const T &reread(const T &x)
 {
-    const double4 *__restrict__ qrho = A.qrho;
-    double *p = A.p, *eps = A.eps;
-    const uint32_t *__restrict__ id = A.id;
-    const uint32_t *__restrict__ pair_off = A.pair_off;
-    const uint32_t *__restrict__ part_off = A.part_off;
-    const uint64_t *__restrict__ pairs = A.pairs;
-    const uint32_t *__restrict__ part_list = A.part_list;
-    const uint32_t pair_cap = A.pair_cap, part_cap = A.part_cap;
-    const uint64_t *__restrict__ dstep = A.dstep;
-    const double dt = A.dt;
-    double *draws = A.draws;
-    uint32_t *err = A.err;
-    const int CP = L.cap_p, CE = L.cap_e;
-    double *s_p = (double *)lds;
-    double *s_eps = s_p + 3 * CP;
-    uint32_t *s_gidx = (uint32_t *)(s_eps + CP);
-    uint32_t *s_sorted = s_gidx + CP;                 // A-side | B-side << 16
-    uint32_t *s_hist = s_sorted + CE;
-    uint32_t *s_off = s_hist + (FD_NLVL + 2);
-    uint32_t *s_cur = s_off + (FD_NLVL + 2);
-    uint32_t *s_eoff = s_cur + (FD_NLVL + 2);        // pair-entry offsets of the range's tasks
-    uint32_t *s_poff = s_eoff + (FD_MAXTASKS + 1);   // particle-list offsets
-    int *s_maxlv = (int *)(s_poff + (FD_MAXTASKS + 1));
-    int *s_ntot = s_maxlv + 1;                        // sorted entries of the window
+    const uint64_t u = (uint64_t)&x;   // uniform: said so, where the compiler cannot tell
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    auto *c = (const __attribute__((address_space(4))) T *)(((uint64_t)hi << 32) | lo);
+    __asm__ volatile("" : "+s"(c));
+    return *(const T *)c;
+}
 
+// The first argument of a kernel in place (in memory), for reread
+template <class T>
+__device__ __forceinline__ const T &kernel_argument()
+{
+    return *(const T *)(const __attribute__((address_space(4))) T *)
+               __builtin_amdgcn_kernarg_segment_ptr();
+}
+
+__device__ __forceinline__ uint32_t lane_u32(uint32_t v, int lane)   // uniform lane
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+
+// Range b of the launch L (consecutive tasks of one of its phases): lane t
+// holds the offsets of task t (pair entries and particle-list entries, first
+// and end; lanes past the range: empty tasks).
+struct FdRange {
+    int R;                       // tasks, at most one per lane
+    int64_t T0;                  // the first one, in sweep order
+    uint32_t e_lo, e_hi, p_lo, p_hi;
+    uint32_t phase_p0;           // first particle-list entry of the phase
+    uint32_t rec0;               // record of pair entry e: rec0 + e
+    bool ok;                     // the schedule holds all of its entries
+};
+
+__device__ __forceinline__ FdRange fd_range_of(const FdLaunch &L, int64_t b, const FdArgs &A,
+                                               bool group_records)
+{
+    static_assert(FD_WAVES == 1, "lane = thread: offsets and levels are held per lane");
     const int tid = threadIdx.x;
-    const int64_t n = P.n;
-    // phase of this range and its tasks
+    FdRange r;
     int k_ph = 0;
     while (k_ph + 1 < L.nph && b >= L.wg_end[k_ph]) ++k_ph;
     if (k_ph > 0) b -= L.wg_end[k_ph - 1];
     const int64_t tpw = L.tpw[k_ph], ntasks = L.ntasks[k_ph], task_base = L.task_base[k_ph];
     const int64_t t0 = b * tpw;
-    const int R = (int)(t0 + tpw < ntasks ? tpw : ntasks - t0);
-    const int64_t T0 = task_base + t0;
+    r.R = (int)(t0 + tpw < ntasks ? tpw : ntasks - t0);
+    r.T0 = task_base + t0;
+    const int64_t lo = r.T0 + min(tid, r.R), hi = r.T0 + min(tid + 1, r.R);
+    r.e_lo = A.pair_off[lo];
+    r.p_lo = A.part_off[lo];
+    r.e_hi = A.pair_off[hi];
+    r.p_hi = A.part_off[hi];
+    r.phase_p0 = A.part_off[task_base];
+    r.rec0 = 0;
+    if (group_records) {   // place among the entries of the group's phases
+        for (int k = 0; k < k_ph; ++k)
+            r.rec0 += A.pair_off[L.task_base[k] + L.ntasks[k]] - A.pair_off[L.task_base[k]];
+        r.rec0 -= A.pair_off[task_base];
+    }
+    r.ok = lane_u32(r.e_hi, 63) <= A.pair_cap && lane_u32(r.p_hi, 63) <= A.part_cap;
+    return r;
+}
 
-    // offsets of the range's tasks (R + 1 values) and of the phase
-    if (tid < R) {
-        s_eoff[tid] = pair_off[T0 + tid];
-        s_poff[tid] = part_off[T0 + tid];
+// A batch of consecutive tasks k0 .. k - 1 of a range that fits the LDS
+// capacities (scalar work on the lanes' offsets; finding its end with a ballot
+// was slower, 2.08 against 1.95 ms a sweep at 2^20 particles, through the
+// registers it held); a task with more pairs than the list forms one of its
+// own (oversized).
+struct FdBatch {
+    int k0, k, npr, np;          // tasks, pairs, particles
+    uint32_t e_begin, p_begin;
+    bool oversized;
+};
+
+__device__ __forceinline__ FdBatch fd_next_batch(const FdRange &r, int k, int CP, int CE)
+{
+    FdBatch t;
+    t.k0 = k;
+    t.oversized = false;
+    t.e_begin = lane_u32(r.e_lo, k);
+    t.p_begin = lane_u32(r.p_lo, k);
+    while (k < r.R) {
+        const int c = (int)(lane_u32(r.e_hi, k) - lane_u32(r.e_lo, k));
+        const int np_new = (int)(lane_u32(r.p_hi, k) - t.p_begin);
+        const int npr_new = (int)(lane_u32(r.e_hi, k) - t.e_begin);
+        if (k > t.k0 && c > 0 && (np_new > CP || npr_new > CE)) break;
+        t.oversized = c > CE;   // only possible as the first task of a batch
+        ++k;
+        if (t.oversized) break;
     }
-    if (tid == 0) {   // end of the range (R may be FD_THREADS)
-        s_eoff[R] = pair_off[T0 + R];
-        s_poff[R] = part_off[T0 + R];
+    t.k = k;
+    t.npr = (int)(lane_u32(r.e_hi, k - 1) - t.e_begin);
+    t.np = (int)(lane_u32(r.p_hi, k - 1) - t.p_begin);
+    return t;
+}
+
+// global indices of the particles that take part in a pair of the batch
+__device__ __forceinline__ void fd_load_indices(const FdArgs &A, const FdBatch &t, const FdLds &S)
+{
+    const uint32_t *__restrict__ part_list = A.part_list;
+    const int tid = threadIdx.x;
+    for (int base = 0; base < t.np; base += FD_PPL * FD_THREADS) {
+        uint32_t gl[FD_PPL];
+#pragma unroll
+        for (int q = 0; q < FD_PPL; ++q) {
+            const int l = base + q * FD_THREADS + tid;
+            gl[q] = l < t.np ? part_list[t.p_begin + l] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < FD_PPL; ++q) {
+            const int l = base + q * FD_THREADS + tid;
+            if (l < t.np) S.gidx[l] = gl[q];
+        }
     }
-    const uint32_t phase_p0 = part_off[task_base];
     __syncthreads();
-    if (s_eoff[R] > pair_cap || s_poff[R] > part_cap) {   // schedule incomplete
-        if (tid == 0) atomicOr(err, ERR_PAIRCAP);
+}
+
+// Counting sort of the batch's entries of the levels lo .. hi into S.sorted.
+// hi = FD_NLVL, or for an oversized batch the last level up to which the list
+// holds them.  Returns the inclusive prefix over the levels (lane x: level
+// x + 1).
+__device__ __forceinline__ uint32_t fd_sort_window(const FdArgs &A, const FdBatch &t,
+                                                   uint32_t rel0, const FdLds &S, int CE, int lo,
+                                                   int &hi)
+{
+    const uint64_t *__restrict__ pairs = A.pairs;
+    const int tid = threadIdx.x, npr = t.npr, np = t.np;
+    const uint32_t e_begin = t.e_begin;
+    hi = FD_NLVL;
+    S.hist[tid + 1] = 0u;
+    __syncthreads();
+    if (t.oversized) {
+        for (int e = tid; e < npr; e += FD_THREADS) {
+            const int lv = (int)(pairs[e_begin + e] >> 50);
+            if (lv >= 1 && lv <= FD_NLVL) atomicAdd(&S.hist[lv], 1u);
+        }
+        __syncthreads();
+        int acc = 0;
+        for (hi = lo; hi <= FD_NLVL; ++hi) {
+            if (acc + (int)S.hist[hi] > CE) break;
+            acc += (int)S.hist[hi];
+        }
+        --hi;
+        hi = hi < lo ? lo : hi;   // one level (<= 64 pairs) always fits
+        __syncthreads();
+        S.hist[tid + 1] = 0u;
+        __syncthreads();
+    }
+    // histogram pass, prefix, scatter pass.  Entries stay in registers
+    // (FD_EPL per lane) between the passes unless the batch needs several.
+    constexpr int EP = FD_EPL * FD_THREADS;
+    uint64_t ebuf[FD_EPL];
+    const bool one_pass = npr <= EP;
+    for (int base = 0; base < npr; base += EP) {
+#pragma unroll
+        for (int q = 0; q < FD_EPL; ++q) {
+            const int x = base + q * FD_THREADS + tid;
+            ebuf[q] = x < npr ? pairs[e_begin + x] : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < FD_EPL; ++q) {
+            const uint64_t e = ebuf[q];
+            const int lv = (int)(e >> 50);
+            const int li = (int)((uint32_t)(e & POS_MASK) - rel0);
+            const int lj = (int)((uint32_t)((e >> 25) & POS_MASK) - rel0);
+            if (lv >= lo && lv <= hi && lv <= FD_NLVL && li >= 0 && li < np && lj >= 0 && lj < np)
+                atomicAdd(&S.hist[lv], 1u);
+        }
+    }
+    __syncthreads();
+    const uint32_t h = S.hist[tid + 1];
+    uint32_t incl = h;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
+        if (tid >= off) incl += v;
+    }
+    S.cur[tid + 1] = incl - h;
+    __syncthreads();
+    for (int base = 0; base < npr; base += EP) {
+        if (!one_pass) {
+#pragma unroll
+            for (int q = 0; q < FD_EPL; ++q) {
+                const int x = base + q * FD_THREADS + tid;
+                ebuf[q] = x < npr ? pairs[e_begin + x] : 0ull;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < FD_EPL; ++q) {
+            const uint64_t e = ebuf[q];
+            const int lv = (int)(e >> 50);
+            const int li = (int)((uint32_t)(e & POS_MASK) - rel0);
+            const int lj = (int)((uint32_t)((e >> 25) & POS_MASK) - rel0);
+            if (lv >= lo && lv <= hi && lv <= FD_NLVL && li >= 0 && li < np && lj >= 0 &&
+                lj < np) {
+                const uint32_t pos = atomicAdd(&S.cur[lv], 1u);
+                if (pos < (uint32_t)CE) S.sorted[pos] = (uint32_t)li | ((uint32_t)lj << 16);
+            }
+        }
+    }
+    __syncthreads();
+    return incl;
+}
+
+// Records of the ntot sorted entries into planes first, first + 1, ..., all
+// lanes busy.  The ids also orient each pair (i = smaller id); the gathers of
+// the next 64 entries are in flight while these are worked out.
+template <int K>
+__device__ __forceinline__ void fd_form_records(const DevParams &P, const FdArgs &A,
+                                                const FdLds &S, int ntot, const RecPlanes &rec,
+                                                int first)
+{
+    const double4 *__restrict__ qrho = A.qrho;
+    const uint32_t *__restrict__ id = A.id;
+    const uint32_t step = (uint32_t)*A.dstep;   // step index of the Philox counter
+    ColdTable *tab = cold(kDrawTab);
+    const int tid = threadIdx.x;
+    uint32_t pr, ida, idb;
+    double4 qa, qb;
+    auto gather = [&](int e) {
+        pr = S.sorted[min(e, ntot - 1)];
+        const uint32_t ga = S.gidx[pr & 0xFFFFu], gb = S.gidx[pr >> 16];
+        ida = id[ga];
+        idb = id[gb];
+        qa = qrho[ga];
+        qb = qrho[gb];
+    };
+    if (ntot > 0) gather(tid);
+    for (int base = 0; base < ntot; base += FD_THREADS) {
+        const int e = base + tid;
+        const bool swap = ida > idb;
+        const uint32_t ij = swap ? (pr >> 16) | (pr << 16) : pr;
+        const uint32_t id0 = swap ? idb : ida, id1 = swap ? ida : idb;
+        const double4 a = qa, b = qb;
+        if (base + FD_THREADS < ntot) gather(e + FD_THREADS);
+        PairRec g = pair_record<K>(P, A.y_c, step, id0, id1, a, b, tab);
+        // e_ij of the swapped pair (exact)
+        g.ex = swap ? -g.ex : g.ex;
+        g.ey = swap ? -g.ey : g.ey;
+        g.ez = swap ? -g.ez : g.ez;
+        g.ij = ij;
+        if (e < ntot) rec.store(first + e, g);
+    }
+    __syncthreads();
+}
+
+// Momenta and energies of the batch staged over the list; the loads of several
+// particles issue before their LDS writes (an LDS write between two atomic
+// loads makes the second wait).
+template <bool COHERENT>
+__device__ __forceinline__ void fd_stage(const FdArgs &A, int64_t n, int np, const FdLds &S)
+{
+    const double *p = A.p, *eps = A.eps;
+    const int tid = threadIdx.x;
+    constexpr int SPL = 4;
+    for (int base = 0; base < np; base += SPL * FD_THREADS) {
+        double v[SPL][4];
+        int64_t gi[SPL];
+#pragma unroll
+        for (int q = 0; q < SPL; ++q) gi[q] = S.gidx[min(base + q * FD_THREADS + tid, np - 1)];
+#pragma unroll
+        for (int q = 0; q < SPL; ++q) {
+            v[q][0] = state_load<COHERENT>(p + gi[q]);
+            v[q][1] = state_load<COHERENT>(p + n + gi[q]);
+            v[q][2] = state_load<COHERENT>(p + 2 * n + gi[q]);
+            v[q][3] = state_load<COHERENT>(eps + gi[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < SPL; ++q) {
+            const int l = base + q * FD_THREADS + tid;
+            if (l < np) {
+                S.st[2 * l] = make_double2(v[q][0], v[q][1]);
+                S.st[2 * l + 1] = make_double2(v[q][2], v[q][3]);
+            }
+        }
+    }
+    __syncthreads();
+}
+
+template <bool COHERENT>
+__device__ __forceinline__ void fd_write_back(const FdArgs &A, int64_t n, int np, const FdLds &S)
+{
+    double *p = A.p, *eps = A.eps;
+    for (int l = threadIdx.x; l < np; l += FD_THREADS) {
+        const int64_t g = S.gidx[l];
+        const double2 a = S.st[2 * l], c = S.st[2 * l + 1];
+        state_store<COHERENT>(p + g, a.x);
+        state_store<COHERENT>(p + n + g, a.y);
+        state_store<COHERENT>(p + 2 * n + g, c.x);
+        state_store<COHERENT>(eps + g, c.y);
+    }
+    __syncthreads();
+}
+
+// The pair updates: steps of at most 64 records of one level in ascending
+// order (ends: lane x holds the end of level x + 1); the records of step k + 1
+// are in flight while step k runs.
+template <int K>
+__device__ __forceinline__ void fd_run_levels(const DevParams &P, double dt, int ends,
+                                              const RecPlanes &rec, const FdLds &S, FdCount &cnt,
+                                              bool &negeps)
+{
+    const int tid = threadIdx.x;
+    const int ntot = __builtin_amdgcn_readlane(ends, FD_NLVL - 1);
+    const int last = max(ntot - 1, 0);
+    int lev = 0, pos = -FD_THREADS, end = 0;
+    auto advance = [&] {
+        pos += FD_THREADS;
+        while (pos >= end && end < ntot) {   // the next level that is not empty
+            pos = end;
+            end = __builtin_amdgcn_readlane(ends, lev);
+            ++lev;
+        }
+    };
+    const PairRegs<K == 2> c(P);
+    advance();
+    PairRec g0 = rec.load(min(pos + tid, last));
+    bool v0 = pos + tid < end;
+    while (pos < end) {
+        advance();
+        const PairRec g1 = rec.load(min(pos + tid, last));
+        const bool v1 = pos + tid < end;
+        if (v0) fd_pair<K>(P, c, dt, g0, S.st, cnt, negeps);
+        __syncthreads();
+        g0 = g1;
+        v0 = v1;
+    }
+}
+
+// One range of the sweep: batch by batch its entries sorted, its records
+// formed, its state staged, the levels applied, the state written back.
+// K: 0 = general, 1 = the common case (EMS, Lucy kernel, zeta = 0) fixed at
+// compile time, 2 = that case with the FP32 proposal of mixed precision.
+// Only this workgroup reads the records: they go to its own slice (one-launch
+// sweep) or to the batch's place among the entries of its group, which touches
+// every cell once and so holds at most 32 pairs per particle (two cells of a
+// and b particles, at most 64 each, have a b <= 32 (a + b) pairs).
+// wait() is called once, before the first access to momenta and energies:
+// everything before it (entries, lists, ids, positions, the records) is fixed
+// during the sweep, so the level sort and the records of a range overlap the
+// wait for its predecessors.
+template <int K, bool COHERENT, class Wait>
+__device__ __forceinline__ void fd_range(const DevParams &P, const FdLaunch &L, int64_t b,
+                                         unsigned char *lds, const FdArgs &A, FdCount &cnt,
+                                         bool &negeps, Wait &wait)
+{
+    const int CP = L.cap_p, CE = L.cap_e;
+    const FdLds S(lds, CP);
+    const FdRange r = fd_range_of(L, b, A, !COHERENT);
+    if (!r.ok) {   // schedule incomplete
+        if (threadIdx.x == 0) atomicOr(A.err, ERR_PAIRCAP);
         return;
     }
+    for (int k = 0; k < r.R;) {
+        const FdBatch t = fd_next_batch(r, k, CP, CE);
+        k = t.k;
+        if (t.npr == 0) continue;
+        const FdArgs &B = reread(A);
+        const RecPlanes rec =
+            COHERENT ? RecPlanes{B.rec + (int64_t)blockIdx.x * B.rec_stride, min(t.npr, CE)}
+                     : RecPlanes{B.rec + 4 * (int64_t)(uint32_t)(r.rec0 + t.e_begin), t.npr};
+        fd_load_indices(B, t, S);
+        // windows of levels: one, unless a single task overflows the list
+        for (int lo = 1, hi; lo <= FD_NLVL; lo = hi + 1) {
+            const uint32_t ends = fd_sort_window(B, t, t.p_begin - r.phase_p0, S, CE, lo, hi);
+            fd_form_records<K>(reread(P), B, S, min((int)lane_u32(ends, FD_NLVL - 1), CE), rec, 0);
+            wait();
+            fd_stage<COHERENT>(reread(A), reread(P).n, t.np, S);
+            fd_run_levels<K>(reread(P), reread(A).dt, min((int)ends, CE), rec, S, cnt, negeps);
+            fd_write_back<COHERENT>(reread(A), reread(P).n, t.np, S);
+            if (!t.oversized) break;
+            // the next window stages what this one has written
+            __builtin_amdgcn_s_waitcnt(0);
+        }
+    }
+}
 
-    int k = 0;
-    while (k < R) {
-        // ---- a batch of consecutive tasks that fits (LDS reads only)
-        const int k0 = k;
-        bool oversized = false;
-        while (k < R) {
-            const int c = (int)(s_eoff[k + 1] - s_eoff[k]);
-            const int np_new = (int)(s_poff[k + 1] - s_poff[k0]);
-            const int npr_new = (int)(s_eoff[k + 1] - s_eoff[k0]);
-            if (k > k0 && c > 0 && (np_new > CP || npr_new > CE)) break;
-            oversized = c > CE;   // only possible as the first task of a batch
-            ++k;
-            if (oversized) break;
+// Small boxes with one launch per group: the records and level ends of every
+// range by a launch of their own (fd_records), so that the 27 dependent
+// launches only stage, apply the levels and write back (fd_levels).
+template <int K>
+__device__ __forceinline__ void fd_records(const DevParams &P, const FdLaunch &L, int64_t b,
+                                           unsigned char *lds, const FdArgs &A)
+{
+    const int CP = L.cap_p, CE = L.cap_e, tid = threadIdx.x;
+    const FdLds S(lds, CP);
+    const FdRange r = fd_range_of(L, b, A, false);
+    if (!r.ok) {   // schedule incomplete
+        if (tid == 0) atomicOr(A.err, ERR_PAIRCAP);
+        return;
+    }
+    for (int k = 0; k < r.R;) {
+        const FdBatch t = fd_next_batch(r, k, CP, CE);
+        k = t.k;
+        if (t.npr == 0) continue;
+        const RecPlanes rec{A.rec + 4 * (int64_t)t.e_begin, t.npr};
+        fd_load_indices(A, t, S);
+        int done = 0;        // records of the levels before lo
+        uint32_t ends = 0;
+        for (int lo = 1, hi; lo <= FD_NLVL; lo = hi + 1) {
+            const uint32_t incl = fd_sort_window(A, t, t.p_begin - r.phase_p0, S, CE, lo, hi);
+            const int ntot = min((int)lane_u32(incl, FD_NLVL - 1), CE);
+            if (tid + 1 >= lo) ends = (uint32_t)done + min(incl, (uint32_t)CE);
+            fd_form_records<K>(P, A, S, ntot, rec, done);
+            done += ntot;
+            if (!t.oversized) break;
         }
-        const uint32_t e_begin = s_eoff[k0], p_begin = s_poff[k0];
-        const int npr = (int)(s_eoff[k] - e_begin), np = (int)(s_poff[k] - p_begin);
-        if (npr == 0) continue;
-        const uint32_t rel0 = p_begin - phase_p0;   // list position of batch particle 0
-        // ---- global indices of the particles that take part in a pair
-        for (int base = 0; base < np; base += FD_PPL * FD_THREADS) {
-            uint32_t gl[FD_PPL];
-#pragma unroll
-            for (int r = 0; r < FD_PPL; ++r) {
-                const int l = base + r * FD_THREADS + tid;
-                gl[r] = l < np ? part_list[p_begin + l] : 0u;
-            }
-#pragma unroll
-            for (int r = 0; r < FD_PPL; ++r) {
-                const int l = base + r * FD_THREADS + tid;
-                if (l < np) s_gidx[l] = gl[r];
-            }
-        }
-        __syncthreads();
-        bool staged = false;   // momenta and energies of the batch in LDS
-        // ---- windows of levels (one window unless a single task overflows
-        //      the LDS pair list; then consecutive level ranges that fit)
-        int lo = 1;
-        while (lo <= FD_NLVL) {
-            int hi = FD_NLVL;
-            if (tid < FD_NLVL) s_hist[tid + 1] = 0u;
-            if (tid == 0) *s_maxlv = 0;
-            __syncthreads();
-            if (oversized) {
-                for (int e = tid; e < npr; e += FD_THREADS) {
-                    const int lv = (int)(pairs[e_begin + e] >> 50);
-                    if (lv >= 1 && lv <= FD_NLVL) atomicAdd(&s_hist[lv], 1u);
-                }
-                __syncthreads();
-                int acc = 0;
-                for (hi = lo; hi <= FD_NLVL; ++hi) {
-                    if (acc + (int)s_hist[hi] > CE) break;
-                    acc += (int)s_hist[hi];
-                }
-                --hi;
-                hi = hi < lo ? lo : hi;   // one level (<= 64 pairs) always fits
-                __syncthreads();
-                if (tid < FD_NLVL) s_hist[tid + 1] = 0u;
-                __syncthreads();
-            }
-            // counting sort of the batch's entries by level: histogram pass,
-            // prefix, scatter pass.  Entries stay in registers (FD_EPL per
-            // lane) between the passes unless the batch needs several passes.
-            constexpr int EP = FD_EPL * FD_THREADS;
-            uint64_t ebuf[FD_EPL];
-            const bool one_pass = npr <= EP;
-            for (int base = 0; base < npr; base += EP) {
-#pragma unroll
-                for (int r = 0; r < FD_EPL; ++r) {
-                    const int x = base + r * FD_THREADS + tid;
-                    ebuf[r] = x < npr ? pairs[e_begin + x] : 0ull;
-                }
-#pragma unroll
-                for (int r = 0; r < FD_EPL; ++r) {
-                    const uint64_t e = ebuf[r];
-                    const int lv = (int)(e >> 50);
-                    const int li = (int)((uint32_t)(e & POS_MASK) - rel0);
-                    const int lj = (int)((uint32_t)((e >> 25) & POS_MASK) - rel0);
-                    if (lv >= lo && lv <= hi && lv <= FD_NLVL && li >= 0 && li < np && lj >= 0 &&
-                        lj < np)
-                        atomicAdd(&s_hist[lv], 1u);
-                }
-            }
-            __syncthreads();
-            if (tid < 64) {   // exclusive prefix over levels (first wave): lane x holds level x + 1
-                const uint32_t h = s_hist[tid + 1];
-                uint32_t incl = h;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
-                    if (tid >= off) incl += v;
-                }
-                s_off[tid + 1] = incl - h;
-                s_cur[tid + 1] = incl - h;
-                const uint64_t nz = __ballot(h != 0u);
-                if (tid == 0) *s_maxlv = nz ? 64 - __clzll(nz) : 0;
-                if (tid == 63) *s_ntot = (int)incl;
-            }
-            __syncthreads();
-            for (int base = 0; base < npr; base += EP) {
-                if (!one_pass) {
-#pragma unroll
-                    for (int r = 0; r < FD_EPL; ++r) {
-                        const int x = base + r * FD_THREADS + tid;
-                        ebuf[r] = x < npr ? pairs[e_begin + x] : 0ull;
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < FD_EPL; ++r) {
-                    const uint64_t e = ebuf[r];
-                    const int lv = (int)(e >> 50);
-                    const int li = (int)((uint32_t)(e & POS_MASK) - rel0);
-                    const int lj = (int)((uint32_t)((e >> 25) & POS_MASK) - rel0);
-                    if (lv >= lo && lv <= hi && lv <= FD_NLVL && li >= 0 && li < np && lj >= 0 &&
-                        lj < np) {
-                        const uint32_t pos = atomicAdd(&s_cur[lv], 1u);
-                        if (pos < (uint32_t)CE) s_sorted[pos] = (uint32_t)li | ((uint32_t)lj << 16);
-                    }
-                }
-            }
-            __syncthreads();
-            // draws of the window's pairs in sorted order, all lanes busy; the
-            // ids also orient each entry (A side = smaller id)
-            {
-                const uint32_t step = (uint32_t)*dstep;   // step index of the Philox counter
-                const int ntot = min(*s_ntot, CE);
-                double *wdraws = draws + 4 * (int64_t)e_begin;
-                constexpr int DPL = 4;   // entries per lane per pass: id loads in flight
-                for (int base = 0; base < ntot; base += DPL * FD_THREADS) {
-                    uint32_t pr[DPL], ida[DPL], idb[DPL];
-#pragma unroll
-                    for (int r = 0; r < DPL; ++r) {
-                        const int e = base + r * FD_THREADS + tid;
-                        pr[r] = e < ntot ? s_sorted[e] : 0u;
-                        ida[r] = e < ntot ? id[s_gidx[pr[r] & 0xFFFFu]] : 0u;
-                        idb[r] = e < ntot ? id[s_gidx[pr[r] >> 16]] : 0u;
-                    }
-#pragma unroll
-                    for (int r = 0; r < DPL; ++r) {
-                        const int e = base + r * FD_THREADS + tid;
-                        if (e < ntot) {
-                            uint32_t i0 = ida[r], i1 = idb[r];
-                            if (i0 > i1) {
-                                s_sorted[e] = (pr[r] >> 16) | (pr[r] << 16);
-                                const uint32_t t = i0;
-                                i0 = i1;
-                                i1 = t;
-                            }
-                            double d[4];
-                            if (K == 2)   // mixed precision: FP32 Box-Muller
-                                pair_draws_f32(P, step, i0, i1, d);
-                            else
-                                pair_draws_stored(P, step, i0, i1, d);
-                            double2 *dst = reinterpret_cast<double2 *>(wdraws) + 2 * (int64_t)e;
-                            dst[0] = make_double2(d[0], d[1]);
-                            dst[1] = make_double2(d[2], d[3]);
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-            if (!staged) {
-                // ---- stage momenta and energies (after the wait for the
-                //      range's predecessors, on the first batch)
-                wait();
-                for (int base = 0; base < np; base += FD_PPL * FD_THREADS) {
-                    // SPL > 0: the loads of SPL particles issued before their
-                    // LDS writes (an LDS write between two atomic loads makes
-                    // the second wait for the first; plain loads the
-                    // compiler reorders by itself, SPL = 0)
-                    constexpr int SPB = SPL > 0 ? SPL : 1;
-#pragma unroll
-                    for (int r0 = 0; r0 < FD_PPL; r0 += SPB) {
-                        if (SPL == 0) {
-                            const int l = base + r0 * FD_THREADS + tid;
-                            if (l < np) {
-                                const int64_t g = s_gidx[l];
-                                s_p[l] = state_load<COHERENT>(p + g);
-                                s_p[CP + l] = state_load<COHERENT>(p + n + g);
-                                s_p[2 * CP + l] = state_load<COHERENT>(p + 2 * n + g);
-                                s_eps[l] = state_load<COHERENT>(eps + g);
-                            }
-                            continue;
-                        }
-                        double v[SPB][4];
-#pragma unroll
-                        for (int r = 0; r < SPB; ++r) {
-                            const int l = base + (r0 + r) * FD_THREADS + tid;
-                            if (l < np) {
-                                const int64_t g = s_gidx[l];
-                                v[r][0] = state_load<COHERENT>(p + g);
-                                v[r][1] = state_load<COHERENT>(p + n + g);
-                                v[r][2] = state_load<COHERENT>(p + 2 * n + g);
-                                v[r][3] = state_load<COHERENT>(eps + g);
-                            }
-                        }
-#pragma unroll
-                        for (int r = 0; r < SPB; ++r) {
-                            const int l = base + (r0 + r) * FD_THREADS + tid;
-                            if (l < np) {
-                                s_p[l] = v[r][0];
-                                s_p[CP + l] = v[r][1];
-                                s_p[2 * CP + l] = v[r][2];
-                                s_eps[l] = v[r][3];
-                            }
-                        }
-                    }
-                }
-                staged = true;
-                __syncthreads();
-            }
-            // level steps: (level, first sorted position) in ascending order;
-            // the read-only data of steps k + 1 and k + 2 is in flight while
-            // step k runs (the gathers only read LDS entries fixed above)
-            const int top = *s_maxlv;
-            const double *wdr = draws + 4 * (int64_t)e_begin;
-            // the step after (l, b): next FD_THREADS entries of level l, else
-            // the first entry of the next non-empty level (l > top: none)
-            auto advance = [&](int &l, int &b) {
-                b += FD_THREADS;
-                while (l <= top && b >= (int)(s_off[l] + s_hist[l])) {
-                    ++l;
-                    if (l <= top) b = (int)s_off[l];
-                }
-            };
-            auto fetch = [&](int l, int b, int &li, int &lj, PairGeo &g) {
-                bool v = false;
-                if (l <= top) {
-                    const int e = b + tid;
-                    v = e < (int)(s_off[l] + s_hist[l]);
-                    if (v) fd_gather(s_sorted, s_gidx, qrho, wdr, e, li, lj, g);
-                }
-                return v;
-            };
-            // the constants the pair update reads are held in vector registers
-            // for the level loop where they fit (VREG: the one-box kernels of
-            // the common case); otherwise they stay scalar loads from P
-            PairRegs pr;
-            if (VREG) {
-                for (int a = 0; a < 3; ++a) {
-                    pr.box[a] = P.box[a];
-                    pr.half_box[a] = P.half_box[a];
-                    __asm__ volatile("" : "+v"(pr.box[a]), "+v"(pr.half_box[a]));
-                }
-                pr.inv_Cv = P.inv_Cv;
-                pr.kB = P.kB;
-                pr.two_over_Cv = P.two_over_Cv;
-                pr.inv_m = P.inv_m;
-                pr.b2_c = P.b2_c;
-                pr.kperp_c = P.kperp_c;
-                pr.cF = P.cF;
-                __asm__ volatile("" : "+v"(pr.inv_Cv), "+v"(pr.kB), "+v"(pr.two_over_Cv),
-                                 "+v"(pr.inv_m), "+v"(pr.b2_c), "+v"(pr.kperp_c), "+v"(pr.cF));
-            }
-            int l0 = lo, b0 = (int)s_off[lo] - FD_THREADS;
-            advance(l0, b0);
-            int l1 = l0, b1 = b0;
-            advance(l1, b1);
-            PairGeo g0 = {}, g1 = {};
-            int li0 = 0, lj0 = 0, li1 = 0, lj1 = 0;
-            bool v0 = fetch(l0, b0, li0, lj0, g0);
-            bool v1 = fetch(l1, b1, li1, lj1, g1);
-            while (l0 <= top) {
-                int l2 = l1, b2 = b1;
-                advance(l2, b2);
-                PairGeo g2 = {};
-                int li2 = 0, lj2 = 0;
-                const bool v2 = fetch(l2, b2, li2, lj2, g2);
-                if (v0) {
-                    if (VREG)
-                        fd_pair<K != 0, K == 2>(P, pr, dt, li0, lj0, g0, s_p, CP, s_eps, cnt, negeps);
-                    else
-                        fd_pair<K != 0, K == 2>(P, P, dt, li0, lj0, g0, s_p, CP, s_eps, cnt, negeps);
-                }
-                __syncthreads();
-                g0 = g1;
-                li0 = li1;
-                lj0 = lj1;
-                v0 = v1;
-                l0 = l1;
-                g1 = g2;
-                li1 = li2;
-                lj1 = lj2;
-                v1 = v2;
-                l1 = l2;
-                b1 = b2;
-            }
-            lo = hi + 1;
-            if (!oversized) break;
-        }
-        // ---- write back momenta and energies
-        for (int l = tid; staged && l < np; l += FD_THREADS) {
-            const int64_t g = s_gidx[l];
-            state_store<COHERENT>(p + g, s_p[l]);
-            state_store<COHERENT>(p + n + g, s_p[CP + l]);
-            state_store<COHERENT>(p + 2 * n + g, s_p[2 * CP + l]);
-            state_store<COHERENT>(eps + g, s_eps[l]);
-        }
-        __syncthreads();
+        A.lvl[(r.T0 + t.k0) * FD_NLVL + tid] = (uint16_t)ends;
+    }
+}
+
+template <int K>
+__device__ __forceinline__ void fd_levels(const DevParams &P, const FdLaunch &L, int64_t b,
+                                          unsigned char *lds, const FdArgs &A, FdCount &cnt,
+                                          bool &negeps)
+{
+    const int CP = L.cap_p, CE = L.cap_e;
+    const FdLds S(lds, CP);
+    const FdRange r = fd_range_of(L, b, A, false);
+    if (!r.ok) return;   // reported by the record pass
+    for (int k = 0; k < r.R;) {
+        const FdBatch t = fd_next_batch(r, k, CP, CE);
+        k = t.k;
+        if (t.npr == 0) continue;
+        const RecPlanes rec{A.rec + 4 * (int64_t)t.e_begin, t.npr};
+        const int ends = (int)A.lvl[(r.T0 + t.k0) * FD_NLVL + threadIdx.x];
+        fd_load_indices(A, t, S);
+        fd_stage<false>(A, P.n, t.np, S);
+        fd_run_levels<K>(P, A.dt, ends, rec, S, cnt, negeps);
+        fd_write_back<false>(A, P.n, t.np, S);
     }
 }
 
@@ -539,17 +638,28 @@ __device__ __forceinline__ void fd_phase_body(const FdPhaseArgs &a, uint32_t blk
     FdCount cnt = {0u, 0u, 0u, 0u, 0u};
     bool negeps = false;
     auto no_wait = [] {};
-    fd_range<K, false, K != 0, 0>(*a.Pp, a.L, (int64_t)blk, lds, a.A, cnt, negeps, no_wait);
+    fd_range<K, false>(*a.Pp, a.L, (int64_t)blk, lds, a.A, cnt, negeps, no_wait);
     fd_flush_counters(cnt, negeps, a.counters, a.A.err);
 }
 template <int K>
-__global__ __launch_bounds__(FD_THREADS) void k_fd_phase(FdPhaseArgs a)
+__global__ __launch_bounds__(FD_THREADS) void k_fd_phase(FdPhaseArgs)
 {
-    fd_phase_body<K>(a, blockIdx.x);
+    fd_phase_body<K>(kernel_argument<FdPhaseArgs>(), blockIdx.x);
 }
 SDPD_MULTI_KERNEL(k_fd_phase_gen_multi, FdPhaseArgs, fd_phase_body<0>, FD_THREADS)
 SDPD_MULTI_KERNEL(k_fd_phase_fast_multi, FdPhaseArgs, fd_phase_body<1>, FD_THREADS)
 SDPD_MULTI_KERNEL(k_fd_phase_mix_multi, FdPhaseArgs, fd_phase_body<2>, FD_THREADS)
+
+// the same with the records already formed (k_fd_records)
+template <int K>
+__global__ __launch_bounds__(FD_THREADS) void k_fd_levels(FdPhaseArgs a)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    FdCount cnt = {0u, 0u, 0u, 0u, 0u};
+    bool negeps = false;
+    fd_levels<K>(*a.Pp, a.L, (int64_t)blockIdx.x, lds, a.A, cnt, negeps);
+    fd_flush_counters(cnt, negeps, a.counters, a.A.err);
+}
 
 // The whole sweep in one launch.  Its ranges, group by group (group 0 =
 // phase 0, then the groups of mutually disjoint phases; inside a group in
@@ -573,9 +683,22 @@ struct FdSweep {
 };
 constexpr uint64_t kWaitTicks = 20ull * 100000000ull;   // 20 s
 
+// The records of all ranges of the sweep, one workgroup per range.
+template <int K>
+__global__ __launch_bounds__(FD_THREADS) void k_fd_records(const DevParams *__restrict__ Pp,
+                                                           const FdSweep *__restrict__ SW,
+                                                           FdArgs A)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    const uint32_t it = blockIdx.x;
+    int g = 0;
+    while (it >= SW->group_end[g]) ++g;
+    fd_records<K>(*Pp, SW->launch[g], (int64_t)(it - (g > 0 ? SW->group_end[g - 1] : 0u)), lds, A);
+}
+
 // One range of the one-launch sweep: range b of group g, waiting until the
 // cells of its tasks have epoch g and setting them to g + 1 afterwards.
-template <int K, bool VREG, int SPL>
+template <int K>
 __device__ __forceinline__ void fd_flow_range(const DevParams &P, const FdLaunch &L, int g,
                                               int64_t b, const FdArgs &A, uint32_t *epoch,
                                               unsigned char *lds, FdCount &cnt, bool &negeps)
@@ -626,7 +749,7 @@ __device__ __forceinline__ void fd_flow_range(const DevParams &P, const FdLaunch
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     };
-    fd_range<K, true, VREG, SPL>(P, L, b, lds, A, cnt, negeps, wait);
+    fd_range<K, true>(P, L, b, lds, A, cnt, negeps, wait);
     // a range without pairs still orders its cells behind the predecessors
     wait();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -641,33 +764,38 @@ __device__ __forceinline__ void fd_flow_range(const DevParams &P, const FdLaunch
     }
 }
 
-template <int K>
-__global__ __launch_bounds__(FD_THREADS) void k_fd_sweep(const DevParams *__restrict__ Pp,
-                                                 const FdSweep *__restrict__ SW,
-                                                 const uint32_t *__restrict__ order, FdArgs A,
-                                                 uint32_t *work, uint32_t *epoch,
-                                                 unsigned long long *counters)
+struct FdSweepArgs {
+    const DevParams *Pp;
+    const FdSweep *SW;
+    const uint32_t *order;
+    FdArgs A;
+    uint32_t *work, *epoch;
+    unsigned long long *counters;
+};
+// W: waves per SIMD the registers are held to (see FD_WIDE_MIN).
+template <int K, int W>
+__global__ __launch_bounds__(FD_THREADS, W) void k_fd_sweep(FdSweepArgs)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ uint32_t s_item;
-    const DevParams &P = *Pp;
+    const FdSweepArgs &a = kernel_argument<FdSweepArgs>();
     const int tid = threadIdx.x;
     FdCount cnt = {0u, 0u, 0u, 0u, 0u};
     bool negeps = false;
-    const uint32_t nitems = SW->nitems;
     for (;;) {
-        if (tid == 0) s_item = atomicAdd(work, 1u);
+        const FdSweepArgs &b = reread(a);
+        if (tid == 0) s_item = atomicAdd(b.work, 1u);
         __syncthreads();
         const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_item);
-        if (it >= nitems) break;
+        const FdSweep &SW = reread(*b.SW);
+        if (it >= SW.nitems) break;
         int g = 0;
-        while (it >= SW->group_end[g]) ++g;
+        while (it >= SW.group_end[g]) ++g;
         // range index within group g
-        // batched state loads; the constants held in vector registers too
-        // where both fit in 256 VGPRs (the FP32-proposal kernel, K = 2)
-        fd_flow_range<K, K == 2, 2>(P, SW->launch[g], g, order[it], A, epoch, lds, cnt, negeps);
+        fd_flow_range<K>(*b.Pp, SW.launch[g], g, b.order[it], b.A, b.epoch, lds, cnt, negeps);
     }
-    fd_flush_counters(cnt, negeps, counters, A.err);
+    const FdSweepArgs &b = reread(a);
+    fd_flush_counters(cnt, negeps, b.counters, b.A.err);
 }
 
 // The one-launch sweep of many boxes (batched replicas, fused layout): the
@@ -718,7 +846,7 @@ __global__ __launch_bounds__(FD_THREADS) void k_fd_sweep_boxes(const FdBoxDesc *
         const uint32_t gbeg = g > 0 ? D.SW->group_end[g - 1] : 0u;
         FdCount cnt = {0u, 0u, 0u, 0u, 0u};
         bool negeps = false;
-        fd_flow_range<K, false, 0>(*D.Pp, D.SW->launch[g], g, D.order[gbeg + (it - row[lo])], D.A, D.epoch,
+        fd_flow_range<K>(*D.Pp, D.SW->launch[g], g, D.order[gbeg + (it - row[lo])], D.A, D.epoch,
                          lds, cnt, negeps);
         fd_flush_counters(cnt, negeps, D.counters, D.A.err);
     }
@@ -766,7 +894,13 @@ constexpr Allow kAllow[4] = {
     {14.7, 10.0, 25.2, 20.0, 1.0},    // edge
     {6.7, 5.0, 5.4, 4.5, 1.0},        // corner
 };
-constexpr int kDefaultTasks[4] = {8 * FD_WAVES, 8 * FD_WAVES, 16 * FD_WAVES, 24 * FD_WAVES};
+// Tasks of one range: enough that the level steps of a batch hold many pairs
+constexpr int kDefaultTasks[4] = {8, 8, 16, 24};
+// A sweep of at least FD_WIDE_MIN particles runs three waves per SIMD (168
+// registers, 13.6 KB of LDS a workgroup), a smaller one two: its chain gains
+// more from larger ranges (two against three waves, ms: 0.79 / 0.85 at 48^3,
+// 0.83 / 0.90 at 64^3, 1.05 / 1.04 at 80^3, 1.90 / 1.81 at 2^20).
+constexpr int64_t FD_WIDE_MIN = 400000;
 
 int round_up(double x, int q)
 {
@@ -797,6 +931,9 @@ void fd_class_caps(const sdpd_ctx *c, int k, int t, int &cp, int &ce)
 
 void fd_default_tuning(sdpd_ctx *c)
 {
+    c->fd_wide = c->n >= FD_WIDE_MIN;
+    // LDS share of one workgroup at that many waves per SIMD
+    c->lds_share = std::max(c->lds_cu / (c->fd_wide ? 12 : 8), 4096);
     for (int k = 0; k < 4; ++k) {
         int cp, ce;
         fd_class_caps(c, k, kDefaultTasks[k], cp, ce);
@@ -807,8 +944,13 @@ void fd_default_tuning(sdpd_ctx *c)
     if (c->max_lds > 65536) {
         // allow dynamic LDS beyond 64 KiB where the device has it
         const void *kerns[] = {(const void *)k_fd_phase<0>, (const void *)k_fd_phase<1>,
-                               (const void *)k_fd_phase<2>, (const void *)k_fd_sweep<0>,
-                               (const void *)k_fd_sweep<1>, (const void *)k_fd_sweep<2>,
+                               (const void *)k_fd_phase<2>, (const void *)k_fd_sweep<0, 2>,
+                               (const void *)k_fd_sweep<1, 2>, (const void *)k_fd_sweep<2, 2>,
+                               (const void *)k_fd_sweep<0, 3>, (const void *)k_fd_sweep<1, 3>,
+                               (const void *)k_fd_sweep<2, 3>,
+                               (const void *)k_fd_records<0>, (const void *)k_fd_records<1>,
+                               (const void *)k_fd_records<2>, (const void *)k_fd_levels<0>,
+                               (const void *)k_fd_levels<1>, (const void *)k_fd_levels<2>,
                                (const void *)k_fd_phase_gen_multi,
                                (const void *)k_fd_phase_fast_multi,
                                (const void *)k_fd_phase_mix_multi};
@@ -829,7 +971,7 @@ int fd_check_tuning(const sdpd_ctx *c, const sdpd_tuning *t)
         if (t->fd_tasks[k] < 1 || t->fd_tasks[k] > FD_MAXTASKS) return SDPD_EINVAL;
         if (t->fd_lds_particles[k] < 128 || t->fd_lds_particles[k] > 65535) return SDPD_EINVAL;
         if (t->fd_lds_pairs[k] < 64 || t->fd_lds_pairs[k] > (1 << 24)) return SDPD_EINVAL;
-        if (fd_lds_bytes(t->fd_lds_particles[k], t->fd_lds_pairs[k]) > (size_t)c->max_lds)
+        if (fd_lds_checked_bytes(t->fd_lds_particles[k], t->fd_lds_pairs[k]) > (size_t)c->max_lds)
             return SDPD_EINVAL;
     }
     return SDPD_OK;
@@ -904,6 +1046,14 @@ static int fd_kind(const sdpd_ctx *c)
     return fd_fast(c) ? (c->dp.mixed ? 2 : 1) : 0;
 }
 
+using SweepKernel = void (*)(FdSweepArgs);
+static SweepKernel fd_sweep_kernel(const sdpd_ctx *c)
+{
+    static const SweepKernel kern[2][3] = {{k_fd_sweep<0, 2>, k_fd_sweep<1, 2>, k_fd_sweep<2, 2>},
+                                           {k_fd_sweep<0, 3>, k_fd_sweep<1, 3>, k_fd_sweep<2, 3>}};
+    return kern[c->fd_wide][fd_kind(c)];
+}
+
 static FdArgs fd_args(const sdpd_ctx *c, const sdpd_state *s, double dt_fd)
 {
     FdArgs A;
@@ -919,7 +1069,10 @@ static FdArgs fd_args(const sdpd_ctx *c, const sdpd_state *s, double dt_fd)
     A.part_cap = (uint32_t)c->part_cap;
     A.dstep = c->dstep;
     A.dt = dt_fd;
-    A.draws = c->draws;
+    A.y_c = -2.0 * dt_fd * c->dp.inv_m * c->dp.kperp_c * c->dp.cF;
+    A.rec = reinterpret_cast<double2 *>(c->rec_buf);
+    A.rec_stride = 0;
+    A.lvl = c->lvl_end;
     A.err = c->err;
     return A;
 }
@@ -936,7 +1089,7 @@ bool fd_one_launch(const sdpd_ctx *c)
 
 // one launch per group
 static int launch_phases(sdpd_ctx *c, const sdpd_state *s, const int *phases, int nph,
-                         double dt_fd)
+                         double dt_fd, bool records)
 {
     FdLaunch L;
     const int64_t wg = fd_launch_geometry(c, phases, nph, L);
@@ -944,9 +1097,13 @@ static int launch_phases(sdpd_ctx *c, const sdpd_state *s, const int *phases, in
     if (wg > 0x7fffffffLL) return SDPD_EINVAL;
     const size_t lds = fd_lds_bytes(L.cap_p, L.cap_e);
     if (lds > (size_t)c->max_lds) return SDPD_EINVAL;
-    timer_begin(c, TK_FD);
     const FdPhaseArgs args{c->dparams, L, fd_args(c, s, dt_fd), c->counters};
     const int kind = fd_kind(c);
+    if (!records) {   // formed by k_fd_records
+        auto kern = kind == 2 ? k_fd_levels<2> : kind == 1 ? k_fd_levels<1> : k_fd_levels<0>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)wg), dim3(FD_THREADS), lds, c->stream, args);
+        return check_hip(hipGetLastError());
+    }
     const int rc =
         kind == 2 ? launch_or_record(c, k_fd_phase<2>, k_fd_phase_mix_multi, (unsigned)wg,
                                      FD_THREADS, lds, args)
@@ -954,7 +1111,6 @@ static int launch_phases(sdpd_ctx *c, const sdpd_state *s, const int *phases, in
                                        FD_THREADS, lds, args)
                     : launch_or_record(c, k_fd_phase<0>, k_fd_phase_gen_multi, (unsigned)wg,
                                        FD_THREADS, lds, args);
-    timer_end(c, TK_FD);
     return rc;
 }
 
@@ -1028,6 +1184,31 @@ static std::vector<uint32_t> fd_range_order(const sdpd_ctx *c, const FdSweep &h)
     return order;
 }
 
+// Record slices of the one-launch sweep's workgroups: in the context's record
+// buffer when they fit (large boxes), else in a buffer of their own.
+static int fd_flow_records(sdpd_ctx *c, const FdSweep &h)
+{
+    int64_t ce = 1;   // records of the largest batch of any range
+    for (int g = 0; g < h.ngroups; ++g) ce = std::max<int64_t>(ce, h.launch[g].cap_e);
+    c->sweep_rec_stride = 4 * ce;
+    const size_t need = sizeof(double2) * (size_t)c->sweep_rec_stride * (size_t)c->sweep_grid;
+    const bool own = need > c->rec_bytes;
+    if (c->flow_rec && (!own || c->flow_rec_bytes < need)) {
+        (void)hipFree(c->flow_rec);
+        c->flow_rec = nullptr;
+        c->flow_rec_bytes = 0;
+    }
+    if (own && !c->flow_rec) {
+        if (hipMalloc((void **)&c->flow_rec, need) != hipSuccess) {
+            c->flow_rec = nullptr;
+            (void)hipGetLastError();
+            return SDPD_ENOMEM;
+        }
+        c->flow_rec_bytes = need;
+    }
+    return SDPD_OK;
+}
+
 int fd_prepare_sweep(sdpd_ctx *c)
 {
     // the table and the order are rewritten in place: no sweep may be running
@@ -1077,9 +1258,7 @@ int fd_prepare_sweep(sdpd_ctx *c)
                                   hipMemcpyHostToDevice))))
         return rc;
     int per_cu = 0, cus = 0;
-    const int kind = fd_kind(c);
-    const void *kern = kind == 2 ? (const void *)k_fd_sweep<2>
-                       : kind == 1 ? (const void *)k_fd_sweep<1> : (const void *)k_fd_sweep<0>;
+    const void *kern = (const void *)fd_sweep_kernel(c);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, FD_THREADS, lds) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) !=
             hipSuccess || per_cu < 1 || cus < 1) {
@@ -1088,10 +1267,11 @@ int fd_prepare_sweep(sdpd_ctx *c)
     }
     c->sweep_lds = lds;
     c->sweep_grid = (int)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(total, 1));
-    // one launch when the sweep holds several GPU-fulls of ranges; a small box
-    // would mostly wait on its chain of 27 groups, and one launch per group
-    // then wastes no workgroup slots on waiting
-    c->fd_dataflow = total >= 4 * (int64_t)per_cu * cus;
+    if ((rc = fd_flow_records(c, h))) return rc;
+    // one launch when the sweep holds several GPU-fulls of ranges (at two waves
+    // per SIMD); a small box would mostly wait on its chain of 27 groups, and
+    // one launch per group then wastes no workgroup slots on waiting
+    c->fd_dataflow = total >= 4 * 8 * (int64_t)cus;
     c->sweep_ok = 1;
     return SDPD_OK;
 }
@@ -1142,6 +1322,7 @@ int fd_launch_sweep(sdpd_ctx *c, const sdpd_state *s, double dt_fd)
 {
     if (!c->sweep_ok) return SDPD_EINVAL;
     int rc;
+    const int kind = fd_kind(c);
     if (c->rec && c->fd_record_flow) {
         // fused batch: the epochs start at zero, then the sweep is recorded
         // as this box's part of one multi-box launch
@@ -1158,25 +1339,39 @@ int fd_launch_sweep(sdpd_ctx *c, const sdpd_state *s, double dt_fd)
         r.grid = 1;
         r.block = FD_THREADS;
         r.lds = c->sweep_lds;
-        r.flow_kind = fd_kind(c);
+        r.flow_kind = kind;
         r.args.resize(sizeof d);
         memcpy(r.args.data(), &d, sizeof d);
         c->rec->push_back(std::move(r));
         return SDPD_OK;
     }
     if (!fd_one_launch(c)) {
+        // records of the whole sweep first, where the context holds them all
+        // (a small box on its own; recorded launches share the GPU with other
+        // boxes, where forming the records in the launches is faster)
+        const bool whole = c->lvl_end && !c->rec && !c->fd_per_group;
+        timer_begin(c, TK_FD);
+        if (whole) {
+            auto kern = kind == 2 ? k_fd_records<2> : kind == 1 ? k_fd_records<1> : k_fd_records<0>;
+            hipLaunchKernelGGL(kern, dim3(c->sweep_group_end[c->sweep_ngroups - 1]),
+                               dim3(FD_THREADS), c->sweep_lds, c->stream, c->dparams,
+                               (const FdSweep *)c->sweep, fd_args(c, s, dt_fd));
+            if ((rc = check_hip(hipGetLastError()))) return rc;
+        }
         for (const std::vector<int> &g : fd_groups())
-            if ((rc = launch_phases(c, s, g.data(), (int)g.size(), dt_fd))) return rc;
+            if ((rc = launch_phases(c, s, g.data(), (int)g.size(), dt_fd, !whole))) return rc;
+        timer_end(c, TK_FD);
         return SDPD_OK;
     }
     // epochs of the cells and the range counter start at zero
     if ((rc = launch_fill_u32(c, c->epoch, 0u, c->ncell + 1))) return rc;
     timer_begin(c, TK_FD);
-    const int kind = fd_kind(c);
-    auto kern = kind == 2 ? k_fd_sweep<2> : kind == 1 ? k_fd_sweep<1> : k_fd_sweep<0>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)c->sweep_grid), dim3(FD_THREADS), c->sweep_lds, c->stream,
-                       c->dparams, (const FdSweep *)c->sweep, c->sweep_order, fd_args(c, s, dt_fd),
-                       c->epoch + c->ncell, c->epoch, c->counters);
+    FdArgs A = fd_args(c, s, dt_fd);
+    A.rec = reinterpret_cast<double2 *>(c->flow_rec ? c->flow_rec : c->rec_buf);
+    A.rec_stride = c->sweep_rec_stride;
+    hipLaunchKernelGGL(fd_sweep_kernel(c), dim3((unsigned)c->sweep_grid), dim3(FD_THREADS), c->sweep_lds, c->stream,
+                       FdSweepArgs{c->dparams, (const FdSweep *)c->sweep, c->sweep_order, A,
+                                   c->epoch + c->ncell, c->epoch, c->counters});
     timer_end(c, TK_FD);
     return check_hip(hipGetLastError());
 }
@@ -1191,12 +1386,14 @@ int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
     out.ngroups = ctxs[0]->sweep_ngroups;
     std::vector<FdBoxDesc> desc(nbox);
     out.lds = 0;
+    int64_t stride = 0;   // record slice of a workgroup: the largest of any box
     for (int b = 0; b < nbox; ++b) {
         if (recs[b]->flow_kind != out.kind || ctxs[b]->sweep_ngroups != out.ngroups ||
             recs[b]->args.size() != sizeof(FdBoxDesc))
             return SDPD_EINVAL;
         memcpy(&desc[b], recs[b]->args.data(), sizeof(FdBoxDesc));
         out.lds = std::max(out.lds, recs[b]->lds);
+        stride = std::max(stride, ctxs[b]->sweep_rec_stride);
     }
     // group-major item numbering: all boxes' ranges of group 0, then group 1, ...
     std::vector<uint32_t> off((size_t)out.ngroups * (nbox + 1));
@@ -1227,6 +1424,12 @@ int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
         return SDPD_EHIP;
     }
     out.grid = (unsigned)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(item, 1));
+    if (hipMalloc((void **)&out.rec, sizeof(double2) * (size_t)stride * out.grid) != hipSuccess)
+        return SDPD_ENOMEM;
+    for (FdBoxDesc &d : desc) {
+        d.A.rec = reinterpret_cast<double2 *>(out.rec);
+        d.A.rec_stride = stride;
+    }
     if (hipMalloc(&out.boxes, sizeof(FdBoxDesc) * nbox) != hipSuccess ||
         hipMalloc((void **)&out.item_off, sizeof(uint32_t) * off.size()) != hipSuccess ||
         hipMalloc((void **)&out.work, sizeof(uint32_t)) != hipSuccess)
@@ -1268,6 +1471,8 @@ void fd_flow_free(FlowSweep &f)
     if (f.boxes) (void)hipFree(f.boxes);
     if (f.item_off) (void)hipFree(f.item_off);
     if (f.work) (void)hipFree(f.work);
+    if (f.rec) (void)hipFree(f.rec);
+    f.rec = nullptr;
     f.boxes = nullptr;
     f.item_off = nullptr;
     f.work = nullptr;

@@ -14,16 +14,40 @@
 //   * sin(pi t), cos(pi t): t reduced by multiples of 1/2 to |r| <= 1/4,
 //     Taylor polynomials of sin(pi r) and cos(pi r) to degree 19 / 18, then a
 //     quarter-turn rotation.
-//   * reciprocal and reciprocal square root: the hardware estimate (relative
-//     error below 6e-8) and one second-order correction; sqrt: the
-//     reciprocal square root and one Newton correction of the product.
+//   * reciprocal, reciprocal square root and square root: the hardware
+//     estimate (relative error below 6e-8) and one second-order correction.
 //   * expm1: x = k ln 2 + r with |r| <= ln 2 / 2 (two-part ln 2), the Taylor
 //     polynomial of expm1(r) to degree 13 (its tail is below 2^-53 |r|), and
 //     expm1(x) = 2^k expm1(r) + (2^k - 1) in one fused step; for |x| <= ln 2 / 2
 //     k = 0 and the polynomial alone is the result.  When no active lane of
 //     a wave has |x| > 2^-5 the wave takes the Taylor polynomial of expm1(x)
 //     to degree 8 instead.
+// Every function with more than a few coefficients takes them from a table t
+// (any pointer to double): the device code passes tables in constant memory
+// (fd_math.hpp), the plain forms fd_* the same coefficients as literals.
 #pragma once
+
+// expm1: 1/13! ... 1/3!, 1/2; log2 e, ln 2 in two parts
+#define SDPD_EXPM1_COEF                                                                       \
+    1.6059043836821613e-10, 2.08767569878681e-09, 2.505210838544172e-08,                      \
+        2.755731922398589e-07, 2.7557319223985893e-06, 2.48015873015873e-05,                  \
+        0.0001984126984126984, 0.001388888888888889, 0.008333333333333333,                    \
+        0.041666666666666664, 0.16666666666666666, 0.5, 1.4426950408889634,                   \
+        0.6931471803691238, 1.9082149292705877e-10
+// log: 2/23, 2/21, ... 2/3; sqrt(1/2), ln 2 in two parts
+#define SDPD_LOG_COEF                                                                         \
+    0.08695652173913043, 0.09523809523809523, 0.10526315789473684, 0.11764705882352941,       \
+        0.13333333333333333, 0.15384615384615385, 0.18181818181818182, 0.2222222222222222,    \
+        0.2857142857142857, 0.4, 0.6666666666666666, 0.7071067811865476, 0.6931471803691238,  \
+        1.9082149292705877e-10
+// sin(pi r)/r in r^2 (r^21 down to r^1), then cos(pi r) in r^2 (r^18 down to r^2)
+#define SDPD_SINCOS_COEF                                                                      \
+    5.392664662608129e-10, -2.2948428997269873e-08, 7.952054001475513e-07,                    \
+        -2.1915353447830217e-05, 0.00046630280576761255, -0.0073704309457143504,              \
+        0.08214588661112823, -0.5992645293207921, 2.5501640398773455, -5.16771278004997,      \
+        3.141592653589793, -1.3878952462213771e-07, 4.303069587032947e-06,                    \
+        -0.0001046381049248457, 0.0019295743094039231, -0.02580689139001406,                  \
+        0.2353306303588932, -1.3352627688545895, 4.0587121264167685, -4.934802200544679
 
 namespace sdpd {
 
@@ -53,132 +77,134 @@ __device__ __forceinline__ double fast_rsq(double x)
 // values tolerate it
 __device__ __forceinline__ double fd_sqrt_pair(double x) { return x * fast_rsq(x); }
 
+// sqrt(x) from the estimate y and s = x y: with r = (1 - s y)/2, measured on
+// the rounded s, sqrt(x) = s (1 + r + 3 r^2/2) to order r^3, below one ulp
+// (half of the rounding of s remains)
 __device__ __forceinline__ double fd_sqrt(double x)
 {
-    const double y = fast_rsq(x);
+    const double y = __builtin_amdgcn_rsq(x);
     const double s = x * y;
-    return fma(0.5 * y, fma(-s, s, x), s);
+    const double r = fma(-s, 0.5 * y, 0.5);
+    return fma(s, r * fma(1.5, r, 1.0), s);
 }
 
-// expm1(x) for finite x with |x| < 700
-__device__ __forceinline__ double fd_expm1(double x)
+constexpr double kExpm1Coef[15] = {SDPD_EXPM1_COEF};
+constexpr double kLogCoef[14] = {SDPD_LOG_COEF};
+constexpr double kSinCosCoef[20] = {SDPD_SINCOS_COEF};
+
+// expm1(x) for finite x with |x| < 700 (t: the expm1 table)
+template <class T>
+__device__ __forceinline__ double elem_expm1(double x, T t)
 {
-    const double k = rint(x * 1.4426950408889634);
-    const double r = fma(-k, 1.9082149292705877e-10, fma(-k, 0.6931471803691238, x));
-    double p = 1.6059043836821613e-10;   // 1/13!
-    p = fma(p, r, 2.08767569878681e-09);   // 1/12!
-    p = fma(p, r, 2.505210838544172e-08);  // 1/11!
-    p = fma(p, r, 2.755731922398589e-07);  // 1/10!
-    p = fma(p, r, 2.7557319223985893e-06); // 1/9!
-    p = fma(p, r, 2.48015873015873e-05);   // 1/8!
-    p = fma(p, r, 0.0001984126984126984);  // 1/7!
-    p = fma(p, r, 0.001388888888888889);   // 1/6!
-    p = fma(p, r, 0.008333333333333333);   // 1/5!
-    p = fma(p, r, 0.041666666666666664);   // 1/4!
-    p = fma(p, r, 0.16666666666666666);    // 1/3!
-    p = fma(p, r, 0.5);
+    const double k = rint(x * t[12]);
+    const double r = fma(-k, t[14], fma(-k, t[13], x));
+    double p = t[0];
+#pragma unroll
+    for (int i = 1; i < 12; ++i) p = fma(p, r, t[i]);
     p = fma(p * r, r, r);                  // r + r^2 (1/2 + r/6 + ...)
-    const double t = ldexp(1.0, (int)k);
-    return fma(t, p, t - 1.0);
+    const double s = ldexp(1.0, (int)k);
+    return fma(s, p, s - 1.0);
 }
+__device__ __forceinline__ double fd_expm1(double x) { return elem_expm1(x, kExpm1Coef); }
 
 // expm1(x) for |x| <= 2^-5: its Taylor polynomial to x^8 (the first term
 // left out, x^9/9!, is below 2^-58 |x| there)
+template <class T>
+__device__ __forceinline__ double elem_expm1_small(double x, T t)
+{
+    double p = t[5];                       // 1/8!
+#pragma unroll
+    for (int i = 6; i < 12; ++i) p = fma(p, x, t[i]);
+    return fma(p * x, x, x);               // x + x^2 (1/2 + x/6 + ...)
+}
 __device__ __forceinline__ double fd_expm1_small(double x)
 {
-    double p = 2.48015873015873e-05;      // 1/8!
-    p = fma(p, x, 0.0001984126984126984);  // 1/7!
-    p = fma(p, x, 0.001388888888888889);   // 1/6!
-    p = fma(p, x, 0.008333333333333333);   // 1/5!
-    p = fma(p, x, 0.041666666666666664);   // 1/4!
-    p = fma(p, x, 0.16666666666666666);    // 1/3!
-    p = fma(p, x, 0.5);
-    return fma(p * x, x, x);               // x + x^2 (1/2 + x/6 + ...)
+    return elem_expm1_small(x, kExpm1Coef);
 }
 
 // expm1 with the short form when no active lane of the wave has |x| > 2^-5
-// (the friction exponents of a step of ordinary size), else fd_expm1
+// (the friction exponents of a step of ordinary size), else in full; the table
+// of the full form is asked for only where it runs
+template <class T, class Full>
+__device__ __forceinline__ double elem_expm1_wave(double x, T t, Full full)
+{
+    if (__ballot(fabs(x) > 0x1p-5) == 0ull) return elem_expm1_small(x, t);
+    return elem_expm1(x, full());
+}
 __device__ __forceinline__ double fd_expm1_wave(double x)
 {
-    if (__ballot(fabs(x) > 0x1p-5) == 0ull) return fd_expm1_small(x);
-    return fd_expm1(x);
+    return elem_expm1_wave(x, kExpm1Coef, [] { return kExpm1Coef; });
 }
 
-__device__ __forceinline__ double fd_log(double x)
+// log(x) (t: the log table)
+template <class T>
+__device__ __forceinline__ double elem_log(double x, T t)
 {
     int e;
     double m = frexp(x, &e);   // m in [0.5, 1)
-    const bool low = m < 0.7071067811865476;
+    const bool low = m < t[11];
     m = low ? 2.0 * m : m;
     e = low ? e - 1 : e;
     const double f = (m - 1.0) * fast_rcp(m + 1.0);
     const double s = f * f;
     // 2 atanh(f) = 2 f + f s (2/3 + 2/5 s + 2/7 s^2 + ... + 2/23 s^10)
-    double p = 0.08695652173913043;
-    p = fma(p, s, 0.09523809523809523);
-    p = fma(p, s, 0.10526315789473684);
-    p = fma(p, s, 0.11764705882352941);
-    p = fma(p, s, 0.13333333333333333);
-    p = fma(p, s, 0.15384615384615385);
-    p = fma(p, s, 0.18181818181818182);
-    p = fma(p, s, 0.2222222222222222);
-    p = fma(p, s, 0.2857142857142857);
-    p = fma(p, s, 0.4);
-    p = fma(p, s, 0.6666666666666666);
-    const double lm = fma(f * s, p, 2.0 * f);
+    double p = t[0];
+#pragma unroll
+    for (int i = 1; i < 11; ++i) p = fma(p, s, t[i]);
     const double de = (double)e;
-    return fma(de, 0.6931471803691238, fma(de, 1.9082149292705877e-10, lm));
+    return fma(de, t[12], fma(de, t[13], fma(f * s, p, 2.0 * f)));
 }
+__device__ __forceinline__ double fd_log(double x) { return elem_log(x, kLogCoef); }
 
 // log(1 + x) for x > -1
-__device__ __forceinline__ double fd_log1p(double x)
+template <class T>
+__device__ __forceinline__ double elem_log1p(double x, T t)
 {
     const double y = 1.0 + x;
     const double c = fabs(x) < 1.0 ? x - (y - 1.0) : 1.0 - (y - x);
-    return fd_log(y) + c * fast_rcp(y);
+    return elem_log(y, t) + c * fast_rcp(y);
 }
+__device__ __forceinline__ double fd_log1p(double x) { return elem_log1p(x, kLogCoef); }
 
-__device__ __forceinline__ void fd_sincospi_reduced(double r, double &s, double &c)
+// sin(pi a), cos(pi a) for 0 <= a <= 2 (t: the sine and cosine table)
+template <class T>
+__device__ __forceinline__ void elem_sincospi(double a, double &s, double &c, T t)
 {
+    const double k = rint(2.0 * a);   // quarter turns, 0..4
+    const double r = a - 0.5 * k;     // exact, |r| <= 1/4
     const double z = r * r;
-    double ps = -2.2948428997269873e-08;
-    ps = fma(ps, z, 7.952054001475513e-07);
-    ps = fma(ps, z, -2.1915353447830217e-05);
-    ps = fma(ps, z, 0.00046630280576761255);
-    ps = fma(ps, z, -0.0073704309457143504);
-    ps = fma(ps, z, 0.08214588661112823);
-    ps = fma(ps, z, -0.5992645293207921);
-    ps = fma(ps, z, 2.5501640398773455);
-    ps = fma(ps, z, -5.16771278004997);
-    ps = fma(ps, z, 3.141592653589793);
-    double pc = -1.3878952462213771e-07;
-    pc = fma(pc, z, 4.303069587032947e-06);
-    pc = fma(pc, z, -0.0001046381049248457);
-    pc = fma(pc, z, 0.0019295743094039231);
-    pc = fma(pc, z, -0.02580689139001406);
-    pc = fma(pc, z, 0.2353306303588932);
-    pc = fma(pc, z, -1.3352627688545895);
-    pc = fma(pc, z, 4.0587121264167685);
-    pc = fma(pc, z, -4.934802200544679);
-    pc = fma(pc, z, 1.0);
-    s = r * ps;
-    c = pc;
-}
-
-// sin(pi t), cos(pi t) for 0 <= t <= 2
-__device__ __forceinline__ void fd_sincospi(double t, double &s, double &c)
-{
-    const double k = rint(2.0 * t);   // quarter turns, 0..4
-    const double r = t - 0.5 * k;     // exact, |r| <= 1/4
-    double sr, cr;
-    fd_sincospi_reduced(r, sr, cr);
+    double ps = t[1], pc = t[11];
+#pragma unroll
+    for (int i = 2; i < 11; ++i) ps = fma(ps, z, t[i]);
+#pragma unroll
+    for (int i = 12; i < 20; ++i) pc = fma(pc, z, t[i]);
+    const double sr = r * ps, cr = fma(pc, z, 1.0);
     // quarter-turn rotation as selects (no branches): odd q swaps sin and
     // cos; sin changes sign for q = 2, 3 and cos for q = 1, 2
     const int q = ((int)k) & 3;
     const bool sw = (q & 1) != 0;
-    const double a = sw ? cr : sr, b = sw ? sr : cr;
-    s = (q & 2) ? -a : a;
-    c = ((q + 1) & 2) ? -b : b;
+    const double u = sw ? cr : sr, v = sw ? sr : cr;
+    s = (q & 2) ? -u : u;
+    c = ((q + 1) & 2) ? -v : v;
+}
+__device__ __forceinline__ void fd_sincospi(double t, double &s, double &c)
+{
+    elem_sincospi(t, s, c, kSinCosCoef);
+}
+
+// cos(pi a) alone for 0 <= a <= 2, as sin(pi r) with r = 1/2 - a or a - 3/2 in
+// [-1/2, 1/2] (exact for multiples of 2^-32): one polynomial, the Taylor series
+// of sin(pi r) to r^21 (tail below 2^-59), instead of the two that the
+// quarter-turn form selects from
+template <class T>
+__device__ __forceinline__ double elem_cospi(double a, T t)
+{
+    const double r = a <= 1.0 ? 0.5 - a : a - 1.5;
+    const double z = r * r;
+    double p = t[0];
+#pragma unroll
+    for (int i = 1; i < 11; ++i) p = fma(p, z, t[i]);
+    return r * p;
 }
 
 }  // namespace sdpd

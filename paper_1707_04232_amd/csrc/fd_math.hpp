@@ -8,6 +8,32 @@
 
 namespace sdpd {
 
+// ---------------------------------------------------------------- constants
+// The polynomial coefficients of the draws and of the pair update, as scalar
+// loads at the place that uses them.  Written as literals they are moved out of
+// the persistent loop of the sweep and held in registers for the whole kernel;
+// some 100 of them displaced what the level steps need (spills into vector
+// lanes, parameters read from memory inside the loop).  `cold` keeps the loads
+// below the point where it is called.
+typedef const __attribute__((address_space(4))) double ColdTable;
+__device__ __forceinline__ ColdTable *cold(const double *tab)
+{
+    ColdTable *c = (ColdTable *)tab;
+    __asm__ volatile("" : "+s"(c));
+    return c;
+}
+
+static __constant__ double kExpm1Tab[15] = {SDPD_EXPM1_COEF};
+static __constant__ double kLogTab[14] = {SDPD_LOG_COEF};
+constexpr int kDrawSinCos = 14;   // draws: the log table, then sine and cosine
+static __constant__ double kDrawTab[34] = {SDPD_LOG_COEF, SDPD_SINCOS_COEF};
+
+// expm1 of the friction exponents
+__device__ __forceinline__ double expm1_wave(double x, ColdTable *t)
+{
+    return elem_expm1_wave(x, t, [] { return cold(kExpm1Tab); });
+}
+
 // ---------------------------------------------------------------- Philox
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds, each two
 // 32x32->64 products with multipliers 0xD2511F53 and 0xCD9E8D57, key
@@ -32,27 +58,27 @@ __device__ __forceinline__ void philox4x32_10(uint32_t &x0, uint32_t &x1, uint32
 
 __device__ __forceinline__ double open_unit(uint32_t w)
 {
-    return ((double)w + 0.5) * 2.3283064365386962890625e-10;  // (w + 1/2) 2^-32
+    return fma((double)w, 0x1p-32, 0x1p-33);   // (w + 1/2) 2^-32, exact
 }
 
-// Gaussian vector (Box-Muller on the first block) and uniform of one pair
+// Gaussian vector (Box-Muller on the first block) and the word of the uniform
+// U = open_unit(u) of one pair
 __device__ __forceinline__ void pair_draws(const DevParams &P, uint32_t step, uint32_t id_i,
-                                           uint32_t id_j, double G[3], double &U)
+                                           uint32_t id_j, double G[3], uint32_t &u, ColdTable *t)
 {
 #pragma clang fp contract(fast)
     uint32_t a0 = step, a1 = id_i, a2 = id_j, a3 = P.replica * 2u;
     uint32_t b0 = step, b1 = id_i, b2 = id_j, b3 = P.replica * 2u + 1u;
     philox4x32_10(a0, a1, a2, a3, P.seed_lo, P.seed_hi);
     philox4x32_10(b0, b1, b2, b3, P.seed_lo, P.seed_hi);
-    const double R1 = fd_sqrt(-2.0 * fd_log(open_unit(a0)));
-    const double R2 = fd_sqrt(-2.0 * fd_log(open_unit(a2)));
-    double s1, c1, s3, c3;
-    fd_sincospi(2.0 * open_unit(a1), s1, c1);
-    fd_sincospi(2.0 * open_unit(a3), s3, c3);
+    const double R1 = fd_sqrt(-2.0 * elem_log(open_unit(a0), t));
+    const double R2 = fd_sqrt(-2.0 * elem_log(open_unit(a2), t));
+    double s1, c1;
+    elem_sincospi(2.0 * open_unit(a1), s1, c1, t + kDrawSinCos);
     G[0] = R1 * c1;
     G[1] = R1 * s1;
-    G[2] = R2 * c3;
-    U = open_unit(b0);
+    G[2] = R2 * elem_cospi(2.0 * open_unit(a3), t + kDrawSinCos);
+    u = b0;
 }
 
 // Mixed precision: the Gaussian vector from the same Philox words through
@@ -84,14 +110,14 @@ __device__ __forceinline__ void gauss3_f32(uint32_t a0, uint32_t a1, uint32_t a2
     G[2] = (double)(R2 * __builtin_amdgcn_cosf(t3));
 }
 __device__ __forceinline__ void pair_draws_f32(const DevParams &P, uint32_t step, uint32_t id_i,
-                                               uint32_t id_j, double out[4])
+                                               uint32_t id_j, double G[3], uint32_t &u)
 {
     uint32_t a0 = step, a1 = id_i, a2 = id_j, a3 = P.replica * 2u;
     uint32_t b0 = step, b1 = id_i, b2 = id_j, b3 = P.replica * 2u + 1u;
     philox4x32_10(a0, a1, a2, a3, P.seed_lo, P.seed_hi);
     philox4x32_10(b0, b1, b2, b3, P.seed_lo, P.seed_hi);
-    gauss3_f32(a0, a1, a2, a3, out);
-    out[3] = open_unit(b0);
+    gauss3_f32(a0, a1, a2, a3, G);
+    u = b0;
 }
 
 // ---------------------------------------------------------------- coefficients
@@ -102,34 +128,51 @@ __device__ __forceinline__ void pair_draws_f32(const DevParams &P, uint32_t step
 // to m kB T_red (1 - alpha^2)/(1 - d) with T_red = T_i T_j/(T_i + T_j), so
 // b^2 = (4 kB/m) T_red (1 - alpha^2)/(1 - d).  With e = expm1(-2 gamma dt/m):
 // alpha = 1 + e and 1 - alpha^2 = -e (2 + e), both without cancellation.
+// The constants of the pair update, held in vector registers by the level loop
+// (read once per batch): read from the parameters inside the loop they become
+// vector loads there, whose waits also hold up the prefetch of the records.
+template <bool MIX>
+struct PairRegs {
+    double inv_m, m_over_8, m_over_2, ent_c, d_c, b2_red;
+    ColdTable *tab;   // expm1
+    __device__ __forceinline__ PairRegs(const DevParams &P)
+        : inv_m(P.inv_m), m_over_8(P.m_over_8), m_over_2(P.m_over_2), ent_c(P.ent_c),
+          d_c(P.d_c), b2_red(P.b2_red), tab(cold(kExpm1Tab))
+    {
+        __asm__ volatile("" : "+v"(inv_m), "+v"(m_over_8), "+v"(m_over_2), "+v"(ent_c));
+        if (!MIX) __asm__ volatile("" : "+v"(d_c), "+v"(b2_red));
+    }
+};
+
 struct Coef {
-    double al_par, al_perp, b2_par, b2_perp;
+    double e_par, e_perp;   // alpha - 1
+    double q_par, q_perp;   // alpha^2 - 1 = e (2 + e)
+    double b2_par, b2_perp;
     double b_par, b_perp;   // square roots of b2 (set by fd_coef_f32 only)
 };
 
-// When zeta = 0 the parallel friction is exactly twice the perpendicular one,
-// and expm1(2y) = e (2 + e) with e = expm1(y) saves one exponential.
-// FAST = the common case fixed at compile time: EMS, Lucy kernel, zeta = 0
-template <bool FAST, class R>
-__device__ __forceinline__ Coef fd_coef(const DevParams &P, const R &pr, double kpar, double kperp,
-                                        double ei, double ej, double dt)
+// At energies of sum S and product Q (T_red = Q / (Cv S), d = (2 kB/Cv) Q/S^2)
+// and the pair's exponent y = -2 dt kappa_perp / m (that of d = 0).  When
+// zeta = 0 the parallel friction is exactly twice the perpendicular one, and
+// expm1(2x) = e (2 + e) with e = expm1(x) saves one exponential (and is also
+// q_perp).  FAST = the common case fixed at compile time: EMS, Lucy, zeta = 0
+template <bool FAST>
+__device__ __forceinline__ Coef fd_coef(const DevParams &P, const PairRegs<false> &c, double y, double S,
+                                        double Q)
 {
 #pragma clang fp contract(fast)
-    const double Ti = ei * pr.inv_Cv, Tj = ej * pr.inv_Cv;
-    const double inv_Ts = fast_rcp(Ti + Tj);
-    const double Tred = Ti * Tj * inv_Ts;
-    const double d = pr.kB * Tred * inv_Ts * pr.two_over_Cv;
-    const double omd = 1.0 - d;
-    const double c = -2.0 * dt * pr.inv_m * omd;
-    const double e_perp = fd_expm1_wave(c * kperp);
-    const double e_par =
-        (FAST || P.par_twice_perp) ? e_perp * (2.0 + e_perp) : fd_expm1_wave(c * kpar);
-    const double s = pr.b2_c * Tred * fast_rcp(omd);
+    const double inv_S = fast_rcp(S);
+    const double red = Q * inv_S;
+    const double omd = 1.0 - c.d_c * (red * inv_S);
+    const double ye = y * omd;
     Coef r;
-    r.al_par = 1.0 + e_par;
-    r.al_perp = 1.0 + e_perp;
-    r.b2_par = -s * e_par * (2.0 + e_par);
-    r.b2_perp = -s * e_perp * (2.0 + e_perp);
+    r.e_perp = expm1_wave(ye, c.tab);
+    r.q_perp = r.e_perp * (2.0 + r.e_perp);
+    r.e_par = (FAST || P.par_twice_perp) ? r.q_perp : expm1_wave(ye * P.kpar_over_kperp, c.tab);
+    r.q_par = r.e_par * (2.0 + r.e_par);
+    const double s = c.b2_red * red * fast_rcp(omd);
+    r.b2_par = -s * r.q_par;
+    r.b2_perp = -s * r.q_perp;
     return r;
 }
 
@@ -175,8 +218,10 @@ __device__ __forceinline__ Coef fd_coef_f32(const DevParams &P, float kperp, dou
     const float bp = __builtin_amdgcn_sqrtf(-s * e_par * (2.0f + e_par));
     const float bq = __builtin_amdgcn_sqrtf(-s * e_perp * (2.0f + e_perp));
     Coef r;
-    r.al_par = 1.0 + (double)e_par;
-    r.al_perp = 1.0 + (double)e_perp;
+    r.e_par = (double)e_par;
+    r.e_perp = (double)e_perp;
+    r.q_par = fma(r.e_par, r.e_par, 2.0 * r.e_par);
+    r.q_perp = fma(r.e_perp, r.e_perp, 2.0 * r.e_perp);
     r.b_par = (double)bp;
     r.b_perp = (double)bq;
     r.b2_par = r.b_par * r.b_par;
@@ -188,24 +233,67 @@ struct FdCount {
     uint32_t proposed, rej_energy, rej_ratio, marginal, negeps;
 };
 
-// Read-only data of one oriented pair (i = smaller id): positions,
-// densities and its random draws (Gaussian vector and uniform), gathered
-// from global memory one level step ahead of its use.
-struct PairGeo {
-    double xi, yi, zi, xj, yj, zj, rho_i, rho_j;
-    double G0, G1, G2, U;
+// Everything of one oriented pair (i = smaller id) that does not change
+// during a sweep: the unit vector e_ij, the exponent y = -2 dt kappa_perp/m
+// (mixed precision: kappa_perp itself, an FP32 value), the Gaussian vector,
+// the Philox word of the uniform and the pair's two places in the batch (i in
+// the low half).  Formed once per pair at full lane occupancy before the level
+// steps, where lanes idle: 64 bytes a pair, stored as four planes of 16 bytes
+// so that the lanes of a step read consecutive addresses.
+struct PairRec {
+    double ex, ey, ez, y, G0, G1, G2;
+    uint32_t u, ij;
 };
 
-// The draws of the pair (id_i < id_j) as stored for the sweep: G1, G2, G3, U
-__device__ __forceinline__ void pair_draws_stored(const DevParams &P, uint32_t step,
-                                                  uint32_t id_i, uint32_t id_j, double out[4])
+// separation component d = x_i - x_j to its minimum image: the same rounding
+// as adding the shift -+box where |d| > box/2 (k box is exact for |k| <= 1)
+__device__ __forceinline__ double nearest_image(double d, double box, double inv_box)
 {
-    double G[3], U;
-    pair_draws(P, step, id_i, id_j, G, U);
-    out[0] = G[0];
-    out[1] = G[1];
-    out[2] = G[2];
-    out[3] = U;
+    return fma(-rint(d * inv_box), box, d);
+}
+
+// K: 0 = general, 1 = EMS, Lucy, zeta = 0, 2 = that case with the FP32 proposal
+template <int K>
+__device__ __forceinline__ PairRec pair_record(const DevParams &P, double y_c, uint32_t step,
+                                               uint32_t id_i, uint32_t id_j, double4 a, double4 b,
+                                               ColdTable *t)
+{
+#pragma clang fp contract(fast)
+    // geometry (Sec. 2.1.1): r_ij, e_ij, F_ij
+    const double dx = nearest_image(a.x - b.x, P.box[0], P.inv_box[0]);
+    const double dy = nearest_image(a.y - b.y, P.box[1], P.inv_box[1]);
+    const double dz = nearest_image(a.z - b.z, P.box[2], P.inv_box[2]);
+    PairRec r;
+    if (K == 2) {
+        const float xf = (float)dx, yf = (float)dy, zf = (float)dz;
+        const float r2 = xf * xf + yf * yf + zf * zf;
+        const float inv_r = __builtin_amdgcn_rsqf(r2);
+        const float w = 1.0f - r2 * inv_r * P.inv_h_f;
+        r.ex = (double)(xf * inv_r);
+        r.ey = (double)(yf * inv_r);
+        r.ez = (double)(zf * inv_r);
+        // kappa_perp of Sec. 2.2.2 with Lucy's F
+        r.y = (double)(P.kperp_c_f * (P.cF_f * (w * w)) *
+                       __builtin_amdgcn_rcpf((float)(a.w * b.w)));
+    } else {
+        const double r2 = dx * dx + dy * dy + dz * dz;
+        const double inv_r = fast_rsq(r2);
+        r.ex = dx * inv_r;
+        r.ey = dy * inv_r;
+        r.ez = dz * inv_r;
+        const double x = r2 * inv_r * P.inv_h, w = 1.0 - x;
+        double F;   // over its prefactor cF, which y_c holds
+        if (K == 1 || P.kernel == SDPD_KERNEL_LUCY) F = w * w;
+        else F = x <= 0.5 ? 2.0 - 3.0 * x : P.h * (w * w) * inv_r;
+        r.y = y_c * F * fast_rcp(a.w * b.w);
+    }
+    double G[3];
+    if (K == 2) pair_draws_f32(P, step, id_i, id_j, G, r.u);   // FP32 Box-Muller
+    else pair_draws(P, step, id_i, id_j, G, r.u, t);
+    r.G0 = G[0];
+    r.G1 = G[1];
+    r.G2 = G[2];
+    return r;
 }
 
 // x - x^2/2 + x^3/3.  For |x| <= 1/2 the alternating series of log(1 + x)
@@ -213,7 +301,7 @@ __device__ __forceinline__ void pair_draws_stored(const DevParams &P, uint32_t s
 // most |x|^4 / (4 (1 - |x|))).
 __device__ __forceinline__ double log1p_cubic(double x)
 {
-    return x * (1.0 + x * (-0.5 + x * 0.3333333333333333));
+    return x * fma(x, fma(x, 0.3333333333333333, -0.5), 1.0);
 }
 
 // Brackets closer than this are decided with the logarithms evaluated: it
@@ -221,84 +309,62 @@ __device__ __forceinline__ double log1p_cubic(double x)
 // rounding of both evaluations (below 1e-13 for the values that occur).
 constexpr double kLazyMargin = 2e-9;
 
-// The parameters the pair update reads in its dependent chain (the box for
-// the minimum image, the constants of the coefficients), by the names of
-// DevParams: the update takes either DevParams itself or this copy, which
-// the level loop holds in vector registers (read once per batch), so that
-// no scalar load waits inside the loop.
-struct PairRegs {
-    double box[3], half_box[3];
-    double inv_Cv, kB, two_over_Cv, inv_m, b2_c, kperp_c, cF;
-};
-
-// One pair update; li has the smaller id.  Momenta (x, y, z planes at
-// stride ps) and energies are LDS-resident.  MIX (with FAST only): the
-// geometry and the proposal coefficients in FP32 (fd_coef_f32).
-template <bool FAST, bool MIX = false, class R = DevParams>
-__device__ __forceinline__ void fd_pair(const DevParams &P, const R &bx, double dt, int li,
-                                        int lj, const PairGeo &pg, double *s_p, int ps,
-                                        double *s_eps, FdCount &cnt, bool &negeps)
+// One pair update; the low half of g.ij has the smaller id.  The state of a particle is
+// (p_x, p_y, p_z, eps) in LDS.  K as in pair_record.
+//
+// The move is written in scalars of the pair: with v_par = v.e, the
+// perpendicular parts enter only through |v_perp|^2 = v^2 - v_par^2,
+// v_perp.G_perp = v.G - v_par G_par and |G_perp|^2 = G^2 - G_par^2, and every
+// difference is formed from e = alpha - 1, so that
+//   |v'|^2 - |v|^2 = sum_theta q |v|^2 + 2 alpha b (v.G) + b^2 |G|^2,
+//   v - alpha' v'  = -(E v + alpha' b G),  E = e + e' + e e' = alpha alpha' - 1
+// have no cancelling terms of order v^2 (the reverse move's quadratic form is
+// of order b^2).
+template <int K>
+__device__ __forceinline__ void fd_pair(const DevParams &P, const PairRegs<K == 2> &c, double dt,
+                                        const PairRec &g, double2 *s_st, FdCount &cnt,
+                                        bool &negeps)
 {
 #pragma clang fp contract(fast)
-    static_assert(!MIX || FAST, "the FP32 proposal covers EMS, Lucy's kernel, zeta = 0");
-    // geometry (Sec. 2.1.1): r_ij, e_ij, F_ij
-    const double dx = min_image(pg.xi - pg.xj, bx.box[0], bx.half_box[0]);
-    const double dy = min_image(pg.yi - pg.yj, bx.box[1], bx.half_box[1]);
-    const double dz = min_image(pg.zi - pg.zj, bx.box[2], bx.half_box[2]);
-    double ex, ey, ez, kpar = 0.0, kperp = 0.0;
-    float kperp_f = 0.0f;
-    if (MIX) {
-        const float xf = (float)dx, yf = (float)dy, zf = (float)dz;
-        const float r2 = xf * xf + yf * yf + zf * zf;
-        const float inv_r = __builtin_amdgcn_rsqf(r2);
-        const float t = 1.0f - r2 * inv_r * P.inv_h_f;
-        ex = (double)(xf * inv_r);
-        ey = (double)(yf * inv_r);
-        ez = (double)(zf * inv_r);
-        // kappa_perp of Sec. 2.2.2 with Lucy's F
-        kperp_f = P.kperp_c_f * (P.cF_f * (t * t)) *
-                  __builtin_amdgcn_rcpf((float)(pg.rho_i * pg.rho_j));
-    } else {
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        const double inv_r = fast_rsq(r2);
-        const double r = r2 * inv_r;
-        ex = dx * inv_r;
-        ey = dy * inv_r;
-        ez = dz * inv_r;
-        const double x = r * P.inv_h, t = 1.0 - x;
-        double F;
-        if (FAST || P.kernel == SDPD_KERNEL_LUCY) F = bx.cF * (t * t);
-        else F = x <= 0.5 ? bx.cF * (2.0 - 3.0 * x) : bx.cF * P.h * (t * t) * inv_r;
-        // kappa^theta of Sec. 2.2.2
-        const double kfac = F * fast_rcp(pg.rho_i * pg.rho_j);
-        kpar = P.kpar_c * kfac;
-        kperp = bx.kperp_c * kfac;
-    }
-
-    const double ei = s_eps[li], ej = s_eps[lj];
-    const double vx = (s_p[li] - s_p[lj]) * P.inv_m;
-    const double vy = (s_p[ps + li] - s_p[ps + lj]) * P.inv_m;
-    const double vz = (s_p[2 * ps + li] - s_p[2 * ps + lj]) * P.inv_m;
-
-    const double G[3] = {pg.G0, pg.G1, pg.G2};
+    constexpr bool FAST = K != 0, MIX = K == 2;
+    const uint32_t li = g.ij & 0xFFFFu, lj = g.ij >> 16;
+    const double2 i0 = s_st[2 * li], i1 = s_st[2 * li + 1];
+    const double2 j0 = s_st[2 * lj], j1 = s_st[2 * lj + 1];
+    const double px = i0.x - j0.x, py = i0.y - j0.y, pz = i1.x - j1.x;
+    const double ei = i1.y, ej = j1.y;
+    const double vpar = (px * g.ex + py * g.ey + pz * g.ez) * c.inv_m;
+    const double vG = (px * g.G0 + py * g.G1 + pz * g.G2) * c.inv_m;
+    const double v2 = (px * px + py * py + pz * pz) * (c.inv_m * c.inv_m);
+    const double Gpar = g.G0 * g.ex + g.G1 * g.ey + g.G2 * g.ez;
+    const double G2 = g.G0 * g.G0 + g.G1 * g.G1 + g.G2 * g.G2;
+    const double vv = vpar * vpar, vg = vpar * Gpar, gg = Gpar * Gpar;
+    // |v_perp|^2 = v^2 - (1 + z) v_par^2 with z = 1 - |e|^2, and so on: z is
+    // rounding (taken as 0) unless e_ij is an FP32 vector
+    const double z = MIX ? 1.0 - (g.ex * g.ex + g.ey * g.ey + g.ez * g.ez) : 0.0;
+    const double z1 = 1.0 + z;
+    const double vvq = MIX ? v2 - vv * z1 : v2 - vv;
+    const double vgq = MIX ? vG - vg * z1 : vG - vg;
+    const double ggq = MIX ? G2 - gg * z1 : G2 - gg;
 
     // proposal, eq. (proposal): v' = A(v) v + B(v) G, B = (2/m) zeta^theta P^theta
-    const Coef f = MIX ? fd_coef_f32(P, kperp_f, ei, ej, (float)dt)
-                       : fd_coef<FAST>(P, bx, kpar, kperp, ei, ej, dt);
+    const double S = ei + ej, Q = ei * ej;
+    auto coef = [&](double a, double b, double sum, double product) -> Coef {
+        if constexpr (MIX) return fd_coef_f32(P, (float)g.y, a, b, (float)dt);
+        else return fd_coef<FAST>(P, c, g.y, sum, product);
+    };
+    const Coef f = coef(ei, ej, S, Q);
     const double b_par = MIX ? f.b_par : fd_sqrt(f.b2_par);
     const double b_perp = MIX ? f.b_perp : fd_sqrt(f.b2_perp);
-    const double vpar = vx * ex + vy * ey + vz * ez;
-    const double Gpar = G[0] * ex + G[1] * ey + G[2] * ez;
-    const double vqx = vx - vpar * ex, vqy = vy - vpar * ey, vqz = vz - vpar * ez;
-    const double Gqx = G[0] - Gpar * ex, Gqy = G[1] - Gpar * ey, Gqz = G[2] - Gpar * ez;
-    const double npar = f.al_par * vpar + b_par * Gpar;
-    const double nqx = f.al_perp * vqx + b_perp * Gqx;
-    const double nqy = f.al_perp * vqy + b_perp * Gqy;
-    const double nqz = f.al_perp * vqz + b_perp * Gqz;
-    const double nvx = npar * ex + nqx, nvy = npar * ey + nqy, nvz = npar * ez + nqz;
     // energy change, eq. (proposal-update)
-    const double delta = P.m_over_8 * ((nvx * nvx + nvy * nvy + nvz * nvz)
-                                       - (vx * vx + vy * vy + vz * vz));
+    const double ab_par = b_par + f.e_par * b_par, ab_perp = b_perp + f.e_perp * b_perp;
+    double dv2 = (f.q_par * vv + (2.0 * ab_par) * vg + f.b2_par * gg) +
+                 (f.q_perp * vvq + (2.0 * ab_perp) * vgq + f.b2_perp * ggq);
+    if (MIX) {   // |e| != 1: the parts of v' along e and across it are not orthogonal
+        const double n_par = vpar + (f.e_par * vpar + b_par * Gpar);
+        const double n_perp = vpar + (f.e_perp * vpar + b_perp * Gpar);
+        dv2 += z * (2.0 * n_par * n_perp - n_par * n_par - vv);
+    }
+    const double delta = c.m_over_8 * dv2;
     const double emin = fmin(ei, ej);
     bool accept = true;
     cnt.proposed += 1;
@@ -315,27 +381,25 @@ __device__ __forceinline__ void fd_pair(const DevParams &P, const R &bx, double 
         } else if (FAST || P.fd == SDPD_FD_EMS) {
             // reverse move from v' at the proposed energies, eq. (metropolis-ratio)
             const double ei2 = ei - delta, ej2 = ej - delta;
-            const Coef g = MIX ? fd_coef_f32(P, kperp_f, ei2, ej2, (float)dt)
-                               : fd_coef<FAST>(P, bx, kpar, kperp, ei2, ej2, dt);
-            const double wpar = vpar - g.al_par * npar;
-            const double wqx = vqx - g.al_perp * nqx;
-            const double wqy = vqy - g.al_perp * nqy;
-            const double wqz = vqz - g.al_perp * nqz;
+            const Coef r = coef(ei2, ej2, ei2 + ej2, ei2 * ej2);
+            const double E_par = f.e_par + (r.e_par + f.e_par * r.e_par);
+            const double E_perp = f.e_perp + (r.e_perp + f.e_perp * r.e_perp);
+            const double c_par = b_par + r.e_par * b_par, c_perp = b_perp + r.e_perp * b_perp;
+            const double w_par = E_par * vpar + c_par * Gpar;
+            const double ww_perp =
+                (E_perp * E_perp) * vvq + c_perp * ((2.0 * E_perp) * vgq + c_perp * ggq);
             // one reciprocal serves both inverse variances and the determinant
-            // ratio: inv = 1/(b'_par^2 b'_perp^2)
-            const double inv = fast_rcp(g.b2_par * g.b2_perp);
-            const double quad = wpar * wpar * (g.b2_perp * inv)
-                                + (wqx * wqx + wqy * wqy + wqz * wqz) * (g.b2_par * inv);
-            const double G2 = G[0] * G[0] + G[1] * G[1] + G[2] * G[2];
-            const double A = 0.5 * G2 - 0.5 * quad;
+            // ratio, inv = 1/(b'_par^2 b'_perp^2), and the energies' 1/Q
+            const double bb = r.b2_par * r.b2_perp, inv_all = fast_rcp(bb * Q);
+            const double inv = inv_all * Q;
+            const double quad = (w_par * w_par * r.b2_perp + ww_perp * r.b2_par) * inv;
+            const double A = 0.5 * (G2 - quad);
             // log|B(v)| - log|B(v')| = (1/2) log Dr, Dr = b_par^2 b_perp^4 / (b'_par^2 b'_perp^4)
-            const double Dr = (f.b2_par * f.b2_perp * f.b2_perp) * (g.b2_par * (inv * inv));
+            const double Dr = (f.b2_par * f.b2_perp * f.b2_perp) * (r.b2_par * (inv * inv));
             // ideal gas: sum_k (S(eps'_k) - S(eps_k))/kB - log T(eps'_k) + log T(eps_k)
             //          = (Cv/kB - 1) log(1 + w), 1 + w = (1 - delta/ei)(1 - delta/ej)
-            const double inv_eiej = fast_rcp(ei * ej);
-            const double ui = -delta * ej * inv_eiej, uj = -delta * ei * inv_eiej;
-            const double w = ui + uj + ui * uj;
-            const double U = pg.U;
+            const double w = delta * (delta - S) * (inv_all * bb);
+            const double U = open_unit(g.u);
             // a = A + logdet + ent is compared with log U (reject iff U > exp(a)).
             // Both are first bracketed with the cubic bounds of log1p_cubic;
             // the logarithms are evaluated only when the brackets come within
@@ -345,8 +409,8 @@ __device__ __forceinline__ void fd_pair(const DevParams &P, const R &bx, double 
             const double xd = Dr - 1.0, xu = U - 1.0;
             if (fabs(xd) <= 0.5 && fabs(w) <= 0.5) {
                 const double xd2 = xd * xd, w2 = w * w;
-                const double am = A + 0.5 * log1p_cubic(xd) + P.ent_c * log1p_cubic(w);
-                const double ar = 0.25 * xd2 * xd2 + 0.5 * fabs(P.ent_c) * w2 * w2;
+                const double am = A + 0.5 * log1p_cubic(xd) + c.ent_c * log1p_cubic(w);
+                const double ar = 0.25 * xd2 * xd2 + 0.5 * fabs(c.ent_c) * w2 * w2;
                 double lu_lo, lu_hi;
                 if (xu >= -0.5) {
                     const double xu2 = xu * xu;
@@ -366,10 +430,11 @@ __device__ __forceinline__ void fd_pair(const DevParams &P, const R &bx, double 
                 }
             }
             if (evaluate) {
-                const double logdet = 0.5 * fd_log(Dr);
-                const double ent = P.ent_c * fd_log1p(w);
+                ColdTable *t = cold(kLogTab);
+                const double logdet = 0.5 * elem_log(Dr, t);
+                const double ent = c.ent_c * elem_log1p(w, t);
                 const double a = A + logdet + ent;
-                const double lnU = fd_log(U);
+                const double lnU = elem_log(U, t);
                 if (fabs(a - lnU) <= 1e-9) cnt.marginal += 1;
                 if (!(lnU <= a)) {
                     accept = false;
@@ -379,16 +444,16 @@ __device__ __forceinline__ void fd_pair(const DevParams &P, const R &bx, double 
         }
     }
     if (accept) {
-        const double hm = P.m_over_2;
-        const double dpx = hm * (nvx - vx), dpy = hm * (nvy - vy), dpz = hm * (nvz - vz);
-        s_p[li] += dpx;
-        s_p[ps + li] += dpy;
-        s_p[2 * ps + li] += dpz;
-        s_p[lj] -= dpx;
-        s_p[ps + lj] -= dpy;
-        s_p[2 * ps + lj] -= dpz;
-        s_eps[li] = ei - delta;
-        s_eps[lj] = ej - delta;
+        // dp = (m/2)(v' - v): along e, along v (in momentum units) and along G
+        const double ke = c.m_over_2 * ((f.e_par - f.e_perp) * vpar + (b_par - b_perp) * Gpar);
+        const double kp = 0.5 * f.e_perp, kg = c.m_over_2 * b_perp;
+        const double dpx = ke * g.ex + (kp * px + kg * g.G0);
+        const double dpy = ke * g.ey + (kp * py + kg * g.G1);
+        const double dpz = ke * g.ez + (kp * pz + kg * g.G2);
+        s_st[2 * li] = make_double2(i0.x + dpx, i0.y + dpy);
+        s_st[2 * li + 1] = make_double2(i1.x + dpz, ei - delta);
+        s_st[2 * lj] = make_double2(j0.x - dpx, j0.y - dpy);
+        s_st[2 * lj + 1] = make_double2(j1.x - dpz, ej - delta);
     }
 }
 

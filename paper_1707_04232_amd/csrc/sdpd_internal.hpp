@@ -41,7 +41,7 @@ constexpr int FD_MAXTASKS = FD_THREADS;   // tasks per workgroup range of the F/
 // on the host.
 struct DevParams {
     int64_t n;
-    double box[3], half_box[3], inv_cell[3];
+    double box[3], inv_cell[3];
     int nc[3];
     int64_t ncell;
     double m, inv_m, h, h2, inv_h, kB, Cv, inv_Cv, A;
@@ -54,8 +54,10 @@ struct DevParams {
     double eps_exp;     // A kB / Cv (constant-entropy exponent)
     double kpar_c;      // (10/3 eta + 4 zeta) m^2
     double kperp_c;     // (5/3 eta - zeta) m^2
-    double two_over_Cv; // 1/C_i + 1/C_j
-    double b2_c;        // 4 kB / m
+    double d_c;         // kB (1/C_i + 1/C_j) = 2 kB / Cv
+    double b2_red;      // 4 kB / (m Cv)
+    double kpar_over_kperp;
+    double inv_box[3];
     double ent_c;       // Cv/kB - 1
     double m_over_8, m_over_2;
     int par_twice_perp;     // kpar_c == 2 kperp_c exactly (zeta = 0)
@@ -164,11 +166,19 @@ struct sdpd_ctx {
     int fd_swept;                // a schedule has been built (sdpd_fd_schedule_size)
     sdpd_tuning tuning;          // F/D workgroup sizes and LDS capacities per phase class
     int max_lds;                 // LDS bytes one workgroup may use
-    int lds_share;               // LDS bytes of one sweep workgroup at two waves per SIMD
+    int lds_cu;                  // LDS bytes of a CU
+    int lds_share;               // ... and of one sweep workgroup at its waves per SIMD
+    int fd_wide;                 // the one-launch sweep runs three waves per SIMD (else two)
     // pair schedule (rebuilt before every sweep)
     uint32_t *task_count, *task_np, *pair_off, *part_off, *part_list;
     uint64_t *pairs;
-    double *draws;               // 4 per pair entry: the sweep's random draws in sorted order
+    double *rec_buf;             // pair records, 64 B each: of one group of the sweep (32 per
+                                 // particle), or of a whole one (64 per particle, with lvl_end)
+    size_t rec_bytes = 0;
+    uint16_t *lvl_end = nullptr; // small boxes: ends of a batch's levels (64), at its first task
+    double *flow_rec = nullptr;  // record slices of the one-launch sweep that rec_buf cannot hold
+    size_t flow_rec_bytes = 0;
+    int64_t sweep_rec_stride = 0;   // 16-byte units of one slice
     void *sweep = nullptr;       // device table of the sweep kernel (fd.hip)
     uint32_t *sweep_order = nullptr;   // hand-out order of the ranges inside each group
     int tune_gen = 0;            // counts sdpd_tune calls (captured batches check it)
@@ -233,6 +243,7 @@ struct FlowSweep {
     void *boxes = nullptr;          // device: the boxes' descriptors
     uint32_t *item_off = nullptr;   // device: ngroups x (nbox + 1) first items
     uint32_t *work = nullptr;       // device: the range counter
+    void *rec = nullptr;            // device: the workgroups' record slices
 };
 int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
                   const std::vector<const RecordedLaunch *> &recs, FlowSweep &out);
@@ -278,15 +289,6 @@ int launch_or_record(sdpd_ctx *c, void (*single)(A), MultiKernel multi, unsigned
 
 // --------------------------------------------------------------- device helpers
 namespace sdpd {
-
-// minimum-image component (pairs within h never straddle half a box since
-// every box length is at least 4 h)
-__device__ __forceinline__ double min_image(double d, double box, double half)
-{
-    if (d > half) return d - box;
-    if (d < -half) return d + box;
-    return d;
-}
 
 // neighbour cell k (offset index 0..26, z slowest) of cell (cx, cy, cz) and
 // the periodic shift that turns x_i - x_j into the minimum image for it
