@@ -236,7 +236,9 @@ int sdpd_timing(sdpd_ctx *ctx, double ms[6], int64_t launches[6]);
  * equal to 0 in sdpd_tune keep the current value, and a negative LDS field
  * selects the capacities the defaults give the class's (new) task count
  * (sdpd_tune waits for the context's stream first); sdpd_get_tuning reports
- * the values in use (the defaults scale with the mean particles per cell).
+ * the values in use (the defaults follow the number of cells and the mean
+ * particles per cell; a context that was never tuned takes its share of a
+ * batch's launches with defaults of the batch).
  * SDPD_EINVAL for out-of-range values; nothing is changed then.          */
 typedef struct {
     int32_t fd_tasks[4];
@@ -309,7 +311,8 @@ int sdpd_batch_create(sdpd_ctx *const *ctxs, const sdpd_state *states, int nbox,
  *                      own step, taken from device tables), the launches of
  *                      fd_every steps captured in a graph; the boxes are
  *                      dealt into `parts` parts of about equal particle
- *                      count (<= 0: min(GPU_MAX_HW_QUEUES, 16)), each with
+ *                      count (<= 0: one fewer than GPU_MAX_HW_QUEUES, 1 to
+ *                      16: the batch's own stream takes a queue), each with
  *                      its own graph and stream, which run side by side;
  *                      ~50 launches per part and step for any number of
  *                      boxes.  Boxes of any size, precision and scheme.

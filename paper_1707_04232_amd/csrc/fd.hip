@@ -894,8 +894,14 @@ constexpr Allow kAllow[4] = {
     {14.7, 10.0, 25.2, 20.0, 1.0},    // edge
     {6.7, 5.0, 5.4, 4.5, 1.0},        // corner
 };
-// Tasks of one range: enough that the level steps of a batch hold many pairs
+// Tasks of one range: enough that the level steps of a batch hold many pairs ...
 constexpr int kDefaultTasks[4] = {8, 8, 16, 24};
+// ... unless a group then has fewer ranges than the GPU has slots to run them:
+// below these ranges per group (own cell, face, edge, corner) a box is bound
+// by the chain of 27 groups, which shorter ranges shorten (one-launch sweeps,
+// ms, at 1 / 4 / 8 tasks: 0.61 / 0.65 / 0.70 for 32^3 particles, 1.23 / 0.74 /
+// 0.79 for 48^3, 2.73 / 0.88 / 0.81 for 64^3).
+constexpr int kGroupRanges[4] = {1700, 850, 600, 512};
 // A sweep of at least FD_WIDE_MIN particles runs three waves per SIMD (168
 // registers, 13.6 KB of LDS a workgroup), a smaller one two: its chain gains
 // more from larger ranges (two against three waves, ms: 0.79 / 0.85 at 48^3,
@@ -929,17 +935,42 @@ void fd_class_caps(const sdpd_ctx *c, int k, int t, int &cp, int &ce)
     }
 }
 
+// tasks per range t (about) of class k with the LDS capacities that go with it;
+// a task of a box with dense cells has more pairs, as the density squared, and
+// a range fewer tasks
+static void fd_set_class(const sdpd_ctx *c, sdpd_tuning &u, int k, int t)
+{
+    const double s = c->ncell > 0 ? ((double)c->n / (double)c->ncell) / 17.5 : 1.0;
+    if (s > 1.0) t = (int)std::lround(t / (s * s));
+    t = std::min(std::max(t, 1), FD_MAXTASKS);
+    int cp, ce;
+    fd_class_caps(c, k, t, cp, ce);
+    u.fd_tasks[k] = t;
+    u.fd_lds_particles[k] = cp;
+    u.fd_lds_pairs[k] = ce;
+}
+
+sdpd_tuning fd_batch_tuning(const sdpd_ctx *c, int64_t total)
+{
+    sdpd_tuning u;
+    // many boxes share each launch, which ends with its slowest range: the
+    // defaults, twice them where a launch holds several GPU-fulls of ranges
+    // (ms per step at 8 / 16 tasks, cells of 17.5: 2.6 / 3.4 for 16 replica
+    // boxes, 5.3 / 5.6 for 64, 18.0 / 16.6 for 192)
+    for (int k = 0; k < 4; ++k)
+        fd_set_class(c, u, k, kDefaultTasks[k] * (total > ((int64_t)1 << 21) ? 2 : 1));
+    return u;
+}
+
 void fd_default_tuning(sdpd_ctx *c)
 {
     c->fd_wide = c->n >= FD_WIDE_MIN;
     // LDS share of one workgroup at that many waves per SIMD
     c->lds_share = std::max(c->lds_cu / (c->fd_wide ? 12 : 8), 4096);
     for (int k = 0; k < 4; ++k) {
-        int cp, ce;
-        fd_class_caps(c, k, kDefaultTasks[k], cp, ce);
-        c->tuning.fd_tasks[k] = kDefaultTasks[k];
-        c->tuning.fd_lds_particles[k] = cp;
-        c->tuning.fd_lds_pairs[k] = ce;
+        const int64_t tasks = k == 0 ? c->ncell : c->ncell / 2;   // of a group of class k
+        const int64_t fit = std::max<int64_t>(tasks / kGroupRanges[k], 1);
+        fd_set_class(c, c->tuning, k, (int)std::min<int64_t>(kDefaultTasks[k], fit));
     }
     if (c->max_lds > 65536) {
         // allow dynamic LDS beyond 64 KiB where the device has it
@@ -1268,10 +1299,11 @@ int fd_prepare_sweep(sdpd_ctx *c)
     c->sweep_lds = lds;
     c->sweep_grid = (int)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(total, 1));
     if ((rc = fd_flow_records(c, h))) return rc;
-    // one launch when the sweep holds several GPU-fulls of ranges (at two waves
-    // per SIMD); a small box would mostly wait on its chain of 27 groups, and
-    // one launch per group then wastes no workgroup slots on waiting
-    c->fd_dataflow = total >= 4 * 8 * (int64_t)cus;
+    // one launch when the sweep holds at least three GPU-fulls of ranges (at
+    // two waves per SIMD; boxes of some 450 cells); a smaller one mostly waits
+    // on its chain of 27 groups, and one launch per group then holds no
+    // workgroup slots while it waits
+    c->fd_dataflow = total >= 3 * 8 * (int64_t)cus;
     c->sweep_ok = 1;
     return SDPD_OK;
 }
@@ -1376,6 +1408,46 @@ int fd_launch_sweep(sdpd_ctx *c, const sdpd_state *s, double dt_fd)
     return check_hip(hipGetLastError());
 }
 
+// A box's range table and hand-out order for a launch shared with other boxes:
+// those of its batch tuning, in buffers of the launch's own (the context keeps
+// its tables for sweeps on its own).
+static int fd_flow_tables(sdpd_ctx *c, int64_t total, FdBoxDesc &d, size_t &lds, int64_t &stride,
+                          uint32_t *group_end, FlowSweep &out)
+{
+    const sdpd_tuning saved = c->tuning;
+    const bool own = c->tune_gen == 0;
+    int rc = SDPD_OK;
+    if (own) {
+        c->tuning = fd_batch_tuning(c, total);
+        rc = fd_prepare_sweep(c);
+    }
+    if (!rc) {
+        memcpy(group_end, c->sweep_group_end, sizeof c->sweep_group_end);
+        lds = c->sweep_lds;
+        stride = c->sweep_rec_stride;
+    }
+    if (!rc && own) {
+        const size_t bytes[2] = {sizeof(FdSweep),
+                                 sizeof(uint32_t) * (size_t)group_end[c->sweep_ngroups - 1]};
+        const void *src[2] = {c->sweep, c->sweep_order};
+        void *dst[2] = {nullptr, nullptr};
+        for (int k = 0; k < 2 && !rc; ++k) {
+            if (hipMalloc(&dst[k], bytes[k] ? bytes[k] : 4) != hipSuccess) rc = SDPD_ENOMEM;
+            else out.tables.push_back(dst[k]);
+            if (!rc && bytes[k])
+                rc = check_hip(hipMemcpy(dst[k], src[k], bytes[k], hipMemcpyDeviceToDevice));
+        }
+        d.SW = (const FdSweep *)dst[0];
+        d.order = (const uint32_t *)dst[1];
+    }
+    if (own) {
+        c->tuning = saved;
+        const int rc2 = fd_prepare_sweep(c);
+        rc = rc ? rc : rc2;
+    }
+    return rc;
+}
+
 int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
                   const std::vector<const RecordedLaunch *> &recs, FlowSweep &out)
 {
@@ -1385,15 +1457,22 @@ int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
     out.nbox = nbox;
     out.ngroups = ctxs[0]->sweep_ngroups;
     std::vector<FdBoxDesc> desc(nbox);
+    std::vector<uint32_t> ends((size_t)nbox * FD_MAXGROUPS);
     out.lds = 0;
-    int64_t stride = 0;   // record slice of a workgroup: the largest of any box
+    int64_t stride = 0, total = 0;   // record slice of a workgroup: the largest of any box
+    for (sdpd_ctx *c : ctxs) total += c->n;
     for (int b = 0; b < nbox; ++b) {
         if (recs[b]->flow_kind != out.kind || ctxs[b]->sweep_ngroups != out.ngroups ||
             recs[b]->args.size() != sizeof(FdBoxDesc))
             return SDPD_EINVAL;
         memcpy(&desc[b], recs[b]->args.data(), sizeof(FdBoxDesc));
-        out.lds = std::max(out.lds, recs[b]->lds);
-        stride = std::max(stride, ctxs[b]->sweep_rec_stride);
+        size_t lds = 0;
+        int64_t st = 0;
+        const int rc = fd_flow_tables(ctxs[b], total, desc[b], lds, st,
+                                      &ends[(size_t)b * FD_MAXGROUPS], out);
+        if (rc) return rc;
+        out.lds = std::max(out.lds, lds);
+        stride = std::max(stride, st);
     }
     // group-major item numbering: all boxes' ranges of group 0, then group 1, ...
     std::vector<uint32_t> off((size_t)out.ngroups * (nbox + 1));
@@ -1402,7 +1481,7 @@ int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
         for (int b = 0; b <= nbox; ++b) {
             off[(size_t)g * (nbox + 1) + b] = (uint32_t)item;
             if (b < nbox) {
-                const uint32_t *ge = ctxs[b]->sweep_group_end;
+                const uint32_t *ge = &ends[(size_t)b * FD_MAXGROUPS];
                 item += ge[g] - (g > 0 ? ge[g - 1] : 0u);
                 if (item > 0x7fffffffull) return SDPD_EINVAL;
             }
@@ -1473,6 +1552,8 @@ void fd_flow_free(FlowSweep &f)
     if (f.work) (void)hipFree(f.work);
     if (f.rec) (void)hipFree(f.rec);
     f.rec = nullptr;
+    for (void *t : f.tables) (void)hipFree(t);
+    f.tables.clear();
     f.boxes = nullptr;
     f.item_off = nullptr;
     f.work = nullptr;

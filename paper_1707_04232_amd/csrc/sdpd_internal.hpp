@@ -227,6 +227,9 @@ int fd_sweep_prepare(sdpd_ctx *c, const sdpd_state *s, bool packed);
 int fd_launch_sweep(sdpd_ctx *c, const sdpd_state *s, double dt_fd);
 int enqueue_step(sdpd_ctx *c, const sdpd_state *s, uint64_t step, bool set_step);
 void fd_default_tuning(sdpd_ctx *c);
+// the tuning of a box whose launches are shared with other boxes (`total`
+// particles in all), unless the caller has tuned it
+sdpd_tuning fd_batch_tuning(const sdpd_ctx *c, int64_t total);
 // LDS capacities (particles, pair entries) the defaults give phase class k
 // at t tasks per workgroup
 void fd_class_caps(const sdpd_ctx *c, int k, int t, int &cp, int &ce);
@@ -244,6 +247,7 @@ struct FlowSweep {
     uint32_t *item_off = nullptr;   // device: ngroups x (nbox + 1) first items
     uint32_t *work = nullptr;       // device: the range counter
     void *rec = nullptr;            // device: the workgroups' record slices
+    std::vector<void *> tables;     // device: range tables and orders of the boxes
 };
 int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
                   const std::vector<const RecordedLaunch *> &recs, FlowSweep &out);
