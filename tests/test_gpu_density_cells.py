@@ -1,0 +1,48 @@
+"""Density, masks and forces at the edges of the cell-wise passes: few cells (a
+workgroup per cell, a wave per particle) and many (a wave per cell, a lane per
+particle), empty cells, cells of more than 32 particles (two mask words) and
+nearly full ones.  The forces are sums over the masks, so a wrong bit shows in
+them.  FP64 against the oracle as in the other parity tests (1e-12 of the largest
+value); mixed precision rho within 2e-5 (FP32 separations, see the tests there)."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1707_04232_amd.workload import uniform_state
+
+pytestmark = pytest.mark.gpu
+
+# (particles, box): cells of edge 2.5 = h, 1024 and 1152 of them (the former is
+# the largest box with a workgroup per cell), dilute or with 36 particles a cell
+BOXES = {
+    "dilute_1024_cells": (3001, (20.0, 20.0, 40.0)),
+    "dilute_1152_cells": (3001, (20.0, 20.0, 45.0)),
+    "dense_64_cells": (2450, (10.0, 10.0, 10.0)),
+    "dense_1152_cells": (41003, (20.0, 20.0, 45.0)),
+    "few_particles": (5, (10.0, 15.0, 10.0)),
+}
+
+
+@pytest.mark.parametrize("name", list(BOXES))
+@pytest.mark.parametrize("form", ["lucy", "cubic", "mixed"])
+def test_cell_edges(name, form):
+    from paper_1707_04232_amd import sdpd
+    n, box = BOXES[name]
+    print("[case]", name, form, flush=True)
+    q, p, eps, ids = uniform_state(n, box, seed=7)
+    edges = [np.linspace(0.0, b, int(round(b / 2.5)) + 1) for b in box]
+    full = int(np.histogramdd(np.asarray(q).reshape(3, n).T, bins=edges)[0].max())
+    assert full <= 64 and (full > 48 or not name.startswith("dense"))
+    kernel = 1 if form == "cubic" else 0
+    S = sdpd.DeviceState.from_numpy(q, p, eps, ids)
+    with sdpd.Context(sdpd.SdpdParams(n=n, box=box, kernel=kernel,
+                                      prec=1 if form == "mixed" else 0)) as ctx:
+        ctx.prepare(S)
+        ctx.sync()
+    R = O.State.from_arrays(q, p, eps, ids)
+    O.prepare(O.OracleParams(n=n, box=box, kernel=kernel), R)
+    G = S.to_numpy()
+    assert np.array_equal(G["id"], R.id)
+    assert np.abs(G["rho"] - R.rho).max() <= (2e-5 if form == "mixed" else 1e-12) * R.rho.max()
+    if form != "mixed":
+        assert np.abs(G["f"] - R.f).max() <= 1e-12 * max(np.abs(R.f).max(), 1e-300)
