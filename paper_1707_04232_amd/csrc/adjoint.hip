@@ -45,7 +45,7 @@
 #include <utility>
 #include <vector>
 
-#include "sdpd_internal.hpp"
+#include "neighbours.hpp"
 
 namespace sdpd {
 
@@ -62,7 +62,8 @@ struct AdjointWork {
     double *lq = nullptr, *lp = nullptr, *G = nullptr, *H = nullptr;   // id order
     double *Ge = nullptr, *He = nullptr;   // final-energy path (id order)
     double *eps0 = nullptr, *rho0 = nullptr;                             // id order
-    double *vc = nullptr, *wc = nullptr, *pibar = nullptr, *rhobar = nullptr;   // cell order
+    double4 *v4 = nullptr;       // (v, Pi), cell order
+    double *rhobar = nullptr;    // cell order
     uint32_t *idcount = nullptr;
     std::vector<void *> owned;
 };
@@ -125,26 +126,6 @@ __global__ void k_count_ids(int64_t n, const uint32_t *id, uint32_t *count, uint
     if (atomicAdd(&count[i], 1u) != 0u) atomicOr(err, ERR_IDS);
 }
 
-// dst (cell order) = scale * src (id order), ncomp planes
-__global__ void k_gather_id(int64_t n, int ncomp, const uint32_t *id, double scale,
-                            const double *src, double *dst)
-{
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int64_t i = id[k];
-    for (int c = 0; c < ncomp; ++c) dst[c * n + k] = scale * src[c * n + i];
-}
-
-// dst (id order) += weight * src (cell order); each id appears once
-__global__ void k_scatter_add_id(int64_t n, int ncomp, const uint32_t *id, double weight,
-                                 const double *src, double *dst)
-{
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int64_t i = id[k];
-    for (int c = 0; c < ncomp; ++c) dst[c * n + i] += weight * src[c * n + k];
-}
-
 __global__ void k_axpy(int64_t len, double a, const double *x, double *y)
 {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -158,128 +139,120 @@ __global__ void k_to_id(int64_t n, const uint32_t *id, const double *src, double
     if (k < n) dst[id[k]] = src[k];
 }
 
-__device__ __forceinline__ double kernel_F(const DevParams &P, double r)
+// v = (h lp, Pi) per particle in cell order
+__global__ void k_pack_v(DevParams P, const uint32_t *id, const double *lp, const double *eps,
+                         const double *rho, double4 *v4)
 {
-    const double x = r * P.inv_h, t = 1.0 - x;
-    if (P.kernel == SDPD_KERNEL_LUCY) return P.cF * (t * t);
-    if (x <= 0.5) return P.cF * (2.0 - 3.0 * x);
-    return P.cF * P.h * (t * t) / r;
+    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= P.n) return;
+    const int64_t i = id[k];
+    const double h = 0.5 * P.dt;
+    double4 r;
+    r.x = h * lp[i];
+    r.y = h * lp[P.n + i];
+    r.z = h * lp[2 * P.n + i];
+    r.w = P.cPi * eps[k] / rho[k];
+    v4[k] = r;
 }
 
-// dF/dr
-__device__ __forceinline__ double kernel_dF(const DevParams &P, double r)
+// rhobar into the w slots of the position records (id: rhobar in id order)
+__global__ void k_pack_rhobar(int64_t n, const uint32_t *id, const double *rhobar, double *q4)
 {
-    const double x = r * P.inv_h;
-    if (P.kernel == SDPD_KERNEL_LUCY) return -2.0 * P.cF * (1.0 - x) * P.inv_h;
-    if (x <= 0.5) return -3.0 * P.cF * P.inv_h;
-    return -P.cF * P.h * (1.0 - x * x) / (r * r);
+    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n) q4[4 * k + 3] = rhobar[id ? id[k] : k];
 }
 
-// pibar, rhobar (cell order); G, H accumulate (id order) with the weight
-__global__ __launch_bounds__(256) void k_vjp_pi(DevParams P, const double *__restrict__ q,
-                                                const double *__restrict__ v,
-                                                const double *__restrict__ eps,
-                                                const double *__restrict__ rho,
-                                                const uint32_t *__restrict__ id,
-                                                const uint32_t *__restrict__ cell_sorted,
-                                                const uint32_t *__restrict__ cell_start,
-                                                const uint64_t *__restrict__ masks,
-                                                double weight, double *pibar, double *rhobar,
-                                                double *G, double *H)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P.n) return;
-    const int64_t n = P.n;
-    const uint32_t c = cell_sorted[i];
-    const int cx = (int)(c % (uint32_t)P.nc[0]);
-    const int cy = (int)((c / (uint32_t)P.nc[0]) % (uint32_t)P.nc[1]);
-    const int cz = (int)(c / ((uint32_t)P.nc[0] * (uint32_t)P.nc[1]));
-    const double xi = q[i], yi = q[n + i], zi = q[2 * n + i];
-    const double vx = v[i], vy = v[n + i], vz = v[2 * n + i];
-    double acc = 0.0;
-    for (int k = 0; k < 27; ++k) {
-        uint64_t mask = masks[(int64_t)k * n + i];
-        if (!mask) continue;
-        const NbCell nb = neighbour_cell(P, cx, cy, cz, k);
-        const uint32_t s = cell_start[nb.c];
-        while (mask) {
-            const uint32_t j = s + (uint32_t)__builtin_ctzll(mask);
-            mask &= mask - 1ull;
-            const double dx = (xi - q[j]) + nb.sx;
-            const double dy = (yi - q[n + j]) + nb.sy;
-            const double dz = (zi - q[2 * n + j]) + nb.sz;
-            const double r = sqrt(dx * dx + dy * dy + dz * dz);
-            const double ru = dx * (vx - v[j]) + dy * (vy - v[n + j]) + dz * (vz - v[2 * n + j]);
-            acc += kernel_F(P, r) * ru;
+// F (r . u)
+template <bool LUCY>
+struct PiTerm {
+    const DevParams &P;
+    const double4 *__restrict__ v4;
+    double4 v;
+    __device__ __forceinline__ void at(int64_t i) { v = v4[i]; }
+    __device__ __forceinline__ void operator()(uint32_t j, const double4 &, const double4 &,
+                                               const double d[3], double r2, double out[1]) const
+    {
+        const double4 u = v4[j];
+        const double ru = d[0] * (v.x - u.x) + d[1] * (v.y - u.y) + d[2] * (v.z - u.z);
+        out[0] = ModelF64::force<LUCY>(P, r2) * ru;
+    }
+};
+
+// m^2 (Pi_i + Pi_j) [F u + (F'/r)(r . u) r] - m (rhobar_i + rhobar_j) F r over cF;
+// without the first part if !FORCE
+template <bool LUCY, bool FORCE>
+struct QTerm {
+    const DevParams &P;
+    const double4 *__restrict__ v4;
+    double4 v;
+    __device__ __forceinline__ void at(int64_t i) { if (FORCE) v = v4[i]; }
+    __device__ __forceinline__ void operator()(uint32_t j, const double4 &qi, const double4 &qj,
+                                               const double d[3], double r2, double out[3]) const
+    {
+        // r^2 + DBL_MIN: r^2 for every distinct pair; finite, and times zero, for r = 0
+        const double y = fast_rsq(r2 + DBL_MIN), x = r2 * y * P.inv_h, t = 1.0 - x;
+        double F, dFr;   // F, F'/r
+        if (LUCY) {
+            F = t * t;
+            dFr = -2.0 * t * P.inv_h * y;
+        } else if (x <= 0.5) {
+            F = 2.0 - 3.0 * x;
+            dFr = -3.0 * P.inv_h * y;
+        } else {
+            F = P.h * (t * t) * y;
+            dFr = -P.h * (1.0 - x * x) * (y * y) * y;
+        }
+        const double sr = -P.m * (qi.w + qj.w) * F;
+        for (int c = 0; c < 3; ++c) out[c] = sr * d[c];
+        if (FORCE) {
+            const double4 vj = v4[j];
+            const double u[3] = {v.x - vj.x, v.y - vj.y, v.z - vj.z};
+            const double Pij = P.m * P.m * (v.w + vj.w);
+            const double ru = (d[0] * u[0] + d[1] * u[1] + d[2] * u[2]) * dFr;
+            for (int c = 0; c < 3; ++c) out[c] += Pij * (F * u[c] + ru * d[c]);
         }
     }
-    const double pb = P.m * P.m * acc;
-    const double Pi = P.cPi * eps[i] / rho[i];
-    pibar[i] = pb;
-    rhobar[i] = pb * (P.eps_exp - 1.0) * Pi / rho[i];
+};
+
+// rhobar (cell order, also into the w slots of q4); G, H accumulate (id order) with
+// the weight
+template <bool LUCY>
+__global__ __launch_bounds__(256) void k_vjp_pi(PartnerArgs a, const double4 *v4,
+                                                const double *__restrict__ rho,
+                                                const uint32_t *__restrict__ id, double weight,
+                                                double *rhobar, double *q4, double *G, double *H)
+{
+    const DevParams &P = a.P;
+    bool live;
+    const int64_t i = partner_particle<ModelF64>(P, xcd_block(blockIdx.x, gridDim.x), live);
+    const int lane = threadIdx.x & 63;
+    PartnerSums<ModelF64, 1, PiTerm<LUCY>> sums{a, P, nullptr, lane,
+                                                (uint32_t)lane % ModelF64::kLanes};
+    const double acc = sums.run(i, live, PiTerm<LUCY>{P, v4, double4()});
+    if (!live || sums.s != 0u) return;
+    const double pb = P.m * P.m * P.cF * acc, Pi = v4[i].w;
+    const double rb = pb * (P.eps_exp - 1.0) * Pi / rho[i];
+    rhobar[i] = rb;
+    q4[4 * i + 3] = rb;
     const int64_t g = id[i];
     G[g] += weight * pb * Pi;
     H[g] += weight * pb * Pi * log(rho[i]);
 }
 
-// qbar (cell order): the force term (with_force) and the density term
-__global__ __launch_bounds__(256) void k_vjp_q(DevParams P, const double *__restrict__ q,
-                                               const double *__restrict__ v,
-                                               const double *__restrict__ eps,
-                                               const double *__restrict__ rho,
-                                               const double *__restrict__ rhobar,
-                                               const uint32_t *__restrict__ cell_sorted,
-                                               const uint32_t *__restrict__ cell_start,
-                                               const uint64_t *__restrict__ masks,
-                                               int with_force, double *w)
+// lq (id order) += weight * qbar: the density term, and the force term (FORCE)
+template <bool LUCY, bool FORCE>
+__global__ __launch_bounds__(256) void k_vjp_q(PartnerArgs a, const double4 *v4,
+                                               const uint32_t *__restrict__ id, double weight,
+                                               double *lq)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P.n) return;
-    const int64_t n = P.n;
-    const uint32_t c = cell_sorted[i];
-    const int cx = (int)(c % (uint32_t)P.nc[0]);
-    const int cy = (int)((c / (uint32_t)P.nc[0]) % (uint32_t)P.nc[1]);
-    const int cz = (int)(c / ((uint32_t)P.nc[0] * (uint32_t)P.nc[1]));
-    const double xi = q[i], yi = q[n + i], zi = q[2 * n + i];
-    const double vx = with_force ? v[i] : 0.0, vy = with_force ? v[n + i] : 0.0,
-                 vz = with_force ? v[2 * n + i] : 0.0;
-    const double Pii = P.cPi * eps[i] / rho[i];
-    const double rbi = rhobar[i];
-    const double m2 = P.m * P.m;
-    double wx = 0.0, wy = 0.0, wz = 0.0;
-    for (int k = 0; k < 27; ++k) {
-        uint64_t mask = masks[(int64_t)k * n + i];
-        if (!mask) continue;
-        const NbCell nb = neighbour_cell(P, cx, cy, cz, k);
-        const uint32_t s = cell_start[nb.c];
-        while (mask) {
-            const uint32_t j = s + (uint32_t)__builtin_ctzll(mask);
-            mask &= mask - 1ull;
-            const double dx = (xi - q[j]) + nb.sx;
-            const double dy = (yi - q[n + j]) + nb.sy;
-            const double dz = (zi - q[2 * n + j]) + nb.sz;
-            const double r = sqrt(dx * dx + dy * dy + dz * dz);
-            const double F = kernel_F(P, r);
-            // density term: -m (rhobar_i + rhobar_j) F r
-            double sx = -P.m * (rbi + rhobar[j]) * F;
-            double tx = sx * dx, ty = sx * dy, tz = sx * dz;
-            if (with_force) {
-                const double ux = vx - v[j], uy = vy - v[n + j], uz = vz - v[2 * n + j];
-                const double Pij = m2 * (Pii + P.cPi * eps[j] / rho[j]);
-                const double dFr = kernel_dF(P, r) / r;
-                const double ru = dx * ux + dy * uy + dz * uz;
-                tx += Pij * (F * ux + dFr * ru * dx);
-                ty += Pij * (F * uy + dFr * ru * dy);
-                tz += Pij * (F * uz + dFr * ru * dz);
-            }
-            wx += tx;
-            wy += ty;
-            wz += tz;
-        }
-    }
-    w[i] = wx;
-    w[n + i] = wy;
-    w[2 * n + i] = wz;
+    const DevParams &P = a.P;
+    bool live;
+    const int64_t i = partner_particle<ModelF64>(P, xcd_block(blockIdx.x, gridDim.x), live);
+    const int lane = threadIdx.x & 63;
+    PartnerSums<ModelF64, 3, QTerm<LUCY, FORCE>> sums{a, P, nullptr, lane,
+                                                      (uint32_t)lane % ModelF64::kLanes};
+    const double w = sums.run(i, live, QTerm<LUCY, FORCE>{P, v4, double4()});
+    if (live && sums.s < 3u) lq[sums.s * P.n + id[i]] += weight * (P.cF * w);
 }
 
 // cotangents of the final energies and densities (id order, either may be
@@ -326,21 +299,22 @@ static int vjp_config(sdpd_ctx *c, AdjointWork *a, const sdpd_state &Ws, double 
     int rc;
     if ((rc = run_build_cells(c, &Ws, 0))) return rc;
     if ((rc = run_density(c, &Ws, 0))) return rc;
-    const double h = 0.5 * c->prm.dt;
-    hipLaunchKernelGGL(k_gather_id, dim3(nblk(n)), dim3(256), 0, c->stream, n, 3, Ws.id, h, a->lp,
-                       a->vc);
-    hipLaunchKernelGGL(k_vjp_pi, dim3(nblk(n)), dim3(256), 0, c->stream, c->dp, Ws.q, a->vc,
-                       Ws.eps, Ws.rho, Ws.id, c->cell_sorted, c->cell_start, c->masks, weight,
-                       a->pibar, a->rhobar, a->G, a->H);
-    if (deps || drho)
+    const bool lucy = c->dp.kernel == SDPD_KERNEL_LUCY;
+    const PartnerArgs pa = partner_args(c, c->q4);
+    hipLaunchKernelGGL(k_pack_v, dim3(nblk(n)), dim3(256), 0, c->stream, c->dp, Ws.id, a->lp,
+                       Ws.eps, Ws.rho, a->v4);
+    hipLaunchKernelGGL(lucy ? k_vjp_pi<true> : k_vjp_pi<false>, dim3(nblk(ModelF64::kLanes * n)), dim3(256),
+                       0, c->stream, pa, a->v4, Ws.rho, Ws.id, weight, a->rhobar, c->q4, a->G,
+                       a->H);
+    if (deps || drho) {
         hipLaunchKernelGGL(k_final_cotangent, dim3(nblk(n)), dim3(256), 0, c->stream, n,
                            c->dp.eps_exp, Ws.id, deps, drho, Ws.eps, Ws.rho, a->rhobar, a->Ge,
                            a->He);
-    hipLaunchKernelGGL(k_vjp_q, dim3(nblk(n)), dim3(256), 0, c->stream, c->dp, Ws.q, a->vc,
-                       Ws.eps, Ws.rho, a->rhobar, c->cell_sorted, c->cell_start, c->masks, 1,
-                       a->wc);
-    hipLaunchKernelGGL(k_scatter_add_id, dim3(nblk(n)), dim3(256), 0, c->stream, n, 3, Ws.id,
-                       weight, a->wc, a->lq);
+        hipLaunchKernelGGL(k_pack_rhobar, dim3(nblk(n)), dim3(256), 0, c->stream, n,
+                           (const uint32_t *)nullptr, a->rhobar, c->q4);
+    }
+    hipLaunchKernelGGL((lucy ? k_vjp_q<true, true> : k_vjp_q<false, true>), dim3(nblk(ModelF64::kLanes * n)),
+                       dim3(256), 0, c->stream, pa, a->v4, Ws.id, weight, a->lq);
     return check_hip(hipGetLastError());
 }
 
@@ -371,11 +345,11 @@ int sdpd_adjoint_forward(sdpd_ctx *c, sdpd_state *s, int nsteps, int every)
     for (auto &b : a->seg)
         if (!rc) rc = state_alloc(a, b, n);
     if (!rc) rc = state_alloc(a, a->w, n);
-    for (double **p : {&a->lq, &a->lp, &a->vc, &a->wc})
+    for (double **p : {&a->lq, &a->lp})
         if (!rc) rc = walloc(a, (void **)p, sizeof(double) * 3 * n);
-    for (double **p : {&a->G, &a->H, &a->Ge, &a->He, &a->eps0, &a->rho0, &a->pibar,
-                       &a->rhobar})
+    for (double **p : {&a->G, &a->H, &a->Ge, &a->He, &a->eps0, &a->rho0, &a->rhobar})
         if (!rc) rc = walloc(a, (void **)p, sizeof(double) * n);
+    if (!rc) rc = walloc(a, (void **)&a->v4, sizeof(double4) * n);
     if (!rc) rc = walloc(a, (void **)&a->idcount, sizeof(uint32_t) * n);
     if (rc) {
         adjoint_free(a);
@@ -448,13 +422,12 @@ static int adjoint_backward(sdpd_ctx *c, const double *dJ_dq, const double *dJ_d
     hipLaunchKernelGGL(k_initial_path, dim3(nblk(n)), dim3(256), 0, c->stream, n, g, a->G, a->Ge,
                        a->eps0, a->rho0, eps0bar, a->rhobar);   // rhobar: id order here
     // W holds configuration 0 with its cells and masks (last vjp_config)
-    hipLaunchKernelGGL(k_gather_id, dim3(nblk(n)), dim3(256), 0, c->stream, n, 1, Ws.id, 1.0,
-                       a->rhobar, a->pibar);                    // pibar: rho0bar in cell order
-    hipLaunchKernelGGL(k_vjp_q, dim3(nblk(n)), dim3(256), 0, c->stream, c->dp, Ws.q, a->vc,
-                       Ws.eps, Ws.rho, a->pibar, c->cell_sorted, c->cell_start, c->masks, 0,
-                       a->wc);
-    hipLaunchKernelGGL(k_scatter_add_id, dim3(nblk(n)), dim3(256), 0, c->stream, n, 3, Ws.id,
-                       1.0, a->wc, a->lq);
+    hipLaunchKernelGGL(k_pack_rhobar, dim3(nblk(n)), dim3(256), 0, c->stream, n, Ws.id, a->rhobar,
+                       c->q4);
+    hipLaunchKernelGGL((c->dp.kernel == SDPD_KERNEL_LUCY ? k_vjp_q<true, false>
+                                                         : k_vjp_q<false, false>),
+                       dim3(nblk(ModelF64::kLanes * n)), dim3(256), 0, c->stream, partner_args(c, c->q4),
+                       a->v4, Ws.id, 1.0, a->lq);
     if ((rc = check_hip(hipGetLastError()))) return rc;
     if ((rc = check_hip(hipMemcpyAsync(dJ_dq0, a->lq, d3, hipMemcpyDeviceToDevice, c->stream))))
         return rc;

@@ -167,7 +167,7 @@ static void free_ctx(sdpd_ctx *c)
 {
     void *bufs[] = {c->cell_of, c->count, c->cursor, c->cell_start, c->block_sums, c->tmp_idx,
                     c->perm, c->cell_sorted, c->tq, c->tp, c->teps, c->trho, c->tf, c->tid,
-                    c->masks, c->counters, c->err, c->obs_partial, c->obs_out,
+                    c->masks, c->list, c->list_count, c->counters, c->err, c->obs_partial, c->obs_out,
                     c->dparams, c->task_count, c->task_np, c->pair_off, c->part_off,
                     c->part_list, c->pairs, c->rec_buf, c->lvl_end, c->flow_rec, c->q4f, c->dstep, c->q4,
                     c->sweep, c->epoch, c->sweep_order};
@@ -300,6 +300,16 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     // and at most 27 list entries per particle (1 own-cell + 2 x 13 tasks)
     c->pair_cap = std::max<int64_t>(64 * c->n, 1024);
     c->part_cap = std::max<int64_t>(27 * c->n, 1024);
+    // partner lists: half as many again as the mean at the box's density and 16
+    // more (a uniform random box of 10^5 particles with 65 partners on average has
+    // none with more than 105); particles with more are looked up without a list
+    {
+        const double h = c->prm.h;
+        double v = 4.0 / 3.0 * 3.14159265358979323846 * h * h * h * (double)c->n;
+        for (int k = 0; k < 3; ++k) v /= c->prm.box[k];
+        c->list_cap = (uint32_t)std::min(1.5 * v + 16.0, (double)(NNB * MAX_CAP));
+        c->list_cap = (c->list_cap + 31u) / 32u * 32u;   // (lists begin on their own cache lines)
+    }
     rc = SDPD_OK;
     rc = rc ? rc : dalloc(&c->cell_of, n);
     rc = rc ? rc : dalloc(&c->count, nce);
@@ -317,7 +327,9 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     rc = rc ? rc : dalloc(&c->tid, n);
     rc = rc ? rc : dalloc(&c->q4, 4 * n);
     if (c->dp.mixed) rc = rc ? rc : dalloc(&c->q4f, 4 * n);
-    rc = rc ? rc : dalloc(&c->masks, (size_t)NNB * n);
+    rc = rc ? rc : dalloc(&c->masks, (size_t)NMASK * n);
+    rc = rc ? rc : dalloc(&c->list, (size_t)c->list_cap * n);
+    rc = rc ? rc : dalloc(&c->list_count, n);
     rc = rc ? rc : dalloc(&c->counters, (size_t)CNT_N);
     rc = rc ? rc : dalloc(&c->err, 1);
     rc = rc ? rc : dalloc(&c->obs_partial, (size_t)c->obs_blocks * 6);

@@ -33,15 +33,14 @@ __global__ void k_pressure_term(PressureArgs a) { pressure_term_body(a, blockIdx
 SDPD_MULTI_KERNEL(k_pressure_term_multi, PressureArgs, pressure_term_body, 256)
 
 // f_i = sum_{j != i, r < h} m^2 (Pi_i + Pi_j) F_ij r_ij over the partners
-// recorded in the 27 active-pair masks of the density pass (same positions),
-// in the fixed order (offset index, then slot); optionally p_i += dt/2 f_i.
+// listed by the density pass (same positions); optionally p_i += dt/2 f_i.
 __device__ __forceinline__ void forces_lucy_body(const ForcesArgs &a, uint32_t blk)
 {
-    forces_lane<ModelF64, true, 1>(a, blk);
+    forces_body<ModelF64, true>(a, blk);
 }
 __device__ __forceinline__ void forces_cubic_body(const ForcesArgs &a, uint32_t blk)
 {
-    forces_lane<ModelF64, false, 1>(a, blk);
+    forces_body<ModelF64, false>(a, blk);
 }
 SDPD_MULTI_KERNEL(k_forces_lucy_multi, ForcesArgs, forces_lucy_body, 256)
 SDPD_MULTI_KERNEL(k_forces_cubic_multi, ForcesArgs, forces_cubic_body, 256)
@@ -54,8 +53,7 @@ int run_forces(sdpd_ctx *c, const sdpd_state *s, int half_kick)
     timer_begin(c, TK_FORCE);
     int rc = launch_or_record(c, k_pressure_term, k_pressure_term_multi, g, 256, 0,
                               PressureArgs{c->dp, s->q, s->eps, s->rho, c->q4});
-    const ForcesArgs args{c->dp, c->q4, c->cell_sorted, c->cell_start, c->masks,
-                          s->f, s->p, half_kick};
+    const ForcesArgs args{partner_args(c, c->q4), s->f, s->p, half_kick};
     if (!rc)
         rc = c->dp.kernel == SDPD_KERNEL_LUCY
                  ? launch_forces<ModelF64, true>(c, args, k_forces_lucy_multi)

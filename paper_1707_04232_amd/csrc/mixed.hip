@@ -18,11 +18,11 @@ __device__ __forceinline__ void density_cubic_body(const DensityArgs &a, uint32_
 }
 __device__ __forceinline__ void forces_lucy_body(const ForcesArgs &a, uint32_t blk)
 {
-    forces_lane<ModelF32, true, 1>(a, blk);
+    forces_body<ModelF32, true>(a, blk);
 }
 __device__ __forceinline__ void forces_cubic_body(const ForcesArgs &a, uint32_t blk)
 {
-    forces_lane<ModelF32, false, 1>(a, blk);
+    forces_body<ModelF32, false>(a, blk);
 }
 SDPD_MULTI_KERNEL(k_density_f32_lucy_multi, DensityArgs, density_lucy_body, 64 * kCellWaves)
 SDPD_MULTI_KERNEL(k_density_f32_cubic_multi, DensityArgs, density_cubic_body, 64 * kCellWaves)
@@ -47,7 +47,7 @@ int run_density_f32(sdpd_ctx *c, const sdpd_state *s, int update_eps)
 {
     timer_begin(c, TK_DENSITY);
     const DensityArgs args{c->dp, c->q4f, c->cell_start, s->rho, s->eps,
-                           update_eps, c->masks, c->err, nullptr};
+                           update_eps, c->masks, c->list, c->list_count, c->list_cap, c->err, nullptr};
     const int rc = c->dp.kernel == SDPD_KERNEL_LUCY
                        ? launch_density<ModelF32, true>(c, args, k_density_f32_lucy_multi)
                        : launch_density<ModelF32, false>(c, args, k_density_f32_cubic_multi);
@@ -61,8 +61,7 @@ int run_forces_f32(sdpd_ctx *c, const sdpd_state *s, int half_kick)
     int rc = launch_or_record(c, k_pressure_term_f32, k_pressure_term_f32_multi,
                               (unsigned)((c->n + 255) / 256), 256, 0,
                               PressureF32Args{c->dp, s->eps, s->rho, c->q4f});
-    const ForcesArgs args{c->dp, c->q4f, c->cell_sorted, c->cell_start, c->masks,
-                          s->f, s->p, half_kick};
+    const ForcesArgs args{partner_args(c, c->q4f), s->f, s->p, half_kick};
     if (!rc)
         rc = c->dp.kernel == SDPD_KERNEL_LUCY
                  ? launch_forces<ModelF32, true>(c, args, k_forces_f32_lucy_multi)

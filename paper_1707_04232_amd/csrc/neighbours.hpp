@@ -7,15 +7,16 @@
 
 #include <float.h>
 
+#include <type_traits>
+
 namespace sdpd {
 
 // ---------------------------------------------------------------- arithmetic
 // A model of the arithmetic: the type of positions and sums, the packed record
 // (x, y, z and a scalar), the periodic shift of axis a for neighbour offset o
 // (0, 1, 2) of a cell that is the first (lo) or the last (hi) of the axis, the
-// active test and the terms.  Sums are formed in candidate order (offset index
-// k = 0..26 with z slowest, then slot) in every form of a pass, so that the
-// forms agree bit for bit.
+// active test and the terms.  Densities are summed in candidate order (offset
+// index k = 0..26 with z slowest, then slot).
 
 // FP64: absolute positions; the image is chosen per neighbour cell: a cell
 // reached across the box boundary contributes (x_i - x_j) +- L, which is the
@@ -25,7 +26,9 @@ struct ModelF64 {
     typedef double Real;
     typedef double4 Vec;
     static constexpr bool kShiftEverywhere = false;
+    static constexpr int kDensityOcc = 5;
     static constexpr int kChunks = 4, kEdgeChunks = 2;   // see DensityWave
+    static constexpr int kLanes = 8;                     // see PartnerSums
     static __device__ __forceinline__ Real shift(const DevParams &P, int a, int o, bool lo, bool hi)
     {
         return o == 0 && lo ? P.box[a] : (o == 2 && hi ? -P.box[a] : 0.0);
@@ -71,7 +74,9 @@ struct ModelF32 {
     typedef float Real;
     typedef float4 Vec;
     static constexpr bool kShiftEverywhere = true;
-    static constexpr int kChunks = 3, kEdgeChunks = 3;
+    static constexpr int kDensityOcc = 6;
+    static constexpr int kChunks = 4, kEdgeChunks = 4;
+    static constexpr int kLanes = 4;
     static __device__ __forceinline__ Real shift(const DevParams &P, int a, int o, bool, bool)
     {
         return -(float)(o - 1) * P.cell_f[a];
@@ -191,14 +196,13 @@ struct CellWave {
     }
     // the cell of position t < total and the particle there; called by the whole
     // wave (a lane that is switched off gives no value to the others)
-    __device__ __forceinline__ void find(uint32_t t, int &k, uint32_t &j, uint32_t &slot) const
+    __device__ __forceinline__ void find(uint32_t t, int &k, uint32_t &j) const
     {
         k = 0;
 #pragma unroll
         for (int step = 16; step; step >>= 1)
             if ((uint32_t)__shfl((int)b, k + step) <= t) k += step;
-        slot = t - (uint32_t)__shfl((int)b, k);
-        j = (uint32_t)__shfl((int)s, k) + slot;
+        j = (uint32_t)__shfl((int)s, k) + (t - (uint32_t)__shfl((int)b, k));
     }
 };
 
@@ -209,10 +213,25 @@ struct DensityArgs {
     const uint32_t *cell_start;
     double *rho, *eps;
     int update_eps;
-    uint64_t *masks;         // masks[k * n + i]: slot bits of the partners in cell k
+    uint64_t *masks;         // masks[(k - 13) n + i]: slot bits of the partners in cell k,
+                             // k = 13 (the own cell, without i itself) .. 26
+    uint32_t *list, *count;  // partners of particle i (itself included) in candidate order:
+    uint32_t list_cap;       // list[list_cap i + r], r < count[i], complete if count <= list_cap
     uint32_t *err;
     double *rho_w;           // FP64: also into the w slot of the record, or NULL
 };
+
+// an entry of the list: particle and offset index (n < 2^27: the pair records
+// alone would take more than 256 GB)
+constexpr int kEntryBits = 27;
+__device__ __forceinline__ uint32_t list_entry(uint32_t j, int k)
+{
+    return j | (uint32_t)k << kEntryBits;
+}
+__device__ __forceinline__ uint32_t entry_particle(uint32_t e)
+{
+    return e & ((1u << kEntryBits) - 1u);
+}
 
 __device__ __forceinline__ void density_store(const DensityArgs &a, int64_t i, double rho)
 {
@@ -238,24 +257,31 @@ __device__ __forceinline__ void density_store(const DensityArgs &a, int64_t i, d
 // and no mask is taken apart.
 //
 // Bound by the VALU: 460 candidates of a particle (17 per cell, h = 0.98 cell
-// edges) take 7.2 lane-parallel tests of 14 instructions.  A thread per particle
+// edges) take 7.2 lane-parallel tests of 15 instructions.  A thread per particle
 // reads 24 B of every candidate through the L1 instead and runs to the largest
-// cell of its wave: 677 us for 1M particles in FP64 (now 512), 3590 us for 8M in
-// FP32 (now 2830), 251 us for 262k (now 169).
+// cell of its wave: 677 us for 1M particles in FP64 (now 633, of which the partner
+// list takes 120), 251 us for 262k (214), 168 us for 137k in FP32 (90).
+//
+// The list saves the force and gradient passes the walk through the masks (1M
+// particles: forces 410 -> 216 us).  A window's entries of a particle go through
+// LDS and out in one store; storing them where they are found took 690 us, and a
+// queue of entries beside that of the terms, emptied with it, 718.
 //
 // K: more candidates per lane mean fewer windows, each with its own pass over the
-// particles, and fewer waves per SIMD.  1M particles, K = 3, 4, 5, 8: 547, 515,
-// 562, 864 us; 8M in FP32, K = 3, 4, 5: 2826, 2940, 3477.  FP64 cells at the
-// boundary carry shifts (three doubles more per candidate) and take K = 2 (K = 4
-// there: 532 us), or 4 where a wave per SIMD is all there is (SPLIT: 25 us
-// against 28 for 8064 particles).
-constexpr int kTerms = 832;        // queue entries of a wave
+// particles, and fewer waves per SIMD.  1M particles, K = 3, 4: 676, 638 us; 8M in
+// FP32, K = 3, 4: 3703, 3552; without the list K = 5, 8 took 9 and 70 % longer
+// than 4.  FP64 cells at the boundary carry shifts (three doubles more per
+// candidate) and take K = 2, or 4 where a wave per SIMD is all there is (SPLIT).
+// kDensityOcc: the waves per SIMD that the compiler has to allow (1M particles, 4
+// and 5: 689 and 638 us).
+constexpr int kTerms = 640;        // queue entries of a wave
 constexpr int kTail = 256;         // particles of a workgroup's shared last part
 
 template <class M, bool SPLIT>
 struct DensityLds {
     typename M::Real terms[kCellWaves][kTerms + 64];
     double rho[kTail];
+    uint32_t part[kCellWaves][64 * M::kChunks + 64];   // list entries of a particle and window
     uint32_t words[SPLIT ? kCellWaves : 1][SPLIT ? 64 * kCellWaves : 1];
 };
 
@@ -263,7 +289,7 @@ struct DensityLds {
 // slots w q .. w q + q - 1 (q = ceil(m / 4)) of it, and put their words together
 // in LDS: for boxes of so few cells that a wave per cell leaves SIMDs idle and the
 // pass takes as long as one wave's chain (1000 particles: 18 us, a wave per cell
-// 34, four lanes per particle 66)
+// 34, four lanes of a thread per particle 66)
 template <class M, bool LUCY, bool SPLIT>
 struct DensityWave {
     typedef typename M::Real Real;
@@ -275,6 +301,7 @@ struct DensityWave {
     Real *terms;
     Real x, y, z, acc;       // lane i < m: particle i of the cell and its sum
     uint32_t beg, end;       // ... its terms in the queue
+    uint32_t partners;       // ... its list entries
     uint32_t fill;
 
     // the queued squared distances to terms, and each lane's added to its sum
@@ -298,31 +325,30 @@ struct DensityWave {
         fill = beg = end = 0u;
     }
 
-    template <bool SHIFT, int K>
+    // WORDS: the window has cells whose masks for this one are kept
+    template <bool SHIFT, int K, bool WORDS>
     __device__ __forceinline__ void window(uint32_t base, uint32_t width)
     {
         const Real *__restrict__ q4 = static_cast<const Real *>(a.q4);
         const int chunks = (int)((width + 63u) / 64u);
         Real cx[K], cy[K], cz[K], sh[K][3];
-        uint32_t at[K];          // the candidate
-        uint32_t self[K];        // k << 8 | slot
+        uint32_t entry[K];
 #pragma unroll
         for (int c = 0; c < K; ++c) {
             cx[c] = cy[c] = cz[c] = (Real)0;
-            at[c] = self[c] = 0u;
+            entry[c] = 0u;
             for (int d = 0; d < 3; ++d) sh[c][d] = (Real)0;
             if (c >= chunks) continue;
             const uint32_t t = 64u * c + lane;
             int k;
-            uint32_t j, slot;
-            cw.find(base + min(t, width - 1u), k, j, slot);   // (every lane takes part)
+            uint32_t j;
+            cw.find(base + min(t, width - 1u), k, j);   // (every lane takes part)
             const typename M::Vec v = load_vec<M>(q4, j);
             // a lane past the end: out of range of everything
             cx[c] = t < width ? v.x : (Real)1e18;
             cy[c] = v.y;
             cz[c] = v.z;
-            at[c] = j;
-            self[c] = (uint32_t)k << 8 | slot;
+            entry[c] = list_entry(j, k);
             if (SHIFT) {
                 const int o[3] = {k % 3, (k / 3) % 3, k / 9};
                 for (int d = 0; d < 3; ++d)
@@ -339,8 +365,11 @@ struct DensityWave {
             for (int i = min(hi, 32 * half + 32) - 1; i >= first_slot; --i) {
                 const Real xi = lane_of(x, i), yi = lane_of(y, i), zi = lane_of(z, i);
                 if (fill + 64u * K + 3u > (uint32_t)kTerms) flush();
-                const uint32_t first = fill;
+                const uint32_t first = fill, had = lane_of(partners, i);
+                uint32_t total = 0u;
+                uint32_t *const list = a.list + (int64_t)(cw.own + (uint32_t)i) * a.list_cap;
                 Real *const unused = terms + kTerms + lane;
+                uint32_t *const part = lds.part[wave], *const unused_part = part + 64 * K + lane;
 #pragma unroll
                 for (int c = 0; c < K; ++c) {
                     if (c >= chunks) break;
@@ -353,21 +382,30 @@ struct DensityWave {
                     const Real r2 = dx * dx + dy * dy + dz * dz;
                     const bool near = M::near(P, r2);
                     const uint64_t hit = __ballot(near);
-                    w[c] = w[c] + w[c] + (near ? 1u : 0u);
+                                        if (WORDS) w[c] = w[c] + w[c] + (near ? 1u : 0u);
                     // (no branch: the other lanes write to slots that nothing reads)
-                    uint32_t off = below(hit, 0u);
-                    asm volatile("" : "+v"(off));   // (computed, not branched around)
-                    *(near ? terms + fill + off : unused) = r2;
+                    uint32_t at = below(hit, 0u);
+                    asm volatile("" : "+v"(at));   // (computed, not branched around)
+                    *(near ? terms + fill + at : unused) = r2;
+                    *(near ? part + total + at : unused_part) = entry[c];
                     fill += (uint32_t)__popcll(hit);
+                    total += (uint32_t)__popcll(hit);
                 }
+                // the window's part of the list
+                wave_sync();
+                if (had + total <= a.list_cap)
+                    for (uint32_t r = lane; r < total; r += 64u) list[had + r] = part[r];
+                wave_sync();
                 // up to a multiple of four with entries without a term
                 if (lane < 3) terms[fill + lane] = (Real)-1;
                 fill = (fill + 3u) & ~3u;
                 if (lane == i) {
                     beg = first;
                     end = fill;
+                    partners = had + total;
                 }
             }
+            if (!WORDS) continue;
             // lane j's word: the partners of candidate j in this cell
             if (SPLIT) {
                 __syncthreads();   // (the last words have been read)
@@ -381,16 +419,18 @@ struct DensityWave {
             for (int c = 0; c < K; ++c) {
                 if (SPLIT && c != wave) continue;
                 if (c < chunks && 64u * c + lane < width) {
-                    const uint32_t k = self[c] >> 8, slot = self[c] & 255u;
+                    const uint32_t k = entry[c] >> kEntryBits, j = entry_particle(entry[c]);
+                    if (k > (uint32_t)OWN_NB) continue;
                     uint32_t v = w[c];
                     if (SPLIT) {
                         v = 0u;
                         for (int o = 0; o < kCellWaves; ++o) v |= lds.words[o][64 * c + lane];
                     }
                     // i itself is no partner
+                    const uint32_t slot = j - cw.own;
                     if (k == (uint32_t)OWN_NB && (slot >> 5) == (uint32_t)half)
                         v &= ~(1u << (slot & 31u));
-                    const int64_t e = (int64_t)((uint32_t)(NNB - 1) - k) * P.n + at[c];
+                    const int64_t e = (int64_t)((uint32_t)OWN_NB - k) * P.n + j;
                     if (m > 32) words[2 * e + half] = v;
                     else a.masks[e] = v;
                 }
@@ -404,7 +444,8 @@ struct DensityWave {
         for (int k0 = 0; k0 < NNB;) {
             const int k1 = cw.window(k0, 64u * K);
             const uint32_t base = lane_of(cw.b, k0), width = lane_of(cw.b, k1) - base;
-            window<SHIFT, K>(base, width);
+            if (k0 <= OWN_NB) window<SHIFT, K, true>(base, width);
+            else window<SHIFT, K, false>(base, width);
             flush();   // (a lane has one segment of the queue at a time)
             k0 = k1;
         }
@@ -414,7 +455,7 @@ struct DensityWave {
     {
         terms = lds.terms[wave];
         x = y = z = acc = (Real)0;
-        beg = end = fill = 0u;
+        beg = end = fill = partners = 0u;
         if ((uint32_t)lane < cw.m) {
             const typename M::Vec v =
                 load_vec<M>(static_cast<const Real *>(a.q4), cw.own + (uint32_t)lane);
@@ -429,10 +470,14 @@ struct DensityWave {
         if (over && lane == 0) atomicOr(a.err, ERR_CELLCAP);
         for (; over; over &= over - 1ull) {
             const int k = __builtin_ctzll(over);
+            if (k > OWN_NB) break;
             const uint32_t s = lane_of(cw.s, k), cnt = lane_of(cw.raw, k);
-            for (uint32_t r = lane; r < cnt; r += 64u)
-                a.masks[(int64_t)(NNB - 1 - k) * P.n + s + r] = 0ull;
+            for (uint32_t r = lane; r < cnt; r += 64u) {
+                a.masks[(int64_t)(OWN_NB - k) * P.n + s + r] = 0ull;
+                if (k == OWN_NB) a.count[s + r] = 0u;
+            }
         }
+        if (lane >= lo && lane < hi) a.count[cw.own + (uint32_t)lane] = partners;
     }
 };
 
@@ -476,253 +521,246 @@ __device__ __forceinline__ void density_cells(const DensityArgs &a, uint32_t blk
     }
 }
 
+// ---------------------------------------------------------------- partner sums
+// Sums over a particle's partners, from the lists of the density pass (same
+// positions): kLanes lanes per particle, lane s with entries s, s + kLanes, ...
+// FP64: each lane adds up its own and the lanes are added at the end; FP32: every
+// lane adds the terms of all in list order.  Particles with more partners than the
+// list holds are looked up among their candidates by the whole wave.
+//
+// Bound by the gathers of the partners' records (two 16 B loads per pair, 22 clocks
+// each in the address unit) and, in small boxes, by the chain of a lane.  A lane per
+// particle that walks the 27 masks took 410 us for 1M particles (now 216), 56 for
+// 1000 (13), 2170 for 8M in FP32 (1470); the gradient's two passes at 262k particles
+// 580 us.  Lanes per particle: FP64 8 (4: 284 us at 1M), FP32 4 (8 with sums through
+// LDS: 2570 at 8M).  Lists that begin on cache lines: 225 -> 216, 1680 -> 1470.
+struct PartnerArgs {
+    DevParams P;
+    const void *q4;          // packed records of the model
+    const uint32_t *cell_sorted, *cell_start;
+    const uint32_t *list, *count;
+    uint32_t list_cap;
+};
+
+
+// x of another lane (CTRL: the DPP control word)
+template <int CTRL>
+__device__ __forceinline__ float moved(float x)
+{
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double moved(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// Value v of the sum over particle i's partners in lane s == v < NV of its lanes.  term(j, d, r2, out): the NV values of partner j at separation d = q_i -
+// q_j, all zero for r2 = 0; term.at(i): called before with the particle of the lane.
+template <class M, int NV, class Term>
+struct PartnerSums {
+    typedef typename M::Real Real;
+    static constexpr int kLanes = M::kLanes;
+    const PartnerArgs &a;
+    const DevParams &P;
+    float4 *shift;           // FP32: 27 entries in LDS
+    const int lane;
+    const uint32_t s;
+
+    // a particle without a complete list (uniform in the wave)
+    __device__ __forceinline__ void direct(int64_t i, Term term, Real sum[NV])
+    {
+        const CellXyz cc(P, (uint32_t)__builtin_amdgcn_readfirstlane((int)a.cell_sorted[i]));
+        const CellWave cw(P, cc, a.cell_start);
+        const typename M::Vec qi = load_vec<M>(static_cast<const Real *>(a.q4), i);
+        term.at(i);
+        for (int v = 0; v < NV; ++v) sum[v] = (Real)0;
+        for (uint32_t t0 = 0; t0 < cw.total; t0 += 64u) {
+            int k;
+            uint32_t j;
+            cw.find(min(t0 + (uint32_t)lane, cw.total - 1u), k, j);
+            const typename M::Vec qj = load_vec<M>(static_cast<const Real *>(a.q4), j);
+            Real d[3] = {qi.x - qj.x, qi.y - qj.y, qi.z - qj.z};
+            const int o[3] = {k % 3, (k / 3) % 3, k / 9};
+            for (int x = 0; x < 3; ++x)
+                d[x] += M::shift(P, x, o[x], (cw.steps.lo >> x) & 1u, (cw.steps.hi >> x) & 1u);
+            const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+            Real out[NV];
+            for (int v = 0; v < NV; ++v) out[v] = (Real)0;
+            if (t0 + (uint32_t)lane < cw.total && M::near(P, r2)) term(j, qi, qj, d, r2, out);
+            for (int v = 0; v < NV; ++v)   // in candidate order
+                for (int l = 0; l < 64; ++l) sum[v] = sum[v] + lane_of(out[v], l);
+        }
+    }
+
+    __device__ __forceinline__ Real run(int64_t i, bool live, Term term)
+    {
+        const Real *__restrict__ q4 = static_cast<const Real *>(a.q4);
+        const typename M::Vec qi = load_vec<M>(q4, i);
+        const uint32_t all = live ? a.count[i] : 0u;
+        const bool over = all > a.list_cap;
+        const uint32_t cnt = over ? 0u : all;
+        const uint32_t *__restrict__ list = a.list + i * (int64_t)a.list_cap;
+        const uint32_t self = list_entry((uint32_t)i, OWN_NB);
+        term.at(i);
+        Real mine = (Real)0;
+        // entry r (past the end: the particle itself, whose terms are zero)
+        auto entry = [&](uint32_t r) { return r < cnt ? list[r] : self; };
+        if constexpr (sizeof(Real) == 8) {
+            // partners across the boundary only for particles within h of it
+            bool edge = false;
+            const double margin = 1.001 * P.h;
+            const double x[3] = {qi.x, qi.y, qi.z};
+            for (int d = 0; d < 3; ++d)
+                edge = edge || x[d] < margin || x[d] > P.box[d] - margin;
+            double acc[NV];
+            for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+            auto loop = [&](auto shifted) {
+                constexpr bool SHIFT = decltype(shifted)::value;
+                uint32_t e[2] = {entry(s), entry(s + kLanes)};
+                for (uint32_t r = s; __any(r < cnt); r += 2 * kLanes) {
+                    typename M::Vec qj[2];
+                    uint32_t j[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        j[u] = entry_particle(e[u]);
+                        qj[u] = load_vec<M>(q4, j[u]);
+                    }
+                    e[0] = entry(r + 2 * kLanes);
+                    e[1] = entry(r + 3 * kLanes);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        double d[3] = {qi.x - qj[u].x, qi.y - qj[u].y, qi.z - qj[u].z};
+                        if (SHIFT)
+                            for (int x = 0; x < 3; ++x)
+                                d[x] += d[x] > P.h ? -P.box[x] : (d[x] < -P.h ? P.box[x] : 0.0);
+                        const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                        double out[NV];
+                        term(j[u], qi, qj[u], d, r2, out);
+                        for (int v = 0; v < NV; ++v) acc[v] += out[v];
+                    }
+                }
+            };
+            if (__any(edge)) loop(std::true_type());
+            else loop(std::false_type());
+            for (int v = 0; v < NV; ++v) {
+                acc[v] += moved<0xb1>(acc[v]);    // lanes 1 0 3 2 of four
+                acc[v] += moved<0x4e>(acc[v]);    // lanes 2 3 0 1
+                acc[v] += moved<0x141>(acc[v]);   // eight lanes mirrored
+                if (s == (uint32_t)v) mine = acc[v];
+            }
+        } else {
+            if (lane < NNB) {
+                const int o[3] = {lane % 3, (lane / 3) % 3, lane / 9};
+                shift[lane] = make_float4(M::shift(P, 0, o[0], false, false),
+                                          M::shift(P, 1, o[1], false, false),
+                                          M::shift(P, 2, o[2], false, false), 0.0f);
+            }
+            wave_sync();
+            float acc[NV];
+            for (int v = 0; v < NV; ++v) acc[v] = 0.0f;
+            uint32_t e[2] = {entry(s), entry(s + kLanes)};
+            for (uint32_t r = s; __any(r < cnt); r += 2 * kLanes) {
+                typename M::Vec qj[2];
+                float4 sh[2];
+                uint32_t j[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    j[u] = entry_particle(e[u]);
+                    qj[u] = load_vec<M>(q4, j[u]);
+                    sh[u] = shift[e[u] >> kEntryBits];
+                }
+                e[0] = entry(r + 2 * kLanes);
+                e[1] = entry(r + 3 * kLanes);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const float d[3] = {(qi.x - qj[u].x) + sh[u].x, (qi.y - qj[u].y) + sh[u].y,
+                                        (qi.z - qj[u].z) + sh[u].z};
+                    const float r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                    float out[NV];
+                    term(j[u], qi, qj[u], d, r2, out);
+                    for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x00>(out[v]);
+                    for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x55>(out[v]);
+                    for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0xaa>(out[v]);
+                    for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0xff>(out[v]);
+                }
+            }
+            for (int v = 0; v < NV; ++v)
+                if (s == (uint32_t)v) mine = acc[v];
+        }
+        for (uint64_t todo = __ballot(over && s == 0u); todo; todo &= todo - 1ull) {
+            const int l = __builtin_ctzll(todo);
+            const int64_t at = (int64_t)lane_of((uint32_t)i, l);
+            Real sum[NV];
+            Term whole = term;
+            direct(at, whole, sum);
+            if (lane / kLanes == l / kLanes)
+                for (int v = 0; v < NV; ++v)
+                    if (s == (uint32_t)v) mine = sum[v];
+        }
+        return mine;
+    }
+};
+
+// particle of this lane's group (past the last one: the last, live = false)
+template <class M>
+__device__ __forceinline__ int64_t partner_particle(const DevParams &P, uint32_t blk, bool &live)
+{
+    const int64_t i = (int64_t)blk * (blockDim.x / M::kLanes) + threadIdx.x / M::kLanes;
+    live = i < P.n;
+    return live ? i : P.n - 1;
+}
+
 // ---------------------------------------------------------------- forces
 struct ForcesArgs {
-    DevParams P;
-    const void *q4;          // packed records of the model: x, y, z, Pi
-    const uint32_t *cell_sorted, *cell_start;
-    const uint64_t *masks;
+    PartnerArgs a;           // records (x, y, z, Pi)
     double *f, *p;
     int half_kick;
 };
 
-__device__ __forceinline__ void force_store(const ForcesArgs &a, int64_t i, int axis, double f)
-{
-    const int64_t at = axis * a.P.n + i;
-    a.f[at] = f;
-    if (a.half_kick) a.p[at] += 0.5 * a.P.dt * f;
-}
-
-// One lane per particle: one loop over the lane's partners in the fixed order.
-// The trip count is the lane's partner count, and a lane moves on to its next
-// non-empty neighbour cell inside the loop body, whose cell start and mask are
-// loaded one cell ahead.  A wave then runs as many iterations as its busiest
-// lane has partners, instead of the sum over the cells of the busiest lane in
-// each.  EDGE: some lane of the wave sits in a first or last cell of an axis,
-// where neighbour steps wrap and carry a periodic shift; elsewhere cell k is
-// c + o_x + o_y n_x + o_z n_x n_y - (1 + n_x + n_x n_y) for the offset digits o
-// of k.
-template <class M, bool LUCY, bool EDGE>
-__device__ __forceinline__ void forces_lane_loop(const ForcesArgs &a, int64_t i, uint32_t c,
-                                                 const NbSteps &nb, uint32_t todo, int total,
-                                                 typename M::Vec qi, typename M::Real f[3])
-{
+// m^2 (Pi_i + Pi_j) F_ij r_ij
+template <class M, bool LUCY>
+struct ForceTerm {
     typedef typename M::Real Real;
-    const DevParams &P = a.P;
-    const Real *__restrict__ q4 = static_cast<const Real *>(a.q4);
-    const int64_t n = P.n;
-    const uint32_t nx = (uint32_t)P.nc[0], nxy = nx * (uint32_t)P.nc[1];
-    const uint32_t c0 = c - 1u - nx - nxy;
-    constexpr bool SHIFT = EDGE || M::kShiftEverywhere;
-    const Real ms = M::force_scale(P);
-    struct Cell {
-        uint32_t start;
-        uint64_t mask;
-        Real sh[3];
-    };
-    auto cell = [&](int k) {   // start and mask requested, shift set
-        Cell r;
-        const uint32_t q3 = ((uint32_t)k * 11u) >> 5;   // k / 3 for k < 27
-        const uint32_t o[3] = {(uint32_t)k - 3u * q3, q3 - 3u * ((q3 * 11u) >> 5),
-                               (q3 * 11u) >> 5};
-        uint32_t cn = c0 + o[0] + o[1] * nx + o[2] * nxy;
-        if (EDGE) cn = (uint32_t)nb.get(P, k).c;
-        if (SHIFT)
-            for (int x = 0; x < 3; ++x)
-                r.sh[x] = M::shift(P, x, (int)o[x], (nb.lo >> x) & 1u, (nb.hi >> x) & 1u);
-        r.start = a.cell_start[cn];
-        r.mask = a.masks[(int64_t)k * n + i];
-        return r;
-    };
-    Cell cur, next;
-    cur.mask = next.mask = 0ull;
-    cur.start = next.start = 0u;
-    for (int x = 0; x < 3; ++x) cur.sh[x] = next.sh[x] = (Real)0;
-    if (todo) {
-        next = cell(__builtin_ctz(todo));
-        todo &= todo - 1u;
-    }
-    for (int t = 0; t < total; ++t) {
-        if (cur.mask == 0ull) {   // the prefetched cell becomes current
-            cur = next;
-            if (todo) {
-                next = cell(__builtin_ctz(todo));
-                todo &= todo - 1u;
-            }
-        }
-        const uint32_t j = cur.start + (uint32_t)__builtin_ctzll(cur.mask);
-        cur.mask &= cur.mask - 1ull;
-        const typename M::Vec qj = load_vec<M>(q4, j);
-        Real dx = qi.x - qj.x, dy = qi.y - qj.y, dz = qi.z - qj.z;
-        if (SHIFT) {
-            dx += cur.sh[0];
-            dy += cur.sh[1];
-            dz += cur.sh[2];
-        }
-        const Real r2 = dx * dx + dy * dy + dz * dz;
+    const DevParams &P;
+    const Real ms;
+    __device__ __forceinline__ void at(int64_t) {}
+    __device__ __forceinline__ void operator()(uint32_t, const typename M::Vec &qi,
+                                               const typename M::Vec &qj, const Real d[3],
+                                               Real r2, Real out[3]) const
+    {
         const Real sc = ms * (qi.w + qj.w) * M::template force<LUCY>(P, r2);
-        f[0] += sc * dx;
-        f[1] += sc * dy;
-        f[2] += sc * dz;
-    }
-}
-
-// G = 3: one loop per layer of nine neighbour cells (offsets 9l .. 9l + 8,
-// equal z offset), so that the lanes of a wave read the records of nearby
-// cells at about the same time; G = 1: one loop over all 27 (the same sums in
-// the same order either way)
-template <class M, bool LUCY, int G>
-__device__ __forceinline__ void forces_lane(const ForcesArgs &a, uint32_t blk)
-{
-    const DevParams &P = a.P;
-    const int64_t i = (int64_t)blk * blockDim.x + threadIdx.x;
-    if (i >= P.n) return;
-    const uint32_t c = a.cell_sorted[i];
-    const CellXyz cc(P, c);
-    const NbSteps nb(P, cc.x, cc.y, cc.z);
-    const typename M::Vec qi = load_vec<M>(static_cast<const typename M::Real *>(a.q4), i);
-    const bool edge = __any((nb.lo | nb.hi) != 0u);
-    typename M::Real f[3] = {0, 0, 0};
-    for (int g = 0; g < G; ++g) {
-        // non-empty neighbour cells (bit k) and the number of partners
-        uint32_t todo = 0u;
-        int total = 0;
-        for (int k = g * (27 / G); k < (g + 1) * (27 / G); ++k) {
-            const uint64_t m = a.masks[(int64_t)k * P.n + i];
-            todo |= (m != 0ull ? 1u : 0u) << k;
-            total += __popcll(m);
-        }
-        if (edge) forces_lane_loop<M, LUCY, true>(a, i, c, nb, todo, total, qi, f);
-        else forces_lane_loop<M, LUCY, false>(a, i, c, nb, todo, total, qi, f);
-    }
-    for (int x = 0; x < 3; ++x) force_store(a, i, x, (double)f[x]);
-}
-
-// sum of v[0 .. count) in order, added to acc; eight values in flight (zeros
-// behind the last one)
-template <class Real>
-__device__ __forceinline__ Real ordered_sum(const Real *v, int count, Real acc)
-{
-    for (int r = 0; r < count; r += 8) {
-        Real x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = v[r + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc = acc + x[u];
-    }
-    return acc;
-}
-
-// The partners of particle i, 256 at a time, into LDS entries j | k << 27 in
-// the fixed order (lane k expands the mask of neighbour cell k from its place
-// on); one wave per particle, boxes below 2^27 particles.
-struct WavePartners {
-    static constexpr int kWindow = 256;
-    uint64_t mask;       // lane k: partners in cell k not yet written
-    uint32_t start;      // lane k: first particle of cell k
-    int at, total;       // lane k: place of its next partner; all partners
-
-    __device__ __forceinline__ WavePartners(const DevParams &P, const NbSteps &nb,
-                                            const uint32_t *cell_start, const uint64_t *masks,
-                                            int64_t i)
-    {
-        const int lane = threadIdx.x & 63;
-        mask = 0ull;
-        start = 0u;
-        if (lane < NNB) {
-            start = cell_start[nb.get(P, lane).c];
-            mask = masks[(int64_t)lane * P.n + i];
-        }
-        int incl = __popcll(mask);
-        at = -incl;
-#pragma unroll
-        for (int off = 1; off < 32; off <<= 1) {
-            const int v = __shfl_up(incl, off);
-            if (lane >= off) incl += v;
-        }
-        at += incl;
-        total = __builtin_amdgcn_readlane(incl, NNB - 1);
-    }
-    __device__ __forceinline__ void window(uint32_t *ent, int w0)
-    {
-        const int limit = w0 + kWindow;
-        while (__any(mask != 0ull && at < limit))
-            if (mask != 0ull && at < limit) {
-                ent[at - w0] = (start + (uint32_t)__builtin_ctzll(mask)) |
-                               ((threadIdx.x & 63u) << 27);
-                mask &= mask - 1ull;
-                ++at;
-            }
-        wave_sync();
+        for (int x = 0; x < 3; ++x) out[x] = sc * d[x];
     }
 };
 
-// separation q_i - q_j of entry e (see WavePartners)
-template <class M>
-__device__ __forceinline__ void partner_separation(const DevParams &P, const NbSteps &nb,
-                                                   uint32_t e, const typename M::Vec &qi,
-                                                   const typename M::Vec &qj,
-                                                   typename M::Real d[3])
-{
-    d[0] = qi.x - qj.x;
-    d[1] = qi.y - qj.y;
-    d[2] = qi.z - qj.z;
-    if (M::kShiftEverywhere || (nb.lo | nb.hi) != 0u) {
-        const int k = (int)(e >> 27), o[3] = {k % 3, (k / 3) % 3, k / 9};
-        for (int x = 0; x < 3; ++x)
-            d[x] += M::shift(P, x, o[x], (nb.lo >> x) & 1u, (nb.hi >> x) & 1u);
-    }
-}
-
-// One wave per particle: 64 partners at a time, their terms into LDS, added up
-// in order by one lane per component.
 template <class M, bool LUCY>
-__device__ __forceinline__ void forces_wave(const ForcesArgs &a, int64_t i, uint32_t *ent,
-                                            typename M::Real (*terms)[64])
+__device__ __forceinline__ void forces_body(const ForcesArgs &g, uint32_t blk)
 {
-    typedef typename M::Real Real;
-    const DevParams &P = a.P;
+    __shared__ float4 shift[4][M::kShiftEverywhere ? NNB : 1];
+    const DevParams &P = g.a.P;
+    bool live;
+    const int64_t i = partner_particle<M>(P, blk, live);
     const int lane = threadIdx.x & 63;
-    const Real *q4 = static_cast<const Real *>(a.q4);
-    const CellXyz cc(P, (uint32_t)__builtin_amdgcn_readfirstlane((int)a.cell_sorted[i]));
-    const NbSteps nb(P, cc.x, cc.y, cc.z);
-    const typename M::Vec qi = load_vec<M>(q4, i);
-    WavePartners partners(P, nb, a.cell_start, a.masks, i);
-    const Real ms = M::force_scale(P);
-    Real f = (Real)0;        // lane x < 3: component x
-    for (int w0 = 0; w0 < partners.total; w0 += WavePartners::kWindow) {
-        partners.window(ent, w0);
-        const int cnt = min(partners.total - w0, WavePartners::kWindow);
-        for (int t0 = 0; t0 < cnt; t0 += 64) {
-            Real v[3] = {0, 0, 0};
-            if (t0 + lane < cnt) {
-                const uint32_t e = ent[t0 + lane];
-                const typename M::Vec qj = load_vec<M>(q4, e & ((1u << 27) - 1u));
-                Real d[3];
-                partner_separation<M>(P, nb, e, qi, qj, d);
-                const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-                const Real sc = ms * (qi.w + qj.w) * M::template force<LUCY>(P, r2);
-                for (int x = 0; x < 3; ++x) v[x] = sc * d[x];
-            }
-            for (int x = 0; x < 3; ++x) terms[x][lane] = v[x];
-            wave_sync();
-            if (lane < 3) f = ordered_sum(terms[lane], min(cnt - t0, 64), f);
-            wave_sync();
-        }
-    }
-    if (lane < 3) force_store(a, i, lane, (double)f);
+    PartnerSums<M, 3, ForceTerm<M, LUCY>> sums{g.a, P, shift[threadIdx.x >> 6], lane,
+                                               (uint32_t)lane % M::kLanes};
+    const double f = (double)sums.run(i, live, ForceTerm<M, LUCY>{P, M::force_scale(P)});
+    if (!live || sums.s >= 3u) return;
+    const int64_t at = sums.s * P.n + i;
+    g.f[at] = f;
+    if (g.half_kick) g.p[at] += 0.5 * P.dt * f;
 }
 
 // ---------------------------------------------------------------- launches
-// Both passes choose their form by the box; in launches recorded for a batch all
-// boxes share the GPU, and take the forms of large ones.  The forms agree bit for
-// bit.
-// Density: four waves per cell up to 2^10 cells, one per SIMD of the GPU (384
+// Density: in launches recorded for a batch all boxes share the GPU, and take the
+// form of large ones (the two agree bit for bit); a box on its own: four waves per cell up to 2^10 cells, one per SIMD of the GPU (384
 // cells: 25 us against 50; 1728 cells: 53 against 54; 7128: 102 against 73).
 constexpr int64_t kSplitMaxCells = 1 << 10;
-// Forces: a wave per particle up to 48k particles (1000: 13 us against 56, 8064:
-// 20 against 59, 31680: 42 against 64, 100003: 96 against 70).
-constexpr int64_t kWaveMaxParticles = 48 << 10;
 
 template <class M, bool LUCY>
 __device__ __forceinline__ void density_body(const DensityArgs &a, uint32_t blk)
@@ -731,24 +769,15 @@ __device__ __forceinline__ void density_body(const DensityArgs &a, uint32_t blk)
     density_cells<M, LUCY, false>(a, blk, lds);
 }
 template <class M, bool LUCY, bool SPLIT>
-__global__ __launch_bounds__(64 * kCellWaves) void k_density(DensityArgs a)
+__global__ __launch_bounds__(64 * kCellWaves, SPLIT ? 1 : M::kDensityOcc) void k_density(DensityArgs a)
 {
     __shared__ DensityLds<M, SPLIT> lds;
     density_cells<M, LUCY, SPLIT>(a, xcd_block(blockIdx.x, gridDim.x), lds);
 }
-template <class M, bool LUCY, int G>
-__global__ __launch_bounds__(256) void k_forces(ForcesArgs a)
-{
-    forces_lane<M, LUCY, G>(a, xcd_block(blockIdx.x, gridDim.x));
-}
 template <class M, bool LUCY>
-__global__ __launch_bounds__(256) void k_forces_wave(ForcesArgs a)
+__global__ __launch_bounds__(256) void k_forces(ForcesArgs g)
 {
-    __shared__ uint32_t ent[4][WavePartners::kWindow];
-    __shared__ typename M::Real terms[4][3][64];
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t i = 4 * (int64_t)blockIdx.x + w;
-    if (i < a.P.n) forces_wave<M, LUCY>(a, i, ent[w], terms[w]);
+    forces_body<M, LUCY>(g, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // (multi: the multi-box forms of this model and kernel)
@@ -767,13 +796,14 @@ int launch_density(sdpd_ctx *c, const DensityArgs &args, MultiKernel multi)
 template <class M, bool LUCY>
 int launch_forces(sdpd_ctx *c, const ForcesArgs &args, MultiKernel multi)
 {
-    if (c->n <= kWaveMaxParticles && !c->rec) {
-        hipLaunchKernelGGL((k_forces_wave<M, LUCY>), dim3((unsigned)((c->n + 3) / 4)), dim3(256),
-                           0, c->stream, args);
-        return check_hip(hipGetLastError());
-    }
-    return launch_or_record(c, k_forces<M, LUCY, 3>, multi, (unsigned)((c->n + 255) / 256), 256,
-                            0, args);
+    return launch_or_record(c, k_forces<M, LUCY>, multi,
+                            (unsigned)((c->n + 256 / M::kLanes - 1) / (256 / M::kLanes)), 256, 0, args);
+}
+
+inline PartnerArgs partner_args(const sdpd_ctx *c, const void *q4)
+{
+    return PartnerArgs{c->dp, q4, c->cell_sorted, c->cell_start, c->list, c->list_count,
+                       c->list_cap};
 }
 
 }  // namespace sdpd

@@ -54,7 +54,7 @@ __device__ __forceinline__ void task_count_body(const TaskCountArgs &a, uint32_t
         const uint32_t nB = cell_start[tc.B + 1] - cell_start[tc.B];
         if (nA <= (uint32_t)P.cap && nB <= (uint32_t)P.cap) {
             for (uint32_t a = (uint32_t)x; a < nA; a += COUNT_LANES) {
-                const uint64_t m = masks[(int64_t)(OWN_NB + tc.slot) * P.n + sA + a];
+                const uint64_t m = masks[(int64_t)tc.slot * P.n + sA + a];
                 na += m != 0ull;
                 orb |= m;
                 c += (uint32_t)__popcll(tc.slot == 0 ? (m & ~((2ull << a) - 1ull)) : m);
@@ -141,7 +141,7 @@ __device__ __forceinline__ void schedule_segment(const DevParams &P, const TaskS
     const bool hi = base != 0;
     const M below = (M)(((uint64_t)1 << x) - 1u);   // x < W <= 64
     const uint64_t mask64 = ok && (uint32_t)x < t.nA
-                                ? masks[(int64_t)(OWN_NB + t.tc.slot) * P.n + t.sA + x] : 0ull;
+                                ? masks[(int64_t)t.tc.slot * P.n + t.sA + x] : 0ull;
     const M mask = (M)mask64;   // W = 32: partner slots < 32
     const uint64_t bact = __ballot(mask != 0);
     const M actA = (M)(hi ? (bact >> 32) : bact);

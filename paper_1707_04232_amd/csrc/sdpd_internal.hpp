@@ -26,8 +26,8 @@ enum { CNT_PROPOSED = 0, CNT_REJ_ENERGY, CNT_REJ_RATIO, CNT_MARGINAL, CNT_NEGEPS
 // tasks per cell of the F/D schedule: slot 0 = own cell, slots 1..13 = the
 // 13 forward neighbour cells
 constexpr int NMASK = 14;
-// active-pair masks per particle: one per neighbour cell, offset index
-// k = 0..26 (z slowest); k = 13 is the own cell, 14..26 the forward cells
+// neighbour cells of a cell: offset index k = 0..26 (z slowest), k = 13 the own
+// cell, 14..26 the forward ones; active-pair masks are kept for k >= 13
 constexpr int NNB = 27;
 constexpr int OWN_NB = 13;
 constexpr int MAX_CAP = 64;
@@ -155,7 +155,9 @@ struct sdpd_ctx {
     uint32_t *tid;
     double *q4;                  // (x, y, z, P/rho^2) per particle in cell order, 32 B
     float *q4f;                  // mixed precision: (x, y, z) relative to the cell, P/rho^2
-    uint64_t *masks;             // NNB * n
+    uint64_t *masks;             // NMASK * n
+    uint32_t *list, *list_count; // partner lists of the density pass, list_cap per particle
+    uint32_t list_cap;
     unsigned long long *counters;
     uint32_t *err;
     double *obs_partial;         // per-block observable partials

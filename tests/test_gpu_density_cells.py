@@ -20,6 +20,9 @@ BOXES = {
     "dense_64_cells": (2450, (10.0, 10.0, 10.0)),
     "dense_1152_cells": (41003, (20.0, 20.0, 45.0)),
     "few_particles": (5, (10.0, 15.0, 10.0)),
+    # a third of the particles within 1.6 of a cell corner: more partners than the
+    # lists of the density pass, sized for the mean density, hold
+    "cluster": (900, (20.0, 20.0, 20.0)),
 }
 
 
@@ -30,6 +33,12 @@ def test_cell_edges(name, form):
     n, box = BOXES[name]
     print("[case]", name, form, flush=True)
     q, p, eps, ids = uniform_state(n, box, seed=7)
+    if name == "cluster":
+        rng = np.random.default_rng(3)
+        d = rng.normal(size=(3, 300))
+        d *= 1.6 * rng.uniform(size=300) ** (1 / 3) / np.linalg.norm(d, axis=0)
+        q = np.array(q).reshape(3, n)
+        q[:, ::3] = (d + np.array([[10.0], [20.0], [5.0]])) % 20.0
     edges = [np.linspace(0.0, b, int(round(b / 2.5)) + 1) for b in box]
     full = int(np.histogramdd(np.asarray(q).reshape(3, n).T, bins=edges)[0].max())
     assert full <= 64 and (full > 48 or not name.startswith("dense"))
