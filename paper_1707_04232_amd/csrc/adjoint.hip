@@ -42,12 +42,15 @@
 #include <algorithm>
 
 #include <new>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
 #include "neighbours.hpp"
 
 namespace sdpd {
+
+constexpr int kSumBlocks = 256;   // blocks of the dA sum (and threads of its last one)
 
 struct StateBuf {
     double *q = nullptr, *p = nullptr, *eps = nullptr, *rho = nullptr, *f = nullptr;
@@ -58,58 +61,115 @@ struct StateBuf {
 struct AdjointWork {
     int K = 0, every = 0, nck = 0;
     std::vector<StateBuf> ckpt, seg;
-    StateBuf w;
     double *lq = nullptr, *lp = nullptr, *G = nullptr, *H = nullptr;   // id order
     double *Ge = nullptr, *He = nullptr;   // final-energy path (id order)
     double *eps0 = nullptr, *rho0 = nullptr;                             // id order
     double4 *v4 = nullptr;       // (v, Pi), cell order
     double *rhobar = nullptr;    // cell order
+    double *partial = nullptr;   // sums of dA: per block, then the total
     uint32_t *idcount = nullptr;
-    std::vector<void *> owned;
+    void *base = nullptr;        // all of it: one allocation, kept for the next forward pass
+    size_t bytes = 0;
 };
-
-static int walloc(AdjointWork *a, void **p, size_t bytes)
-{
-    *p = nullptr;
-    if (hipMalloc(p, bytes ? bytes : 8) != hipSuccess) return SDPD_ENOMEM;
-    a->owned.push_back(*p);
-    return SDPD_OK;
-}
-
-static int state_alloc(AdjointWork *a, StateBuf &s, size_t n)
-{
-    int rc = SDPD_OK;
-    rc = rc ? rc : walloc(a, (void **)&s.q, sizeof(double) * 3 * n);
-    rc = rc ? rc : walloc(a, (void **)&s.p, sizeof(double) * 3 * n);
-    rc = rc ? rc : walloc(a, (void **)&s.f, sizeof(double) * 3 * n);
-    rc = rc ? rc : walloc(a, (void **)&s.eps, sizeof(double) * n);
-    rc = rc ? rc : walloc(a, (void **)&s.rho, sizeof(double) * n);
-    rc = rc ? rc : walloc(a, (void **)&s.id, sizeof(uint32_t) * n);
-    return rc;
-}
 
 void adjoint_free(AdjointWork *a)
 {
     if (!a) return;
-    for (void *p : a->owned) (void)hipFree(p);
+    if (a->base) (void)hipFree(a->base);
     delete a;
+}
+
+// the buffers one after the other from base on (NULL: only their size)
+static size_t adjoint_layout(AdjointWork *a, size_t n, char *base)
+{
+    size_t used = 0;
+    auto place = [&](auto *&p, size_t count) {
+        p = reinterpret_cast<typename std::remove_reference<decltype(p)>::type>(base + used);
+        used += (sizeof(*p) * count + 255) / 256 * 256;
+    };
+    auto state = [&](StateBuf &s) {
+        place(s.q, 3 * n);
+        place(s.p, 3 * n);
+        place(s.f, 3 * n);
+        place(s.eps, n);
+        place(s.rho, n);
+        place(s.id, n);
+    };
+    for (auto &s : a->ckpt) state(s);
+    for (auto &s : a->seg) state(s);
+    place(a->v4, n);
+    for (double **p : {&a->lq, &a->lp}) place(*p, 3 * n);
+    for (double **p : {&a->G, &a->H, &a->Ge, &a->He, &a->eps0, &a->rho0, &a->rhobar}) place(*p, n);
+    place(a->partial, kSumBlocks + 1);
+    place(a->idcount, n);
+    return used;
+}
+
+// dst = src, every array of the state
+struct StateCopy {
+    StateBuf dst, src;
+};
+__global__ __launch_bounds__(256) void k_copy_state(int64_t n, StateCopy c)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    double v[11];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+        v[x] = c.src.q[x * n + k];
+        v[3 + x] = c.src.p[x * n + k];
+        v[6 + x] = c.src.f[x * n + k];
+    }
+    v[9] = c.src.eps[k];
+    v[10] = c.src.rho[k];
+    const uint32_t id = c.src.id[k];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+        c.dst.q[x * n + k] = v[x];
+        c.dst.p[x * n + k] = v[3 + x];
+        c.dst.f[x * n + k] = v[6 + x];
+    }
+    c.dst.eps[k] = v[9];
+    c.dst.rho[k] = v[10];
+    c.dst.id[k] = id;
 }
 
 static int copy_state(sdpd_ctx *c, const StateBuf &dst, const sdpd_state &src)
 {
-    const size_t n = (size_t)c->n;
-    const size_t d3 = sizeof(double) * 3 * n, d1 = sizeof(double) * n;
-    int rc = SDPD_OK;
-    auto cp = [&](void *d, const void *s, size_t b) {
-        if (!rc) rc = check_hip(hipMemcpyAsync(d, s, b, hipMemcpyDeviceToDevice, c->stream));
-    };
-    cp(dst.q, src.q, d3);
-    cp(dst.p, src.p, d3);
-    cp(dst.f, src.f, d3);
-    cp(dst.eps, src.eps, d1);
-    cp(dst.rho, src.rho, d1);
-    cp(dst.id, src.id, sizeof(uint32_t) * n);
-    return rc;
+    const StateBuf s{src.q, src.p, src.eps, src.rho, src.f, src.id};
+    hipLaunchKernelGGL(k_copy_state, dim3((unsigned)((c->n + 255) / 256)), dim3(256), 0, c->stream,
+                       c->n, StateCopy{dst, s});
+    return check_hip(hipGetLastError());
+}
+
+// dJ/dA = sum of G / A + kB/Cv (H - G ln rho0 + He - Ge ln rho0): sums of kSumBlocks
+// blocks (first launch), then of those (second, one block, into partial[kSumBlocks])
+struct SumArgs {
+    int64_t n;
+    const double *G, *H, *Ge, *He, *rho0;
+    double inv_A, kc;
+    double *partial;
+    int last;
+};
+__global__ __launch_bounds__(256) void k_sum_dA(SumArgs a)
+{
+    __shared__ double s[256];
+    double v = 0.0;
+    if (a.last) {
+        v = a.partial[threadIdx.x];
+    } else {
+        for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < a.n;
+             k += (int64_t)kSumBlocks * 256) {
+            const double l = log(a.rho0[k]);
+            v += a.G[k] * a.inv_A + a.kc * (a.H[k] - a.G[k] * l) + a.kc * (a.He[k] - a.Ge[k] * l);
+        }
+    }
+    s[threadIdx.x] = v;
+    for (int off = 128; off > 0; off >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
+    }
+    if (threadIdx.x == 0) a.partial[a.last ? kSumBlocks : blockIdx.x] = s[0];
 }
 
 // ---------------------------------------------------------------- kernels
@@ -330,8 +390,8 @@ int sdpd_adjoint_forward(sdpd_ctx *c, sdpd_state *s, int nsteps, int every)
     if (c->prm.fd != SDPD_FD_NONE || c->prm.prec != SDPD_FP64 || c->n == 0) return SDPD_EINVAL;
     if (!s->q || !s->p || !s->eps || !s->rho || !s->f || !s->id) return SDPD_EINVAL;
     const int64_t n = c->n;
-    adjoint_free(c->adj);
-    c->adj = nullptr;
+    // the last pass's memory serves this one if it is large enough, and no more than
+    // twice what is needed
     AdjointWork *a = new (std::nothrow) AdjointWork();
     if (!a) return SDPD_ENOMEM;
     a->K = nsteps;
@@ -339,22 +399,23 @@ int sdpd_adjoint_forward(sdpd_ctx *c, sdpd_state *s, int nsteps, int every)
     a->nck = (nsteps + every - 1) / every;
     a->ckpt.resize(a->nck);
     a->seg.resize(every + 1);
-    int rc = SDPD_OK;
-    for (auto &b : a->ckpt)
-        if (!rc) rc = state_alloc(a, b, n);
-    for (auto &b : a->seg)
-        if (!rc) rc = state_alloc(a, b, n);
-    if (!rc) rc = state_alloc(a, a->w, n);
-    for (double **p : {&a->lq, &a->lp})
-        if (!rc) rc = walloc(a, (void **)p, sizeof(double) * 3 * n);
-    for (double **p : {&a->G, &a->H, &a->Ge, &a->He, &a->eps0, &a->rho0, &a->rhobar})
-        if (!rc) rc = walloc(a, (void **)p, sizeof(double) * n);
-    if (!rc) rc = walloc(a, (void **)&a->v4, sizeof(double4) * n);
-    if (!rc) rc = walloc(a, (void **)&a->idcount, sizeof(uint32_t) * n);
-    if (rc) {
-        adjoint_free(a);
-        return rc;
+    const size_t need = adjoint_layout(a, (size_t)n, nullptr);
+    if (c->adj && c->adj->bytes >= need && c->adj->bytes / 2 <= need) {
+        std::swap(a->base, c->adj->base);
+        a->bytes = c->adj->bytes;
     }
+    adjoint_free(c->adj);
+    c->adj = nullptr;
+    if (!a->base) {
+        if (hipMalloc(&a->base, need) != hipSuccess) {
+            a->base = nullptr;
+            adjoint_free(a);
+            return SDPD_ENOMEM;
+        }
+        a->bytes = need;
+    }
+    adjoint_layout(a, (size_t)n, static_cast<char *>(a->base));
+    int rc = SDPD_OK;
     c->adj = a;
     // ids must be a permutation of 0..n-1 (cotangents are indexed by id)
     if ((rc = launch_fill_u32(c, a->idcount, 0u, n))) return rc;
@@ -393,7 +454,6 @@ static int adjoint_backward(sdpd_ctx *c, const double *dJ_dq, const double *dJ_d
         return rc;
     for (double *z : {a->G, a->H, a->Ge, a->He})
         if ((rc = launch_fill_u64(c, (unsigned long long *)z, 0ull, n))) return rc;
-    const sdpd_state Ws = a->w.view();
     const double dt_m = c->prm.dt / c->prm.m;
     for (int sg = a->nck - 1; sg >= 0; --sg) {
         const int start = sg * a->every, end = std::min(start + a->every, a->K);
@@ -406,14 +466,14 @@ static int adjoint_backward(sdpd_ctx *c, const double *dJ_dq, const double *dJ_d
             if ((rc = enqueue_step(c, &nxt, (uint64_t)(start + k - 1), true))) return rc;
         }
         if (sg == a->nck - 1) {   // the final configuration: second half kick of step K-1
-            if ((rc = copy_state(c, a->w, a->seg[end - start].view()))) return rc;
-            if ((rc = vjp_config(c, a, Ws, 1.0, dJ_deps, dJ_drho))) return rc;
+            if ((rc = vjp_config(c, a, a->seg[end - start].view(), 1.0, dJ_deps, dJ_drho)))
+                return rc;
         }
         for (int N = end - 1; N >= start; --N) {
             hipLaunchKernelGGL(k_axpy, dim3(nblk(3 * n)), dim3(256), 0, c->stream, 3 * n, dt_m,
                                a->lq, a->lp);
-            if ((rc = copy_state(c, a->w, a->seg[N - start].view()))) return rc;
-            if ((rc = vjp_config(c, a, Ws, N > 0 ? 2.0 : 1.0))) return rc;
+            // (its state is not needed again: the product sorts it in place)
+            if ((rc = vjp_config(c, a, a->seg[N - start].view(), N > 0 ? 2.0 : 1.0))) return rc;
         }
     }
     // initial-state path: the entropies come from eps0 and rho(q0)
@@ -421,7 +481,8 @@ static int adjoint_backward(sdpd_ctx *c, const double *dJ_dq, const double *dJ_d
     double *eps0bar = dJ_deps0;
     hipLaunchKernelGGL(k_initial_path, dim3(nblk(n)), dim3(256), 0, c->stream, n, g, a->G, a->Ge,
                        a->eps0, a->rho0, eps0bar, a->rhobar);   // rhobar: id order here
-    // W holds configuration 0 with its cells and masks (last vjp_config)
+    // the last product left configuration 0 with its cells and lists
+    const sdpd_state Ws = a->seg[0].view();
     hipLaunchKernelGGL(k_pack_rhobar, dim3(nblk(n)), dim3(256), 0, c->stream, n, Ws.id, a->rhobar,
                        c->q4);
     hipLaunchKernelGGL((c->dp.kernel == SDPD_KERNEL_LUCY ? k_vjp_q<true, false>
@@ -434,22 +495,17 @@ static int adjoint_backward(sdpd_ctx *c, const double *dJ_dq, const double *dJ_d
     if ((rc = check_hip(hipMemcpyAsync(dJ_dp0, a->lp, d3, hipMemcpyDeviceToDevice, c->stream))))
         return rc;
     if (dJ_dA || dJ_dCv) {
-        std::vector<double> G(n), H(n), Ge(n), He(n), r0(n);
-        const std::pair<double *, const double *> cp[] = {
-            {G.data(), a->G}, {H.data(), a->H}, {Ge.data(), a->Ge}, {He.data(), a->He},
-            {r0.data(), a->rho0}};
-        for (const auto &x : cp)
-            if (!rc)
-                rc = check_hip(hipMemcpyAsync(x.first, x.second, sizeof(double) * n,
-                                              hipMemcpyDeviceToHost, c->stream));
-        if (!rc) rc = check_hip(hipStreamSynchronize(c->stream));
-        if (rc) return rc;
-        const double kc = c->prm.kB / c->prm.Cv;
+        SumArgs s{n, a->G, a->H, a->Ge, a->He, a->rho0, 1.0 / c->dp.A, c->prm.kB / c->prm.Cv,
+                  a->partial, 0};
+        hipLaunchKernelGGL(k_sum_dA, dim3(kSumBlocks), dim3(256), 0, c->stream, s);
+        s.last = 1;
+        hipLaunchKernelGGL(k_sum_dA, dim3(1), dim3(256), 0, c->stream, s);
+        if ((rc = check_hip(hipGetLastError()))) return rc;
         double acc = 0.0;
-        for (int64_t k = 0; k < n; ++k) {
-            const double lr0 = log(r0[k]);
-            acc += G[k] / c->dp.A + kc * (H[k] - G[k] * lr0) + kc * (He[k] - Ge[k] * lr0);
-        }
+        if ((rc = check_hip(hipMemcpyAsync(&acc, a->partial + kSumBlocks, sizeof acc,
+                                           hipMemcpyDeviceToHost, c->stream))))
+            return rc;
+        if ((rc = check_hip(hipStreamSynchronize(c->stream)))) return rc;
         if (dJ_dA) *dJ_dA = acc;
         if (dJ_dCv) *dJ_dCv = -(c->dp.A / c->prm.Cv) * acc;
     }
