@@ -165,8 +165,8 @@ static int dalloc(T **p, size_t count)
 
 static void free_ctx(sdpd_ctx *c)
 {
-    void *bufs[] = {c->cell_of, c->count, c->cursor, c->cell_start, c->block_sums, c->tmp_idx,
-                    c->perm, c->cell_sorted, c->tq, c->tp, c->teps, c->trho, c->tf, c->tid,
+    void *bufs[] = {c->cell_of, c->count, c->slot, c->cell_start, c->block_sums, c->tmp_idx,
+                    c->cell_sorted, c->tq, c->tp, c->teps, c->trho, c->tf, c->tid,
                     c->masks, c->list, c->list_count, c->counters, c->err, c->obs_partial, c->obs_out,
                     c->dparams, c->task_count, c->task_np, c->pair_off, c->part_off,
                     c->part_list, c->pairs, c->rec_buf, c->lvl_end, c->flow_rec, c->q4f, c->dstep, c->q4,
@@ -281,7 +281,7 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     c->n = params->n;
     c->ncell = c->dp.ncell;
     const size_t n = (size_t)c->n, nce = (size_t)c->ncell;
-    c->nscan_blocks = (int64_t)(((size_t)NMASK * nce + 1023) / 1024) + 1;
+    c->nscan_blocks = 2 * (int64_t)(((size_t)NMASK * nce + 1023) / 1024);
     c->obs_blocks = std::max(observe_blocks(c->n), 1);
     {
         int lds = 0;
@@ -313,11 +313,10 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     rc = SDPD_OK;
     rc = rc ? rc : dalloc(&c->cell_of, n);
     rc = rc ? rc : dalloc(&c->count, nce);
-    rc = rc ? rc : dalloc(&c->cursor, nce);
     rc = rc ? rc : dalloc(&c->cell_start, nce + 1);
     rc = rc ? rc : dalloc(&c->block_sums, (size_t)c->nscan_blocks);
     rc = rc ? rc : dalloc(&c->tmp_idx, n);
-    rc = rc ? rc : dalloc(&c->perm, n);
+    rc = rc ? rc : dalloc(&c->slot, n);
     rc = rc ? rc : dalloc(&c->cell_sorted, n);
     rc = rc ? rc : dalloc(&c->tq, 3 * n);
     rc = rc ? rc : dalloc(&c->tp, 3 * n);
@@ -353,6 +352,7 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
         rc = check_hip(hipMemcpyAsync(c->dparams, &c->dp, sizeof c->dp, hipMemcpyHostToDevice,
                                       c->stream));
     if (!rc) rc = launch_fill_u32(c, c->err, 0u, 1);
+    if (!rc) rc = launch_fill_u32(c, c->count, 0u, c->ncell);
     if (!rc) rc = launch_fill_u64(c, c->counters, 0ull, CNT_N);
     if (!rc) rc = check_hip(hipStreamSynchronize(c->stream));
     if (!rc) rc = fd_prepare_sweep(c);
@@ -438,15 +438,18 @@ int enqueue_step(sdpd_ctx *c, const sdpd_state *s, uint64_t step, bool set_step)
 {
     int rc;
     const uint64_t theta = (uint64_t)c->prm.fd_every;
-    if ((rc = run_build_cells(c, s, 1))) return rc;
+    const bool sweep = step % theta == 0;
+    StepStart start{c->counters, nullptr, step};
+    if (sweep && set_step) start.dstep = (unsigned long long *)c->dstep;
+    if ((rc = run_build_cells(c, s, 1, start))) return rc;
     // FP64: the density pass leaves (x, y, z, rho) packed for the sweep
     const bool packed = !c->dp.mixed;
     if ((rc = run_density(c, s, 1, packed))) return rc;
-    if ((rc = launch_fill_u64(c, c->counters, 0ull, CNT_N))) return rc;
-    if (step % theta == 0) {
-        if (set_step &&
-            (rc = launch_fill_u64(c, (unsigned long long *)c->dstep, step, 1)))
-            return rc;
+    if (c->n == 0) {   // (no launch over the particles has done it)
+        if ((rc = launch_fill_u64(c, c->counters, 0ull, CNT_N))) return rc;
+        if (start.dstep && (rc = launch_fill_u64(c, start.dstep, step, 1))) return rc;
+    }
+    if (sweep) {
         if ((rc = run_fd_sweep(c, s, c->prm.dt * (double)theta, packed))) return rc;
     }
     if ((rc = run_forces(c, s, 1))) return rc;

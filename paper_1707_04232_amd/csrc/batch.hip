@@ -159,14 +159,18 @@ static int build_fused(sdpd_batch *b, int nparts)
     std::vector<LaunchRecord> recs(nbox);
     const BatchTuning shared(b->ctx);
     int rc = SDPD_OK;
+    int64_t cells = 0;
+    for (const sdpd_ctx *c : b->ctx) cells += c->ncell;
     for (int i = 0; i < nbox && !rc; ++i) {
         sdpd_ctx *c = b->ctx[i];
         c->rec = &recs[i];
         c->fd_per_group = 1;
         c->fd_record_flow = b->flow ? 1 : 0;
+        c->batch_cells = cells / std::max(1, std::min(nparts, nbox));
         for (int k = 0; k < b->theta && !rc; ++k) rc = enqueue_step(c, &b->st[i], (uint64_t)k, false);
         c->fd_per_group = 0;
         c->fd_record_flow = 0;
+        c->batch_cells = 0;
         c->rec = nullptr;
     }
     if (rc) return rc;

@@ -5,6 +5,8 @@
 // the order of the pairwise fluctuation/dissipation updates.
 #include "sdpd_internal.hpp"
 
+#include <algorithm>
+
 namespace sdpd {
 
 struct FillU32Args {
@@ -63,7 +65,8 @@ struct KickDriftArgs {
     double *q, *p;
     const double *f;
     int kick_drift;
-    uint32_t *cell_of, *count, *err;
+    uint32_t *cell_of, *slot, *count, *err;   // slot: place among the cell's, any order
+    StepStart start;
 };
 __device__ __forceinline__ void kick_drift_assign_body(const KickDriftArgs &a, uint32_t blk)
 {
@@ -73,6 +76,8 @@ __device__ __forceinline__ void kick_drift_assign_body(const KickDriftArgs &a, u
     const int kick_drift = a.kick_drift;
     uint32_t *cell_of = a.cell_of, *count = a.count, *err = a.err;
     int64_t i = (int64_t)blk * blockDim.x + threadIdx.x;
+    if (a.start.counters && i < CNT_N) a.start.counters[i] = 0ull;
+    if (a.start.dstep && i == 0) *a.start.dstep = a.start.step;
     if (i >= P.n) return;
     const int64_t n = P.n;
     int cc[3];
@@ -94,12 +99,12 @@ __device__ __forceinline__ void kick_drift_assign_body(const KickDriftArgs &a, u
     if (!finite) atomicOr(err, ERR_NONFINITE);
     uint32_t c = (uint32_t)(cc[0] + P.nc[0] * (cc[1] + P.nc[1] * cc[2]));
     cell_of[i] = c;
-    (void)wave_counted_inc(count, c);
+    a.slot[i] = wave_counted_inc(count, c);
 }
 __global__ void k_kick_drift_assign(KickDriftArgs a) { kick_drift_assign_body(a, blockIdx.x); }
 SDPD_MULTI_KERNEL(k_kick_drift_assign_multi, KickDriftArgs, kick_drift_assign_body, 256)
 
-// --- exclusive scan of the cell counts into cell_start (3 passes) ---------
+// --- exclusive prefix sums (cell counts, pairs and particles of the tasks) ---
 constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_PER_THREAD = 4;
 constexpr int SCAN_BLOCK = SCAN_THREADS * SCAN_PER_THREAD;
@@ -121,172 +126,129 @@ __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s, uint32_t *tota
     return incl - v;
 }
 
-struct ScanLocalArgs {
-    const uint32_t *count;
-    int64_t ncell;
-    int cap;
-    uint32_t *out, *block_sums, *err;
+// Up to two arrays of one length in one launch (workgroups 0 .. nblocks - 1 and
+// nblocks .. 2 nblocks - 1): prefix sums inside each block of SCAN_BLOCK values, then
+// each block adds the sum of the blocks before it, which it forms itself (a launch
+// for those sums costs more than they do: 4.5 us, and 54 us for 6900 blocks).
+struct ScanArgs {
+    uint32_t *in[2];
+    uint32_t *out[2], *sums[2];
+    int64_t count, nblocks;
+    int cap, clear;          // clear: in is zero afterwards
+    uint32_t *err;
 };
-__device__ __forceinline__ void scan_local_body(const ScanLocalArgs &a, uint32_t blk)
+__device__ __forceinline__ void scan_local_body(const ScanArgs &a, uint32_t blk)
 {
-    const uint32_t *count = a.count;
-    const int64_t ncell = a.ncell;
-    const int cap = a.cap;
-    uint32_t *out = a.out, *block_sums = a.block_sums, *err = a.err;
+    const int which = blk >= a.nblocks;
+    const int64_t b = (int64_t)blk - (which ? a.nblocks : 0);
+    uint32_t *in = a.in[which], *out = a.out[which];
     __shared__ uint32_t s[SCAN_THREADS];
-    int64_t base = (int64_t)blk * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
+    int64_t base = b * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
     uint32_t v[SCAN_PER_THREAD], sum = 0;
     bool over = false;
 #pragma unroll
     for (int k = 0; k < SCAN_PER_THREAD; ++k) {
-        v[k] = base + k < ncell ? count[base + k] : 0u;
-        over = over || (cap >= 0 && v[k] > (uint32_t)cap);
+        v[k] = base + k < a.count ? in[base + k] : 0u;
+        if (a.clear && base + k < a.count) in[base + k] = 0u;
+        over = over || (a.cap >= 0 && v[k] > (uint32_t)a.cap);
         sum += v[k];
     }
-    if (over) atomicOr(err, ERR_CELLCAP);
+    if (over) atomicOr(a.err, ERR_CELLCAP);
     uint32_t total;
     uint32_t ex = block_exclusive_scan(sum, s, &total);
 #pragma unroll
     for (int k = 0; k < SCAN_PER_THREAD; ++k) {
-        if (base + k < ncell) out[base + k] = ex;
+        if (base + k < a.count) out[base + k] = ex;
         ex += v[k];
     }
-    if (threadIdx.x == 0) block_sums[blk] = total;
+    if (threadIdx.x == 0) {
+        a.sums[which][b] = total;
+        if (a.nblocks == 1) out[a.count] = total;
+    }
 }
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_local(ScanLocalArgs a)
+__global__ __launch_bounds__(SCAN_THREADS) void k_scan_local(ScanArgs a)
 {
     scan_local_body(a, blockIdx.x);
 }
-SDPD_MULTI_KERNEL(k_scan_local_multi, ScanLocalArgs, scan_local_body, SCAN_THREADS)
+SDPD_MULTI_KERNEL(k_scan_local_multi, ScanArgs, scan_local_body, SCAN_THREADS)
 
-// one workgroup: exclusive scan of the block sums, in place; the grand
-// total goes to block_sums[nblocks]
-struct ScanSumsArgs {
-    uint32_t *block_sums;
-    int64_t nblocks;
-};
-__device__ __forceinline__ void scan_sums_body(const ScanSumsArgs &a, uint32_t)
+__device__ __forceinline__ void scan_add_body(const ScanArgs &a, uint32_t blk)
 {
-    uint32_t *block_sums = a.block_sums;
-    const int64_t nblocks = a.nblocks;
+    const int which = blk >= a.nblocks;
+    const int64_t b = (int64_t)blk - (which ? a.nblocks : 0);
+    const uint32_t *sums = a.sums[which];
+    uint32_t *out = a.out[which];
     __shared__ uint32_t s[SCAN_THREADS];
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < nblocks; base += SCAN_THREADS) {
-        int64_t i = base + threadIdx.x;
-        uint32_t v = i < nblocks ? block_sums[i] : 0u;
-        uint32_t total;
-        uint32_t ex = block_exclusive_scan(v, s, &total);
-        if (i < nblocks) block_sums[i] = ex + carry;
-        carry += total;
+    uint32_t before = 0u;
+    for (int64_t i = threadIdx.x; i < b; i += SCAN_THREADS) before += sums[i];
+    s[threadIdx.x] = before;
+    for (int off = SCAN_THREADS / 2; off > 0; off >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
     }
-    if (threadIdx.x == 0) block_sums[nblocks] = carry;
-}
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_sums(ScanSumsArgs a)
-{
-    scan_sums_body(a, 0u);
-}
-SDPD_MULTI_KERNEL(k_scan_sums_multi, ScanSumsArgs, scan_sums_body, SCAN_THREADS)
-
-struct ScanAddArgs {
-    uint32_t *out;
-    const uint32_t *block_sums;
-    int64_t count, nblocks;
-};
-__device__ __forceinline__ void scan_add_body(const ScanAddArgs &a, uint32_t blk)
-{
-    int64_t base = (int64_t)blk * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
-    uint32_t add = a.block_sums[blk];
+    __syncthreads();
+    const uint32_t add = s[0];
+    int64_t base = b * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
 #pragma unroll
     for (int k = 0; k < SCAN_PER_THREAD; ++k)
-        if (base + k < a.count) a.out[base + k] += add;
-    if (blk == 0 && threadIdx.x == 0) a.out[a.count] = a.block_sums[a.nblocks];
+        if (base + k < a.count) out[base + k] += add;
+    if (b == a.nblocks - 1 && threadIdx.x == 0) out[a.count] = add + sums[b];
 }
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_add(ScanAddArgs a)
+__global__ __launch_bounds__(SCAN_THREADS) void k_scan_add(ScanArgs a)
 {
     scan_add_body(a, blockIdx.x);
 }
-SDPD_MULTI_KERNEL(k_scan_add_multi, ScanAddArgs, scan_add_body, SCAN_THREADS)
+SDPD_MULTI_KERNEL(k_scan_add_multi, ScanArgs, scan_add_body, SCAN_THREADS)
 
-// out[0..count] = exclusive prefix sums of in[0..count), out[count] = total.
-// block_sums needs ceil(count / 1024) + 1 entries.  A value above cap sets
-// ERR_CELLCAP (cap < 0: no check).
-int run_scan(sdpd_ctx *c, const uint32_t *in, uint32_t *out, int64_t count, uint32_t *block_sums,
-             int cap)
+// out[0..count] = exclusive prefix sums of in[0..count), out[count] = total, for one
+// array or two (in2 not NULL).  block_sums needs ceil(count / 1024) entries for each.
+// A value above cap sets ERR_CELLCAP (cap < 0: no check).
+int run_scan(sdpd_ctx *c, uint32_t *in, uint32_t *out, uint32_t *in2, uint32_t *out2,
+             int64_t count, uint32_t *block_sums, int cap, bool clear)
 {
     const int64_t nb = (count + SCAN_BLOCK - 1) / SCAN_BLOCK;
-    if (nb == 0) return launch_fill_u32(c, out, 0u, 1);
-    int rc = launch_or_record(c, k_scan_local, k_scan_local_multi, (unsigned)nb, SCAN_THREADS, 0,
-                              ScanLocalArgs{in, count, cap, out, block_sums, c->err});
-    if (!rc)
-        rc = launch_or_record(c, k_scan_sums, k_scan_sums_multi, 1u, SCAN_THREADS, 0,
-                              ScanSumsArgs{block_sums, nb});
-    if (!rc)
-        rc = launch_or_record(c, k_scan_add, k_scan_add_multi, (unsigned)nb, SCAN_THREADS, 0,
-                              ScanAddArgs{out, block_sums, count, nb});
+    if (nb == 0) {
+        const int rc = launch_fill_u32(c, out, 0u, 1);
+        return rc || !in2 ? rc : launch_fill_u32(c, out2, 0u, 1);
+    }
+    const ScanArgs args{{in, in2}, {out, out2}, {block_sums, block_sums + nb}, count, nb, cap,
+                        clear ? 1 : 0, c->err};
+    const unsigned grid = (unsigned)(in2 ? 2 * nb : nb);
+    int rc = launch_or_record(c, k_scan_local, k_scan_local_multi, grid, SCAN_THREADS, 0, args);
+    // (recorded also for one block: the boxes of a batch make the same launches)
+    if (!rc && (nb > 1 || c->rec))
+        rc = launch_or_record(c, k_scan_add, k_scan_add_multi, grid, SCAN_THREADS, 0, args);
     return rc;
 }
 
-// particle i goes to an arbitrary free position of its cell
+// particle i goes to its slot of its cell (any order)
 struct ScatterArgs {
-    const uint32_t *cell_of, *cell_start;
-    uint32_t *cursor, *tmp_idx;
+    const uint32_t *cell_of, *cell_start, *slot;
+    uint32_t *tmp_idx;
     int64_t n;
 };
 __device__ __forceinline__ void scatter_body(const ScatterArgs &a, uint32_t blk)
 {
     int64_t i = (int64_t)blk * blockDim.x + threadIdx.x;
     if (i >= a.n) return;
-    uint32_t c = a.cell_of[i];
-    uint32_t pos = a.cell_start[c] + wave_counted_inc(a.cursor, c);
-    a.tmp_idx[pos] = (uint32_t)i;
+    a.tmp_idx[a.cell_start[a.cell_of[i]] + a.slot[i]] = (uint32_t)i;
 }
 __global__ void k_scatter(ScatterArgs a) { scatter_body(a, blockIdx.x); }
 SDPD_MULTI_KERNEL(k_scatter_multi, ScatterArgs, scatter_body, 256)
 
-// final position = cell start + rank of the id inside the cell (ties, which
-// only invalid input with repeated ids has, broken by the scatter position so
-// that every slot is written once); cells above the capacity keep the
-// scatter order (the overflow is reported by the scan)
-struct RankArgs {
-    const uint32_t *tmp_idx, *cell_of, *cell_start, *id;
-    uint32_t *perm;
-    int64_t n;
-    int cap;
-};
-__device__ __forceinline__ void rank_body(const RankArgs &a, uint32_t blk)
-{
-    const uint32_t *tmp_idx = a.tmp_idx, *cell_of = a.cell_of, *cell_start = a.cell_start,
-                   *id = a.id;
-    uint32_t *perm = a.perm;
-    const int cap = a.cap;
-    int64_t k = (int64_t)blk * blockDim.x + threadIdx.x;
-    if (k >= a.n) return;
-    uint32_t i = tmp_idx[k];
-    uint32_t c = cell_of[i];
-    uint32_t s = cell_start[c], e = cell_start[c + 1];
-    if (e - s > (uint32_t)cap) {
-        perm[k] = i;
-        return;
-    }
-    uint32_t my = id[i], rank = 0;
-    for (uint32_t t = s; t < e; ++t) {
-        const uint32_t o = id[tmp_idx[t]];
-        rank += (o < my || (o == my && t < (uint32_t)k)) ? 1u : 0u;
-    }
-    perm[s + rank] = i;
-}
-__global__ void k_rank(RankArgs a) { rank_body(a, blockIdx.x); }
-SDPD_MULTI_KERNEL(k_rank_multi, RankArgs, rank_body, 256)
-
-// gather into (cell, id) order; with q4f (mixed precision) also the FP32
-// position relative to the particle's cell origin, in the x, y, z slots of
-// the particle's 16-byte record (the w slot takes P/rho^2 later)
+// Sort into (cell, id) order: final position = cell start + rank of the id inside the
+// cell (ties, which only invalid input with repeated ids has, broken by the scatter
+// position so that every slot is written once); cells above the capacity keep the
+// scatter order (the overflow is reported by the scan).  With q4f (mixed precision)
+// also the FP32 position relative to the particle's cell origin, in the x, y, z slots
+// of the particle's 16-byte record (the w slot takes P/rho^2 later).
 struct GatherArgs {
     DevParams P;
     int64_t n;
-    const uint32_t *perm, *cell_of;
+    const uint32_t *tmp_idx, *cell_of, *cell_start;
     const double *q, *p, *eps, *rho, *f;
     const uint32_t *id;
+    int cap;
     double *tq, *tp, *teps, *trho, *tf;
     uint32_t *tid, *cell_sorted;
     float *q4f;
@@ -296,18 +258,27 @@ __device__ __forceinline__ void gather_body(const GatherArgs &a, uint32_t blk)
 {
     const DevParams &P = a.P;
     const int64_t n = a.n;
-    const uint32_t *perm = a.perm, *cell_of = a.cell_of;
+    const uint32_t *tmp_idx = a.tmp_idx;
     const double *q = a.q, *p = a.p, *eps = a.eps, *rho = a.rho, *f = a.f;
     const uint32_t *id = a.id;
     double *tq = a.tq, *tp = a.tp, *teps = a.teps, *trho = a.trho, *tf = a.tf;
     uint32_t *tid = a.tid, *cell_sorted = a.cell_sorted;
     float *q4f = a.q4f;
     double *q4 = a.q4;
-    int64_t k = (int64_t)blk * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    uint32_t i = perm[k];
+    const int64_t from = (int64_t)blk * blockDim.x + threadIdx.x;
+    if (from >= n) return;
+    const uint32_t i = tmp_idx[from], c = a.cell_of[i];
+    const uint32_t s = a.cell_start[c], e = a.cell_start[c + 1], my = id[i];
+    int64_t k = from;
+    if (e - s <= (uint32_t)a.cap) {
+        uint32_t rank = 0;
+        for (uint32_t t = s; t < e; ++t) {
+            const uint32_t o = id[tmp_idx[t]];
+            rank += (o < my || (o == my && t < (uint32_t)from)) ? 1u : 0u;
+        }
+        k = (int64_t)s + rank;
+    }
     if (q4f) {
-        const uint32_t c = cell_of[i];
         const int cc[3] = {(int)(c % (uint32_t)P.nc[0]), (int)((c / (uint32_t)P.nc[0]) % (uint32_t)P.nc[1]),
                            (int)(c / ((uint32_t)P.nc[0] * (uint32_t)P.nc[1]))};
 #pragma unroll
@@ -318,15 +289,15 @@ __device__ __forceinline__ void gather_body(const GatherArgs &a, uint32_t blk)
     q4[4 * k + 1] = q[n + i];
     q4[4 * k + 2] = q[2 * n + i];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        tq[c * n + k] = q[c * n + i];
-        tp[c * n + k] = p[c * n + i];
-        if (tf) tf[c * n + k] = f[c * n + i];
+    for (int d = 0; d < 3; ++d) {
+        tq[d * n + k] = q[d * n + i];
+        tp[d * n + k] = p[d * n + i];
+        if (tf) tf[d * n + k] = f[d * n + i];
     }
     teps[k] = eps[i];
     trho[k] = rho[i];
-    tid[k] = id[i];
-    cell_sorted[k] = cell_of[i];
+    tid[k] = my;
+    cell_sorted[k] = c;
 }
 __global__ void k_gather(GatherArgs a) { gather_body(a, blockIdx.x); }
 SDPD_MULTI_KERNEL(k_gather_multi, GatherArgs, gather_body, 256)
@@ -394,37 +365,35 @@ int launch_fill_u64(sdpd_ctx *c, unsigned long long *p, unsigned long long v, in
 }
 
 // Sort the state by (cell, id).  With kick_drift the first half kick and the
-// drift of the step are applied first.
-int run_build_cells(sdpd_ctx *c, const sdpd_state *s, int kick_drift)
+// drift of the step are applied first; start: counters and step index to set.
+int run_build_cells(sdpd_ctx *c, const sdpd_state *s, int kick_drift, const StepStart &start)
 {
     const int64_t n = c->n, nc = c->ncell;
     int rc;
     timer_begin(c, TK_CELLS);
-    if ((rc = launch_fill_u32(c, c->count, 0u, nc))) return rc;
-    if ((rc = launch_fill_u32(c, c->cursor, 0u, nc))) return rc;
+    // c->count is zero: the scan of the last build left it so
     if (n > 0 &&
         (rc = launch_or_record(c, k_kick_drift_assign, k_kick_drift_assign_multi,
-                               blocks_for(n, 256), 256, 0,
+                               blocks_for(std::max<int64_t>(n, CNT_N), 256), 256, 0,
                                KickDriftArgs{c->dp, s->q, s->p, s->f, kick_drift, c->cell_of,
-                                             c->count, c->err})))
+                                             c->slot, c->count, c->err, start})))
         return rc;
-    if ((rc = run_scan(c, c->count, c->cell_start, nc, c->block_sums, c->prm.cell_cap))) return rc;
+    if ((rc = run_scan(c, c->count, c->cell_start, nullptr, nullptr, nc, c->block_sums,
+                       c->prm.cell_cap, true)))
+        return rc;
     if (n > 0) {
         unsigned g = blocks_for(n, 256);
         // inside a step (kick_drift) the forces are recomputed before
         // anything reads them, so they are not carried through the sort
         double *tf = kick_drift ? nullptr : c->tf;
         rc = launch_or_record(c, k_scatter, k_scatter_multi, g, 256, 0,
-                              ScatterArgs{c->cell_of, c->cell_start, c->cursor, c->tmp_idx, n});
-        if (!rc)
-            rc = launch_or_record(c, k_rank, k_rank_multi, g, 256, 0,
-                                  RankArgs{c->tmp_idx, c->cell_of, c->cell_start, s->id, c->perm,
-                                           n, c->prm.cell_cap});
+                              ScatterArgs{c->cell_of, c->cell_start, c->slot, c->tmp_idx, n});
         if (!rc)
             rc = launch_or_record(c, k_gather, k_gather_multi, g, 256, 0,
-                                  GatherArgs{c->dp, n, c->perm, c->cell_of, s->q, s->p, s->eps,
-                                             s->rho, s->f, s->id, c->tq, c->tp, c->teps, c->trho,
-                                             tf, c->tid, c->cell_sorted, c->q4f, c->q4});
+                                  GatherArgs{c->dp, n, c->tmp_idx, c->cell_of, c->cell_start,
+                                             s->q, s->p, s->eps, s->rho, s->f, s->id,
+                                             c->prm.cell_cap, c->tq, c->tp, c->teps, c->trho, tf,
+                                             c->tid, c->cell_sorted, c->q4f, c->q4});
         if (!rc)
             rc = launch_or_record(c, k_copy_back, k_copy_back_multi, g, 256, 0,
                                   CopyBackArgs{n, c->tq, c->tp, tf, c->teps, c->trho, c->tid, s->q,

@@ -13,8 +13,10 @@ __device__ __forceinline__ void density_cubic_body(const DensityArgs &a, uint32_
 {
     density_body<ModelF64, false>(a, blk);
 }
-SDPD_MULTI_KERNEL(k_density_lucy_multi, DensityArgs, density_lucy_body, 64 * kCellWaves)
-SDPD_MULTI_KERNEL(k_density_cubic_multi, DensityArgs, density_cubic_body, 64 * kCellWaves)
+SDPD_MULTI_KERNEL(k_density_lucy_multi, DensityArgs, density_lucy_body, 64 * kCellWaves,
+                  ModelF64::kDensityOcc)
+SDPD_MULTI_KERNEL(k_density_cubic_multi, DensityArgs, density_cubic_body, 64 * kCellWaves,
+                  ModelF64::kDensityOcc)
 
 int run_density(sdpd_ctx *c, const sdpd_state *s, int update_eps, bool pack_rho)
 {

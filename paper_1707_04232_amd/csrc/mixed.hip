@@ -24,8 +24,10 @@ __device__ __forceinline__ void forces_cubic_body(const ForcesArgs &a, uint32_t 
 {
     forces_body<ModelF32, false>(a, blk);
 }
-SDPD_MULTI_KERNEL(k_density_f32_lucy_multi, DensityArgs, density_lucy_body, 64 * kCellWaves)
-SDPD_MULTI_KERNEL(k_density_f32_cubic_multi, DensityArgs, density_cubic_body, 64 * kCellWaves)
+SDPD_MULTI_KERNEL(k_density_f32_lucy_multi, DensityArgs, density_lucy_body, 64 * kCellWaves,
+                  ModelF32::kDensityOcc)
+SDPD_MULTI_KERNEL(k_density_f32_cubic_multi, DensityArgs, density_cubic_body, 64 * kCellWaves,
+                  ModelF32::kDensityOcc)
 SDPD_MULTI_KERNEL(k_forces_f32_lucy_multi, ForcesArgs, forces_lucy_body, 256)
 SDPD_MULTI_KERNEL(k_forces_f32_cubic_multi, ForcesArgs, forces_cubic_body, 256)
 

@@ -501,19 +501,25 @@ __device__ __forceinline__ void schedule_tasks(const ScheduleArgs &a, int64_t T0
         sched_sync();
     }
 }
-__global__ __launch_bounds__(64 * SCHED_TASK_WAVES) void k_schedule_tasks(ScheduleArgs a)
+__device__ __forceinline__ void schedule_tasks_body(const ScheduleArgs &a, uint32_t blk)
 {
     __shared__ ScheduleLds lds[SCHED_TASK_WAVES];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t T0 = ((int64_t)xcd_block(blockIdx.x, gridDim.x) * SCHED_TASK_WAVES + wave) *
-                       SCHED_TASKS;
+    const int64_t T0 = ((int64_t)blk * SCHED_TASK_WAVES + wave) * SCHED_TASKS;
     if (T0 < (int64_t)NMASK * a.Pp->ncell) schedule_tasks(a, T0, lds[wave]);
 }
+__global__ __launch_bounds__(64 * SCHED_TASK_WAVES) void k_schedule_tasks(ScheduleArgs a)
+{
+    schedule_tasks_body(a, xcd_block(blockIdx.x, gridDim.x));
+}
+SDPD_MULTI_KERNEL(k_schedule_tasks_multi, ScheduleArgs, schedule_tasks_body,
+                  64 * SCHED_TASK_WAVES)
 
 // With fewer cells a lane's pairs one after the other take longer than they save:
 // counts, scans and schedule of 1728 cells 46 us (tasks on lanes: 88), 7128 cells
-// 109 (102), 13824 cells 162 (130), 61250 cells 600 (336).  Boxes whose launches are
-// recorded for a batch keep the multi-box form.
+// 109 (102), 13824 cells 162 (130), 61250 cells 600 (336).  In launches recorded for
+// a batch the cells of all boxes that share the launch count (64 boxes of 1000 to
+// 17000 particles, two steps: 8.87 -> 8.69 ms).
 constexpr int64_t SCHED_TASKS_MIN_CELLS = 6 << 10;
 
 int run_schedule(sdpd_ctx *c)
@@ -527,19 +533,20 @@ int run_schedule(sdpd_ctx *c)
                               TaskCountArgs{c->dparams, c->cell_start, c->masks, c->task_count,
                                             c->task_np});
     if (rc) return rc;
-    if ((rc = run_scan(c, c->task_count, c->pair_off, ntask, c->block_sums, -1))) return rc;
-    if ((rc = run_scan(c, c->task_np, c->part_off, ntask, c->block_sums, -1))) return rc;
+    if ((rc = run_scan(c, c->task_count, c->pair_off, c->task_np, c->part_off, ntask,
+                       c->block_sums, -1, false)))
+        return rc;
     // one workgroup per pair of tasks: many independent short waves hide the
     // load latency
     const int64_t grid = std::min<int64_t>((ntask / 2 + SCHED_WAVES - 1) / SCHED_WAVES, 0x7fffffffLL);
     const ScheduleArgs args{c->dparams, c->cell_start, c->masks, c->pair_off, c->part_off,
                             c->pairs, c->part_list, (uint32_t)c->pair_cap, (uint32_t)c->part_cap,
                             c->err, (uint32_t)grid};
-    if (c->ncell >= SCHED_TASKS_MIN_CELLS && !c->rec) {
+    if (std::max(c->ncell, c->batch_cells) >= SCHED_TASKS_MIN_CELLS) {
         const int64_t per = (int64_t)SCHED_TASK_WAVES * SCHED_TASKS;
-        hipLaunchKernelGGL(k_schedule_tasks, dim3((unsigned)((ntask + per - 1) / per)),
-                           dim3(64 * SCHED_TASK_WAVES), 0, c->stream, args);
-        rc = check_hip(hipGetLastError());
+        rc = launch_or_record(c, k_schedule_tasks, k_schedule_tasks_multi,
+                              (unsigned)((ntask + per - 1) / per), 64 * SCHED_TASK_WAVES, 0,
+                              args);
     } else {
         rc = launch_or_record(c, k_schedule, k_schedule_multi, (unsigned)grid, 64 * SCHED_WAVES,
                               0, args);

@@ -129,9 +129,9 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n)
     return base + (o % kXcd) * kRun + o / kXcd;
 }
 
-#define SDPD_MULTI_KERNEL(NAME, ARGS, BODY, THREADS)                                          \
-    __global__ __launch_bounds__(THREADS) void NAME(const void *__restrict__ tab,              \
-                                                    const uint2 *__restrict__ wg)              \
+#define SDPD_MULTI_KERNEL(NAME, ARGS, BODY, ...)   /* ...: launch bounds */                      \
+    __global__ __launch_bounds__(__VA_ARGS__) void NAME(const void *__restrict__ tab,          \
+                                                        const uint2 *__restrict__ wg)          \
     {                                                                                          \
         const uint2 w = wg[blockIdx.x];                                                        \
         const ARGS *__restrict__ t = static_cast<const ARGS *>(tab);                           \
@@ -148,7 +148,7 @@ struct sdpd_ctx {
     int device;
     int64_t n, ncell;
     // cell list
-    uint32_t *cell_of, *count, *cursor, *cell_start, *block_sums, *tmp_idx, *perm, *cell_sorted;
+    uint32_t *cell_of, *count, *cell_start, *block_sums, *tmp_idx, *slot, *cell_sorted;
     int64_t nscan_blocks;
     // gather targets of the sort (same shapes as the state)
     double *tq, *tp, *teps, *trho, *tf;
@@ -186,6 +186,7 @@ struct sdpd_ctx {
     int tune_gen = 0;            // counts sdpd_tune calls (captured batches check it)
     int fd_dataflow = 0;         // SDPD_SWEEP_AUTO chooses one launch (large boxes)
     int fd_per_group = 0;        // force one launch per group (set while a batch captures)
+    int64_t batch_cells = 0;     // recording: cells of the boxes that share a launch
     int fd_record_flow = 0;      // recording: the sweep as one multi-box launch (fused batch)
     int sweep_ngroups = 0;       // host copy of the sweep table's group ends
     uint32_t sweep_group_end[32] = {};
@@ -211,10 +212,16 @@ int check_hip(hipError_t e);
 int launch_fill_u32(sdpd_ctx *c, uint32_t *p, uint32_t v, int64_t n);
 int launch_fill_u64(sdpd_ctx *c, unsigned long long *p, unsigned long long v, int64_t n);
 int launch_incr_u64(sdpd_ctx *c, unsigned long long *p);
-int run_scan(sdpd_ctx *c, const uint32_t *in, uint32_t *out, int64_t count, uint32_t *block_sums,
-             int cap);
+int run_scan(sdpd_ctx *c, uint32_t *in, uint32_t *out, uint32_t *in2, uint32_t *out2,
+             int64_t count, uint32_t *block_sums, int cap, bool clear);
 int run_schedule(sdpd_ctx *c);
-int run_build_cells(sdpd_ctx *c, const sdpd_state *s, int kick_drift);
+// what a step sets before anything else: counters to zero, the step index (NULL: not)
+struct StepStart {
+    unsigned long long *counters = nullptr, *dstep = nullptr;
+    unsigned long long step = 0;
+};
+int run_build_cells(sdpd_ctx *c, const sdpd_state *s, int kick_drift,
+                    const StepStart &start = StepStart());
 // pack_rho: also write rho into the w slot of the packed position records,
 // where a sweep that follows in the same step reads it (FP64 path)
 int run_density(sdpd_ctx *c, const sdpd_state *s, int update_eps, bool pack_rho = false);
