@@ -188,12 +188,6 @@ struct CellWave {
         m = lane_of(cnt, OWN_NB);
     }
     __device__ __forceinline__ bool edge() const { return (steps.lo | steps.hi) != 0u; }
-    // cells k0 .. window(k0, limit) - 1 hold at most `limit` (>= 64) positions
-    __device__ __forceinline__ int window(int k0, uint32_t limit) const
-    {
-        return __popcll(__ballot((threadIdx.x & 63u) < (uint32_t)NNB &&
-                                 b + cnt <= lane_of(b, k0) + limit));
-    }
     // the cell of position t < total and the particle there; called by the whole
     // wave (a lane that is switched off gives no value to the others)
     __device__ __forceinline__ void find(uint32_t t, int &k, uint32_t &j) const
@@ -248,7 +242,7 @@ __device__ __forceinline__ void density_store(const DensityArgs &a, int64_t i, d
 }
 
 // Density and masks, one cell per wave.  The candidates sit in the lanes' registers,
-// 64 K of them at a time (a window: whole neighbour cells); the wave goes through
+// 64 K of them at a time (a window); the wave goes through
 // the cell's particles, tests its candidates against one of them at once, queues
 // the squared distances in range in LDS, in candidate order, and evaluates the
 // kernel for the queue at full lane occupancy; lane i then adds up the terms of
@@ -441,13 +435,12 @@ struct DensityWave {
     template <bool SHIFT, int K>
     __device__ __forceinline__ void windows()
     {
-        for (int k0 = 0; k0 < NNB;) {
-            const int k1 = cw.window(k0, 64u * K);
-            const uint32_t base = lane_of(cw.b, k0), width = lane_of(cw.b, k1) - base;
-            if (k0 <= OWN_NB) window<SHIFT, K, true>(base, width);
+        const uint32_t words = lane_of(cw.b, OWN_NB + 1);   // positions with a mask kept
+        for (uint32_t base = 0; base < cw.total; base += 64u * K) {
+            const uint32_t width = min(cw.total - base, 64u * K);
+            if (base < words) window<SHIFT, K, true>(base, width);
             else window<SHIFT, K, false>(base, width);
             flush();   // (a lane has one segment of the queue at a time)
-            k0 = k1;
         }
     }
 
