@@ -27,7 +27,7 @@ struct ModelF64 {
     typedef double4 Vec;
     static constexpr bool kShiftEverywhere = false;
     static constexpr int kDensityOcc = 5;
-    static constexpr int kChunks = 4, kEdgeChunks = 2;   // see DensityWave
+    static constexpr int kChunks = 3;                    // see DensityWave
     static constexpr int kLanes = 8;                     // see PartnerSums
     static __device__ __forceinline__ Real shift(const DevParams &P, int a, int o, bool lo, bool hi)
     {
@@ -74,8 +74,8 @@ struct ModelF32 {
     typedef float Real;
     typedef float4 Vec;
     static constexpr bool kShiftEverywhere = true;
-    static constexpr int kDensityOcc = 6;
-    static constexpr int kChunks = 4, kEdgeChunks = 4;
+    static constexpr int kDensityOcc = 7;
+    static constexpr int kChunks = 3;
     static constexpr int kLanes = 4;
     static __device__ __forceinline__ Real shift(const DevParams &P, int a, int o, bool, bool)
     {
@@ -131,6 +131,23 @@ struct CellXyz {
         z = (int)(c / ((uint32_t)P.nc[0] * (uint32_t)P.nc[1]));
     }
 };
+
+// x of another lane (CTRL: the DPP control word)
+template <int CTRL>
+__device__ __forceinline__ float moved(float x)
+{
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double moved(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
 
 // ---------------------------------------------------------------- cells
 constexpr int kCellWaves = 4;      // waves, and cells, per workgroup
@@ -241,40 +258,40 @@ __device__ __forceinline__ void density_store(const DensityArgs &a, int64_t i, d
     }
 }
 
-// Density and masks, one cell per wave.  The candidates sit in the lanes' registers,
-// 64 K of them at a time (a window); the wave goes through
-// the cell's particles, tests its candidates against one of them at once, queues
-// the squared distances in range in LDS, in candidate order, and evaluates the
-// kernel for the queue at full lane occupancy; lane i then adds up the terms of
-// particle i in order.  The test of particle i is bit i of a lane's word, which
-// ends as the mask of its candidate for this cell: no pair is looked at twice
-// and no mask is taken apart.
+// Density, masks and partner lists, one cell per wave.  The candidates that come
+// within h of the box around the cell's particles are listed in LDS, in candidate
+// order, and taken into the lanes' registers 64 K at a time (a window); the wave goes
+// through the cell's particles, tests its candidates against one of them at once,
+// queues the squared distances in range in LDS and evaluates the kernel for the queue
+// at full lane occupancy; lane i then adds up the terms of particle i in order.  The
+// test of particle i is bit i of a lane's word, which ends as the mask of its
+// candidate for this cell: no pair is looked at twice and no mask is taken apart.
 //
-// Bound by the VALU: 460 candidates of a particle (17 per cell, h = 0.98 cell
-// edges) take 7.2 lane-parallel tests of 15 instructions.  A thread per particle
-// reads 24 B of every candidate through the L1 instead and runs to the largest
-// cell of its wave: 677 us for 1M particles in FP64 (now 633, of which the partner
-// list takes 120), 251 us for 262k (214), 168 us for 137k in FP32 (90).
+// Bound by the VALU: of 460 candidates per particle (17 per cell, h = 0.98 cell
+// edges) 310 are in reach of the cell, 4.8 lane-parallel tests of 16 instructions,
+// and each window costs some 35 more per particle.  A thread per particle reads 24 B
+// of every candidate through the L1 instead and runs to the largest cell of its wave:
+// 677 us for 1M particles in FP64 (now 542, of which the list takes 120), 251 us for
+// 262k (156), 168 us for 137k in FP32 (84), 3590 us for 8M (3310).  Without the test
+// against the box: 601, 195, 88, 3400.
 //
 // The list saves the force and gradient passes the walk through the masks (1M
 // particles: forces 410 -> 216 us).  A window's entries of a particle go through
-// LDS and out in one store; storing them where they are found took 690 us, and a
-// queue of entries beside that of the terms, emptied with it, 718.
+// LDS and out in one store; storing them where they are found took 8 % longer, and a
+// queue of entries beside that of the terms, emptied with it, 12 %.
 //
-// K: more candidates per lane mean fewer windows, each with its own pass over the
-// particles, and fewer waves per SIMD.  1M particles, K = 3, 4: 676, 638 us; 8M in
-// FP32, K = 3, 4: 3703, 3552; without the list K = 5, 8 took 9 and 70 % longer
-// than 4.  FP64 cells at the boundary carry shifts (three doubles more per
-// candidate) and take K = 2, or 4 where a wave per SIMD is all there is (SPLIT).
-// kDensityOcc: the waves per SIMD that the compiler has to allow (1M particles, 4
-// and 5: 689 and 638 us).
-constexpr int kTerms = 640;        // queue entries of a wave
+// K: more candidates per lane mean fewer windows and fewer waves per SIMD.  1M
+// particles, K = 2, 3, 4, 5: 543, 542, 578, 615 us; 8M in FP32, K = 2, 3, 4, 5: 3362,
+// 3313, 3658, 3615.  kDensityOcc: the waves per SIMD that the compiler has to allow
+// (1M particles, 4 and 5: 8 % apart).
+constexpr int kTerms = 576;        // queue entries of a wave
 constexpr int kTail = 256;         // particles of a workgroup's shared last part
 
 template <class M, bool SPLIT>
 struct DensityLds {
     typename M::Real terms[kCellWaves][kTerms + 64];
     double rho[kTail];
+    uint32_t near[kCellWaves][64 * M::kChunks + 64];   // candidates that are not out of reach
     uint32_t part[kCellWaves][64 * M::kChunks + 64];   // list entries of a particle and window
     uint32_t words[SPLIT ? kCellWaves : 1][SPLIT ? 64 * kCellWaves : 1];
 };
@@ -294,6 +311,8 @@ struct DensityWave {
     const int lane, wave, lo, hi;   // slots lo .. hi - 1 are this wave's
     Real *terms;
     Real x, y, z, acc;       // lane i < m: particle i of the cell and its sum
+    Real x0[3];              // particle 0
+    float box_lo[3], box_hi[3];   // the box around the cell's particles, relative to it
     uint32_t beg, end;       // ... its terms in the queue
     uint32_t partners;       // ... its list entries
     uint32_t fill;
@@ -321,7 +340,7 @@ struct DensityWave {
 
     // WORDS: the window has cells whose masks for this one are kept
     template <bool SHIFT, int K, bool WORDS>
-    __device__ __forceinline__ void window(uint32_t base, uint32_t width)
+    __device__ __forceinline__ void window(uint32_t width)
     {
         const Real *__restrict__ q4 = static_cast<const Real *>(a.q4);
         const int chunks = (int)((width + 63u) / 64u);
@@ -334,15 +353,15 @@ struct DensityWave {
             for (int d = 0; d < 3; ++d) sh[c][d] = (Real)0;
             if (c >= chunks) continue;
             const uint32_t t = 64u * c + lane;
-            int k;
-            uint32_t j;
-            cw.find(base + min(t, width - 1u), k, j);   // (every lane takes part)
+            const uint32_t e = lds.near[wave][min(t, width - 1u)];
+            const uint32_t j = entry_particle(e);
+            const int k = (int)(e >> kEntryBits);
             const typename M::Vec v = load_vec<M>(q4, j);
             // a lane past the end: out of range of everything
             cx[c] = t < width ? v.x : (Real)1e18;
             cy[c] = v.y;
             cz[c] = v.z;
-            entry[c] = list_entry(j, k);
+            entry[c] = e;
             if (SHIFT) {
                 const int o[3] = {k % 3, (k / 3) % 3, k / 9};
                 for (int d = 0; d < 3; ++d)
@@ -435,13 +454,61 @@ struct DensityWave {
     template <bool SHIFT, int K>
     __device__ __forceinline__ void windows()
     {
-        const uint32_t words = lane_of(cw.b, OWN_NB + 1);   // positions with a mask kept
-        for (uint32_t base = 0; base < cw.total; base += 64u * K) {
-            const uint32_t width = min(cw.total - base, 64u * K);
-            if (base < words) window<SHIFT, K, true>(base, width);
-            else window<SHIFT, K, false>(base, width);
+        uint32_t *const near = lds.near[wave];
+        uint32_t held = 0u;
+        for (uint32_t pos = 0u; pos < cw.total || held;) {
+            for (; held < 64u * K && pos < cw.total; pos += 64u) held = reach<SHIFT>(pos, held);
+            wave_sync();
+            if (held == 0u) break;
+            const uint32_t width = min(held, 64u * K);
+            const int k0 = __builtin_amdgcn_readfirstlane((int)(near[0] >> kEntryBits));
+            if (k0 <= OWN_NB) window<SHIFT, K, true>(width);
+            else window<SHIFT, K, false>(width);
             flush();   // (a lane has one segment of the queue at a time)
+            const uint32_t rest = near[64 * K + lane];   // fewer than 64
+            wave_sync();
+            held -= width;
+            if ((uint32_t)lane < held) near[lane] = rest;
         }
+    }
+
+    // Candidates pos .. pos + 63 that come within h of the box around the cell's
+    // particles, behind the first `held` of the list; the masks of the others (a
+    // quarter to a third of all: cells reached across a corner or an edge) are zero.
+    template <bool SHIFT>
+    __device__ __forceinline__ uint32_t reach(uint32_t pos, uint32_t held)
+    {
+        int k;
+        uint32_t j;
+        cw.find(min(pos + (uint32_t)lane, cw.total - 1u), k, j);   // (every lane takes part)
+        const typename M::Vec v = load_vec<M>(static_cast<const Real *>(a.q4), j);
+        Real d[3] = {v.x - x0[0], v.y - x0[1], v.z - x0[2]};
+        if (SHIFT) {
+            const int o[3] = {k % 3, (k / 3) % 3, k / 9};
+            for (int c = 0; c < 3; ++c)
+                d[c] -= M::shift(P, c, o[c], (cw.steps.lo >> c) & 1u, (cw.steps.hi >> c) & 1u);
+        }
+        float r2 = 0.0f;
+        for (int c = 0; c < 3; ++c) {
+            const float g = (float)d[c], t = fmaxf(fmaxf(box_lo[c] - g, g - box_hi[c]), 0.0f);
+            r2 += t * t;
+        }
+        // (FP32 rounding is some 1e-6 of h^2; any pair in range of the test passes)
+        const bool in = pos + (uint32_t)lane < cw.total, keep = in && r2 <= 1.0001f * (float)P.h2;
+        const uint64_t kept = __ballot(keep);
+        if (keep) lds.near[wave][held + below(kept, 0u)] = list_entry(j, k);
+        else if (in && k <= OWN_NB) a.masks[(int64_t)(OWN_NB - k) * P.n + j] = 0ull;
+        return held + (uint32_t)__popcll(kept);
+    }
+
+    // smallest value of the wave (rows of 16 lanes, then the four rows)
+    static __device__ __forceinline__ float wave_min(float v)
+    {
+        v = fminf(v, moved<0xb1>(v));
+        v = fminf(v, moved<0x4e>(v));
+        v = fminf(v, moved<0x141>(v));
+        v = fminf(v, moved<0x140>(v));
+        return fminf(fminf(lane_of(v, 0), lane_of(v, 16)), fminf(lane_of(v, 32), lane_of(v, 48)));
     }
 
     __device__ __forceinline__ void run()
@@ -456,8 +523,17 @@ struct DensityWave {
             y = v.y;
             z = v.z;
         }
-        if (!M::kShiftEverywhere && cw.edge()) windows<true, SPLIT ? M::kChunks : M::kEdgeChunks>();
-        else windows<M::kShiftEverywhere, M::kChunks>();
+        x0[0] = lane_of(x, 0);
+        x0[1] = lane_of(y, 0);
+        x0[2] = lane_of(z, 0);
+        const float rel[3] = {(float)(x - x0[0]), (float)(y - x0[1]), (float)(z - x0[2])};
+        for (int c = 0; c < 3; ++c) {   // (empty cell: nothing is in reach)
+            const bool own = (uint32_t)lane < cw.m;
+            box_lo[c] = wave_min(own ? rel[c] : FLT_MAX);
+            box_hi[c] = -wave_min(own ? -rel[c] : FLT_MAX);
+        }
+        if (M::kShiftEverywhere || cw.edge()) windows<true, M::kChunks>();
+        else windows<false, M::kChunks>();
         // overflowing cells: reported, not visited
         uint64_t over = __ballot(cw.raw != cw.cnt);
         if (over && lane == 0) atomicOr(a.err, ERR_CELLCAP);
@@ -535,23 +611,6 @@ struct PartnerArgs {
     uint32_t list_cap;
 };
 
-
-// x of another lane (CTRL: the DPP control word)
-template <int CTRL>
-__device__ __forceinline__ float moved(float x)
-{
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double moved(double x)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
-    const uint32_t hi =
-        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
-}
 
 // Value v of the sum over particle i's partners in lane s == v < NV of its lanes.  term(j, d, r2, out): the NV values of partner j at separation d = q_i -
 // q_j, all zero for r2 = 0; term.at(i): called before with the particle of the lane.
