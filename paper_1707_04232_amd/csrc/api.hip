@@ -6,6 +6,8 @@
 
 #include <mutex>
 #include <new>
+#include <utility>
+#include <vector>
 
 #include "sdpd_internal.hpp"
 
@@ -163,14 +165,46 @@ static int dalloc(T **p, size_t count)
     return hipMalloc((void **)p, sizeof(T) * count) == hipSuccess ? SDPD_OK : SDPD_ENOMEM;
 }
 
+// The buffers of a context, requested one by one and made in one allocation
+// (hipMalloc takes longer than the kernels of a small box's whole preparation).
+struct Arena {
+    std::vector<std::pair<void **, size_t>> parts;
+    template <class T>
+    void add(T **p, size_t count)
+    {
+        *p = nullptr;
+        parts.emplace_back((void **)p, sizeof(T) * (count ? count : 1));
+    }
+    // cache lines; buffers of many pages begin on a page of 2 MB, as they would alone
+    static size_t padded(size_t bytes)
+    {
+        const size_t to = bytes >= ((size_t)16 << 20) ? (size_t)2 << 20 : 256;
+        return (bytes + to - 1) / to * to;
+    }
+    int make(void **base)
+    {
+        // largest first: every part then begins at its own alignment
+        std::stable_sort(parts.begin(), parts.end(),
+                         [](const std::pair<void **, size_t> &x,
+                            const std::pair<void **, size_t> &y) { return x.second > y.second; });
+        size_t total = 0;
+        for (const auto &x : parts) total += padded(x.second);
+        if (hipMalloc(base, total) != hipSuccess) {
+            *base = nullptr;
+            return SDPD_ENOMEM;
+        }
+        char *at = (char *)*base;
+        for (const auto &x : parts) {
+            *x.first = at;
+            at += padded(x.second);
+        }
+        return SDPD_OK;
+    }
+};
+
 static void free_ctx(sdpd_ctx *c)
 {
-    void *bufs[] = {c->cell_of, c->count, c->slot, c->cell_start, c->block_sums, c->tmp_idx,
-                    c->cell_sorted, c->tq, c->tp, c->teps, c->trho, c->tf, c->tid,
-                    c->masks, c->list, c->list_count, c->counters, c->err, c->obs_partial, c->obs_out,
-                    c->dparams, c->task_count, c->task_np, c->pair_off, c->part_off,
-                    c->part_list, c->pairs, c->rec_buf, c->lvl_end, c->flow_rec, c->q4f, c->dstep, c->q4,
-                    c->sweep, c->epoch, c->sweep_order};
+    void *bufs[] = {c->arena, c->obs_out, c->flow_rec, c->sweep, c->sweep_order};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     for (hipEvent_t e : c->timer.pool) (void)hipEventDestroy(e);
@@ -310,44 +344,45 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
         c->list_cap = (uint32_t)std::min(1.5 * v + 16.0, (double)(NNB * MAX_CAP));
         c->list_cap = (c->list_cap + 31u) / 32u * 32u;   // (lists begin on their own cache lines)
     }
-    rc = SDPD_OK;
-    rc = rc ? rc : dalloc(&c->cell_of, n);
-    rc = rc ? rc : dalloc(&c->count, nce);
-    rc = rc ? rc : dalloc(&c->cell_start, nce + 1);
-    rc = rc ? rc : dalloc(&c->block_sums, (size_t)c->nscan_blocks);
-    rc = rc ? rc : dalloc(&c->tmp_idx, n);
-    rc = rc ? rc : dalloc(&c->slot, n);
-    rc = rc ? rc : dalloc(&c->cell_sorted, n);
-    rc = rc ? rc : dalloc(&c->tq, 3 * n);
-    rc = rc ? rc : dalloc(&c->tp, 3 * n);
-    rc = rc ? rc : dalloc(&c->tf, 3 * n);
-    rc = rc ? rc : dalloc(&c->teps, n);
-    rc = rc ? rc : dalloc(&c->trho, n);
-    rc = rc ? rc : dalloc(&c->tid, n);
-    rc = rc ? rc : dalloc(&c->q4, 4 * n);
-    if (c->dp.mixed) rc = rc ? rc : dalloc(&c->q4f, 4 * n);
-    rc = rc ? rc : dalloc(&c->masks, (size_t)NMASK * n);
-    rc = rc ? rc : dalloc(&c->list, (size_t)c->list_cap * n);
-    rc = rc ? rc : dalloc(&c->list_count, n);
-    rc = rc ? rc : dalloc(&c->counters, (size_t)CNT_N);
-    rc = rc ? rc : dalloc(&c->err, 1);
-    rc = rc ? rc : dalloc(&c->obs_partial, (size_t)c->obs_blocks * 6);
-    rc = rc ? rc : alloc_records(c);
-    rc = rc ? rc : dalloc(&c->dparams, 1);
-    rc = rc ? rc : dalloc(&c->task_count, (size_t)NMASK * nce);
-    rc = rc ? rc : dalloc(&c->task_np, (size_t)NMASK * nce);
-    rc = rc ? rc : dalloc(&c->pair_off, (size_t)NMASK * nce + 1);
-    rc = rc ? rc : dalloc(&c->part_off, (size_t)NMASK * nce + 1);
-    rc = rc ? rc : dalloc(&c->pairs, (size_t)c->pair_cap);
-    rc = rc ? rc : dalloc(&c->epoch, (size_t)c->ncell + 1);
-    rc = rc ? rc : dalloc(&c->dstep, 1);
-    rc = rc ? rc : dalloc(&c->part_list, (size_t)c->part_cap);
+    Arena mem;
+    mem.add(&c->cell_of, n);
+    mem.add(&c->count, nce);
+    mem.add(&c->cell_start, nce + 1);
+    mem.add(&c->block_sums, (size_t)c->nscan_blocks);
+    mem.add(&c->tmp_idx, n);
+    mem.add(&c->slot, n);
+    mem.add(&c->cell_sorted, n);
+    mem.add(&c->tq, 3 * n);
+    mem.add(&c->tp, 3 * n);
+    mem.add(&c->tf, 3 * n);
+    mem.add(&c->teps, n);
+    mem.add(&c->trho, n);
+    mem.add(&c->tid, n);
+    mem.add(&c->q4, 4 * n);
+    if (c->dp.mixed) mem.add(&c->q4f, 4 * n);
+    mem.add(&c->masks, (size_t)NMASK * n);
+    mem.add(&c->list, (size_t)c->list_cap * n);
+    mem.add(&c->list_count, n);
+    mem.add(&c->counters, (size_t)CNT_N);
+    mem.add(&c->err, 1);
+    mem.add(&c->obs_partial, (size_t)c->obs_blocks * 6);
+    mem.add(&c->dparams, 1);
+    mem.add(&c->task_count, (size_t)NMASK * nce);
+    mem.add(&c->task_np, (size_t)NMASK * nce);
+    mem.add(&c->pair_off, (size_t)NMASK * nce + 1);
+    mem.add(&c->part_off, (size_t)NMASK * nce + 1);
+    mem.add(&c->pairs, (size_t)c->pair_cap);
+    mem.add(&c->epoch, (size_t)c->ncell + 1);
+    mem.add(&c->dstep, 1);
+    mem.add(&c->part_list, (size_t)c->part_cap);
     // pair records: of one group of the sweep (it touches every cell once: at
     // most 32 pairs per particle), for small boxes of a whole sweep
     const bool whole = c->n <= kWholeRecordsMaxParticles;
     c->rec_bytes = sizeof(double) * (whole ? 8 : 4) * (size_t)c->pair_cap;
-    rc = rc ? rc : dalloc(&c->rec_buf, c->rec_bytes / sizeof(double));
-    if (whole) rc = rc ? rc : dalloc(&c->lvl_end, (size_t)NMASK * nce * 64);
+    mem.add(&c->rec_buf, c->rec_bytes / sizeof(double));
+    if (whole) mem.add(&c->lvl_end, (size_t)NMASK * nce * 64);
+    rc = mem.make(&c->arena);
+    rc = rc ? rc : alloc_records(c);
     if (!rc)
         rc = check_hip(hipMemcpyAsync(c->dparams, &c->dp, sizeof c->dp, hipMemcpyHostToDevice,
                                       c->stream));

@@ -1176,13 +1176,15 @@ static std::vector<uint32_t> fd_range_order(const sdpd_ctx *c, const FdSweep &h)
     std::vector<uint32_t> order(h.nitems);
     std::vector<int64_t> last(c->ncell, -1);   // hand-out position of the range that last touched c
     std::vector<std::pair<int64_t, uint32_t>> keyed;
-    std::vector<std::vector<int64_t>> cells;
+    std::vector<int64_t> cells;          // of the group's ranges, one after the other
+    std::vector<size_t> cells_end;
     uint32_t begin = 0;
     for (int g = 0; g < h.ngroups; ++g) {
         const FdLaunch &L = h.launch[g];
         const uint32_t nb = h.group_end[g] - begin;
         keyed.assign(nb, std::make_pair((int64_t)-1, 0u));
-        cells.assign(nb, std::vector<int64_t>());
+        cells.clear();
+        cells_end.resize(nb);
         for (uint32_t b = 0; b < nb; ++b) {
             int k_ph = 0;
             while (k_ph + 1 < L.nph && (int64_t)b >= L.wg_end[k_ph]) ++k_ph;
@@ -1193,14 +1195,15 @@ static std::vector<uint32_t> fd_range_order(const sdpd_ctx *c, const FdSweep &h)
             for (int64_t t = t0; t < t1; ++t) {
                 int64_t A, B;
                 task_cells_host(c, L.task_base[k_ph] + t, A, B);
-                cells[b].push_back(A);
+                cells.push_back(A);
                 key = std::max(key, last[A]);
                 if (B >= 0) {
-                    cells[b].push_back(B);
+                    cells.push_back(B);
                     key = std::max(key, last[B]);
                 }
             }
             keyed[b] = std::make_pair(key, b);
+            cells_end[b] = cells.size();
         }
         std::stable_sort(keyed.begin(), keyed.end(),
                          [](const std::pair<int64_t, uint32_t> &x,
@@ -1208,7 +1211,8 @@ static std::vector<uint32_t> fd_range_order(const sdpd_ctx *c, const FdSweep &h)
         for (uint32_t r = 0; r < nb; ++r) {
             const uint32_t b = keyed[r].second;
             order[begin + r] = b;
-            for (int64_t cc : cells[b]) last[cc] = begin + r;
+            for (size_t x = b ? cells_end[b - 1] : 0; x < cells_end[b]; ++x)
+                last[cells[x]] = begin + r;
         }
         begin = h.group_end[g];
     }

@@ -147,6 +147,7 @@ struct sdpd_ctx {
     hipStream_t stream;
     int device;
     int64_t n, ncell;
+    void *arena = nullptr;       // one allocation that holds the buffers below
     // cell list
     uint32_t *cell_of, *count, *cell_start, *block_sums, *tmp_idx, *slot, *cell_sorted;
     int64_t nscan_blocks;
