@@ -81,12 +81,11 @@ struct sdpd_batch {
     int theta = 1;
 };
 
-// hardware queues HIP gives the process (its default is 4)
-static int hw_queues()
+int sdpd::hw_queues()
 {
     const char *v = getenv("GPU_MAX_HW_QUEUES");
     const int q = v ? atoi(v) : 0;
-    return q > 0 ? q : 4;
+    return q > 0 ? q : 4;   // (HIP's own default)
 }
 
 using namespace sdpd;

@@ -1306,8 +1306,14 @@ int fd_prepare_sweep(sdpd_ctx *c)
     // one launch when the sweep holds at least three GPU-fulls of ranges (at
     // two waves per SIMD; boxes of some 450 cells); a smaller one mostly waits
     // on its chain of 27 groups, and one launch per group then holds no
-    // workgroup slots while it waits
-    c->fd_dataflow = total >= 3 * 8 * (int64_t)cus;
+    // workgroup slots while it waits.  Where the process asks for more queues than
+    // the default four, boxes on many streams would hold them against each other:
+    // sixteen times that (256 boxes of 13^3 to 40^3 particles stepped eagerly on 32
+    // streams and queues: 312 ms per step with the line of few queues, 88 with this
+    // one; 48 boxes on four streams and queues: 23 ms, and 25 with launches per
+    // group only; on one stream 38 and 45)
+    const int64_t full = 8 * (int64_t)cus;
+    c->fd_dataflow = total >= (hw_queues() > 4 ? 16 : 1) * 3 * full;
     c->sweep_ok = 1;
     return SDPD_OK;
 }

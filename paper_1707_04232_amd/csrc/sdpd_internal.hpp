@@ -221,6 +221,8 @@ struct StepStart {
     unsigned long long *counters = nullptr, *dstep = nullptr;
     unsigned long long step = 0;
 };
+// hardware queues of the process (environment GPU_MAX_HW_QUEUES, 4 when unset)
+int hw_queues();
 int run_build_cells(sdpd_ctx *c, const sdpd_state *s, int kick_drift,
                     const StepStart &start = StepStart());
 // pack_rho: also write rho into the w slot of the packed position records,
