@@ -31,19 +31,13 @@ HBM_PEAK_GBS = 8000.0
 # by the FP64 operations of its gfx950 implementation (46, 63, 38, 16, 9, 10
 # and 43 flops): 209 + 564 = 773.
 FLOPS_PER_EMS_PAIR = 773.0
-# What a pair executes: the bracketed Metropolis test replaces the two
-# logarithms and the log1p of the comparison (2 x 46 + 63 = 155 flops) by
-# cubic bounds (33 flops), so a pair that the bounds decide executes
-# 773 - 155 + 33 = 651 flops and a pair whose logarithms are evaluated
-# 773 + 33 = 806.
-# 1.1 % of the pairs of this workload's relaxed state reach the evaluated
-# comparison (0.06 % in the first steps from the lattice), counted with a
-# build of the sweep whose marginal counter counts every evaluation.
-FLOPS_PER_PAIR_BRACKETED = 651.0
-FLOPS_PER_PAIR_EVALUATED = 806.0
-EVALUATED_SHARE = 0.011
-FLOPS_PER_PAIR_EXECUTED = (FLOPS_PER_PAIR_BRACKETED * (1.0 - EVALUATED_SHARE)
-                           + FLOPS_PER_PAIR_EVALUATED * EVALUATED_SHARE)
+# What a pair executes, from counters of one sweep of this workload's relaxed state:
+# 64 SQ_INSTS_VALU_FLOPS_FP64 x (SQ_THREAD_CYCLES_VALU / 64 SQ_ACTIVE_INST_VALU) / pairs
+# (the flops of the issued FP64 instructions at the share of lanes that are active).
+# Fewer than the formulas': the bracketed Metropolis test replaces the logarithms of
+# all but 1.1 % of the pairs by cubic bounds, and the update works on scalars of the
+# pair instead of vectors.
+FLOPS_PER_PAIR_EXECUTED = 595.0
 # Whole-step floor.  Compulsory HBM bytes per particle-step of the method in
 # FP64 (one pass over the state per stage): cells re-sorted every step (keys
 # and ids 32 B, gather of q, p, eps, rho, id 136 B), density and energy update
