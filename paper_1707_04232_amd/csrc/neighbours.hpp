@@ -7,6 +7,7 @@
 
 #include <float.h>
 
+#include <algorithm>
 #include <type_traits>
 
 namespace sdpd {
@@ -230,7 +231,19 @@ struct DensityArgs {
     uint32_t list_cap;       // list[list_cap i + r], r < count[i], complete if count <= list_cap
     uint32_t *err;
     double *rho_w;           // FP64: also into the w slot of the record, or NULL
+    float reach2;            // h^2 and the rounding of the FP32 test for it (density_reach2)
 };
+
+// Squared distance, in FP32, up to which a candidate is kept for the tests: the
+// separations are rounded relative to positions of up to two cell edges (2^-24 of
+// them, three times per axis), which moves the square by less than 2.2e-6 h edge
+// (h^2 is a relative 1e-4 of its own apart; cells may be much wider than h).
+inline float density_reach2(const DevParams &P)
+{
+    double edge = 0.0;
+    for (int a = 0; a < 3; ++a) edge = std::max(edge, 1.0 / P.inv_cell[a]);
+    return (float)(P.h * P.h * 1.0001 + 8e-6 * P.h * edge + 1e-11 * edge * edge);
+}
 
 // an entry of the list: particle and offset index (n < 2^27: the pair records
 // alone would take more than 256 GB)
@@ -493,8 +506,7 @@ struct DensityWave {
             const float g = (float)d[c], t = fmaxf(fmaxf(box_lo[c] - g, g - box_hi[c]), 0.0f);
             r2 += t * t;
         }
-        // (FP32 rounding is some 1e-6 of h^2; any pair in range of the test passes)
-        const bool in = pos + (uint32_t)lane < cw.total, keep = in && r2 <= 1.0001f * (float)P.h2;
+        const bool in = pos + (uint32_t)lane < cw.total, keep = in && r2 <= a.reach2;
         const uint64_t kept = __ballot(keep);
         if (keep) lds.near[wave][held + below(kept, 0u)] = list_entry(j, k);
         else if (in && k <= OWN_NB) a.masks[(int64_t)(OWN_NB - k) * P.n + j] = 0ull;

@@ -55,3 +55,31 @@ def test_cell_edges(name, form):
     assert np.abs(G["rho"] - R.rho).max() <= (2e-5 if form == "mixed" else 1e-12) * R.rho.max()
     if form != "mixed":
         assert np.abs(G["f"] - R.f).max() <= 1e-12 * max(np.abs(R.f).max(), 1e-300)
+
+
+@pytest.mark.parametrize("edge", [25.0, 2000.0])
+def test_wide_cells_keep_pairs_at_the_cutoff(edge):
+    """Cells far wider than h (the caller's choice of the grid): pairs a relative 1e-9
+    to 1e-4 inside the cutoff, in all directions and across cells and the boundary, are
+    all proposed by a sweep, and pairs as far outside are not."""
+    from paper_1707_04232_amd import sdpd
+    print("[case] wide cells", edge, flush=True)
+    h, L, m = 2.5, 4 * edge, 120
+    rng = np.random.default_rng(11)
+    a = rng.uniform(0.0, L, size=(3, m))
+    a[:, ::4] = edge * rng.integers(0, 4, size=(3, m // 4)) + rng.uniform(-1.0, 1.0, (3, m // 4))
+    d = rng.normal(size=(3, m))
+    d /= np.linalg.norm(d, axis=0)
+    off = 10.0 ** rng.uniform(-9, -4, m) * np.where(np.arange(m) % 3 == 0, 1.0, -1.0)
+    q = np.concatenate([a % L, (a + h * (1.0 + off) * d) % L], axis=1)
+    n = 2 * m
+    dist = [q[k][:, None] - q[k][None, :] for k in range(3)]
+    r2 = sum((x - L * np.rint(x / L)) ** 2 for x in dist)
+    inside = int(np.count_nonzero(np.triu(r2 < h * h, 1)))
+    assert inside >= m // 2
+    p, eps, ids = np.zeros((3, n)), np.ones(n), np.arange(n, dtype=np.uint32)
+    S = sdpd.DeviceState.from_numpy(q, p, eps, ids)
+    with sdpd.Context(sdpd.SdpdParams(n=n, box=L, h=h, ncell=(4, 4, 4), dt=1e-6)) as ctx:
+        ctx.prepare(S)
+        stats = ctx.fd_metropolis(S, step=0)
+    assert stats["proposed"] == inside
