@@ -336,12 +336,15 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     c->part_cap = std::max<int64_t>(27 * c->n, 1024);
     // partner lists: half as many again as the mean at the box's density and 16
     // more (a uniform random box of 10^5 particles with 65 partners on average has
-    // none with more than 105); particles with more are looked up without a list
+    // none with more than 105), and 128 at least, twice what a particle has in a
+    // liquid at the usual h (most of a box may be empty); particles with more are
+    // looked up without a list
     {
         const double h = c->prm.h;
         double v = 4.0 / 3.0 * 3.14159265358979323846 * h * h * h * (double)c->n;
         for (int k = 0; k < 3; ++k) v /= c->prm.box[k];
-        c->list_cap = (uint32_t)std::min(1.5 * v + 16.0, (double)(NNB * MAX_CAP));
+        c->list_cap =
+            (uint32_t)std::min(std::max(1.5 * v + 16.0, 128.0), (double)(NNB * MAX_CAP));
         c->list_cap = (c->list_cap + 31u) / 32u * 32u;   // (lists begin on their own cache lines)
     }
     Arena mem;

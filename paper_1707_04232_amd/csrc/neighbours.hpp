@@ -222,7 +222,7 @@ struct CellWave {
 struct DensityArgs {
     DevParams P;
     const void *q4;          // packed records of the model
-    const uint32_t *cell_start;
+    const uint32_t *cell_sorted, *cell_start;
     double *rho, *eps;
     int update_eps;
     uint64_t *masks;         // masks[(k - 13) n + i]: slot bits of the partners in cell k,
@@ -602,6 +602,53 @@ __device__ __forceinline__ void density_cells(const DensityArgs &a, uint32_t blk
     }
 }
 
+// The same sums, masks and lists, bit for bit, with a lane per particle, for large
+// boxes whose cells are mostly empty or hold few particles: a wave per cell then mostly
+// finds that there is nothing to do.
+template <class M, bool LUCY>
+__device__ __forceinline__ void density_sparse(const DensityArgs &a, uint32_t blk)
+{
+    typedef typename M::Real Real;
+    const DevParams &P = a.P;
+    const int64_t n = P.n, i = (int64_t)blk * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const Real *__restrict__ q4 = static_cast<const Real *>(a.q4);
+    const CellXyz cc(P, a.cell_sorted[i]);
+    const NbSteps steps(P, cc.x, cc.y, cc.z);
+    const typename M::Vec qi = load_vec<M>(q4, i);
+    uint32_t *const list = a.list + i * (int64_t)a.list_cap;
+    Real acc = (Real)0;
+    uint32_t partners = 0u;
+    for (int k = 0; k < NNB; ++k) {
+        const int o[3] = {k % 3, (k / 3) % 3, k / 9};
+        const uint32_t cn = (uint32_t)steps.get(P, k).c, s = a.cell_start[cn];
+        uint32_t cnt = a.cell_start[cn + 1] - s;
+        if (cnt > (uint32_t)P.cap) {   // overflowing cell: reported, not visited
+            atomicOr(a.err, ERR_CELLCAP);
+            cnt = 0u;
+        }
+        Real sh[3];
+        for (int x = 0; x < 3; ++x)
+            sh[x] = M::shift(P, x, o[x], (steps.lo >> x) & 1u, (steps.hi >> x) & 1u);
+        uint64_t mask = 0ull;
+        for (uint32_t t = 0; t < cnt; ++t) {
+            const typename M::Vec v = load_vec<M>(q4, s + t);
+            const Real dx = (qi.x - v.x) + sh[0], dy = (qi.y - v.y) + sh[1],
+                       dz = (qi.z - v.z) + sh[2];
+            const Real r2 = dx * dx + dy * dy + dz * dz;
+            if (!M::near(P, r2)) continue;
+            acc = acc + M::template density<LUCY>(P, r2);
+            if (partners < a.list_cap) list[partners] = list_entry(s + t, k);
+            ++partners;
+            mask |= 1ull << t;
+        }
+        if (k == OWN_NB && cnt) mask &= ~(1ull << (i - (int64_t)s));   // i itself is no partner
+        if (k >= OWN_NB) a.masks[(int64_t)(k - OWN_NB) * n + i] = mask;
+    }
+    a.count[i] = partners;
+    density_store(a, i, M::density_scale(P, acc));
+}
+
 // ---------------------------------------------------------------- partner sums
 // Sums over a particle's partners, from the lists of the density pass (same
 // positions): kLanes lanes per particle, lane s with entries s, s + kLanes, ...
@@ -657,9 +704,18 @@ struct PartnerSums {
             Real out[NV];
             for (int v = 0; v < NV; ++v) out[v] = (Real)0;
             if (t0 + (uint32_t)lane < cw.total && M::near(P, r2)) term(j, qi, qj, d, r2, out);
-            for (int v = 0; v < NV; ++v)   // in candidate order
-                for (int l = 0; l < 64; ++l) sum[v] = sum[v] + lane_of(out[v], l);
+            for (int v = 0; v < NV; ++v) {
+                if constexpr (sizeof(Real) == 8) {
+                    sum[v] += out[v];
+                } else {   // in candidate order
+                    for (int l = 0; l < 64; ++l) sum[v] = sum[v] + lane_of(out[v], l);
+                }
+            }
         }
+        if constexpr (sizeof(Real) == 8)   // over the lanes, in each of them
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) sum[v] += __shfl_xor(sum[v], off);
     }
 
     __device__ __forceinline__ Real run(int64_t i, bool live, Term term)
@@ -825,6 +881,10 @@ __device__ __forceinline__ void forces_body(const ForcesArgs &g, uint32_t blk)
 // form of large ones (the two agree bit for bit); a box on its own: four waves per cell up to 2^10 cells, one per SIMD of the GPU (384
 // cells: 25 us against 50; 1728 cells: 53 against 54; 7128: 102 against 73).
 constexpr int64_t kSplitMaxCells = 1 << 10;
+// A lane per particle from 2^15 cells of fewer than four particles on average on: 64000
+// cells of 0.25, 1, 2, 3, 4 particles 34, 48, 67, 91, 124 us, a wave per cell 64, 78, 91,
+// 109, 124; 13824 cells, whose waves all fit at once, 32, 45, 58, 69 against 21, 24, 27, 32.
+constexpr int64_t kSparsePerCell = 4, kSparseMinCells = 1 << 15;
 
 template <class M, bool LUCY>
 __device__ __forceinline__ void density_body(const DensityArgs &a, uint32_t blk)
@@ -839,6 +899,11 @@ __global__ __launch_bounds__(64 * kCellWaves, SPLIT ? 1 : M::kDensityOcc) void k
     density_cells<M, LUCY, SPLIT>(a, xcd_block(blockIdx.x, gridDim.x), lds);
 }
 template <class M, bool LUCY>
+__global__ __launch_bounds__(256) void k_density_sparse(DensityArgs a)
+{
+    density_sparse<M, LUCY>(a, xcd_block(blockIdx.x, gridDim.x));
+}
+template <class M, bool LUCY>
 __global__ __launch_bounds__(256) void k_forces(ForcesArgs g)
 {
     forces_body<M, LUCY>(g, xcd_block(blockIdx.x, gridDim.x));
@@ -846,8 +911,11 @@ __global__ __launch_bounds__(256) void k_forces(ForcesArgs g)
 
 // (multi: the multi-box forms of this model and kernel)
 template <class M, bool LUCY>
-int launch_density(sdpd_ctx *c, const DensityArgs &args, MultiKernel multi)
+int launch_density(sdpd_ctx *c, const DensityArgs &args, MultiKernel multi, MultiKernel sparse)
 {
+    if (c->ncell >= kSparseMinCells && c->n < kSparsePerCell * c->ncell)
+        return launch_or_record(c, k_density_sparse<M, LUCY>, sparse,
+                                (unsigned)((c->n + 255) / 256), 256, 0, args);
     if (c->ncell <= kSplitMaxCells && !c->rec) {
         hipLaunchKernelGGL((k_density<M, LUCY, true>), dim3((unsigned)c->ncell),
                            dim3(64 * kCellWaves), 0, c->stream, args);

@@ -1,9 +1,10 @@
-"""Density, masks and forces at the edges of the cell-wise passes: few cells (a
-workgroup per cell, a wave per particle) and many (a wave per cell, a lane per
-particle), empty cells, cells of more than 32 particles (two mask words) and
-nearly full ones.  The forces are sums over the masks, so a wrong bit shows in
-them.  FP64 against the oracle as in the other parity tests (1e-12 of the largest
-value); mixed precision rho within 2e-5 (FP32 separations, see the tests there)."""
+"""Density, masks, lists and forces at the edges of the cell-wise passes: few cells
+(a workgroup per cell), many (a wave per cell), many nearly empty ones (a lane per
+particle), empty cells, cells of more than 32 particles (two mask words) and nearly
+full ones, and particles with more partners than their lists hold.  The forces are
+sums over the lists, so a wrong entry shows in them.  FP64 against the oracle as in the
+other parity tests (1e-12 of the largest value); mixed precision rho within 2e-5 (FP32
+separations, see the tests there)."""
 import numpy as np
 import pytest
 
@@ -19,6 +20,8 @@ BOXES = {
     "dilute_1152_cells": (3001, (20.0, 20.0, 45.0)),
     "dense_64_cells": (2450, (10.0, 10.0, 10.0)),
     "dense_1152_cells": (41003, (20.0, 20.0, 45.0)),
+    # 34^3 cells: a lane per particle
+    "sparse_39304_cells": (20011, (85.0, 85.0, 85.0)),
     "few_particles": (5, (10.0, 15.0, 10.0)),
     # a third of the particles within 1.6 of a cell corner: more partners than the
     # lists of the density pass, sized for the mean density, hold
