@@ -41,3 +41,39 @@ def test_schedule_forms(box):
     R = O.State.from_arrays(q, p, eps, ids)
     O.prepare(P, R)
     PU.sweep_and_compare(P, R, 5, S.to_numpy(), stats, 1e-10, say)
+
+
+# 4096 cells each: the schedule of one box runs in rounds, that of a launch shared by
+# both (8192 cells) with tasks on lanes; with a part for each box both run in rounds
+@pytest.mark.parametrize("parts", [1, 2])
+def test_batch_schedule_equals_eager(parts):
+    import torch
+    from paper_1707_04232_amd import sdpd
+    from paper_1707_04232_amd.workload import lattice_state
+    say("batch schedule, parts", parts)
+    outs = []
+    for batch in (False, True):
+        ctxs, states = [], []
+        for b in range(2):
+            q, p, eps, ids = lattice_state(40, jitter=0.2, Cv=10.0, T=1.0, seed=b)
+            states.append(sdpd.DeviceState.from_numpy(q, p, eps, ids))
+            ctxs.append(sdpd.Context(sdpd.SdpdParams(n=len(eps), box=40.0, seed=9, replica=b),
+                                     stream=torch.cuda.Stream()))
+            ctxs[-1].prepare(states[-1])
+        torch.cuda.synchronize()
+        if batch:
+            B = sdpd.Batch(ctxs, states, layout=sdpd.BATCH_FUSED, parts=parts)
+            B.run(0, 3)
+            torch.cuda.synchronize()
+            B.close()
+        else:
+            for c, S in zip(ctxs, states):
+                c.step(S, 0, 3, stats=False)
+        for c in ctxs:
+            c.sync()
+        outs.append([S.to_numpy() for S in states])
+        for c in ctxs:
+            c.close()
+    for x, y in zip(*outs):
+        for k in ("id", "q", "p", "eps", "rho", "f"):
+            assert np.array_equal(x[k], y[k]), k
