@@ -56,6 +56,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <memory>
 #include <vector>
 
 #include "fd_math.hpp"
@@ -1039,9 +1040,10 @@ static std::vector<std::vector<int>> fd_groups()
     return groups;
 }
 
-// workgroup ranges of one launch over the tasks of up to FD_MAXPH mutually
-// disjoint phases; returns the number of ranges
-static int64_t fd_launch_geometry(const sdpd_ctx *c, const int *phases, int nph, FdLaunch &L)
+// workgroup ranges that tuning u gives one launch over the tasks of up to
+// FD_MAXPH mutually disjoint phases; returns the number of ranges
+static int64_t fd_launch_geometry(const sdpd_ctx *c, const sdpd_tuning &u, const int *phases,
+                                  int nph, FdLaunch &L)
 {
     L.nph = nph;
     L.cap_p = 0;
@@ -1056,13 +1058,50 @@ static int64_t fd_launch_geometry(const sdpd_ctx *c, const int *phases, int nph,
         const int cls = phase_geom(ph).cls;
         L.task_base[k] = ph == 0 ? 0 : c->ncell + (int64_t)(ph - 1) * (c->ncell / 8);
         L.ntasks[k] = ph == 0 ? c->ncell : c->ncell / 8;
-        L.tpw[k] = c->tuning.fd_tasks[cls];
+        L.tpw[k] = u.fd_tasks[cls];
         wg += (L.ntasks[k] + L.tpw[k] - 1) / L.tpw[k];
         L.wg_end[k] = wg;
-        L.cap_p = std::max(L.cap_p, (int)c->tuning.fd_lds_particles[cls]);
-        L.cap_e = std::max(L.cap_e, (int)c->tuning.fd_lds_pairs[cls]);
+        L.cap_p = std::max(L.cap_p, (int)u.fd_lds_particles[cls]);
+        L.cap_e = std::max(L.cap_e, (int)u.fd_lds_pairs[cls]);
     }
     return wg;
+}
+
+// The ranges of a whole sweep, group by group, that tuning u gives, and the LDS
+// of a workgroup.  The epochs need every group to touch every cell exactly once:
+// its phases' parity sets partition the 8 parities (true of the 26 groups of the
+// 13 forward offsets; checked).
+static int fd_sweep_ranges(const sdpd_ctx *c, const sdpd_tuning &u, FdSweep &h, size_t &lds)
+{
+    const std::vector<std::vector<int>> groups = fd_groups();
+    if ((int)groups.size() > FD_MAXGROUPS) return SDPD_EINVAL;
+    memset(&h, 0, sizeof h);
+    h.ngroups = (int)groups.size();
+    int64_t total = 0;
+    lds = 0;
+    for (size_t g = 0; g < groups.size(); ++g) {
+        unsigned cover = 0;
+        for (int ph : groups[g]) {
+            const unsigned ps = phase_geom(ph).parity_set;
+            if (cover & ps) return SDPD_EINVAL;
+            cover |= ps;
+        }
+        if (cover != 0xFFu) return SDPD_EINVAL;
+        total += fd_launch_geometry(c, u, groups[g].data(), (int)groups[g].size(), h.launch[g]);
+        if (total > 0x7fffffffLL) return SDPD_EINVAL;
+        h.group_end[g] = (uint32_t)total;
+        lds = std::max(lds, fd_lds_bytes(h.launch[g].cap_p, h.launch[g].cap_e));
+    }
+    h.nitems = (uint32_t)total;
+    return lds > (size_t)c->max_lds ? SDPD_EINVAL : SDPD_OK;
+}
+
+// 16-byte units of the records of the largest batch of any range
+static int64_t fd_record_slice(const FdSweep &h)
+{
+    int64_t ce = 1;
+    for (int g = 0; g < h.ngroups; ++g) ce = std::max<int64_t>(ce, h.launch[g].cap_e);
+    return 4 * ce;
 }
 
 static bool fd_fast(const sdpd_ctx *c)
@@ -1108,10 +1147,6 @@ static FdArgs fd_args(const sdpd_ctx *c, const sdpd_state *s, double dt_fd)
     return A;
 }
 
-// Table of the sweep kernel (ranges of every group, in sweep order) and its
-// launch size, rebuilt whenever the tuning changes.  The epochs need every
-// group to touch every cell exactly once: its phases' parity sets partition
-// the 8 parities (true of the 26 groups of the 13 forward offsets; checked).
 bool fd_one_launch(const sdpd_ctx *c)
 {
     if (c->fd_per_group || c->sweep_mode == SDPD_SWEEP_PER_GROUP) return false;
@@ -1120,21 +1155,16 @@ bool fd_one_launch(const sdpd_ctx *c)
 
 // one launch per group
 static int launch_phases(sdpd_ctx *c, const sdpd_state *s, const int *phases, int nph,
-                         double dt_fd, bool records)
+                         double dt_fd)
 {
     FdLaunch L;
-    const int64_t wg = fd_launch_geometry(c, phases, nph, L);
+    const int64_t wg = fd_launch_geometry(c, c->tuning, phases, nph, L);
     if (wg == 0) return SDPD_OK;
     if (wg > 0x7fffffffLL) return SDPD_EINVAL;
     const size_t lds = fd_lds_bytes(L.cap_p, L.cap_e);
     if (lds > (size_t)c->max_lds) return SDPD_EINVAL;
     const FdPhaseArgs args{c->dparams, L, fd_args(c, s, dt_fd), c->counters};
     const int kind = fd_kind(c);
-    if (!records) {   // formed by k_fd_records
-        auto kern = kind == 2 ? k_fd_levels<2> : kind == 1 ? k_fd_levels<1> : k_fd_levels<0>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)wg), dim3(FD_THREADS), lds, c->stream, args);
-        return check_hip(hipGetLastError());
-    }
     const int rc =
         kind == 2 ? launch_or_record(c, k_fd_phase<2>, k_fd_phase_mix_multi, (unsigned)wg,
                                      FD_THREADS, lds, args)
@@ -1143,6 +1173,29 @@ static int launch_phases(sdpd_ctx *c, const sdpd_state *s, const int *phases, in
                     : launch_or_record(c, k_fd_phase<0>, k_fd_phase_gen_multi, (unsigned)wg,
                                        FD_THREADS, lds, args);
     return rc;
+}
+
+// The same with the records of the whole sweep formed first.  Both kernels cut
+// the tasks into ranges and batches, and find the records and level ends by them:
+// both take the ranges from the context's sweep table.
+static int launch_records_and_levels(sdpd_ctx *c, const sdpd_state *s, double dt_fd)
+{
+    const FdSweep &h = *c->sweep_host;
+    const FdArgs A = fd_args(c, s, dt_fd);
+    const int kind = fd_kind(c);
+    if (h.nitems == 0u) return SDPD_OK;
+    auto records = kind == 2 ? k_fd_records<2> : kind == 1 ? k_fd_records<1> : k_fd_records<0>;
+    hipLaunchKernelGGL(records, dim3(h.nitems), dim3(FD_THREADS), c->sweep_lds, c->stream,
+                       c->dparams, (const FdSweep *)c->sweep, A);
+    auto levels = kind == 2 ? k_fd_levels<2> : kind == 1 ? k_fd_levels<1> : k_fd_levels<0>;
+    for (int g = 0; g < h.ngroups; ++g) {
+        const FdLaunch &L = h.launch[g];
+        const uint32_t wg = h.group_end[g] - (g > 0 ? h.group_end[g - 1] : 0u);
+        if (wg == 0u) continue;
+        hipLaunchKernelGGL(levels, dim3(wg), dim3(FD_THREADS), fd_lds_bytes(L.cap_p, L.cap_e),
+                           c->stream, FdPhaseArgs{c->dparams, L, A, c->counters});
+    }
+    return check_hip(hipGetLastError());
 }
 
 // cells of task T (the host form of task_cells); B = -1 for a phase-0 task
@@ -1223,9 +1276,7 @@ static std::vector<uint32_t> fd_range_order(const sdpd_ctx *c, const FdSweep &h)
 // buffer when they fit (large boxes), else in a buffer of their own.
 static int fd_flow_records(sdpd_ctx *c, const FdSweep &h)
 {
-    int64_t ce = 1;   // records of the largest batch of any range
-    for (int g = 0; g < h.ngroups; ++g) ce = std::max<int64_t>(ce, h.launch[g].cap_e);
-    c->sweep_rec_stride = 4 * ce;
+    c->sweep_rec_stride = fd_record_slice(h);
     const size_t need = sizeof(double2) * (size_t)c->sweep_rec_stride * (size_t)c->sweep_grid;
     const bool own = need > c->rec_bytes;
     if (c->flow_rec && (!own || c->flow_rec_bytes < need)) {
@@ -1244,41 +1295,24 @@ static int fd_flow_records(sdpd_ctx *c, const FdSweep &h)
     return SDPD_OK;
 }
 
+// Table of the sweep kernel (ranges of every group, in sweep order) and its
+// launch size, rebuilt whenever the tuning changes.
 int fd_prepare_sweep(sdpd_ctx *c)
 {
     // the table and the order are rewritten in place: no sweep may be running
     if (hipStreamSynchronize(c->stream) != hipSuccess) return SDPD_EHIP;
     c->sweep_ok = 0;
-    const std::vector<std::vector<int>> groups = fd_groups();
-    if ((int)groups.size() > FD_MAXGROUPS) return SDPD_EINVAL;
-    FdSweep h;
-    memset(&h, 0, sizeof h);
-    h.ngroups = (int)groups.size();
-    int64_t total = 0;
+    auto table = std::make_shared<FdSweep>();
+    FdSweep &h = *table;
     size_t lds = 0;
-    for (size_t g = 0; g < groups.size(); ++g) {
-        unsigned cover = 0;
-        for (int ph : groups[g]) {
-            const unsigned ps = phase_geom(ph).parity_set;
-            if (cover & ps) return SDPD_EINVAL;
-            cover |= ps;
-        }
-        if (cover != 0xFFu) return SDPD_EINVAL;
-        total += fd_launch_geometry(c, groups[g].data(), (int)groups[g].size(), h.launch[g]);
-        if (total > 0x7fffffffLL) return SDPD_EINVAL;
-        h.group_end[g] = (uint32_t)total;
-        lds = std::max(lds, fd_lds_bytes(h.launch[g].cap_p, h.launch[g].cap_e));
-    }
-    h.nitems = (uint32_t)total;
-    if (lds > (size_t)c->max_lds) return SDPD_EINVAL;
-    c->sweep_ngroups = h.ngroups;
-    memcpy(c->sweep_group_end, h.group_end, sizeof h.group_end);
+    int rc = fd_sweep_ranges(c, c->tuning, h, lds);
+    if (rc) return rc;
+    c->sweep_host = table;
     if (!c->sweep && hipMalloc(&c->sweep, sizeof(FdSweep)) != hipSuccess) {
         c->sweep = nullptr;
         return SDPD_ENOMEM;
     }
-    int rc = check_hip(hipMemcpy(c->sweep, &h, sizeof h, hipMemcpyHostToDevice));
-    if (rc) return rc;
+    if ((rc = check_hip(hipMemcpy(c->sweep, &h, sizeof h, hipMemcpyHostToDevice)))) return rc;
     const std::vector<uint32_t> order = fd_range_order(c, h);
     // one range per task at most: the buffer is sized once and never moves
     const size_t order_cap = (size_t)NMASK * (size_t)c->ncell + 1;
@@ -1301,7 +1335,7 @@ int fd_prepare_sweep(sdpd_ctx *c)
         return SDPD_EHIP;
     }
     c->sweep_lds = lds;
-    c->sweep_grid = (int)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(total, 1));
+    c->sweep_grid = (int)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(h.nitems, 1));
     if ((rc = fd_flow_records(c, h))) return rc;
     // one launch when the sweep holds at least three GPU-fulls of ranges (at
     // two waves per SIMD; boxes of some 450 cells); a smaller one mostly waits
@@ -1313,7 +1347,7 @@ int fd_prepare_sweep(sdpd_ctx *c)
     // one; 48 boxes on four streams and queues: 23 ms, and 25 with launches per
     // group only; on one stream 38 and 45)
     const int64_t full = 8 * (int64_t)cus;
-    c->fd_dataflow = total >= (hw_queues() > 4 ? 16 : 1) * 3 * full;
+    c->fd_dataflow = (int64_t)h.nitems >= (hw_queues() > 4 ? 16 : 1) * 3 * full;
     c->sweep_ok = 1;
     return SDPD_OK;
 }
@@ -1394,14 +1428,11 @@ int fd_launch_sweep(sdpd_ctx *c, const sdpd_state *s, double dt_fd)
         const bool whole = c->lvl_end && !c->rec && !c->fd_per_group;
         timer_begin(c, TK_FD);
         if (whole) {
-            auto kern = kind == 2 ? k_fd_records<2> : kind == 1 ? k_fd_records<1> : k_fd_records<0>;
-            hipLaunchKernelGGL(kern, dim3(c->sweep_group_end[c->sweep_ngroups - 1]),
-                               dim3(FD_THREADS), c->sweep_lds, c->stream, c->dparams,
-                               (const FdSweep *)c->sweep, fd_args(c, s, dt_fd));
-            if ((rc = check_hip(hipGetLastError()))) return rc;
+            if ((rc = launch_records_and_levels(c, s, dt_fd))) return rc;
+        } else {
+            for (const std::vector<int> &g : fd_groups())
+                if ((rc = launch_phases(c, s, g.data(), (int)g.size(), dt_fd))) return rc;
         }
-        for (const std::vector<int> &g : fd_groups())
-            if ((rc = launch_phases(c, s, g.data(), (int)g.size(), dt_fd, !whole))) return rc;
         timer_end(c, TK_FD);
         return SDPD_OK;
     }
@@ -1418,44 +1449,28 @@ int fd_launch_sweep(sdpd_ctx *c, const sdpd_state *s, double dt_fd)
     return check_hip(hipGetLastError());
 }
 
-// A box's range table and hand-out order for a launch shared with other boxes:
-// those of its batch tuning, in buffers of the launch's own (the context keeps
-// its tables for sweeps on its own).
-static int fd_flow_tables(sdpd_ctx *c, int64_t total, FdBoxDesc &d, size_t &lds, int64_t &stride,
-                          uint32_t *group_end, FlowSweep &out)
+// A box's ranges in a launch shared with other boxes (`total` particles in all): those
+// of its batch tuning, with table and order in buffers of the launch's own, or of the
+// box's own tuning where its user has set one (a later change invalidates the batch).
+static int fd_flow_tables(sdpd_ctx *c, int64_t total, FdBoxDesc &d, size_t &lds, FdSweep &h,
+                          FlowSweep &out)
 {
-    const sdpd_tuning saved = c->tuning;
     const bool own = c->tune_gen == 0;
-    int rc = SDPD_OK;
-    if (own) {
-        c->tuning = fd_batch_tuning(c, total);
-        rc = fd_prepare_sweep(c);
+    int rc = fd_sweep_ranges(c, own ? fd_batch_tuning(c, total) : c->tuning, h, lds);
+    if (rc || !own) return rc;
+    const std::vector<uint32_t> order = fd_range_order(c, h);
+    const size_t bytes[2] = {sizeof h, sizeof(uint32_t) * order.size()};
+    const void *src[2] = {&h, order.data()};
+    void *dst[2] = {nullptr, nullptr};
+    for (int k = 0; k < 2; ++k) {
+        if (hipMalloc(&dst[k], bytes[k] ? bytes[k] : 4) != hipSuccess) return SDPD_ENOMEM;
+        out.tables.push_back(dst[k]);
+        if (bytes[k] && (rc = check_hip(hipMemcpy(dst[k], src[k], bytes[k], hipMemcpyHostToDevice))))
+            return rc;
     }
-    if (!rc) {
-        memcpy(group_end, c->sweep_group_end, sizeof c->sweep_group_end);
-        lds = c->sweep_lds;
-        stride = c->sweep_rec_stride;
-    }
-    if (!rc && own) {
-        const size_t bytes[2] = {sizeof(FdSweep),
-                                 sizeof(uint32_t) * (size_t)group_end[c->sweep_ngroups - 1]};
-        const void *src[2] = {c->sweep, c->sweep_order};
-        void *dst[2] = {nullptr, nullptr};
-        for (int k = 0; k < 2 && !rc; ++k) {
-            if (hipMalloc(&dst[k], bytes[k] ? bytes[k] : 4) != hipSuccess) rc = SDPD_ENOMEM;
-            else out.tables.push_back(dst[k]);
-            if (!rc && bytes[k])
-                rc = check_hip(hipMemcpy(dst[k], src[k], bytes[k], hipMemcpyDeviceToDevice));
-        }
-        d.SW = (const FdSweep *)dst[0];
-        d.order = (const uint32_t *)dst[1];
-    }
-    if (own) {
-        c->tuning = saved;
-        const int rc2 = fd_prepare_sweep(c);
-        rc = rc ? rc : rc2;
-    }
-    return rc;
+    d.SW = (const FdSweep *)dst[0];
+    d.order = (const uint32_t *)dst[1];
+    return SDPD_OK;
 }
 
 int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
@@ -1465,24 +1480,24 @@ int fd_flow_build(const std::vector<sdpd_ctx *> &ctxs,
     if (nbox < 1 || recs.size() != ctxs.size()) return SDPD_EINVAL;
     out.kind = recs[0]->flow_kind;
     out.nbox = nbox;
-    out.ngroups = ctxs[0]->sweep_ngroups;
+    out.ngroups = ctxs[0]->sweep_host ? ctxs[0]->sweep_host->ngroups : 0;
     std::vector<FdBoxDesc> desc(nbox);
     std::vector<uint32_t> ends((size_t)nbox * FD_MAXGROUPS);
     out.lds = 0;
     int64_t stride = 0, total = 0;   // record slice of a workgroup: the largest of any box
     for (sdpd_ctx *c : ctxs) total += c->n;
     for (int b = 0; b < nbox; ++b) {
-        if (recs[b]->flow_kind != out.kind || ctxs[b]->sweep_ngroups != out.ngroups ||
-            recs[b]->args.size() != sizeof(FdBoxDesc))
+        if (recs[b]->flow_kind != out.kind || recs[b]->args.size() != sizeof(FdBoxDesc))
             return SDPD_EINVAL;
         memcpy(&desc[b], recs[b]->args.data(), sizeof(FdBoxDesc));
         size_t lds = 0;
-        int64_t st = 0;
-        const int rc = fd_flow_tables(ctxs[b], total, desc[b], lds, st,
-                                      &ends[(size_t)b * FD_MAXGROUPS], out);
+        FdSweep h;
+        const int rc = fd_flow_tables(ctxs[b], total, desc[b], lds, h, out);
         if (rc) return rc;
+        if (h.ngroups != out.ngroups) return SDPD_EINVAL;
+        memcpy(&ends[(size_t)b * FD_MAXGROUPS], h.group_end, sizeof h.group_end);
         out.lds = std::max(out.lds, lds);
-        stride = std::max(stride, st);
+        stride = std::max(stride, fd_record_slice(h));
     }
     // group-major item numbering: all boxes' ranges of group 0, then group 1, ...
     std::vector<uint32_t> off((size_t)out.ngroups * (nbox + 1));

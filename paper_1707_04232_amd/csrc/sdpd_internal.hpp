@@ -6,6 +6,7 @@
 
 #include <string.h>
 
+#include <memory>
 #include <vector>
 
 #include "sdpd.h"
@@ -19,6 +20,7 @@ enum : uint32_t {
     ERR_STALL = 32u
 };
 struct AdjointWork;   // adjoint.hip
+struct FdSweep;       // fd.hip
 
 // F/D counters, in this order in the device counter array
 enum { CNT_PROPOSED = 0, CNT_REJ_ENERGY, CNT_REJ_RATIO, CNT_MARGINAL, CNT_NEGEPS, CNT_N };
@@ -189,8 +191,7 @@ struct sdpd_ctx {
     int fd_per_group = 0;        // force one launch per group (set while a batch captures)
     int64_t batch_cells = 0;     // recording: cells of the boxes that share a launch
     int fd_record_flow = 0;      // recording: the sweep as one multi-box launch (fused batch)
-    int sweep_ngroups = 0;       // host copy of the sweep table's group ends
-    uint32_t sweep_group_end[32] = {};
+    std::shared_ptr<const sdpd::FdSweep> sweep_host;   // host copy of the sweep table
     int sweep_mode = 0;          // SDPD_SWEEP_*
     size_t sweep_lds = 0;
     int sweep_grid = 0, sweep_ok = 0;
