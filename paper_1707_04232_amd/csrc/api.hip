@@ -262,8 +262,11 @@ static const int64_t STEP_RECORDS = 64;
 
 // Boxes of at most this many particles sweep on their own by one launch per
 // group (see fd_prepare_sweep) after one launch that forms the records of the
-// whole sweep; larger ones form them in the sweep's launches.
+// whole sweep; larger ones form them in the sweep's launches.  The ends of the
+// levels take 1792 B per cell: boxes of more cells than this are dilute at so few
+// particles, and sweep by one launch unless told otherwise.
 static const int64_t kWholeRecordsMaxParticles = (int64_t)1 << 14;
+static const int64_t kWholeRecordsMaxCells = (int64_t)1 << 13;
 
 static int alloc_records(sdpd_ctx *c)
 {
@@ -380,7 +383,7 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     mem.add(&c->part_list, (size_t)c->part_cap);
     // pair records: of one group of the sweep (it touches every cell once: at
     // most 32 pairs per particle), for small boxes of a whole sweep
-    const bool whole = c->n <= kWholeRecordsMaxParticles;
+    const bool whole = c->n <= kWholeRecordsMaxParticles && c->ncell <= kWholeRecordsMaxCells;
     c->rec_bytes = sizeof(double) * (whole ? 8 : 4) * (size_t)c->pair_cap;
     mem.add(&c->rec_buf, c->rec_bytes / sizeof(double));
     if (whole) mem.add(&c->lvl_end, (size_t)NMASK * nce * 64);
