@@ -253,9 +253,9 @@ int sdpd_get_tuning(sdpd_ctx *ctx, sdpd_tuning *out);
  * sweep is 27 groups of mutually disjoint phases (phase 0, then 26 groups of
  * 4 inter-cell phases) that must follow one another on each cell.
  *   SDPD_SWEEP_AUTO       one launch for boxes large enough to hold several
- *                         GPU-fulls of task ranges (sixteen times as many
- *                         where GPU_MAX_HW_QUEUES is above 4), else one per
- *                         group;
+ *                         GPU-fulls of task ranges (counted in ranges of the
+ *                         full default size, some 7,900 cells, where
+ *                         GPU_MAX_HW_QUEUES is above 4), else one per group;
  *   SDPD_SWEEP_ONE        one persistent launch: each range waits only for
  *                         the ranges of the previous group on its cells;
  *   SDPD_SWEEP_PER_GROUP  27 launches.

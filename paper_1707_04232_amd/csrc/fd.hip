@@ -1337,17 +1337,28 @@ int fd_prepare_sweep(sdpd_ctx *c)
     c->sweep_lds = lds;
     c->sweep_grid = (int)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(h.nitems, 1));
     if ((rc = fd_flow_records(c, h))) return rc;
-    // one launch when the sweep holds at least three GPU-fulls of ranges (at
+    // One launch when the sweep holds at least three GPU-fulls of ranges (at
     // two waves per SIMD; boxes of some 450 cells); a smaller one mostly waits
     // on its chain of 27 groups, and one launch per group then holds no
     // workgroup slots while it waits.  Where the process asks for more queues than
-    // the default four, boxes on many streams would hold them against each other:
-    // sixteen times that (256 boxes of 13^3 to 40^3 particles stepped eagerly on 32
-    // streams and queues: 312 ms per step with the line of few queues, 88 with this
-    // one; 48 boxes on four streams and queues: 23 ms, and 25 with launches per
-    // group only; on one stream 38 and 45)
+    // the default four, boxes on many streams would hold them against each other
+    // (256 boxes of 13^3 to 40^3 particles stepped eagerly on 32 streams and queues:
+    // 312 ms per step with the line above, 88 with one launch per group; 48 boxes on
+    // four streams and queues: 23 and 25): there only boxes that fill the GPU by
+    // themselves, four GPU-fulls of ranges of full size (some 7,900 cells; one box
+    // alone with eight queues, one launch / one per group, ms: 0.95 / 1.34 at 48^3
+    // particles, 1.21 / 1.57 at 56^3, 3.04 / 4.41 at 2^20).
     const int64_t full = 8 * (int64_t)cus;
-    c->fd_dataflow = (int64_t)h.nitems >= (hw_queues() > 4 ? 16 : 1) * 3 * full;
+    c->fd_dataflow = (int64_t)h.nitems >= 3 * full;
+    if (c->fd_dataflow && hw_queues() > 4) {
+        FdSweep large = h;
+        if (c->tune_gen == 0) {   // (the defaults of smaller boxes are shorter ranges)
+            sdpd_tuning u = c->tuning;
+            for (int k = 0; k < 4; ++k) u.fd_tasks[k] = std::max(u.fd_tasks[k], kDefaultTasks[k]);
+            if ((rc = fd_sweep_ranges(c, u, large, lds))) return rc;
+        }
+        c->fd_dataflow = (int64_t)large.nitems >= 4 * full;
+    }
     c->sweep_ok = 1;
     return SDPD_OK;
 }
