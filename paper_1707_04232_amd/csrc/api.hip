@@ -318,7 +318,6 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     c->n = params->n;
     c->ncell = c->dp.ncell;
     const size_t n = (size_t)c->n, nce = (size_t)c->ncell;
-    c->nscan_blocks = 2 * (int64_t)(((size_t)NMASK * nce + 1023) / 1024);
     c->obs_blocks = std::max(observe_blocks(c->n), 1);
     {
         int lds = 0;
@@ -354,7 +353,7 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     mem.add(&c->cell_of, n);
     mem.add(&c->count, nce);
     mem.add(&c->cell_start, nce + 1);
-    mem.add(&c->block_sums, (size_t)c->nscan_blocks);
+    mem.add(&c->block_sums, (size_t)scan_sums_size((int64_t)NMASK * c->ncell));
     mem.add(&c->tmp_idx, n);
     mem.add(&c->slot, n);
     mem.add(&c->cell_sorted, n);

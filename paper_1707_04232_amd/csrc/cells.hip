@@ -128,14 +128,17 @@ __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s, uint32_t *tota
 
 // Up to two arrays of one length in one launch (workgroups 0 .. nblocks - 1 and
 // nblocks .. 2 nblocks - 1): prefix sums inside each block of SCAN_BLOCK values, then
-// each block adds the sum of the blocks before it, which it forms itself (a launch
-// for those sums costs more than they do: 4.5 us, and 54 us for 6900 blocks).
+// each block adds the sum of the blocks before it.  Up to SCAN_SELF_SUM blocks it forms
+// that sum itself (a launch for those sums costs more than they do: 4.5 us, and 54 us
+// with one workgroup over 6900 blocks); that work grows as the square of the blocks, so
+// above them the blocks' sums are scanned in the same way first, in place (scanned).
 struct ScanArgs {
     uint32_t *in[2];
     uint32_t *out[2], *sums[2];
     int64_t count, nblocks;
     int cap, clear;          // clear: in is zero afterwards
     uint32_t *err;
+    int scanned;             // sums holds the prefix sums of the blocks, then their total
 };
 __device__ __forceinline__ void scan_local_body(const ScanArgs &a, uint32_t blk)
 {
@@ -179,20 +182,26 @@ __device__ __forceinline__ void scan_add_body(const ScanArgs &a, uint32_t blk)
     const uint32_t *sums = a.sums[which];
     uint32_t *out = a.out[which];
     __shared__ uint32_t s[SCAN_THREADS];
-    uint32_t before = 0u;
-    for (int64_t i = threadIdx.x; i < b; i += SCAN_THREADS) before += sums[i];
-    s[threadIdx.x] = before;
-    for (int off = SCAN_THREADS / 2; off > 0; off >>= 1) {
+    uint32_t add;
+    if (a.scanned) {
+        add = sums[b];
+    } else {
+        uint32_t before = 0u;
+        for (int64_t i = threadIdx.x; i < b; i += SCAN_THREADS) before += sums[i];
+        s[threadIdx.x] = before;
+        for (int off = SCAN_THREADS / 2; off > 0; off >>= 1) {
+            __syncthreads();
+            if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
+        }
         __syncthreads();
-        if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
+        add = s[0];
     }
-    __syncthreads();
-    const uint32_t add = s[0];
     int64_t base = b * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
 #pragma unroll
     for (int k = 0; k < SCAN_PER_THREAD; ++k)
         if (base + k < a.count) out[base + k] += add;
-    if (b == a.nblocks - 1 && threadIdx.x == 0) out[a.count] = add + sums[b];
+    if (b == a.nblocks - 1 && threadIdx.x == 0)
+        out[a.count] = a.scanned ? sums[a.nblocks] : add + sums[b];
 }
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_add(ScanArgs a)
 {
@@ -200,8 +209,21 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_add(ScanArgs a)
 }
 SDPD_MULTI_KERNEL(k_scan_add_multi, ScanArgs, scan_add_body, SCAN_THREADS)
 
+constexpr int64_t SCAN_SELF_SUM = 1 << 13;
+
+// entries of block_sums that run_scan needs for two arrays of count values
+int64_t scan_sums_size(int64_t count)
+{
+    int64_t size = 0;
+    do {
+        count = (count + SCAN_BLOCK - 1) / SCAN_BLOCK;
+        size += 2 * (count + 1);
+    } while (count > SCAN_SELF_SUM);
+    return size;
+}
+
 // out[0..count] = exclusive prefix sums of in[0..count), out[count] = total, for one
-// array or two (in2 not NULL).  block_sums needs ceil(count / 1024) entries for each.
+// array or two (in2 not NULL).  in may be out (then in2 is out2).
 // A value above cap sets ERR_CELLCAP (cap < 0: no check).
 int run_scan(sdpd_ctx *c, uint32_t *in, uint32_t *out, uint32_t *in2, uint32_t *out2,
              int64_t count, uint32_t *block_sums, int cap, bool clear)
@@ -211,10 +233,16 @@ int run_scan(sdpd_ctx *c, uint32_t *in, uint32_t *out, uint32_t *in2, uint32_t *
         const int rc = launch_fill_u32(c, out, 0u, 1);
         return rc || !in2 ? rc : launch_fill_u32(c, out2, 0u, 1);
     }
-    const ScanArgs args{{in, in2}, {out, out2}, {block_sums, block_sums + nb}, count, nb, cap,
-                        clear ? 1 : 0, c->err};
+    uint32_t *const sums2 = block_sums + (nb + 1);
+    ScanArgs args{{in, in2}, {out, out2}, {block_sums, sums2}, count, nb, cap,
+                  clear ? 1 : 0, c->err, 0};
     const unsigned grid = (unsigned)(in2 ? 2 * nb : nb);
     int rc = launch_or_record(c, k_scan_local, k_scan_local_multi, grid, SCAN_THREADS, 0, args);
+    if (!rc && nb > SCAN_SELF_SUM) {
+        args.scanned = 1;
+        rc = run_scan(c, block_sums, block_sums, in2 ? sums2 : nullptr, in2 ? sums2 : nullptr, nb,
+                      sums2 + (nb + 1), -1, false);
+    }
     // (recorded also for one block: the boxes of a batch make the same launches)
     if (!rc && (nb > 1 || c->rec))
         rc = launch_or_record(c, k_scan_add, k_scan_add_multi, grid, SCAN_THREADS, 0, args);

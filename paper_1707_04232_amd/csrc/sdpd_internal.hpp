@@ -152,7 +152,6 @@ struct sdpd_ctx {
     void *arena = nullptr;       // one allocation that holds the buffers below
     // cell list
     uint32_t *cell_of, *count, *cell_start, *block_sums, *tmp_idx, *slot, *cell_sorted;
-    int64_t nscan_blocks;
     // gather targets of the sort (same shapes as the state)
     double *tq, *tp, *teps, *trho, *tf;
     uint32_t *tid;
@@ -216,6 +215,7 @@ int launch_fill_u64(sdpd_ctx *c, unsigned long long *p, unsigned long long v, in
 int launch_incr_u64(sdpd_ctx *c, unsigned long long *p);
 int run_scan(sdpd_ctx *c, uint32_t *in, uint32_t *out, uint32_t *in2, uint32_t *out2,
              int64_t count, uint32_t *block_sums, int cap, bool clear);
+int64_t scan_sums_size(int64_t count);
 int run_schedule(sdpd_ctx *c);
 // what a step sets before anything else: counters to zero, the step index (NULL: not)
 struct StepStart {

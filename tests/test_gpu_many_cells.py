@@ -54,3 +54,43 @@ def test_sweep_of_a_dilute_box(box):
     R = O.State.from_arrays(q, p, eps, ids)
     O.prepare(P, R)
     PU.sweep_and_compare(P, R, 5, outs[0], stats[0], 1e-10, say)
+
+
+# 84^3 cells have 8104 blocks of 1024 task counts, 86^3 have 8697: above 8192 the sums of
+# the blocks are scanned on their own.  A wrong offset shows in the sweep.
+@pytest.mark.parametrize("side", [84, 86])
+def test_schedule_of_many_cells(side):
+    from paper_1707_04232_amd import sdpd
+    n, box = 20011, (2.5 * side,) * 3
+    say("schedule of many cells", side)
+    q, p, eps, ids = uniform_state(n, box, seed=6)
+    q = np.array(q).reshape(3, n)
+    q[:, ::2] = np.array([[1.0], [40.0], [170.0]]) + 30.0 * (q[:, ::2] / box[0])   # dense
+    kw = dict(n=n, box=box, dt=0.002, Cv=10.0, seed=11, ncell=(side,) * 3)
+    S = sdpd.DeviceState.from_numpy(q, p, eps, ids)
+    with sdpd.Context(sdpd.SdpdParams(**kw)) as ctx:
+        ctx.prepare(S)
+        stats = ctx.fd_metropolis(S, step=5)
+    kw.pop("ncell")
+    P = O.OracleParams(**kw)
+    R = O.State.from_arrays(q, p, eps, ids)
+    O.prepare(P, R)
+    PU.sweep_and_compare(P, R, 5, S.to_numpy(), stats, 1e-10, say)
+
+
+def test_cells_beyond_the_first_scan():
+    """204^3 cells: 8291 blocks of cell counts (and two levels above them)."""
+    from paper_1707_04232_amd import sdpd
+    side, n = 204, 50021
+    say("cell list of many cells")
+    q, p, eps, ids = uniform_state(n, (2.5 * side,) * 3, seed=8)
+    S = sdpd.DeviceState.from_numpy(q, p, eps, ids)
+    with sdpd.Context(sdpd.SdpdParams(n=n, box=2.5 * side, ncell=(side,) * 3,
+                                      fd=sdpd.FD_NONE)) as ctx:
+        for _ in range(2):   # (the second build counts from what the first one left)
+            ctx.build_cells(S)
+        start = ctx.cell_start()
+    x = np.minimum(np.floor(np.array(q).reshape(3, n) * (side / (2.5 * side))), side - 1)
+    cell = (x[0] + side * (x[1] + side * x[2])).astype(np.int64)
+    want = np.concatenate([[0], np.cumsum(np.bincount(cell, minlength=side ** 3))])
+    assert np.array_equal(start, want)
