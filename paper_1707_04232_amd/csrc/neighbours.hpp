@@ -671,8 +671,10 @@ struct PartnerArgs {
 };
 
 
-// Value v of the sum over particle i's partners in lane s == v < NV of its lanes.  term(j, d, r2, out): the NV values of partner j at separation d = q_i -
-// q_j, all zero for r2 = 0; term.at(i): called before with the particle of the lane.
+// Value v of the sum over particle i's partners in lane s == v < NV of its lanes.
+// term(j, q_i, q_j, d, r2, out): the NV values of partner j at separation d = q_i - q_j;
+// term.at(i): called before with the particle of the lane.  The particle itself, which
+// its list holds and ends with, adds zero whatever its values (they may not be finite).
 template <class M, int NV, class Term>
 struct PartnerSums {
     typedef typename M::Real Real;
@@ -703,7 +705,8 @@ struct PartnerSums {
             const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
             Real out[NV];
             for (int v = 0; v < NV; ++v) out[v] = (Real)0;
-            if (t0 + (uint32_t)lane < cw.total && M::near(P, r2)) term(j, qi, qj, d, r2, out);
+            if (t0 + (uint32_t)lane < cw.total && M::near(P, r2) && j != (uint32_t)i)
+                term(j, qi, qj, d, r2, out);
             for (int v = 0; v < NV; ++v) {
                 if constexpr (sizeof(Real) == 8) {
                     sum[v] += out[v];
@@ -729,7 +732,7 @@ struct PartnerSums {
         const uint32_t self = list_entry((uint32_t)i, OWN_NB);
         term.at(i);
         Real mine = (Real)0;
-        // entry r (past the end: the particle itself, whose terms are zero)
+        // entry r (past the end: the particle itself)
         auto entry = [&](uint32_t r) { return r < cnt ? list[r] : self; };
         if constexpr (sizeof(Real) == 8) {
             // partners across the boundary only for particles within h of it
@@ -762,7 +765,8 @@ struct PartnerSums {
                         const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
                         double out[NV];
                         term(j[u], qi, qj[u], d, r2, out);
-                        for (int v = 0; v < NV; ++v) acc[v] += out[v];
+                        for (int v = 0; v < NV; ++v)
+                            acc[v] += j[u] == (uint32_t)i ? 0.0 : out[v];
                     }
                 }
             };
@@ -804,6 +808,7 @@ struct PartnerSums {
                     const float r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
                     float out[NV];
                     term(j[u], qi, qj[u], d, r2, out);
+                    for (int v = 0; v < NV; ++v) out[v] = j[u] == (uint32_t)i ? 0.0f : out[v];
                     for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x00>(out[v]);
                     for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x55>(out[v]);
                     for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0xaa>(out[v]);
