@@ -118,8 +118,13 @@ typedef struct sdpd_ctx sdpd_ctx;
 
 /* Create a context for params->n particles on the current HIP device.
  * hip_stream: a hipStream_t (NULL = the default stream) that every later
- * call of this context launches on.  *out receives the context.
- * Errors: SDPD_EINVAL (parameters), SDPD_ENOMEM, SDPD_EHIP.                */
+ * call of this context launches on.  *out receives the context.  Its memory
+ * is about 1.4 KB per particle (0.8 with SDPD_FD_NONE) and, for sweeps with
+ * one launch per group, 2 KB more; where the device has no room for the
+ * partner lists in it (512 B per particle) the context does without, and its
+ * forces and gradients take longer.
+ * Errors: SDPD_EINVAL (parameters), SDPD_ENOMEM (also for n >= 2^27),
+ * SDPD_EHIP.                                                               */
 int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out);
 
 /* Destroy a context (synchronises its stream, frees its workspace).       */
@@ -260,7 +265,10 @@ int sdpd_get_tuning(sdpd_ctx *ctx, sdpd_tuning *out);
  *                         the ranges of the previous group on its cells;
  *   SDPD_SWEEP_PER_GROUP  27 launches.
  * Captured batches always use one launch per group.  sdpd_set_sweep_mode
- * returns SDPD_EINVAL for another mode or a NULL context.  sdpd_sweep_mode
+ * returns SDPD_EINVAL for another mode or a NULL context, SDPD_ENOMEM (and
+ * changes nothing) where the launches per group of a large box need memory
+ * that the device does not have (2 KB per particle, taken when they are first
+ * asked for here, in a batch or by the autotuner).  sdpd_sweep_mode
  * returns the mode set (>= 0; SDPD_EINVAL for a NULL context) and writes
  * the layout the next sweep uses (SDPD_SWEEP_ONE or SDPD_SWEEP_PER_GROUP)
  * to *in_use when it is not NULL.                                          */

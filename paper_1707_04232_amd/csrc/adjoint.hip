@@ -409,6 +409,7 @@ int sdpd_adjoint_forward(sdpd_ctx *c, sdpd_state *s, int nsteps, int every)
     if (!a->base) {
         if (hipMalloc(&a->base, need) != hipSuccess) {
             a->base = nullptr;
+            (void)hipGetLastError();
             adjoint_free(a);
             return SDPD_ENOMEM;
         }

@@ -162,7 +162,10 @@ static int dalloc(T **p, size_t count)
 {
     *p = nullptr;
     if (count == 0) count = 1;
-    return hipMalloc((void **)p, sizeof(T) * count) == hipSuccess ? SDPD_OK : SDPD_ENOMEM;
+    if (hipMalloc((void **)p, sizeof(T) * count) == hipSuccess) return SDPD_OK;
+    *p = nullptr;
+    (void)hipGetLastError();   // (the next launch's check must not find it)
+    return SDPD_ENOMEM;
 }
 
 // The buffers of a context, requested one by one and made in one allocation
@@ -191,6 +194,7 @@ struct Arena {
         for (const auto &x : parts) total += padded(x.second);
         if (hipMalloc(base, total) != hipSuccess) {
             *base = nullptr;
+            (void)hipGetLastError();
             return SDPD_ENOMEM;
         }
         char *at = (char *)*base;
@@ -202,11 +206,20 @@ struct Arena {
     }
 };
 
-static void free_ctx(sdpd_ctx *c)
+static void free_buffers(sdpd_ctx *c)
 {
-    void *bufs[] = {c->arena, c->obs_out, c->flow_rec, c->sweep, c->sweep_order};
+    void *bufs[] = {c->arena, c->obs_out, c->rec_own, c->flow_rec, c->sweep, c->sweep_order};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
+    c->arena = c->rec_own = c->sweep = nullptr;
+    c->obs_out = c->flow_rec = nullptr;
+    c->flow_rec_bytes = 0;
+    c->sweep_order = nullptr;
+}
+
+static void free_ctx(sdpd_ctx *c)
+{
+    free_buffers(c);
     for (hipEvent_t e : c->timer.pool) (void)hipEventDestroy(e);
     adjoint_free(c->adj);
     delete c;
@@ -275,6 +288,71 @@ static int alloc_records(sdpd_ctx *c)
     return rc;
 }
 
+// The context's buffers, ready for its first call.  !roomy: without what only saves time, where the device has no
+// room for it (particles are then looked up among their candidates, records formed in
+// the sweep's launches).
+static int make_buffers(sdpd_ctx *c, bool roomy)
+{
+    const size_t n = (size_t)c->n, nce = (size_t)c->ncell;
+    const bool sweeps = c->prm.fd != SDPD_FD_NONE;
+    if (!roomy) c->list_cap = 0;
+    Arena mem;
+    mem.add(&c->cell_of, n);
+    mem.add(&c->count, nce);
+    mem.add(&c->cell_start, nce + 1);
+    mem.add(&c->block_sums, (size_t)scan_sums_size((int64_t)NMASK * c->ncell));
+    mem.add(&c->tmp_idx, n);
+    mem.add(&c->slot, n);
+    mem.add(&c->cell_sorted, n);
+    mem.add(&c->tq, 3 * n);
+    mem.add(&c->tp, 3 * n);
+    mem.add(&c->tf, 3 * n);
+    mem.add(&c->teps, n);
+    mem.add(&c->trho, n);
+    mem.add(&c->tid, n);
+    mem.add(&c->q4, 4 * n);
+    if (c->dp.mixed) mem.add(&c->q4f, 4 * n);
+    mem.add(&c->masks, (size_t)NMASK * n);
+    mem.add(&c->list, (size_t)c->list_cap * n);
+    mem.add(&c->list_count, n);
+    mem.add(&c->counters, (size_t)CNT_N);
+    mem.add(&c->err, 1);
+    mem.add(&c->obs_partial, (size_t)c->obs_blocks * 6);
+    mem.add(&c->dparams, 1);
+    mem.add(&c->task_count, (size_t)NMASK * nce);
+    mem.add(&c->task_np, (size_t)NMASK * nce);
+    mem.add(&c->pair_off, (size_t)NMASK * nce + 1);
+    mem.add(&c->part_off, (size_t)NMASK * nce + 1);
+    if (sweeps) mem.add(&c->pairs, (size_t)c->pair_cap);
+    mem.add(&c->epoch, (size_t)c->ncell + 1);
+    mem.add(&c->dstep, 1);
+    if (sweeps) mem.add(&c->part_list, (size_t)c->part_cap);
+    // pair records: for small boxes of a whole sweep, for large ones of a group unless
+    // they sweep by one launch
+    c->rec_buf = nullptr;
+    c->lvl_end = nullptr;
+    c->rec_bytes = 0;
+    const bool small =
+        c->n <= kWholeRecordsMaxParticles && c->ncell <= kWholeRecordsMaxCells;
+    const bool whole = small && roomy;
+    if (sweeps && (small || !fd_one_launch(c))) {
+        c->rec_bytes = (whole ? 2 : 1) * fd_group_record_bytes(c);
+        mem.add(&c->rec_buf, c->rec_bytes / sizeof(double));
+        if (whole) mem.add(&c->lvl_end, (size_t)NMASK * nce * 64);
+    }
+    int rc = mem.make(&c->arena);
+    rc = rc ? rc : alloc_records(c);
+    if (!rc)
+        rc = check_hip(hipMemcpyAsync(c->dparams, &c->dp, sizeof c->dp, hipMemcpyHostToDevice,
+                                      c->stream));
+    if (!rc) rc = launch_fill_u32(c, c->err, 0u, 1);
+    if (!rc) rc = launch_fill_u32(c, c->count, 0u, c->ncell);
+    if (!rc) rc = launch_fill_u64(c, c->counters, 0ull, CNT_N);
+    if (!rc) rc = check_hip(hipStreamSynchronize(c->stream));
+    if (!rc) rc = fd_prepare_sweep(c);
+    return rc;
+}
+
 }  // namespace sdpd
 
 using namespace sdpd;
@@ -305,6 +383,9 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     int nc[3];
     int rc = check_params(params, nc);
     if (rc) return rc;
+    // particle and neighbour cell share a word in the density pass and the lists (a box
+    // of that many particles takes 190 GB and more)
+    if (params->n >= (int64_t)1 << kEntryBits) return SDPD_ENOMEM;
     sdpd_ctx *c = new (std::nothrow) sdpd_ctx();
     if (!c) return SDPD_ENOMEM;
     c->prm = *params;
@@ -317,7 +398,6 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     }
     c->n = params->n;
     c->ncell = c->dp.ncell;
-    const size_t n = (size_t)c->n, nce = (size_t)c->ncell;
     c->obs_blocks = std::max(observe_blocks(c->n), 1);
     {
         int lds = 0;
@@ -349,53 +429,15 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
             (uint32_t)std::min(std::max(1.5 * v + 16.0, 128.0), (double)(NNB * MAX_CAP));
         c->list_cap = (c->list_cap + 31u) / 32u * 32u;   // (lists begin on their own cache lines)
     }
-    Arena mem;
-    mem.add(&c->cell_of, n);
-    mem.add(&c->count, nce);
-    mem.add(&c->cell_start, nce + 1);
-    mem.add(&c->block_sums, (size_t)scan_sums_size((int64_t)NMASK * c->ncell));
-    mem.add(&c->tmp_idx, n);
-    mem.add(&c->slot, n);
-    mem.add(&c->cell_sorted, n);
-    mem.add(&c->tq, 3 * n);
-    mem.add(&c->tp, 3 * n);
-    mem.add(&c->tf, 3 * n);
-    mem.add(&c->teps, n);
-    mem.add(&c->trho, n);
-    mem.add(&c->tid, n);
-    mem.add(&c->q4, 4 * n);
-    if (c->dp.mixed) mem.add(&c->q4f, 4 * n);
-    mem.add(&c->masks, (size_t)NMASK * n);
-    mem.add(&c->list, (size_t)c->list_cap * n);
-    mem.add(&c->list_count, n);
-    mem.add(&c->counters, (size_t)CNT_N);
-    mem.add(&c->err, 1);
-    mem.add(&c->obs_partial, (size_t)c->obs_blocks * 6);
-    mem.add(&c->dparams, 1);
-    mem.add(&c->task_count, (size_t)NMASK * nce);
-    mem.add(&c->task_np, (size_t)NMASK * nce);
-    mem.add(&c->pair_off, (size_t)NMASK * nce + 1);
-    mem.add(&c->part_off, (size_t)NMASK * nce + 1);
-    mem.add(&c->pairs, (size_t)c->pair_cap);
-    mem.add(&c->epoch, (size_t)c->ncell + 1);
-    mem.add(&c->dstep, 1);
-    mem.add(&c->part_list, (size_t)c->part_cap);
-    // pair records: of one group of the sweep (it touches every cell once: at
-    // most 32 pairs per particle), for small boxes of a whole sweep
-    const bool whole = c->n <= kWholeRecordsMaxParticles && c->ncell <= kWholeRecordsMaxCells;
-    c->rec_bytes = sizeof(double) * (whole ? 8 : 4) * (size_t)c->pair_cap;
-    mem.add(&c->rec_buf, c->rec_bytes / sizeof(double));
-    if (whole) mem.add(&c->lvl_end, (size_t)NMASK * nce * 64);
-    rc = mem.make(&c->arena);
-    rc = rc ? rc : alloc_records(c);
-    if (!rc)
-        rc = check_hip(hipMemcpyAsync(c->dparams, &c->dp, sizeof c->dp, hipMemcpyHostToDevice,
-                                      c->stream));
-    if (!rc) rc = launch_fill_u32(c, c->err, 0u, 1);
-    if (!rc) rc = launch_fill_u32(c, c->count, 0u, c->ncell);
-    if (!rc) rc = launch_fill_u64(c, c->counters, 0ull, CNT_N);
-    if (!rc) rc = check_hip(hipStreamSynchronize(c->stream));
-    if (!rc) rc = fd_prepare_sweep(c);
+    if ((rc = fd_choose_layout(c))) {
+        free_ctx(c);
+        return rc;
+    }
+    rc = make_buffers(c, true);
+    if (rc == SDPD_ENOMEM) {
+        free_buffers(c);
+        rc = make_buffers(c, false);
+    }
     if (rc) {
         free_ctx(c);
         return rc;
@@ -697,8 +739,11 @@ int sdpd_get_tuning(sdpd_ctx *c, sdpd_tuning *out)
 int sdpd_set_sweep_mode(sdpd_ctx *c, int mode)
 {
     if (!c || mode < SDPD_SWEEP_AUTO || mode > SDPD_SWEEP_PER_GROUP) return SDPD_EINVAL;
+    const int before = c->sweep_mode;
     c->sweep_mode = mode;
-    return SDPD_OK;
+    const int rc = fd_one_launch(c) ? SDPD_OK : fd_group_records(c);
+    if (rc) c->sweep_mode = before;
+    return rc;
 }
 
 int sdpd_sweep_mode(sdpd_ctx *c, int *in_use)
@@ -768,8 +813,9 @@ int autotune(sdpd_ctx *c, const sdpd_state *s, int trials, const sdpd_state *w, 
             if (fd_check_tuning(c, &u)) continue;
             c->tuning = u;
             double tm;
-            if ((rc = fd_prepare_sweep(c)) || (rc = time_sweeps(c, s, w, trials, e0, e1, tm)))
-                return rc;
+            rc = fd_prepare_sweep(c);
+            if (rc == SDPD_ENOMEM) continue;   // (no room for what it needs: not a candidate)
+            if (rc || (rc = time_sweeps(c, s, w, trials, e0, e1, tm))) return rc;
             if (tm < 0.99 * tbest) {
                 best = u;
                 tbest = tm;
@@ -781,6 +827,7 @@ int autotune(sdpd_ctx *c, const sdpd_state *s, int trials, const sdpd_state *w, 
     if (mode0 == SDPD_SWEEP_AUTO) {   // the layout too, unless the caller fixed it
         int win = SDPD_SWEEP_AUTO;
         for (int m = SDPD_SWEEP_ONE; m <= SDPD_SWEEP_PER_GROUP; ++m) {
+            if (m == SDPD_SWEEP_PER_GROUP && fd_group_records(c)) break;   // (no room for it)
             c->sweep_mode = m;
             double tm;
             if ((rc = time_sweeps(c, s, w, trials, e0, e1, tm))) return rc;

@@ -339,6 +339,9 @@ int sdpd_batch_create_layout(sdpd_ctx *const *ctxs, const sdpd_state *states, in
     // the boxes' pending work finishes before the capture starts
     for (hipStream_t s : b->streams)
         if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = SDPD_EHIP;
+    if (layout != SDPD_BATCH_FUSED_FLOW)   // (launches per group)
+        for (sdpd_ctx *c : b->ctx)
+            if (!rc) rc = fd_group_records(c);
     if (rc) {
         batch_free(b);
         return rc;

@@ -1012,7 +1012,7 @@ int fd_check_tuning(const sdpd_ctx *c, const sdpd_tuning *t)
 // the launches of a sweep: phase 0, then each phase gets the level 1 + the
 // largest level of the earlier phases whose parity sets intersect its own,
 // and the phases of one level run together (at most FD_MAXPH per launch)
-static std::vector<std::vector<int>> fd_groups()
+static std::vector<std::vector<int>> fd_make_groups()
 {
     std::vector<std::vector<int>> groups(1, std::vector<int>(1, 0));
     int lvl[105];
@@ -1037,6 +1037,11 @@ static std::vector<std::vector<int>> fd_groups()
         }
         if (!g.empty()) groups.push_back(g);
     }
+    return groups;
+}
+static const std::vector<std::vector<int>> &fd_groups()   // (the same for every box)
+{
+    static const std::vector<std::vector<int>> groups = fd_make_groups();
     return groups;
 }
 
@@ -1073,7 +1078,7 @@ static int64_t fd_launch_geometry(const sdpd_ctx *c, const sdpd_tuning &u, const
 // 13 forward offsets; checked).
 static int fd_sweep_ranges(const sdpd_ctx *c, const sdpd_tuning &u, FdSweep &h, size_t &lds)
 {
-    const std::vector<std::vector<int>> groups = fd_groups();
+    const std::vector<std::vector<int>> &groups = fd_groups();
     if ((int)groups.size() > FD_MAXGROUPS) return SDPD_EINVAL;
     memset(&h, 0, sizeof h);
     h.ngroups = (int)groups.size();
@@ -1272,10 +1277,70 @@ static std::vector<uint32_t> fd_range_order(const sdpd_ctx *c, const FdSweep &h)
     return order;
 }
 
+// Layout of the sweep that SDPD_SWEEP_AUTO takes for the ranges h.
+// One launch when the sweep holds at least three GPU-fulls of ranges (at
+// two waves per SIMD; boxes of some 450 cells); a smaller one mostly waits
+// on its chain of 27 groups, and one launch per group then holds no
+// workgroup slots while it waits.  Where the process asks for more queues than
+// the default four, boxes on many streams would hold them against each other
+// (256 boxes of 13^3 to 40^3 particles stepped eagerly on 32 streams and queues:
+// 312 ms per step with the line above, 88 with one launch per group; 48 boxes on
+// four streams and queues: 23 and 25): there only boxes that fill the GPU by
+// themselves, four GPU-fulls of ranges of full size (some 7,900 cells; one box
+// alone with eight queues, one launch / one per group, ms: 0.95 / 1.34 at 48^3
+// particles, 1.21 / 1.57 at 56^3, 3.04 / 4.41 at 2^20).
+static int fd_auto_layout(sdpd_ctx *c, const FdSweep &h)
+{
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) !=
+            hipSuccess || cus < 1) {
+        (void)hipGetLastError();
+        return SDPD_EHIP;
+    }
+    const int64_t full = 8 * (int64_t)cus;
+    c->fd_dataflow = (int64_t)h.nitems >= 3 * full;
+    if (!c->fd_dataflow || hw_queues() <= 4) return SDPD_OK;
+    FdSweep large = h;
+    if (c->tune_gen == 0) {   // (the defaults of smaller boxes are shorter ranges)
+        sdpd_tuning u = c->tuning;
+        for (int k = 0; k < 4; ++k) u.fd_tasks[k] = std::max(u.fd_tasks[k], kDefaultTasks[k]);
+        size_t lds = 0;
+        const int rc = fd_sweep_ranges(c, u, large, lds);
+        if (rc) return rc;
+    }
+    c->fd_dataflow = (int64_t)large.nitems >= 4 * full;
+    return SDPD_OK;
+}
+
+int fd_choose_layout(sdpd_ctx *c)
+{
+    FdSweep h;
+    size_t lds = 0;
+    const int rc = fd_sweep_ranges(c, c->tuning, h, lds);
+    return rc ? rc : fd_auto_layout(c, h);
+}
+
+// The records of one group of the sweep, for launches per group: 2 KB per particle, which
+// a box swept by one launch only takes when it is first asked for another layout.
+int fd_group_records(sdpd_ctx *c)
+{
+    if (c->rec_buf || c->prm.fd == SDPD_FD_NONE || c->n == 0) return SDPD_OK;
+    const size_t bytes = fd_group_record_bytes(c);
+    if (hipMalloc(&c->rec_own, bytes) != hipSuccess) {
+        c->rec_own = nullptr;
+        (void)hipGetLastError();
+        return SDPD_ENOMEM;
+    }
+    c->rec_buf = static_cast<double *>(c->rec_own);
+    c->rec_bytes = bytes;
+    return SDPD_OK;
+}
+
 // Record slices of the one-launch sweep's workgroups: in the context's record
-// buffer when they fit (large boxes), else in a buffer of their own.
+// buffer when they fit, else in a buffer of their own.
 static int fd_flow_records(sdpd_ctx *c, const FdSweep &h)
 {
+    if (c->prm.fd == SDPD_FD_NONE || c->n == 0) return SDPD_OK;
     c->sweep_rec_stride = fd_record_slice(h);
     const size_t need = sizeof(double2) * (size_t)c->sweep_rec_stride * (size_t)c->sweep_grid;
     const bool own = need > c->rec_bytes;
@@ -1310,6 +1375,7 @@ int fd_prepare_sweep(sdpd_ctx *c)
     c->sweep_host = table;
     if (!c->sweep && hipMalloc(&c->sweep, sizeof(FdSweep)) != hipSuccess) {
         c->sweep = nullptr;
+        (void)hipGetLastError();
         return SDPD_ENOMEM;
     }
     if ((rc = check_hip(hipMemcpy(c->sweep, &h, sizeof h, hipMemcpyHostToDevice)))) return rc;
@@ -1320,6 +1386,7 @@ int fd_prepare_sweep(sdpd_ctx *c)
     if (!c->sweep_order &&
         hipMalloc((void **)&c->sweep_order, sizeof(uint32_t) * order_cap) != hipSuccess) {
         c->sweep_order = nullptr;
+        (void)hipGetLastError();
         return SDPD_ENOMEM;
     }
     if (!order.empty() &&
@@ -1337,28 +1404,8 @@ int fd_prepare_sweep(sdpd_ctx *c)
     c->sweep_lds = lds;
     c->sweep_grid = (int)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(h.nitems, 1));
     if ((rc = fd_flow_records(c, h))) return rc;
-    // One launch when the sweep holds at least three GPU-fulls of ranges (at
-    // two waves per SIMD; boxes of some 450 cells); a smaller one mostly waits
-    // on its chain of 27 groups, and one launch per group then holds no
-    // workgroup slots while it waits.  Where the process asks for more queues than
-    // the default four, boxes on many streams would hold them against each other
-    // (256 boxes of 13^3 to 40^3 particles stepped eagerly on 32 streams and queues:
-    // 312 ms per step with the line above, 88 with one launch per group; 48 boxes on
-    // four streams and queues: 23 and 25): there only boxes that fill the GPU by
-    // themselves, four GPU-fulls of ranges of full size (some 7,900 cells; one box
-    // alone with eight queues, one launch / one per group, ms: 0.95 / 1.34 at 48^3
-    // particles, 1.21 / 1.57 at 56^3, 3.04 / 4.41 at 2^20).
-    const int64_t full = 8 * (int64_t)cus;
-    c->fd_dataflow = (int64_t)h.nitems >= 3 * full;
-    if (c->fd_dataflow && hw_queues() > 4) {
-        FdSweep large = h;
-        if (c->tune_gen == 0) {   // (the defaults of smaller boxes are shorter ranges)
-            sdpd_tuning u = c->tuning;
-            for (int k = 0; k < 4; ++k) u.fd_tasks[k] = std::max(u.fd_tasks[k], kDefaultTasks[k]);
-            if ((rc = fd_sweep_ranges(c, u, large, lds))) return rc;
-        }
-        c->fd_dataflow = (int64_t)large.nitems >= 4 * full;
-    }
+    if ((rc = fd_auto_layout(c, h))) return rc;
+    if (!fd_one_launch(c) && (rc = fd_group_records(c))) return rc;
     c->sweep_ok = 1;
     return SDPD_OK;
 }
@@ -1433,6 +1480,7 @@ int fd_launch_sweep(sdpd_ctx *c, const sdpd_state *s, double dt_fd)
         return SDPD_OK;
     }
     if (!fd_one_launch(c)) {
+        if (!c->rec_buf) return SDPD_ENOMEM;   // (made with the layout)
         // records of the whole sweep first, where the context holds them all
         // (a small box on its own; recorded launches share the GPU with other
         // boxes, where forming the records in the launches is faster)

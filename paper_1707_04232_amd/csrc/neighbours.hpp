@@ -245,9 +245,7 @@ inline float density_reach2(const DevParams &P)
     return (float)(P.h * P.h * 1.0001 + 8e-6 * P.h * edge + 1e-11 * edge * edge);
 }
 
-// an entry of the list: particle and offset index (n < 2^27: the pair records
-// alone would take more than 256 GB)
-constexpr int kEntryBits = 27;
+// an entry of the list: particle and offset index
 __device__ __forceinline__ uint32_t list_entry(uint32_t j, int k)
 {
     return j | (uint32_t)k << kEntryBits;

@@ -33,6 +33,8 @@ constexpr int NMASK = 14;
 constexpr int NNB = 27;
 constexpr int OWN_NB = 13;
 constexpr int MAX_CAP = 64;
+// bits of a particle in a word that it shares with an offset index k: n < 2^27
+constexpr int kEntryBits = 27;
 // F/D sweep workgroups: FD_WAVES waves share one batch of tasks (the pairs
 // of a level are split over their lanes); at most one task per lane
 constexpr int FD_WAVES = 1;
@@ -176,9 +178,11 @@ struct sdpd_ctx {
     // pair schedule (rebuilt before every sweep)
     uint32_t *task_count, *task_np, *pair_off, *part_off, *part_list;
     uint64_t *pairs;
-    double *rec_buf;             // pair records, 64 B each: of one group of the sweep (32 per
-                                 // particle), or of a whole one (64 per particle, with lvl_end)
+    double *rec_buf = nullptr;   // pair records, 64 B each: of one group of the sweep (32 per
+                                 // particle), or of a whole one (64 per particle, with lvl_end);
+                                 // NULL: large boxes that have only been swept by one launch
     size_t rec_bytes = 0;
+    void *rec_own = nullptr;     // rec_buf where the arena does not hold it
     uint16_t *lvl_end = nullptr; // small boxes: ends of a batch's levels (64), at its first task
     double *flow_rec = nullptr;  // record slices of the one-launch sweep that rec_buf cannot hold
     size_t flow_rec_bytes = 0;
@@ -249,6 +253,11 @@ void fd_class_caps(const sdpd_ctx *c, int k, int t, int &cp, int &ce);
 int fd_check_tuning(const sdpd_ctx *c, const sdpd_tuning *t);
 int fd_prepare_sweep(sdpd_ctx *c);   // after any change of the tuning
 bool fd_one_launch(const sdpd_ctx *c);   // the sweep runs as one launch
+int fd_choose_layout(sdpd_ctx *c);       // the one SDPD_SWEEP_AUTO takes, from the tuning
+// pair records of one group of the sweep (it touches every cell once: at most 32 pairs
+// per particle), and the buffer, made if the context has none yet
+inline size_t fd_group_record_bytes(const sdpd_ctx *c) { return (size_t)32 * (size_t)c->pair_cap; }
+int fd_group_records(sdpd_ctx *c);
 // The one-launch sweep of many boxes (fused batch): built from the boxes'
 // flow records of one position, launched (with its counter reset) on a stream.
 struct FlowSweep {
