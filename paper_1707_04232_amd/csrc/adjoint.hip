@@ -229,12 +229,13 @@ struct PiTerm {
     const double4 *__restrict__ v4;
     double4 v;
     __device__ __forceinline__ void at(int64_t i) { v = v4[i]; }
-    __device__ __forceinline__ void operator()(uint32_t j, const double4 &, const double4 &,
-                                               const double d[3], double r2, double out[1]) const
+    __device__ __forceinline__ void operator()(uint32_t j, bool own, const double4 &,
+                                               const double4 &, const double d[3], double r2,
+                                               double out[1]) const
     {
         const double4 u = v4[j];
         const double ru = d[0] * (v.x - u.x) + d[1] * (v.y - u.y) + d[2] * (v.z - u.z);
-        out[0] = ModelF64::force<LUCY>(P, r2) * ru;
+        out[0] = own ? 0.0 : ModelF64::force<LUCY>(P, r2) * ru;
     }
 };
 
@@ -246,8 +247,9 @@ struct QTerm {
     const double4 *__restrict__ v4;
     double4 v;
     __device__ __forceinline__ void at(int64_t i) { if (FORCE) v = v4[i]; }
-    __device__ __forceinline__ void operator()(uint32_t j, const double4 &qi, const double4 &qj,
-                                               const double d[3], double r2, double out[3]) const
+    __device__ __forceinline__ void operator()(uint32_t j, bool own, const double4 &qi,
+                                               const double4 &qj, const double d[3], double r2,
+                                               double out[3]) const
     {
         // r^2 + DBL_MIN: r^2 for every distinct pair; finite, and times zero, for r = 0
         const double y = fast_rsq(r2 + DBL_MIN), x = r2 * y * P.inv_h, t = 1.0 - x;
@@ -262,12 +264,12 @@ struct QTerm {
             F = P.h * (t * t) * y;
             dFr = -P.h * (1.0 - x * x) * (y * y) * y;
         }
-        const double sr = -P.m * (qi.w + qj.w) * F;
+        const double sr = own ? 0.0 : -P.m * (qi.w + qj.w) * F;
         for (int c = 0; c < 3; ++c) out[c] = sr * d[c];
         if (FORCE) {
             const double4 vj = v4[j];
             const double u[3] = {v.x - vj.x, v.y - vj.y, v.z - vj.z};
-            const double Pij = P.m * P.m * (v.w + vj.w);
+            const double Pij = own ? 0.0 : P.m * P.m * (v.w + vj.w);
             const double ru = (d[0] * u[0] + d[1] * u[1] + d[2] * u[2]) * dFr;
             for (int c = 0; c < 3; ++c) out[c] += Pij * (F * u[c] + ru * d[c]);
         }

@@ -670,9 +670,10 @@ struct PartnerArgs {
 
 
 // Value v of the sum over particle i's partners in lane s == v < NV of its lanes.
-// term(j, q_i, q_j, d, r2, out): the NV values of partner j at separation d = q_i - q_j;
-// term.at(i): called before with the particle of the lane.  The particle itself, which
-// its list holds and ends with, adds zero whatever its values (they may not be finite).
+// term(j, own, q_i, q_j, d, r2, out): the NV values of partner j at separation d = q_i -
+// q_j; term.at(i): called before with the particle of the lane.  own: j is the particle
+// itself, which its list holds and ends with: zero, whatever its values (they may not be
+// finite).
 template <class M, int NV, class Term>
 struct PartnerSums {
     typedef typename M::Real Real;
@@ -704,7 +705,7 @@ struct PartnerSums {
             Real out[NV];
             for (int v = 0; v < NV; ++v) out[v] = (Real)0;
             if (t0 + (uint32_t)lane < cw.total && M::near(P, r2) && j != (uint32_t)i)
-                term(j, qi, qj, d, r2, out);
+                term(j, false, qi, qj, d, r2, out);
             for (int v = 0; v < NV; ++v) {
                 if constexpr (sizeof(Real) == 8) {
                     sum[v] += out[v];
@@ -762,9 +763,8 @@ struct PartnerSums {
                                 d[x] += d[x] > P.h ? -P.box[x] : (d[x] < -P.h ? P.box[x] : 0.0);
                         const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
                         double out[NV];
-                        term(j[u], qi, qj[u], d, r2, out);
-                        for (int v = 0; v < NV; ++v)
-                            acc[v] += j[u] == (uint32_t)i ? 0.0 : out[v];
+                        term(j[u], j[u] == (uint32_t)i, qi, qj[u], d, r2, out);
+                        for (int v = 0; v < NV; ++v) acc[v] += out[v];
                     }
                 }
             };
@@ -805,8 +805,7 @@ struct PartnerSums {
                                         (qi.z - qj[u].z) + sh[u].z};
                     const float r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
                     float out[NV];
-                    term(j[u], qi, qj[u], d, r2, out);
-                    for (int v = 0; v < NV; ++v) out[v] = j[u] == (uint32_t)i ? 0.0f : out[v];
+                    term(j[u], j[u] == (uint32_t)i, qi, qj[u], d, r2, out);
                     for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x00>(out[v]);
                     for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x55>(out[v]);
                     for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0xaa>(out[v]);
@@ -853,11 +852,11 @@ struct ForceTerm {
     const DevParams &P;
     const Real ms;
     __device__ __forceinline__ void at(int64_t) {}
-    __device__ __forceinline__ void operator()(uint32_t, const typename M::Vec &qi,
+    __device__ __forceinline__ void operator()(uint32_t, bool own, const typename M::Vec &qi,
                                                const typename M::Vec &qj, const Real d[3],
                                                Real r2, Real out[3]) const
     {
-        const Real sc = ms * (qi.w + qj.w) * M::template force<LUCY>(P, r2);
+        const Real sc = own ? (Real)0 : ms * (qi.w + qj.w) * M::template force<LUCY>(P, r2);
         for (int x = 0; x < 3; ++x) out[x] = sc * d[x];
     }
 };
