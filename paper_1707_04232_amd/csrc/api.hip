@@ -208,12 +208,12 @@ struct Arena {
 
 static void free_buffers(sdpd_ctx *c)
 {
-    void *bufs[] = {c->arena, c->obs_out, c->rec_own, c->flow_rec, c->sweep, c->sweep_order};
+    void *bufs[] = {c->arena, c->obs_out, c->rec_own, c->flow_own, c->sweep, c->sweep_order};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
-    c->arena = c->rec_own = c->sweep = nullptr;
-    c->obs_out = c->flow_rec = nullptr;
-    c->flow_rec_bytes = 0;
+    c->arena = c->rec_own = c->flow_own = c->sweep = nullptr;
+    c->obs_out = nullptr;
+    c->flow_own_bytes = 0;
     c->sweep_order = nullptr;
 }
 
@@ -288,10 +288,11 @@ static int alloc_records(sdpd_ctx *c)
     return rc;
 }
 
-// The context's buffers, ready for its first call.  !roomy: without what only saves time, where the device has no
+// The context's buffers, ready for its first call (slices: bytes of the one-launch
+// sweep's record slices).  !roomy: without what only saves time, where the device has no
 // room for it (particles are then looked up among their candidates, records formed in
 // the sweep's launches).
-static int make_buffers(sdpd_ctx *c, bool roomy)
+static int make_buffers(sdpd_ctx *c, size_t slices, bool roomy)
 {
     const size_t n = (size_t)c->n, nce = (size_t)c->ncell;
     const bool sweeps = c->prm.fd != SDPD_FD_NONE;
@@ -327,11 +328,11 @@ static int make_buffers(sdpd_ctx *c, bool roomy)
     mem.add(&c->epoch, (size_t)c->ncell + 1);
     mem.add(&c->dstep, 1);
     if (sweeps) mem.add(&c->part_list, (size_t)c->part_cap);
-    // pair records: for small boxes of a whole sweep, for large ones of a group unless
-    // they sweep by one launch
-    c->rec_buf = nullptr;
+    // pair records: for small boxes of a whole sweep, for large ones of a group, or the
+    // workgroups' slices if they sweep by one launch
+    c->rec_buf = c->slices = nullptr;
     c->lvl_end = nullptr;
-    c->rec_bytes = 0;
+    c->rec_bytes = c->slice_bytes = 0;
     const bool small =
         c->n <= kWholeRecordsMaxParticles && c->ncell <= kWholeRecordsMaxCells;
     const bool whole = small && roomy;
@@ -339,6 +340,10 @@ static int make_buffers(sdpd_ctx *c, bool roomy)
         c->rec_bytes = (whole ? 2 : 1) * fd_group_record_bytes(c);
         mem.add(&c->rec_buf, c->rec_bytes / sizeof(double));
         if (whole) mem.add(&c->lvl_end, (size_t)NMASK * nce * 64);
+    }
+    if (sweeps && fd_one_launch(c) && slices > c->rec_bytes) {
+        c->slice_bytes = slices;
+        mem.add(&c->slices, slices / sizeof(double));
     }
     int rc = mem.make(&c->arena);
     rc = rc ? rc : alloc_records(c);
@@ -429,14 +434,15 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
             (uint32_t)std::min(std::max(1.5 * v + 16.0, 128.0), (double)(NNB * MAX_CAP));
         c->list_cap = (c->list_cap + 31u) / 32u * 32u;   // (lists begin on their own cache lines)
     }
-    if ((rc = fd_choose_layout(c))) {
+    size_t slices = 0;
+    if ((rc = fd_choose_layout(c, slices))) {
         free_ctx(c);
         return rc;
     }
-    rc = make_buffers(c, true);
+    rc = make_buffers(c, slices, true);
     if (rc == SDPD_ENOMEM) {
         free_buffers(c);
-        rc = make_buffers(c, false);
+        rc = make_buffers(c, slices, false);
     }
     if (rc) {
         free_ctx(c);

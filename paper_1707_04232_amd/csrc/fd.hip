@@ -1312,12 +1312,31 @@ static int fd_auto_layout(sdpd_ctx *c, const FdSweep &h)
     return SDPD_OK;
 }
 
-int fd_choose_layout(sdpd_ctx *c)
+// workgroups of the one-launch sweep over the ranges h: as many as run at once
+static int fd_sweep_grid(const sdpd_ctx *c, const FdSweep &h, size_t lds, int &grid)
+{
+    int per_cu = 0, cus = 0;
+    const void *kern = (const void *)fd_sweep_kernel(c);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, FD_THREADS, lds) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) !=
+            hipSuccess || per_cu < 1 || cus < 1) {
+        (void)hipGetLastError();
+        return SDPD_EHIP;
+    }
+    grid = (int)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(h.nitems, 1));
+    return SDPD_OK;
+}
+
+int fd_choose_layout(sdpd_ctx *c, size_t &slices)
 {
     FdSweep h;
     size_t lds = 0;
-    const int rc = fd_sweep_ranges(c, c->tuning, h, lds);
-    return rc ? rc : fd_auto_layout(c, h);
+    int grid = 0;
+    int rc = fd_sweep_ranges(c, c->tuning, h, lds);
+    if (!rc) rc = fd_auto_layout(c, h);
+    if (!rc) rc = fd_sweep_grid(c, h, lds, grid);
+    slices = sizeof(double2) * (size_t)fd_record_slice(h) * (size_t)grid;
+    return rc;
 }
 
 // The records of one group of the sweep, for launches per group: 2 KB per particle, which
@@ -1336,27 +1355,29 @@ int fd_group_records(sdpd_ctx *c)
     return SDPD_OK;
 }
 
-// Record slices of the one-launch sweep's workgroups: in the context's record
-// buffer when they fit, else in a buffer of their own.
+// Record slices of the one-launch sweep's workgroups: in the context's workspace (its
+// slices, or its records of a group) when they fit, else in a buffer of their own.
 static int fd_flow_records(sdpd_ctx *c, const FdSweep &h)
 {
     if (c->prm.fd == SDPD_FD_NONE || c->n == 0) return SDPD_OK;
     c->sweep_rec_stride = fd_record_slice(h);
     const size_t need = sizeof(double2) * (size_t)c->sweep_rec_stride * (size_t)c->sweep_grid;
-    const bool own = need > c->rec_bytes;
-    if (c->flow_rec && (!own || c->flow_rec_bytes < need)) {
-        (void)hipFree(c->flow_rec);
-        c->flow_rec = nullptr;
-        c->flow_rec_bytes = 0;
+    double *const held = need <= c->slice_bytes ? c->slices : need <= c->rec_bytes ? c->rec_buf
+                                                                                   : nullptr;
+    if (c->flow_own && (held || c->flow_own_bytes < need)) {
+        (void)hipFree(c->flow_own);
+        c->flow_own = nullptr;
+        c->flow_own_bytes = 0;
     }
-    if (own && !c->flow_rec) {
-        if (hipMalloc((void **)&c->flow_rec, need) != hipSuccess) {
-            c->flow_rec = nullptr;
+    if (!held && !c->flow_own) {
+        if (hipMalloc(&c->flow_own, need) != hipSuccess) {
+            c->flow_own = nullptr;
             (void)hipGetLastError();
             return SDPD_ENOMEM;
         }
-        c->flow_rec_bytes = need;
+        c->flow_own_bytes = need;
     }
+    c->flow_rec = held ? held : static_cast<double *>(c->flow_own);
     return SDPD_OK;
 }
 
@@ -1393,16 +1414,8 @@ int fd_prepare_sweep(sdpd_ctx *c)
         (rc = check_hip(hipMemcpy(c->sweep_order, order.data(), sizeof(uint32_t) * order.size(),
                                   hipMemcpyHostToDevice))))
         return rc;
-    int per_cu = 0, cus = 0;
-    const void *kern = (const void *)fd_sweep_kernel(c);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, FD_THREADS, lds) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) !=
-            hipSuccess || per_cu < 1 || cus < 1) {
-        (void)hipGetLastError();
-        return SDPD_EHIP;
-    }
+    if ((rc = fd_sweep_grid(c, h, lds, c->sweep_grid))) return rc;
     c->sweep_lds = lds;
-    c->sweep_grid = (int)std::min<int64_t>((int64_t)per_cu * cus, std::max<int64_t>(h.nitems, 1));
     if ((rc = fd_flow_records(c, h))) return rc;
     if ((rc = fd_auto_layout(c, h))) return rc;
     if (!fd_one_launch(c) && (rc = fd_group_records(c))) return rc;
@@ -1499,7 +1512,7 @@ int fd_launch_sweep(sdpd_ctx *c, const sdpd_state *s, double dt_fd)
     if ((rc = launch_fill_u32(c, c->epoch, 0u, c->ncell + 1))) return rc;
     timer_begin(c, TK_FD);
     FdArgs A = fd_args(c, s, dt_fd);
-    A.rec = reinterpret_cast<double2 *>(c->flow_rec ? c->flow_rec : c->rec_buf);
+    A.rec = reinterpret_cast<double2 *>(c->flow_rec);
     A.rec_stride = c->sweep_rec_stride;
     hipLaunchKernelGGL(fd_sweep_kernel(c), dim3((unsigned)c->sweep_grid), dim3(FD_THREADS), c->sweep_lds, c->stream,
                        FdSweepArgs{c->dparams, (const FdSweep *)c->sweep, c->sweep_order, A,

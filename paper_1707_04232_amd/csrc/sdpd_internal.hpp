@@ -184,8 +184,11 @@ struct sdpd_ctx {
     size_t rec_bytes = 0;
     void *rec_own = nullptr;     // rec_buf where the arena does not hold it
     uint16_t *lvl_end = nullptr; // small boxes: ends of a batch's levels (64), at its first task
-    double *flow_rec = nullptr;  // record slices of the one-launch sweep that rec_buf cannot hold
-    size_t flow_rec_bytes = 0;
+    double *flow_rec = nullptr;  // record slices of the one-launch sweep: slices, rec_buf or
+    double *slices = nullptr;    // flow_own
+    size_t slice_bytes = 0;
+    void *flow_own = nullptr;    // ... where the workspace cannot hold them
+    size_t flow_own_bytes = 0;
     int64_t sweep_rec_stride = 0;   // 16-byte units of one slice
     void *sweep = nullptr;       // device table of the sweep kernel (fd.hip)
     uint32_t *sweep_order = nullptr;   // hand-out order of the ranges inside each group
@@ -253,7 +256,8 @@ void fd_class_caps(const sdpd_ctx *c, int k, int t, int &cp, int &ce);
 int fd_check_tuning(const sdpd_ctx *c, const sdpd_tuning *t);
 int fd_prepare_sweep(sdpd_ctx *c);   // after any change of the tuning
 bool fd_one_launch(const sdpd_ctx *c);   // the sweep runs as one launch
-int fd_choose_layout(sdpd_ctx *c);       // the one SDPD_SWEEP_AUTO takes, from the tuning
+// the layout SDPD_SWEEP_AUTO takes, from the tuning, and the bytes of the record slices
+int fd_choose_layout(sdpd_ctx *c, size_t &slices);
 // pair records of one group of the sweep (it touches every cell once: at most 32 pairs
 // per particle), and the buffer, made if the context has none yet
 inline size_t fd_group_record_bytes(const sdpd_ctx *c) { return (size_t)32 * (size_t)c->pair_cap; }
