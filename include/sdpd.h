@@ -119,10 +119,10 @@ typedef struct sdpd_ctx sdpd_ctx;
 /* Create a context for params->n particles on the current HIP device.
  * hip_stream: a hipStream_t (NULL = the default stream) that every later
  * call of this context launches on.  *out receives the context.  Its memory
- * is about 1.4 KB per particle (0.8 with SDPD_FD_NONE) and, for sweeps with
+ * is about 2 KB per particle (1.5 with SDPD_FD_NONE) and, for sweeps with
  * one launch per group, 2 KB more; where the device has no room for the
- * partner lists in it (512 B per particle) the context does without, and its
- * forces and gradients take longer.
+ * partner lists in it (512 B per particle and more) the context does without,
+ * and its forces and gradients take longer.
  * Errors: SDPD_EINVAL (parameters), SDPD_ENOMEM (also for n >= 2^27),
  * SDPD_EHIP.                                                               */
 int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out);

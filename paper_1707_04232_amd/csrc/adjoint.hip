@@ -264,15 +264,16 @@ struct QTerm {
             F = P.h * (t * t) * y;
             dFr = -P.h * (1.0 - x * x) * (y * y) * y;
         }
-        const double sr = own ? 0.0 : -P.m * (qi.w + qj.w) * F;
+        const double sr = -P.m * (qi.w + qj.w) * F;
         for (int c = 0; c < 3; ++c) out[c] = sr * d[c];
         if (FORCE) {
             const double4 vj = v4[j];
             const double u[3] = {v.x - vj.x, v.y - vj.y, v.z - vj.z};
-            const double Pij = own ? 0.0 : P.m * P.m * (v.w + vj.w);
+            const double Pij = P.m * P.m * (v.w + vj.w);
             const double ru = (d[0] * u[0] + d[1] * u[1] + d[2] * u[2]) * dFr;
             for (int c = 0; c < 3; ++c) out[c] += Pij * (F * u[c] + ru * d[c]);
         }
+        for (int c = 0; c < 3; ++c) out[c] = own ? 0.0 : out[c];
     }
 };
 

@@ -296,7 +296,7 @@ static int make_buffers(sdpd_ctx *c, size_t slices, bool roomy)
 {
     const size_t n = (size_t)c->n, nce = (size_t)c->ncell;
     const bool sweeps = c->prm.fd != SDPD_FD_NONE;
-    if (!roomy) c->list_cap = 0;
+    if (!roomy) c->list_len = c->list_cap = 0;
     Arena mem;
     mem.add(&c->cell_of, n);
     mem.add(&c->count, nce);
@@ -424,15 +424,25 @@ int sdpd_create(const sdpd_params *params, void *hip_stream, sdpd_ctx **out)
     // partner lists: half as many again as the mean at the box's density and 16
     // more (a uniform random box of 10^5 particles with 65 partners on average has
     // none with more than 105), and 128 at least, twice what a particle has in a
-    // liquid at the usual h (most of a box may be empty); particles with more are
-    // looked up without a list
+    // liquid at the usual h; with the second part of the list a tenth and 16 more than a
+    // particle has where the cells are full (cell_cap): most of a box may be empty.  A box
+    // that is swept holds 128 partners on average at most (pair_cap): half as many again.
+    // Particles with more, in clusters smaller than a cell, are looked up without a list.
     {
         const double h = c->prm.h;
-        double v = 4.0 / 3.0 * 3.14159265358979323846 * h * h * h * (double)c->n;
-        for (int k = 0; k < 3; ++k) v /= c->prm.box[k];
-        c->list_cap =
-            (uint32_t)std::min(std::max(1.5 * v + 16.0, 128.0), (double)(NNB * MAX_CAP));
-        c->list_cap = (c->list_cap + 31u) / 32u * 32u;   // (lists begin on their own cache lines)
+        const double sphere = 4.0 / 3.0 * 3.14159265358979323846 * h * h * h;
+        double mean = sphere * (double)c->n, full = sphere * c->prm.cell_cap;
+        for (int k = 0; k < 3; ++k) {
+            mean /= c->prm.box[k];
+            full *= c->dp.inv_cell[k];
+        }
+        // (multiples of 32: lists begin on their own cache lines)
+        auto entries = [](double v) {
+            return ((uint32_t)std::min(v, (double)(NNB * MAX_CAP)) + 31u) / 32u * 32u;
+        };
+        c->list_len = entries(std::max(1.5 * mean + 16.0, 128.0));
+        const double swept = c->prm.fd == SDPD_FD_NONE ? NNB * MAX_CAP : 192.0;
+        c->list_cap = std::max(c->list_len, entries(std::min(1.1 * full + 16.0, swept)));
     }
     size_t slices = 0;
     if ((rc = fd_choose_layout(c, slices))) {

@@ -41,7 +41,8 @@ int run_density(sdpd_ctx *c, const sdpd_state *s, int update_eps, bool pack_rho)
     }
     timer_begin(c, TK_DENSITY);
     const DensityArgs args{c->dp, c->q4, c->cell_sorted, c->cell_start, s->rho, s->eps,
-                           update_eps, c->masks, c->list, c->list_count, c->list_cap, c->err,
+                           update_eps, c->masks, c->list, c->list_count, c->list_len,
+                           c->list_cap, c->err,
                            pack_rho ? c->q4 : nullptr, density_reach2(c->dp)};
     const int rc = c->dp.kernel == SDPD_KERNEL_LUCY
                        ? launch_density<ModelF64, true>(c, args, k_density_lucy_multi,

@@ -227,8 +227,12 @@ struct DensityArgs {
     int update_eps;
     uint64_t *masks;         // masks[(k - 13) n + i]: slot bits of the partners in cell k,
                              // k = 13 (the own cell, without i itself) .. 26
-    uint32_t *list, *count;  // partners of particle i (itself included) in candidate order:
-    uint32_t list_cap;       // list[list_cap i + r], r < count[i], complete if count <= list_cap
+    // partners of particle i (itself included) in candidate order: entry r < list_len at
+    // list[list_len i + r], the others behind these parts of all particles, at
+    // list[list_len n + (list_cap - list_len) i + r - list_len]; r < count[i]; complete
+    // if count <= list_cap
+    uint32_t *list, *count;
+    uint32_t list_len, list_cap;
     uint32_t *err;
     double *rho_w;           // FP64: also into the w slot of the record, or NULL
     float reach2;            // h^2 and the rounding of the FP32 test for it (density_reach2)
@@ -253,6 +257,16 @@ __device__ __forceinline__ uint32_t list_entry(uint32_t j, int k)
 __device__ __forceinline__ uint32_t entry_particle(uint32_t e)
 {
     return e & ((1u << kEntryBits) - 1u);
+}
+
+// entry r < list_cap of particle i's list
+__device__ __forceinline__ uint32_t *list_at(const DensityArgs &a, uint32_t i, uint32_t r)
+{
+    const int64_t at = r < a.list_len ? (int64_t)i * a.list_len + r
+                                      : a.P.n * a.list_len +
+                                            (int64_t)i * (a.list_cap - a.list_len) +
+                                            (r - a.list_len);
+    return a.list + at;
 }
 
 __device__ __forceinline__ void density_store(const DensityArgs &a, int64_t i, double rho)
@@ -391,7 +405,7 @@ struct DensityWave {
                 if (fill + 64u * K + 3u > (uint32_t)kTerms) flush();
                 const uint32_t first = fill, had = lane_of(partners, i);
                 uint32_t total = 0u;
-                uint32_t *const list = a.list + (int64_t)(cw.own + (uint32_t)i) * a.list_cap;
+                uint32_t *const list = a.list + (int64_t)(cw.own + (uint32_t)i) * a.list_len;
                 Real *const unused = terms + kTerms + lane;
                 uint32_t *const part = lds.part[wave], *const unused_part = part + 64 * K + lane;
 #pragma unroll
@@ -417,8 +431,11 @@ struct DensityWave {
                 }
                 // the window's part of the list
                 wave_sync();
-                if (had + total <= a.list_cap)
+                if (had + total <= a.list_len)
                     for (uint32_t r = lane; r < total; r += 64u) list[had + r] = part[r];
+                else if (had + total <= a.list_cap)
+                    for (uint32_t r = lane; r < total; r += 64u)
+                        *list_at(a, cw.own + (uint32_t)i, had + r) = part[r];
                 wave_sync();
                 // up to a multiple of four with entries without a term
                 if (lane < 3) terms[fill + lane] = (Real)-1;
@@ -614,7 +631,6 @@ __device__ __forceinline__ void density_sparse(const DensityArgs &a, uint32_t bl
     const CellXyz cc(P, a.cell_sorted[i]);
     const NbSteps steps(P, cc.x, cc.y, cc.z);
     const typename M::Vec qi = load_vec<M>(q4, i);
-    uint32_t *const list = a.list + i * (int64_t)a.list_cap;
     Real acc = (Real)0;
     uint32_t partners = 0u;
     for (int k = 0; k < NNB; ++k) {
@@ -636,7 +652,8 @@ __device__ __forceinline__ void density_sparse(const DensityArgs &a, uint32_t bl
             const Real r2 = dx * dx + dy * dy + dz * dz;
             if (!M::near(P, r2)) continue;
             acc = acc + M::template density<LUCY>(P, r2);
-            if (partners < a.list_cap) list[partners] = list_entry(s + t, k);
+            if (partners < a.list_cap)
+                *list_at(a, (uint32_t)i, partners) = list_entry(s + t, k);
             ++partners;
             mask |= 1ull << t;
         }
@@ -664,10 +681,9 @@ struct PartnerArgs {
     DevParams P;
     const void *q4;          // packed records of the model
     const uint32_t *cell_sorted, *cell_start;
-    const uint32_t *list, *count;
-    uint32_t list_cap;
+    const uint32_t *list, *count;   // (see DensityArgs)
+    uint32_t list_len, list_cap;
 };
-
 
 // Value v of the sum over particle i's partners in lane s == v < NV of its lanes.
 // term(j, own, q_i, q_j, d, r2, out): the NV values of partner j at separation d = q_i -
@@ -704,13 +720,16 @@ struct PartnerSums {
             const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
             Real out[NV];
             for (int v = 0; v < NV; ++v) out[v] = (Real)0;
-            if (t0 + (uint32_t)lane < cw.total && M::near(P, r2) && j != (uint32_t)i)
-                term(j, false, qi, qj, d, r2, out);
+            const bool hit =
+                t0 + (uint32_t)lane < cw.total && M::near(P, r2) && j != (uint32_t)i;
+            if (hit) term(j, false, qi, qj, d, r2, out);
+            const uint64_t hits = __ballot(hit);
             for (int v = 0; v < NV; ++v) {
                 if constexpr (sizeof(Real) == 8) {
                     sum[v] += out[v];
-                } else {   // in candidate order
-                    for (int l = 0; l < 64; ++l) sum[v] = sum[v] + lane_of(out[v], l);
+                } else {   // in candidate order (the terms of the others are zero)
+                    for (uint64_t h = hits; h; h &= h - 1ull)
+                        sum[v] = sum[v] + lane_of(out[v], __builtin_ctzll(h));
                 }
             }
         }
@@ -726,8 +745,18 @@ struct PartnerSums {
         const typename M::Vec qi = load_vec<M>(q4, i);
         const uint32_t all = live ? a.count[i] : 0u;
         const bool over = all > a.list_cap;
-        const uint32_t cnt = over ? 0u : all;
-        const uint32_t *__restrict__ list = a.list + i * (int64_t)a.list_cap;
+        // the list's two parts one after the other: the second is only there for
+        // particles of dense regions, and lists of its length as well in the first
+        // would lie further apart (a gradient of 262k particles took 1.4 % longer)
+        const uint32_t *__restrict__ list = a.list + i * (int64_t)a.list_len;
+        uint32_t left = over ? 0u : all, cnt = min(left, a.list_len);
+        auto next_part = [&] {
+            left -= cnt;
+            if (!__any(left != 0u)) return false;
+            list = a.list + P.n * a.list_len + i * (int64_t)(a.list_cap - a.list_len);
+            cnt = left;
+            return true;
+        };
         const uint32_t self = list_entry((uint32_t)i, OWN_NB);
         term.at(i);
         Real mine = (Real)0;
@@ -744,29 +773,31 @@ struct PartnerSums {
             for (int v = 0; v < NV; ++v) acc[v] = 0.0;
             auto loop = [&](auto shifted) {
                 constexpr bool SHIFT = decltype(shifted)::value;
-                uint32_t e[2] = {entry(s), entry(s + kLanes)};
-                for (uint32_t r = s; __any(r < cnt); r += 2 * kLanes) {
-                    typename M::Vec qj[2];
-                    uint32_t j[2];
+                do {
+                    uint32_t e[2] = {entry(s), entry(s + kLanes)};
+                    for (uint32_t r = s; __any(r < cnt); r += 2 * kLanes) {
+                        typename M::Vec qj[2];
+                        uint32_t j[2];
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        j[u] = entry_particle(e[u]);
-                        qj[u] = load_vec<M>(q4, j[u]);
-                    }
-                    e[0] = entry(r + 2 * kLanes);
-                    e[1] = entry(r + 3 * kLanes);
+                        for (int u = 0; u < 2; ++u) {
+                            j[u] = entry_particle(e[u]);
+                            qj[u] = load_vec<M>(q4, j[u]);
+                        }
+                        e[0] = entry(r + 2 * kLanes);
+                        e[1] = entry(r + 3 * kLanes);
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        double d[3] = {qi.x - qj[u].x, qi.y - qj[u].y, qi.z - qj[u].z};
-                        if (SHIFT)
-                            for (int x = 0; x < 3; ++x)
-                                d[x] += d[x] > P.h ? -P.box[x] : (d[x] < -P.h ? P.box[x] : 0.0);
-                        const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-                        double out[NV];
-                        term(j[u], j[u] == (uint32_t)i, qi, qj[u], d, r2, out);
-                        for (int v = 0; v < NV; ++v) acc[v] += out[v];
+                        for (int u = 0; u < 2; ++u) {
+                            double d[3] = {qi.x - qj[u].x, qi.y - qj[u].y, qi.z - qj[u].z};
+                            if (SHIFT)
+                                for (int x = 0; x < 3; ++x)
+                                    d[x] += d[x] > P.h ? -P.box[x] : (d[x] < -P.h ? P.box[x] : 0.0);
+                            const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                            double out[NV];
+                            term(j[u], j[u] == (uint32_t)i, qi, qj[u], d, r2, out);
+                            for (int v = 0; v < NV; ++v) acc[v] += out[v];
+                        }
                     }
-                }
+                } while (next_part());
             };
             if (__any(edge)) loop(std::true_type());
             else loop(std::false_type());
@@ -786,32 +817,34 @@ struct PartnerSums {
             wave_sync();
             float acc[NV];
             for (int v = 0; v < NV; ++v) acc[v] = 0.0f;
-            uint32_t e[2] = {entry(s), entry(s + kLanes)};
-            for (uint32_t r = s; __any(r < cnt); r += 2 * kLanes) {
-                typename M::Vec qj[2];
-                float4 sh[2];
-                uint32_t j[2];
+            do {
+                uint32_t e[2] = {entry(s), entry(s + kLanes)};
+                for (uint32_t r = s; __any(r < cnt); r += 2 * kLanes) {
+                    typename M::Vec qj[2];
+                    float4 sh[2];
+                    uint32_t j[2];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    j[u] = entry_particle(e[u]);
-                    qj[u] = load_vec<M>(q4, j[u]);
-                    sh[u] = shift[e[u] >> kEntryBits];
-                }
-                e[0] = entry(r + 2 * kLanes);
-                e[1] = entry(r + 3 * kLanes);
+                    for (int u = 0; u < 2; ++u) {
+                        j[u] = entry_particle(e[u]);
+                        qj[u] = load_vec<M>(q4, j[u]);
+                        sh[u] = shift[e[u] >> kEntryBits];
+                    }
+                    e[0] = entry(r + 2 * kLanes);
+                    e[1] = entry(r + 3 * kLanes);
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const float d[3] = {(qi.x - qj[u].x) + sh[u].x, (qi.y - qj[u].y) + sh[u].y,
-                                        (qi.z - qj[u].z) + sh[u].z};
-                    const float r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-                    float out[NV];
-                    term(j[u], j[u] == (uint32_t)i, qi, qj[u], d, r2, out);
-                    for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x00>(out[v]);
-                    for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x55>(out[v]);
-                    for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0xaa>(out[v]);
-                    for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0xff>(out[v]);
+                    for (int u = 0; u < 2; ++u) {
+                        const float d[3] = {(qi.x - qj[u].x) + sh[u].x, (qi.y - qj[u].y) + sh[u].y,
+                                            (qi.z - qj[u].z) + sh[u].z};
+                        const float r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                        float out[NV];
+                        term(j[u], j[u] == (uint32_t)i, qi, qj[u], d, r2, out);
+                        for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x00>(out[v]);
+                        for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0x55>(out[v]);
+                        for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0xaa>(out[v]);
+                        for (int v = 0; v < NV; ++v) acc[v] = acc[v] + moved<0xff>(out[v]);
+                    }
                 }
-            }
+            } while (next_part());
             for (int v = 0; v < NV; ++v)
                 if (s == (uint32_t)v) mine = acc[v];
         }
@@ -937,7 +970,7 @@ int launch_forces(sdpd_ctx *c, const ForcesArgs &args, MultiKernel multi)
 inline PartnerArgs partner_args(const sdpd_ctx *c, const void *q4)
 {
     return PartnerArgs{c->dp, q4, c->cell_sorted, c->cell_start, c->list, c->list_count,
-                       c->list_cap};
+                       c->list_len, c->list_cap};
 }
 
 }  // namespace sdpd

@@ -160,8 +160,10 @@ struct sdpd_ctx {
     double *q4;                  // (x, y, z, P/rho^2) per particle in cell order, 32 B
     float *q4f;                  // mixed precision: (x, y, z) relative to the cell, P/rho^2
     uint64_t *masks;             // NMASK * n
-    uint32_t *list, *list_count; // partner lists of the density pass, list_cap per particle
-    uint32_t list_cap;
+    // partner lists of the density pass, list_cap per particle: the first list_len entries
+    // of all, then the others
+    uint32_t *list, *list_count;
+    uint32_t list_len, list_cap;
     unsigned long long *counters;
     uint32_t *err;
     double *obs_partial;         // per-block observable partials

@@ -23,9 +23,10 @@ def warm():
 
 def test_memory_per_particle():
     """2^20 particles: with the sweep in one launch 512 B of pair entries, 108 of list
-    positions, 112 of masks, 512 of partner lists and about 150 of state copies and
+    positions, 112 of masks, 768 of partner lists and about 150 of state copies and
     indices per particle, and the sweep's record slices (3072 workgroups of up to 20 KB
-    of entries, 16 times as many bytes): below 2.2 KB; without a sweep below 1.2 KB.
+    of entries, 16 times as many bytes): below 2.2 KB; without a sweep, with lists for
+    full cells (1152 B), below 1.5 KB.
     Launches per group take 2 KB more when they are asked for."""
     from paper_1707_04232_amd import sdpd
     print("[case] memory per particle", flush=True)
@@ -38,7 +39,7 @@ def test_memory_per_particle():
     assert 0 < more <= 2100 * n, more / n
     ctx.close()
     ctx, used = used_by(lambda: sdpd.Context(sdpd.SdpdParams(n=n, box=box, fd=sdpd.FD_NONE)))
-    assert used <= 1200 * n, used / n
+    assert used <= 1500 * n, used / n
     ctx.close()
 
 
