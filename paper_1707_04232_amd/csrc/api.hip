@@ -318,6 +318,7 @@ static int make_buffers(sdpd_ctx *c, size_t slices, bool roomy)
     mem.add(&c->list_count, n);
     mem.add(&c->counters, (size_t)CNT_N);
     mem.add(&c->err, 1);
+    mem.add(&c->dense, 1);
     mem.add(&c->obs_partial, (size_t)c->obs_blocks * 6);
     mem.add(&c->dparams, 1);
     mem.add(&c->task_count, (size_t)NMASK * nce);

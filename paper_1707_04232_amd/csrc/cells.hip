@@ -66,6 +66,7 @@ struct KickDriftArgs {
     const double *f;
     int kick_drift;
     uint32_t *cell_of, *slot, *count, *err;   // slot: place among the cell's, any order
+    uint32_t *dense;                          // set to zero
     StepStart start;
 };
 __device__ __forceinline__ void kick_drift_assign_body(const KickDriftArgs &a, uint32_t blk)
@@ -78,6 +79,7 @@ __device__ __forceinline__ void kick_drift_assign_body(const KickDriftArgs &a, u
     int64_t i = (int64_t)blk * blockDim.x + threadIdx.x;
     if (a.start.counters && i < CNT_N) a.start.counters[i] = 0ull;
     if (a.start.dstep && i == 0) *a.start.dstep = a.start.step;
+    if (i == 0) *a.dense = 0u;
     if (i >= P.n) return;
     const int64_t n = P.n;
     int cc[3];
@@ -139,6 +141,7 @@ struct ScanArgs {
     int cap, clear;          // clear: in is zero afterwards
     uint32_t *err;
     int scanned;             // sums holds the prefix sums of the blocks, then their total
+    uint32_t *dense;         // set where a value is kDenseRegion or more (NULL: not)
 };
 __device__ __forceinline__ void scan_local_body(const ScanArgs &a, uint32_t blk)
 {
@@ -148,15 +151,17 @@ __device__ __forceinline__ void scan_local_body(const ScanArgs &a, uint32_t blk)
     __shared__ uint32_t s[SCAN_THREADS];
     int64_t base = b * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
     uint32_t v[SCAN_PER_THREAD], sum = 0;
-    bool over = false;
+    bool over = false, dense = false;
 #pragma unroll
     for (int k = 0; k < SCAN_PER_THREAD; ++k) {
         v[k] = base + k < a.count ? in[base + k] : 0u;
         if (a.clear && base + k < a.count) in[base + k] = 0u;
         over = over || (a.cap >= 0 && v[k] > (uint32_t)a.cap);
+        dense = dense || v[k] >= kDenseRegion;
         sum += v[k];
     }
     if (over) atomicOr(a.err, ERR_CELLCAP);
+    if (a.dense && dense) *a.dense = 1u;   // (all that write it write the same)
     uint32_t total;
     uint32_t ex = block_exclusive_scan(sum, s, &total);
 #pragma unroll
@@ -224,7 +229,8 @@ int64_t scan_sums_size(int64_t count)
 
 // out[0..count] = exclusive prefix sums of in[0..count), out[count] = total, for one
 // array or two (in2 not NULL).  in may be out (then in2 is out2).
-// A value above cap sets ERR_CELLCAP (cap < 0: no check).
+// cap >= 0 (cells): a value above it sets ERR_CELLCAP, and the context learns whether one
+// is kDenseRegion or more.
 int run_scan(sdpd_ctx *c, uint32_t *in, uint32_t *out, uint32_t *in2, uint32_t *out2,
              int64_t count, uint32_t *block_sums, int cap, bool clear)
 {
@@ -235,7 +241,7 @@ int run_scan(sdpd_ctx *c, uint32_t *in, uint32_t *out, uint32_t *in2, uint32_t *
     }
     uint32_t *const sums2 = block_sums + (nb + 1);
     ScanArgs args{{in, in2}, {out, out2}, {block_sums, sums2}, count, nb, cap,
-                  clear ? 1 : 0, c->err, 0};
+                  clear ? 1 : 0, c->err, 0, cap >= 0 ? c->dense : nullptr};
     const unsigned grid = (unsigned)(in2 ? 2 * nb : nb);
     int rc = launch_or_record(c, k_scan_local, k_scan_local_multi, grid, SCAN_THREADS, 0, args);
     if (!rc && nb > SCAN_SELF_SUM) {
@@ -404,7 +410,7 @@ int run_build_cells(sdpd_ctx *c, const sdpd_state *s, int kick_drift, const Step
         (rc = launch_or_record(c, k_kick_drift_assign, k_kick_drift_assign_multi,
                                blocks_for(std::max<int64_t>(n, CNT_N), 256), 256, 0,
                                KickDriftArgs{c->dp, s->q, s->p, s->f, kick_drift, c->cell_of,
-                                             c->slot, c->count, c->err, start})))
+                                             c->slot, c->count, c->err, c->dense, start})))
         return rc;
     if ((rc = run_scan(c, c->count, c->cell_start, nullptr, nullptr, nc, c->block_sums,
                        c->prm.cell_cap, true)))

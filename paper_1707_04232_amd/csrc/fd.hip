@@ -167,29 +167,6 @@ struct FdArgs {
     uint32_t *err;
 };
 
-// x (kernel arguments or parameters in memory, unchanged during the launch)
-// read anew from here on: scalar loads that cannot move above this point, so
-// that what one part of a range needs is not held in registers (and spilled)
-// through the others
-template <class T>
-__device__ __forceinline__ const T &reread(const T &x)
-{
-    const uint64_t u = (uint64_t)&x;   // uniform: said so, where the compiler cannot tell
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
-    auto *c = (const __attribute__((address_space(4))) T *)(((uint64_t)hi << 32) | lo);
-    __asm__ volatile("" : "+s"(c));
-    return *(const T *)c;
-}
-
-// The first argument of a kernel in place (in memory), for reread
-template <class T>
-__device__ __forceinline__ const T &kernel_argument()
-{
-    return *(const T *)(const __attribute__((address_space(4))) T *)
-               __builtin_amdgcn_kernarg_segment_ptr();
-}
-
 __device__ __forceinline__ uint32_t lane_u32(uint32_t v, int lane)   // uniform lane
 {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);

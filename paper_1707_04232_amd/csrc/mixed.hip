@@ -28,12 +28,24 @@ __device__ __forceinline__ void density_sparse_lucy_body(const DensityArgs &a, u
 {
     density_sparse<ModelF32, true>(a, blk);
 }
+__device__ __forceinline__ void density_dense_lucy_body(const DensityArgs &a, uint32_t blk)
+{
+    density_dense<ModelF32, true>(a, blk);
+}
 __device__ __forceinline__ void density_sparse_cubic_body(const DensityArgs &a, uint32_t blk)
 {
     density_sparse<ModelF32, false>(a, blk);
 }
+__device__ __forceinline__ void density_dense_cubic_body(const DensityArgs &a, uint32_t blk)
+{
+    density_dense<ModelF32, false>(a, blk);
+}
 SDPD_MULTI_KERNEL(k_density_f32_sparse_lucy_multi, DensityArgs, density_sparse_lucy_body, 256)
+SDPD_MULTI_KERNEL(k_density_f32_dense_lucy_multi, DensityArgs, density_dense_lucy_body, 64,
+                  ModelF32::kDensityOcc)
 SDPD_MULTI_KERNEL(k_density_f32_sparse_cubic_multi, DensityArgs, density_sparse_cubic_body, 256)
+SDPD_MULTI_KERNEL(k_density_f32_dense_cubic_multi, DensityArgs, density_dense_cubic_body, 64,
+                  ModelF32::kDensityOcc)
 SDPD_MULTI_KERNEL(k_density_f32_lucy_multi, DensityArgs, density_lucy_body, 64 * kCellWaves,
                   ModelF32::kDensityOcc)
 SDPD_MULTI_KERNEL(k_density_f32_cubic_multi, DensityArgs, density_cubic_body, 64 * kCellWaves,
@@ -60,13 +72,13 @@ int run_density_f32(sdpd_ctx *c, const sdpd_state *s, int update_eps)
     timer_begin(c, TK_DENSITY);
     const DensityArgs args{c->dp, c->q4f, c->cell_sorted, c->cell_start, s->rho, s->eps,
                            update_eps, c->masks, c->list, c->list_count, c->list_len,
-                           c->list_cap, c->err,
-                           nullptr, density_reach2(c->dp)};
-    const int rc = c->dp.kernel == SDPD_KERNEL_LUCY
-                       ? launch_density<ModelF32, true>(c, args, k_density_f32_lucy_multi,
-                                                        k_density_f32_sparse_lucy_multi)
-                       : launch_density<ModelF32, false>(c, args, k_density_f32_cubic_multi,
-                                                        k_density_f32_sparse_cubic_multi);
+                           c->list_cap, c->err, nullptr, density_reach2(c->dp), c->dense};
+    const DensityMulti lucy{k_density_f32_lucy_multi, k_density_f32_sparse_lucy_multi,
+                            k_density_f32_dense_lucy_multi};
+    const DensityMulti cubic{k_density_f32_cubic_multi, k_density_f32_sparse_cubic_multi,
+                             k_density_f32_dense_cubic_multi};
+    const int rc = c->dp.kernel == SDPD_KERNEL_LUCY ? launch_density<ModelF32, true>(c, args, lucy)
+                                                    : launch_density<ModelF32, false>(c, args, cubic);
     timer_end(c, TK_DENSITY);
     return rc;
 }

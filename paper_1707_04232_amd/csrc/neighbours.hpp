@@ -236,6 +236,7 @@ struct DensityArgs {
     uint32_t *err;
     double *rho_w;           // FP64: also into the w slot of the record, or NULL
     float reach2;            // h^2 and the rounding of the FP32 test for it (density_reach2)
+    const uint32_t *dense;   // not zero: a cell holds kDenseRegion particles or more
 };
 
 // Squared distance, in FP32, up to which a candidate is kept for the tests: the
@@ -312,13 +313,14 @@ __device__ __forceinline__ void density_store(const DensityArgs &a, int64_t i, d
 constexpr int kTerms = 576;        // queue entries of a wave
 constexpr int kTail = 256;         // particles of a workgroup's shared last part
 
-template <class M, bool SPLIT>
+// WAVES: those of the workgroup
+template <class M, bool SPLIT, int WAVES = kCellWaves>
 struct DensityLds {
-    typename M::Real terms[kCellWaves][kTerms + 64];
-    double rho[kTail];
-    uint32_t near[kCellWaves][64 * M::kChunks + 64];   // candidates that are not out of reach
-    uint32_t part[kCellWaves][64 * M::kChunks + 64];   // list entries of a particle and window
-    uint32_t words[SPLIT ? kCellWaves : 1][SPLIT ? 64 * kCellWaves : 1];
+    typename M::Real terms[WAVES][kTerms + 64];
+    double rho[WAVES > 1 ? kTail : 1];
+    uint32_t near[WAVES][64 * M::kChunks + 64];   // candidates that are not out of reach
+    uint32_t part[WAVES][64 * M::kChunks + 64];   // list entries of a particle and window
+    uint32_t words[SPLIT ? WAVES : 1][SPLIT ? 64 * WAVES : 1];
 };
 
 // SPLIT: the workgroup's waves share one cell, wave w with the particles in
@@ -326,13 +328,13 @@ struct DensityLds {
 // in LDS: for boxes of so few cells that a wave per cell leaves SIMDs idle and the
 // pass takes as long as one wave's chain (1000 particles: 18 us, a wave per cell
 // 34, four lanes of a thread per particle 66)
-template <class M, bool LUCY, bool SPLIT>
+template <class M, bool LUCY, bool SPLIT, int WAVES = kCellWaves>
 struct DensityWave {
     typedef typename M::Real Real;
     const DensityArgs &a;
     const DevParams &P;
     const CellWave &cw;
-    DensityLds<M, SPLIT> &lds;
+    DensityLds<M, SPLIT, WAVES> &lds;
     const int lane, wave, lo, hi;   // slots lo .. hi - 1 are this wave's
     Real *terms;
     Real x, y, z, acc;       // lane i < m: particle i of the cell and its sum
@@ -420,7 +422,7 @@ struct DensityWave {
                     const Real r2 = dx * dx + dy * dy + dz * dz;
                     const bool near = M::near(P, r2);
                     const uint64_t hit = __ballot(near);
-                                        if (WORDS) w[c] = w[c] + w[c] + (near ? 1u : 0u);
+                    if (WORDS) w[c] = w[c] + w[c] + (near ? 1u : 0u);
                     // (no branch: the other lanes write to slots that nothing reads)
                     uint32_t at = below(hit, 0u);
                     asm volatile("" : "+v"(at));   // (computed, not branched around)
@@ -617,26 +619,94 @@ __device__ __forceinline__ void density_cells(const DensityArgs &a, uint32_t blk
     }
 }
 
-// The same sums, masks and lists, bit for bit, with a lane per particle, for large
-// boxes whose cells are mostly empty or hold few particles: a wave per cell then mostly
-// finds that there is nothing to do.
+// The same sums, masks and lists, bit for bit (where no cell overflows), for large boxes
+// whose cells are mostly empty or hold few particles: a wave per cell then mostly finds
+// that there is nothing to do.  A lane per particle (density_lanes), but where the cell
+// pass has found cells of kDenseRegion particles for the cells of dense regions, those with
+// kDenseCell particles and more and the cells around them: they are taken by a wave each
+// (density_dense), the wave that has the cell's first particle among its kHeads ones.
+// One wave per workgroup: most find one such cell or none, and a workgroup's LDS is held
+// until its last wave is done.
+//
+// us, lanes only and now: a droplet of 10^5 particles at h = 2.5 spacings in 60^3 cells
+// 184, 140, one of 10^6 at h = 3.4 in 88^3 cells 1673, 1020, in FP32 1434, 819; uniform
+// boxes of one and three particles per cell 48, 53 and 91, 98 (the launch that finds no
+// dense cell; with both in one launch, lanes in workgroups of one wave too, 55 and 107).
+constexpr uint32_t kDenseCell = 10u;
+constexpr int kHeads = 16;
+
+// The dense cells that begin among particles kHeads blk .. kHeads blk + kHeads - 1
 template <class M, bool LUCY>
-__device__ __forceinline__ void density_sparse(const DensityArgs &a, uint32_t blk)
+__device__ __forceinline__ void density_dense(const DensityArgs &a, uint32_t blk)
+{
+    __shared__ DensityLds<M, false, 1> lds;
+    if (*a.dense == 0u) return;
+    const DevParams &P = a.P;
+    const int lane = threadIdx.x;
+    const int64_t i = (int64_t)blk * kHeads + lane;
+    uint32_t c = 0u;
+    bool dense = false;
+    if (lane < kHeads && i < P.n) {
+        c = a.cell_sorted[i];
+        if ((int64_t)a.cell_start[c] == i) {
+            const CellXyz cc(P, c);
+            const NbSteps steps(P, cc.x, cc.y, cc.z);
+#pragma unroll
+            for (int k = 0; k < NNB; ++k) {
+                const uint32_t cn = (uint32_t)steps.get(P, k).c;
+                dense = dense || a.cell_start[cn + 1] - a.cell_start[cn] >= kDenseCell;
+            }
+        }
+    }
+    for (uint64_t heads = __ballot(dense); heads; heads &= heads - 1ull) {
+        const DensityArgs &b = reread(a);   // (not held through the loop)
+        const CellXyz cc(b.P, lane_of(c, __builtin_ctzll(heads)));
+        const CellWave cw(b.P, cc, b.cell_start);
+        DensityWave<M, LUCY, false, 1> d{b, b.P, cw, lds, lane, 0, 0, (int)cw.m};
+        d.run();
+        if ((uint32_t)lane < cw.m) density_store(b, cw.own + lane, M::density_scale(b.P, d.acc));
+    }
+}
+
+// The particles of the other cells, and of all particles the masks for the cells ahead
+// that no wave takes (a wave writes those for its cell).  DENSE: there are dense cells.
+template <class M, bool LUCY, bool DENSE>
+__device__ __forceinline__ void density_lanes(const DensityArgs &a, uint32_t blk)
 {
     typedef typename M::Real Real;
     const DevParams &P = a.P;
     const int64_t n = P.n, i = (int64_t)blk * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const Real *__restrict__ q4 = static_cast<const Real *>(a.q4);
-    const CellXyz cc(P, a.cell_sorted[i]);
+    const uint32_t c = a.cell_sorted[i];
+    const CellXyz cc(P, c);
     const NbSteps steps(P, cc.x, cc.y, cc.z);
+    if (DENSE && a.cell_start[c + 1] - a.cell_start[c] >= kDenseCell) {
+        // a wave takes all cells around it but empty ones
+#pragma unroll
+        for (int k = OWN_NB + 1; k < NNB; ++k) {
+            const uint32_t cn = (uint32_t)steps.get(P, k).c;
+            if (a.cell_start[cn + 1] == a.cell_start[cn])
+                a.masks[(int64_t)(k - OWN_NB) * n + i] = 0ull;
+        }
+        return;
+    }
+    bool dense = false;   // a wave takes this particle's cell: only masks are left to do
+    if (DENSE) {
+#pragma unroll
+        for (int k = 0; k < NNB; ++k) {
+            const uint32_t cn = (uint32_t)steps.get(P, k).c;
+            dense = dense || a.cell_start[cn + 1] - a.cell_start[cn] >= kDenseCell;
+        }
+    }
     const typename M::Vec qi = load_vec<M>(q4, i);
     Real acc = (Real)0;
     uint32_t partners = 0u;
-    for (int k = 0; k < NNB; ++k) {
+    for (int k = dense ? OWN_NB : 0; k < NNB; ++k) {
         const int o[3] = {k % 3, (k / 3) % 3, k / 9};
         const uint32_t cn = (uint32_t)steps.get(P, k).c, s = a.cell_start[cn];
         uint32_t cnt = a.cell_start[cn + 1] - s;
+        if (DENSE && cnt >= kDenseCell) continue;
         if (cnt > (uint32_t)P.cap) {   // overflowing cell: reported, not visited
             atomicOr(a.err, ERR_CELLCAP);
             cnt = 0u;
@@ -651,17 +721,26 @@ __device__ __forceinline__ void density_sparse(const DensityArgs &a, uint32_t bl
                        dz = (qi.z - v.z) + sh[2];
             const Real r2 = dx * dx + dy * dy + dz * dz;
             if (!M::near(P, r2)) continue;
+            mask |= 1ull << t;
+            if (DENSE && dense) continue;
             acc = acc + M::template density<LUCY>(P, r2);
             if (partners < a.list_cap)
                 *list_at(a, (uint32_t)i, partners) = list_entry(s + t, k);
             ++partners;
-            mask |= 1ull << t;
         }
         if (k == OWN_NB && cnt) mask &= ~(1ull << (i - (int64_t)s));   // i itself is no partner
         if (k >= OWN_NB) a.masks[(int64_t)(k - OWN_NB) * n + i] = mask;
     }
+    if (DENSE && dense) return;
     a.count[i] = partners;
     density_store(a, i, M::density_scale(P, acc));
+}
+
+template <class M, bool LUCY>
+__device__ __forceinline__ void density_sparse(const DensityArgs &a, uint32_t blk)
+{
+    if (*a.dense == 0u) density_lanes<M, LUCY, false>(a, blk);
+    else density_lanes<M, LUCY, true>(a, blk);
 }
 
 // ---------------------------------------------------------------- partner sums
@@ -913,11 +992,12 @@ __device__ __forceinline__ void forces_body(const ForcesArgs &g, uint32_t blk)
 
 // ---------------------------------------------------------------- launches
 // Density: in launches recorded for a batch all boxes share the GPU, and take the
-// form of large ones (the two agree bit for bit); a box on its own: four waves per cell up to 2^10 cells, one per SIMD of the GPU (384
-// cells: 25 us against 50; 1728 cells: 53 against 54; 7128: 102 against 73).
+// form of large ones (the two agree bit for bit); a box on its own: four waves per cell up
+// to 2^10 cells, one per SIMD of the GPU (384 cells: 25 us against 50; 1728 cells: 53
+// against 54; 7128: 102 against 73).
 constexpr int64_t kSplitMaxCells = 1 << 10;
 // A lane per particle from 2^15 cells of fewer than four particles on average on: 64000
-// cells of 0.25, 1, 2, 3, 4 particles 34, 48, 67, 91, 124 us, a wave per cell 64, 78, 91,
+// cells of 0.25, 1, 2, 3, 3.9 particles 38, 53, 73, 98, 125 us, a wave per cell 64, 78, 91,
 // 109, 124; 13824 cells, whose waves all fit at once, 32, 45, 58, 69 against 21, 24, 27, 32.
 constexpr int64_t kSparsePerCell = 4, kSparseMinCells = 1 << 15;
 
@@ -939,24 +1019,36 @@ __global__ __launch_bounds__(256) void k_density_sparse(DensityArgs a)
     density_sparse<M, LUCY>(a, xcd_block(blockIdx.x, gridDim.x));
 }
 template <class M, bool LUCY>
+__global__ __launch_bounds__(64, M::kDensityOcc) void k_density_dense(DensityArgs)
+{
+    density_dense<M, LUCY>(kernel_argument<DensityArgs>(), xcd_block(blockIdx.x, gridDim.x));
+}
+template <class M, bool LUCY>
 __global__ __launch_bounds__(256) void k_forces(ForcesArgs g)
 {
     forces_body<M, LUCY>(g, xcd_block(blockIdx.x, gridDim.x));
 }
 
-// (multi: the multi-box forms of this model and kernel)
+// the multi-box forms of a model and kernel
+struct DensityMulti {
+    MultiKernel cells, sparse, dense;
+};
 template <class M, bool LUCY>
-int launch_density(sdpd_ctx *c, const DensityArgs &args, MultiKernel multi, MultiKernel sparse)
+int launch_density(sdpd_ctx *c, const DensityArgs &args, const DensityMulti &multi)
 {
-    if (c->ncell >= kSparseMinCells && c->n < kSparsePerCell * c->ncell)
-        return launch_or_record(c, k_density_sparse<M, LUCY>, sparse,
+    if (c->ncell >= kSparseMinCells && c->n < kSparsePerCell * c->ncell) {
+        const int rc = launch_or_record(c, k_density_dense<M, LUCY>, multi.dense,
+                                        (unsigned)((c->n + kHeads - 1) / kHeads), 64, 0, args);
+        if (rc) return rc;
+        return launch_or_record(c, k_density_sparse<M, LUCY>, multi.sparse,
                                 (unsigned)((c->n + 255) / 256), 256, 0, args);
+    }
     if (c->ncell <= kSplitMaxCells && !c->rec) {
         hipLaunchKernelGGL((k_density<M, LUCY, true>), dim3((unsigned)c->ncell),
                            dim3(64 * kCellWaves), 0, c->stream, args);
         return check_hip(hipGetLastError());
     }
-    return launch_or_record(c, k_density<M, LUCY, false>, multi,
+    return launch_or_record(c, k_density<M, LUCY, false>, multi.cells,
                             (unsigned)((c->ncell + kCellWaves - 1) / kCellWaves),
                             64 * kCellWaves, 0, args);
 }

@@ -33,6 +33,9 @@ constexpr int NMASK = 14;
 constexpr int NNB = 27;
 constexpr int OWN_NB = 13;
 constexpr int MAX_CAP = 64;
+// with a cell of this many particles a dilute box has dense regions (a uniform one of
+// four particles per cell has none in 3 10^5 cells)
+constexpr uint32_t kDenseRegion = 16u;
 // bits of a particle in a word that it shares with an offset index k: n < 2^27
 constexpr int kEntryBits = 27;
 // F/D sweep workgroups: FD_WAVES waves share one batch of tasks (the pairs
@@ -166,6 +169,7 @@ struct sdpd_ctx {
     uint32_t list_len, list_cap;
     unsigned long long *counters;
     uint32_t *err;
+    uint32_t *dense;             // the last cell pass has found a cell of a dense region
     double *obs_partial;         // per-block observable partials
     int64_t obs_blocks;
     double *obs_out;             // device stats records
@@ -321,6 +325,29 @@ int launch_or_record(sdpd_ctx *c, void (*single)(A), MultiKernel multi, unsigned
 
 // --------------------------------------------------------------- device helpers
 namespace sdpd {
+
+// x (kernel arguments or parameters in memory, unchanged during the launch)
+// read anew from here on: scalar loads that cannot move above this point, so
+// that what one part of a range needs is not held in registers (and spilled)
+// through the others
+template <class T>
+__device__ __forceinline__ const T &reread(const T &x)
+{
+    const uint64_t u = (uint64_t)&x;   // uniform: said so, where the compiler cannot tell
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    auto *c = (const __attribute__((address_space(4))) T *)(((uint64_t)hi << 32) | lo);
+    __asm__ volatile("" : "+s"(c));
+    return *(const T *)c;
+}
+
+// The first argument of a kernel in place (in memory), for reread
+template <class T>
+__device__ __forceinline__ const T &kernel_argument()
+{
+    return *(const T *)(const __attribute__((address_space(4))) T *)
+               __builtin_amdgcn_kernarg_segment_ptr();
+}
 
 // neighbour cell k (offset index 0..26, z slowest) of cell (cx, cy, cz) and
 // the periodic shift that turns x_i - x_j into the minimum image for it

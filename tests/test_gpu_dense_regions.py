@@ -13,6 +13,7 @@ import numpy as np
 import pytest
 
 import oracle as O
+import parity_util as PU
 from paper_1707_04232_amd.workload import uniform_state
 
 pytestmark = pytest.mark.gpu
@@ -103,6 +104,77 @@ def test_density_forces_and_masks(name, kernel, prec):
     worst = (np.abs(G["f"] - R.f) / np.maximum(bound, 1e-300)).max()
     say(f"error over its bound {worst:.3f}, most partners {most}")
     assert worst <= 1.0
+
+
+def droplet_in_vapour():
+    """36^3 cells with 0.6 particles on average, 16 in those of a droplet across a corner
+    of the box: empty and thin cells beside dense ones, on all sides."""
+    side, box = 12, 90.0
+    n = side ** 3 + 28001
+    q, p, eps, ids = uniform_state(n, (box,) * 3, seed=9)
+    q, k = np.array(q).reshape(3, n), side ** 3
+    g = np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij")).reshape(3, k)
+    q[:, ::-1][:, :k] = (g - 5.3 + 0.3 * (q[:, :k] / box)) % box
+    return q, p, eps, ids, box
+
+
+@pytest.mark.parametrize("kernel", [0, 1])
+def test_sweep_of_a_droplet_in_vapour(kernel):
+    from paper_1707_04232_amd import sdpd
+    say("sweep of a droplet in vapour", kernel)
+    q, p, eps, ids, box = droplet_in_vapour()
+    kw = dict(n=len(eps), dt=0.002, Cv=10.0, seed=11, kernel=kernel)
+    S = sdpd.DeviceState.from_numpy(q, p, eps, ids)
+    with sdpd.Context(sdpd.SdpdParams(box=box, **kw)) as ctx:
+        ctx.prepare(S)
+        f = S.to_numpy()["f"]
+        stats = ctx.fd_metropolis(S, step=5)
+    P = O.OracleParams(box=(box,) * 3, **kw)
+    R = O.State.from_arrays(q, p, eps, ids)
+    O.prepare(P, R)
+    assert np.abs(S.to_numpy()["rho"] - R.rho).max() <= 1e-12 * R.rho.max()
+    assert np.abs(f - R.f).max() <= 1e-12 * np.abs(R.f).max()
+    PU.sweep_and_compare(P, R, 5, S.to_numpy(), stats, 1e-10, say)
+
+
+def test_mixed_droplet_in_vapour():
+    """FP32: rho as above; the forces within 2e-4 of the largest possible term of a pair,
+    as in the other mixed-precision tests; after a step those of a box stepped eagerly and
+    in a batch agree bit for bit."""
+    import torch
+    from paper_1707_04232_amd import sdpd
+    say("mixed droplet in vapour")
+    q, p, eps, ids, box = droplet_in_vapour()
+    n = len(eps)
+    P = O.OracleParams(n=n, box=(box,) * 3, Cv=10.0)
+    R = O.State.from_arrays(q, p, eps, ids)
+    O.prepare(P, R)
+    outs = []
+    for batch in (False, True):
+        S = sdpd.DeviceState.from_numpy(q, p, eps, ids)
+        ctx = sdpd.Context(sdpd.SdpdParams(n=n, box=box, Cv=10.0, prec=1, dt=0.002, seed=3),
+                           stream=torch.cuda.Stream())
+        torch.cuda.synchronize()
+        ctx.prepare(S)
+        ctx.sync()
+        G = S.to_numpy()
+        assert np.array_equal(G["id"], R.id)
+        assert np.abs(G["rho"] - R.rho).max() <= 2e-5 * R.rho.max()
+        Pi = (P.Cv / (3 * P.kB)) * P.kB * R.eps / (P.m * P.Cv) / R.rho
+        term = P.m ** 2 * 2 * Pi.max() * 315.0 / (4 * np.pi * P.h ** 4) * 4.0 / 27.0
+        assert np.abs(G["f"] - R.f).max() <= 2e-4 * term
+        if batch:
+            B = sdpd.Batch([ctx], [S], layout=sdpd.BATCH_FUSED)
+            B.run(0, 2)
+            torch.cuda.synchronize()
+            B.close()
+        else:
+            ctx.step(S, 0, 2, stats=False)
+        ctx.sync()
+        outs.append(S.to_numpy())
+        ctx.close()
+    for k in ("id", "q", "p", "eps", "rho", "f"):
+        assert np.array_equal(outs[0][k], outs[1][k]), k
 
 
 @pytest.mark.parametrize("kernel", [0, 1])
