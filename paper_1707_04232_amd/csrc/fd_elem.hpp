@@ -1,5 +1,5 @@
 // Compact FP64 elementary functions for the fluctuation/dissipation update
-// and the particle passes (pair distances).
+// and the particle passes (square roots).
 //
 // Their arguments are always positive, finite and well ranged (uniform draws
 // in (0, 1), energies, ratios of friction amplitudes, squared distances
@@ -73,8 +73,7 @@ __device__ __forceinline__ double fast_rsq(double x)
 }
 
 // sqrt(x) as x / sqrt(x) from the reciprocal square root alone (within
-// about two ulp): the pair distances of the particle passes, whose kernel
-// values tolerate it
+// about two ulp); the host check of these functions holds it beside fd_sqrt
 __device__ __forceinline__ double fd_sqrt_pair(double x) { return x * fast_rsq(x); }
 
 // sqrt(x) from the estimate y and s = x y: with r = (1 - s y)/2, measured on
@@ -206,5 +205,6 @@ __device__ __forceinline__ double elem_cospi(double a, T t)
     for (int i = 1; i < 11; ++i) p = fma(p, z, t[i]);
     return r * p;
 }
+__device__ __forceinline__ double fd_cospi(double a) { return elem_cospi(a, kSinCosCoef); }
 
 }  // namespace sdpd
