@@ -473,17 +473,6 @@ __device__ __forceinline__ uint64_t xor_permute_bits(uint64_t m, uint32_t x)
     return m;
 }
 
-__device__ __forceinline__ uint64_t wave_or64(uint64_t v)
-{
-    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        lo |= (uint32_t)__shfl_xor((int)lo, off);
-        hi |= (uint32_t)__shfl_xor((int)hi, off);
-    }
-    return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 {
 #pragma unroll

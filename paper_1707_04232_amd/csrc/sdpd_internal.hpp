@@ -349,31 +349,17 @@ __device__ __forceinline__ const T &kernel_argument()
                __builtin_amdgcn_kernarg_segment_ptr();
 }
 
-// neighbour cell k (offset index 0..26, z slowest) of cell (cx, cy, cz) and
-// the periodic shift that turns x_i - x_j into the minimum image for it
+// neighbour cell and the periodic shift that turns x_i - x_j into the minimum
+// image for it
 struct NbCell {
     int64_t c;
     double sx, sy, sz;
 };
 
-__device__ __forceinline__ NbCell neighbour_cell(const DevParams &P, int cx, int cy, int cz, int k)
-{
-    NbCell r;
-    int x2 = cx + (k % 3) - 1, y2 = cy + (k / 3) % 3 - 1, z2 = cz + k / 9 - 1;
-    r.sx = x2 < 0 ? P.box[0] : (x2 >= P.nc[0] ? -P.box[0] : 0.0);
-    r.sy = y2 < 0 ? P.box[1] : (y2 >= P.nc[1] ? -P.box[1] : 0.0);
-    r.sz = z2 < 0 ? P.box[2] : (z2 >= P.nc[2] ? -P.box[2] : 0.0);
-    x2 += x2 < 0 ? P.nc[0] : (x2 >= P.nc[0] ? -P.nc[0] : 0);
-    y2 += y2 < 0 ? P.nc[1] : (y2 >= P.nc[1] ? -P.nc[1] : 0);
-    z2 += z2 < 0 ? P.nc[2] : (z2 >= P.nc[2] ? -P.nc[2] : 0);
-    r.c = x2 + (int64_t)P.nc[0] * (y2 + (int64_t)P.nc[1] * z2);
-    return r;
-}
-
-// The same 27 neighbour cells of one cell, with the boundary tests done
-// once: bit a of lo (hi) says the cell is the first (last) of axis a, where
-// an offset of -1 (+1) wraps and carries the shift +L (-L).  Cell indices fit
-// in 32 bits (14 ncell < 2^32).  get(k) equals neighbour_cell(P, cx, cy, cz, k).
+// The 27 neighbour cells k (offset index 0..26, z slowest) of cell (cx, cy, cz),
+// with the boundary tests done once: bit a of lo (hi) says the cell is the first
+// (last) of axis a, where an offset of -1 (+1) wraps and carries the shift +L
+// (-L).  Cell indices fit in 32 bits (14 ncell < 2^32).
 struct NbSteps {
     uint32_t c, lo, hi;
     __device__ __forceinline__ NbSteps(const DevParams &P, int cx, int cy, int cz)
