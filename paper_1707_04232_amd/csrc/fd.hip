@@ -1180,75 +1180,69 @@ static int launch_records_and_levels(sdpd_ctx *c, const sdpd_state *s, double dt
     return check_hip(hipGetLastError());
 }
 
-// cells of task T (the host form of task_cells); B = -1 for a phase-0 task
-static void task_cells_host(const sdpd_ctx *c, int64_t T, int64_t &A, int64_t &B)
-{
-    const int64_t ncell = c->ncell;
-    const int nx = c->dp.nc[0], ny = c->dp.nc[1], nz = c->dp.nc[2];
-    if (T < ncell) {
-        A = T;
-        B = -1;
-        return;
-    }
-    const int64_t per = ncell / 8, u = T - ncell;
-    const int p = 1 + (int)(u / per);
-    const int64_t t = u % per;
-    const int o = (p - 1) / 8, pi = (p - 1) % 8, k = 14 + o;
-    const int64_t hx = nx / 2, hy = ny / 2;
-    const int tx = (int)(t % hx), ty = (int)((t / hx) % hy), tz = (int)(t / (hx * hy));
-    const int ax = 2 * tx + (pi & 1), ay = 2 * ty + ((pi >> 1) & 1), az = 2 * tz + (pi >> 2);
-    const int bx = (ax + k % 3 - 1 + nx) % nx, by = (ay + (k / 3) % 3 - 1 + ny) % ny,
-              bz = (az + k / 9 - 1 + nz) % nz;
-    A = ax + (int64_t)nx * (ay + (int64_t)ny * az);
-    B = bx + (int64_t)nx * (by + (int64_t)ny * bz);
-}
-
 // Order of the ranges inside each group: by the latest position, in the
 // hand-out order, of the ranges of the previous group they wait for (ties in
 // task order), so that ranges whose cells are released first are taken first.
+// Every group touches every cell, so that position lies among those of the previous
+// group: a counting sort.
 static std::vector<uint32_t> fd_range_order(const sdpd_ctx *c, const FdSweep &h)
 {
+    const uint32_t nx = (uint32_t)c->dp.nc[0], ny = (uint32_t)c->dp.nc[1],
+                   nz = (uint32_t)c->dp.nc[2], hx = nx / 2, hy = ny / 2;
+    const uint32_t ncell = (uint32_t)c->ncell, per = ncell / 8;
     std::vector<uint32_t> order(h.nitems);
-    std::vector<int64_t> last(c->ncell, -1);   // hand-out position of the range that last touched c
-    std::vector<std::pair<int64_t, uint32_t>> keyed;
-    std::vector<int64_t> cells;          // of the group's ranges, one after the other
+    std::vector<uint32_t> last(ncell, 0u);   // hand-out position of the range that last touched a cell
+    std::vector<uint32_t> key, at, cells;    // cells: of the group's ranges, one after the other
     std::vector<size_t> cells_end;
-    uint32_t begin = 0;
+    uint32_t before = 0, begin = 0;          // first position of the previous group and of this one
     for (int g = 0; g < h.ngroups; ++g) {
         const FdLaunch &L = h.launch[g];
         const uint32_t nb = h.group_end[g] - begin;
-        keyed.assign(nb, std::make_pair((int64_t)-1, 0u));
+        key.assign(nb, before);
         cells.clear();
         cells_end.resize(nb);
-        for (uint32_t b = 0; b < nb; ++b) {
-            int k_ph = 0;
-            while (k_ph + 1 < L.nph && (int64_t)b >= L.wg_end[k_ph]) ++k_ph;
-            const int64_t bl = k_ph > 0 ? (int64_t)b - L.wg_end[k_ph - 1] : (int64_t)b;
-            const int64_t t0 = bl * L.tpw[k_ph];
-            const int64_t t1 = std::min(t0 + L.tpw[k_ph], L.ntasks[k_ph]);
-            int64_t key = -1;
-            for (int64_t t = t0; t < t1; ++t) {
-                int64_t A, B;
-                task_cells_host(c, L.task_base[k_ph] + t, A, B);
-                cells.push_back(A);
-                key = std::max(key, last[A]);
-                if (B >= 0) {
+        uint32_t b = 0;
+        for (int k_ph = 0; k_ph < L.nph; ++k_ph) {
+            // the phase's tasks (as task_cells numbers them): A of parity pi, B = A + delta_o
+            const bool own = L.task_base[k_ph] == 0;
+            const uint32_t ph = own ? 0u : (uint32_t)(L.task_base[k_ph] - ncell) / per;
+            const uint32_t pi = ph % 8u, k = 14u + ph / 8u;
+            const uint32_t dx = k % 3u + nx - 1u, dy = (k / 3u) % 3u + ny - 1u, dz = k / 9u + nz - 1u;
+            uint32_t tx = 0, ty = 0, tz = 0;
+            for (int64_t t0 = 0; t0 < L.ntasks[k_ph]; t0 += L.tpw[k_ph], ++b) {
+                const int64_t t1 = std::min(t0 + L.tpw[k_ph], L.ntasks[k_ph]);
+                for (int64_t t = t0; t < t1; ++t) {
+                    if (own) {
+                        cells.push_back((uint32_t)t);
+                        continue;
+                    }
+                    const uint32_t ax = 2u * tx + (pi & 1u), ay = 2u * ty + ((pi >> 1) & 1u),
+                                   az = 2u * tz + (pi >> 2);
+                    const uint32_t A = ax + nx * (ay + ny * az);
+                    const uint32_t B = (ax + dx) % nx + nx * ((ay + dy) % ny + ny * ((az + dz) % nz));
+                    cells.push_back(A);
                     cells.push_back(B);
-                    key = std::max(key, last[B]);
+                    key[b] = std::max(key[b], std::max(last[A], last[B]));
+                    if (++tx == hx) {
+                        tx = 0;
+                        if (++ty == hy) {
+                            ty = 0;
+                            ++tz;
+                        }
+                    }
                 }
+                cells_end[b] = cells.size();
             }
-            keyed[b] = std::make_pair(key, b);
-            cells_end[b] = cells.size();
         }
-        std::stable_sort(keyed.begin(), keyed.end(),
-                         [](const std::pair<int64_t, uint32_t> &x,
-                            const std::pair<int64_t, uint32_t> &y) { return x.first < y.first; });
+        at.assign((size_t)(begin - before) + 2u, 0u);   // ranges of each key, then their places
+        for (uint32_t r = 0; r < nb; ++r) ++at[key[r] - before + 1u];
+        for (size_t x = 1; x < at.size(); ++x) at[x] += at[x - 1];
         for (uint32_t r = 0; r < nb; ++r) {
-            const uint32_t b = keyed[r].second;
-            order[begin + r] = b;
-            for (size_t x = b ? cells_end[b - 1] : 0; x < cells_end[b]; ++x)
-                last[cells[x]] = begin + r;
+            const uint32_t place = begin + at[key[r] - before]++;
+            order[place] = r;
+            for (size_t x = r ? cells_end[r - 1] : 0; x < cells_end[r]; ++x) last[cells[x]] = place;
         }
+        before = begin;
         begin = h.group_end[g];
     }
     return order;
