@@ -235,7 +235,9 @@ struct PiTerm {
     {
         const double4 u = v4[j];
         const double ru = d[0] * (v.x - u.x) + d[1] * (v.y - u.y) + d[2] * (v.z - u.z);
-        out[0] = own ? 0.0 : ModelF64::force<LUCY>(P, r2) * ru;
+        double v1 = ModelF64::force<LUCY>(P, r2) * ru;
+        asm volatile("" : "+v"(v1));   // (as in the forces)
+        out[0] = own ? 0.0 : v1;
     }
 };
 

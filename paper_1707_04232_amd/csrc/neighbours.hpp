@@ -968,7 +968,9 @@ struct ForceTerm {
                                                const typename M::Vec &qj, const Real d[3],
                                                Real r2, Real out[3]) const
     {
-        const Real sc = own ? (Real)0 : ms * (qi.w + qj.w) * M::template force<LUCY>(P, r2);
+        Real sc = ms * (qi.w + qj.w) * M::template force<LUCY>(P, r2);
+        asm volatile("" : "+v"(sc));   // (a select, no branch around the factors)
+        sc = own ? (Real)0 : sc;
         for (int x = 0; x < 3; ++x) out[x] = sc * d[x];
     }
 };
