@@ -397,7 +397,9 @@ struct DensityWave {
             }
         }
         const int m = (int)cw.m;
-        for (int half = m > 32 ? 1 : 0; half >= 0; --half) {
+        constexpr bool kHalf = WAVES == 1;   // lo .. hi - 1 within a word of the masks
+        const int last_half = kHalf ? lo >> 5 : 0;
+        for (int half = (kHalf ? hi : m) > 32 ? 1 : 0; half >= last_half; --half) {
             uint32_t w[K];
 #pragma unroll
             for (int c = 0; c < K; ++c) w[c] = 0u;
@@ -624,18 +626,20 @@ __device__ __forceinline__ void density_cells(const DensityArgs &a, uint32_t blk
 // that there is nothing to do.  A lane per particle (density_lanes), but where the cell
 // pass has found cells of kDenseRegion particles for the cells of dense regions, those with
 // kDenseCell particles and more and the cells around them: they are taken by a wave each
-// (density_dense), the wave that has the cell's first particle among its kHeads ones.
-// One wave per workgroup: most find one such cell or none, and a workgroup's LDS is held
-// until its last wave is done.
+// (density_dense), the wave that has the cell's first particle among its kHeads ones, and
+// cells of more than 32 particles by two, one for each word of their masks.  One wave per
+// workgroup: most find one such cell or none, and a workgroup's LDS is held until its last
+// wave is done.
 //
 // us, lanes only and now: a droplet of 10^5 particles at h = 2.5 spacings in 60^3 cells
-// 184, 140, one of 10^6 at h = 3.4 in 88^3 cells 1673, 1020, in FP32 1434, 819; uniform
-// boxes of one and three particles per cell 48, 53 and 91, 98 (the launch that finds no
-// dense cell; with both in one launch, lanes in workgroups of one wave too, 55 and 107).
+// 184, 137, at h = 3.6 in 40^3 452, 262 (a wave for all of a cell 362), one of 10^6 at h =
+// 3.4 in 88^3 cells 1673, 1069, in FP32 1434, 839; uniform boxes of one and three particles
+// per cell 48, 53 and 91, 98 (the launch that finds no dense cell; with both in one launch,
+// lanes in workgroups of one wave too, 55 and 107).
 constexpr uint32_t kDenseCell = 10u;
 constexpr int kHeads = 16;
 
-// The dense cells that begin among particles kHeads blk .. kHeads blk + kHeads - 1
+// The dense cells whose slot 0 or 32 is among particles kHeads blk .. kHeads blk + kHeads - 1
 template <class M, bool LUCY>
 __device__ __forceinline__ void density_dense(const DensityArgs &a, uint32_t blk)
 {
@@ -648,7 +652,7 @@ __device__ __forceinline__ void density_dense(const DensityArgs &a, uint32_t blk
     bool dense = false;
     if (lane < kHeads && i < P.n) {
         c = a.cell_sorted[i];
-        if ((int64_t)a.cell_start[c] == i) {
+        if (((i - (int64_t)a.cell_start[c]) & 31) == 0) {
             const CellXyz cc(P, c);
             const NbSteps steps(P, cc.x, cc.y, cc.z);
 #pragma unroll
@@ -660,11 +664,16 @@ __device__ __forceinline__ void density_dense(const DensityArgs &a, uint32_t blk
     }
     for (uint64_t heads = __ballot(dense); heads; heads &= heads - 1ull) {
         const DensityArgs &b = reread(a);   // (not held through the loop)
-        const CellXyz cc(b.P, lane_of(c, __builtin_ctzll(heads)));
+        const int l = __builtin_ctzll(heads);
+        const CellXyz cc(b.P, lane_of(c, l));
         const CellWave cw(b.P, cc, b.cell_start);
-        DensityWave<M, LUCY, false, 1> d{b, b.P, cw, lds, lane, 0, 0, (int)cw.m};
+        // slots 0 .. 31 or 32 .. 63; all of an overflowing cell's particles are done once
+        const int m = (int)cw.m, lo = (int)((uint32_t)blk * kHeads + (uint32_t)l - cw.own);
+        if (lo > 0 && lo >= m) continue;
+        DensityWave<M, LUCY, false, 1> d{b, b.P, cw, lds, lane, 0, lo, min(lo + 32, m)};
         d.run();
-        if ((uint32_t)lane < cw.m) density_store(b, cw.own + lane, M::density_scale(b.P, d.acc));
+        if (lane >= d.lo && lane < d.hi)
+            density_store(b, cw.own + lane, M::density_scale(b.P, d.acc));
     }
 }
 
